@@ -72,11 +72,9 @@ enum svgd_status {
  */
 #define SVGD_FLAG_CARRY_GRAM 1u
 /*
- * With carried sums, a step whose list of carried partial sums is short runs as ONE kernel launch
- * (the update kernel derives h and K itself, in every workgroup) - by default only on the
- * vector-ALU path, n <= 12, where that measures faster than two launches.  This flag extends it to
- * 13 <= n <= 32, where it measures slower (one launch of 15 us against two launches in 12 us at
- * n = 16, D = 8,577): for measurements, and for callers to whom the launch count matters more.
+ * Accepted for compatibility and without effect: it used to ask for the single-launch step on carried
+ * sums at 13 <= n <= 32.  That step is now the default wherever the list of carried partial sums is
+ * short, at every n <= 32 (n = 16, D = 8,577: 12.4 us in two launches, 9.6 in one).
  */
 #define SVGD_FLAG_FUSE_MFMA 2u
 
@@ -86,8 +84,8 @@ enum svgd_status {
  * the paper's `num_particles` and of the flattened parameter count of its networks (App. B.2, the
  * arguments of the top-level SVGD inference call; its `lengthscale` is svgd_set_bandwidth, its
  * `lr` the eps of svgd_step).  `flags`: 0 or an OR of the SVGD_FLAG_* values above.  Allocates the handle's
- * device scratch: 8192 * max_n * (max_n + 1) / 2 bytes of partial sums (17 MB at max_n = 64) and
- * about 0.2 MB of tables.  On success *out receives the handle.
+ * device scratch: 8192 * max_n * (max_n + 1) / 2 bytes of partial sums (17 MB at max_n = 64; each of
+ * the 2048 vectors rounded up to 16 bytes) and about 0.1 MB of tables.  On success *out receives the handle.
  */
 int svgd_create(svgd_handle_t *out, int max_n, int64_t max_D, int device_id, uint32_t flags);
 
@@ -177,10 +175,10 @@ int svgd_get_last(svgd_handle_t h, double *h_out, float *K_host, void *stream);
  * SVGD_KERNEL_KINDS entries) with the total elapsed milliseconds and the number of launches of
  * kernel kind k, then switches recording off.  At most 2048 launches are recorded per session;
  * the events are created by svgd_profile_begin*, none while recording.
- * Not every kind runs in every step: a short list of partial sums is reduced inside the
- * BANDWIDTH kernel (no REDUCE launch), carried pair sums replace the GRAM pass, a short list of
- * carried sums at n <= 32 is consumed by the UPDATE kernel itself (the whole step is then that one
- * launch), and problems with n <= 8 and n * D <= 16384 run as one kernel, which is counted as
+ * Not every kind runs in every step: a short list of partial sums is reduced inside the kernel
+ * that needs it (no REDUCE launch), carried pair sums replace the GRAM pass, at n <= 32 a short
+ * list is consumed by the UPDATE kernel itself (no BANDWIDTH launch; with carried sums the whole step
+ * is then that one launch), and problems with n <= 8 and n * D <= 16384 run as one kernel, which is counted as
  * UPDATE (as BANDWIDTH when svgd_bandwidth launches it).
  */
 enum svgd_kernel_kind {

@@ -25,6 +25,10 @@ enum GramMode : int {
 
 __host__ __device__ inline int tri(int i, int j, int n) { return i * n - (i * (i - 1)) / 2 + (j - i); }
 
+// Partial-sum vectors lie this many floats apart, so that every one starts on 16 bytes and is read
+// four entries at a time (the up to three floats after the last entry are never used).
+__host__ __device__ inline int pair_stride(int n) { return (n * (n + 1) / 2 + 3) & ~3; }
+
 // Everything the update kernels need from the bandwidth kernel, in device memory.
 struct DevState {
     double h;
@@ -134,20 +138,58 @@ __device__ inline void store4(float *__restrict__ row, int64_t col, int64_t D, b
     if (col + 3 < D) row[col + 3] = v.w;
 }
 
-// Sum over the 64 lanes of a wave, returned in every lane.  Four DPP adds give every lane the sum
-// of its row of 16 (quad swap, quad-pair swap, half-row mirror, row mirror); the four row sums are
-// then read from lanes 0, 16, 32, 48.  No LDS traffic, unlike shuffle-based reductions.
-__device__ inline float wave_sum(float v)
+// Sum over the 16 lanes of each row of a wave, in every lane: quad swap, quad-pair swap, half-row
+// mirror, row mirror.
+__device__ inline float row_sum(float v)
 {
     v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xF, 0xF, false));  // quad_perm [1,0,3,2]
     v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4E, 0xF, 0xF, false));  // quad_perm [2,3,0,1]
     v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x141, 0xF, 0xF, false)); // row_half_mirror
     v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x140, 0xF, 0xF, false)); // row_mirror
+    return v;
+}
+
+// Sum over the 64 lanes of a wave, in every lane: the rows' sums from lanes 0, 16, 32, 48.
+__device__ inline float wave_sum(float v)
+{
+    v = row_sum(v);
     const float r0 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 0));
     const float r1 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 16));
     const float r2 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 32));
     const float r3 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 48));
     return (r0 + r1) + (r2 + r3);
+}
+
+// The sums of P values per lane over the 64 lanes of a wave, to out[0 .. P) (LDS).  The two
+// row-swap steps each add two values at once and leave their sums in different rows of lanes, so
+// the P values shrink to P / 4 registers before the four steps inside a row: about 2.5
+// instructions per value, where summing one value after the other takes eleven (the reduction at the
+// end of the pair-sum kernels at n = 8: 2.2 -> 0.5 us).
+template <int P>
+__device__ inline void wave_sums(const float (&acc)[P], float *out)
+{
+    constexpr int P2 = (P + 1) / 2, P4 = (P2 + 1) / 2;
+    float a[2 * P4];
+    a[2 * P4 - 1] = 0.f;
+#pragma unroll
+    for (int k = 0; k < P2; ++k) { // lanes 0..31: value 2k, lanes 32..63: value 2k + 1
+        const unsigned lo = __float_as_uint(acc[2 * k]), hi = (2 * k + 1 < P) ? __float_as_uint(acc[2 * k + 1 < P ? 2 * k + 1 : 0]) : 0u;
+        const auto r = __builtin_amdgcn_permlane32_swap(lo, hi, false, false);
+        a[k] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    }
+    float b[P4];
+#pragma unroll
+    for (int k = 0; k < P4; ++k) { // rows 0..3: values 4k, 4k + 2, 4k + 1, 4k + 3
+        const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a[2 * k]), __float_as_uint(a[2 * k + 1]), false, false);
+        b[k] = row_sum(__uint_as_float(r[0]) + __uint_as_float(r[1]));
+    }
+    const int row = (threadIdx.x & 63) >> 4;
+    const int sub = ((row & 1) << 1) | (row >> 1);
+    if ((threadIdx.x & 15) == 0) {
+#pragma unroll
+        for (int k = 0; k < P4; ++k)
+            if (4 * k + 3 < P || 4 * k + sub < P) out[4 * k + sub] = b[k];
+    }
 }
 
 } // namespace svgd

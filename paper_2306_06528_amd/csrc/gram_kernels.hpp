@@ -5,6 +5,7 @@
 // a few columns on chip, adds their contribution to every pair, and moves on.
 #pragma once
 #include <type_traits>
+#include "bandwidth_kernels.hpp"
 #include "common.hpp"
 
 namespace svgd {
@@ -15,8 +16,9 @@ namespace svgd {
 // accumulator per pair in registers.
 //   N <= 8 : direct differences (x_i - x_j)^2 - no cancellation at all.
 //   N  > 8 : Gram of the column-centred y = x - mean_i(x); d2 = S_ii + S_jj - 2 S_ij later.
-// Chains are short (D / (4 * threads) terms per accumulator); lanes are combined by DPP adds,
-// waves through LDS, workgroups in fp64 by the reduce kernel.
+// Chains are short (D / (4 * threads) terms per accumulator); lanes are combined by row swaps and
+// DPP adds, waves through LDS, workgroups in fp64 by the kernel that needs the sums (or, for a long list,
+// by the reduce kernel).
 // ---------------------------------------------------------------------------------------------
 
 // One 4-column group's contribution to every pair sum: acc[tri(i, j, N)] += sum over the 4
@@ -101,15 +103,10 @@ __global__ __launch_bounds__(256) void gram_valu_kernel(const float *__restrict_
     }
 
     __shared__ float red[4][P];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-    for (int p = 0; p < P; ++p) {
-        const float v = wave_sum(acc[p]);
-        if (lane == 0) red[wave][p] = v;
-    }
+    wave_sums<P>(acc, red[threadIdx.x >> 6]);
     __syncthreads();
     for (int p = threadIdx.x; p < P; p += 256)
-        partials[(int64_t)blockIdx.x * P + p] = (red[0][p] + red[1][p]) + (red[2][p] + red[3][p]);
+        partials[(int64_t)blockIdx.x * pair_stride(N) + p] = (red[0][p] + red[1][p]) + (red[2][p] + red[3][p]);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -327,8 +324,7 @@ __global__ __launch_bounds__(64 * kGramWaves) void gram_mfma_kernel(const float 
     }
     __syncthreads();
     if (wave == 0) {
-        const int P = n * (n + 1) / 2;
-        float *out = partials + (int64_t)blockIdx.x * P;
+        float *out = partials + (int64_t)blockIdx.x * pair_stride(n);
         int p = 0;
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
@@ -349,29 +345,48 @@ __global__ __launch_bounds__(64 * kGramWaves) void gram_mfma_kernel(const float 
     }
 }
 
-// Sum the per-workgroup fp32 partials in fp64, split into gridDim.y interleaved slices so that
-// many threads share the work: part2[slice][p] = sum_{k = slice (mod nslices)} partials[k][p]
-// (zero for a slice with no partials).
-__global__ __launch_bounds__(256) void reduce_partials_kernel(const float *__restrict__ partials,
-                                                              int nparts, int P,
-                                                              double *__restrict__ part2)
+// Sum the per-workgroup fp32 partials in fp64: sums[p] = sum_k partials[k][p].  A workgroup takes 32
+// entries, eight lanes of four next to each other, and thread group g of 32 the partials g, g + 32,
+// ... with sixteen 16-byte loads in flight: the 512 partials of a large problem are one batch of
+// loads and one LDS exchange, and the result is the sums themselves, not slices for the next kernel
+// to add.  3.7 us at n = 20, 4.7 at n = 32 and 64 (4.9, 4.9 and 4.8 with eight slices read four
+// bytes at a time): the launch, one trip to memory the partials were just written to, the exchange.
+constexpr int kReduceEntries = 32;
+__global__ __launch_bounds__(256) void reduce_partials_kernel(const float *__restrict__ partials, int nparts, int n,
+                                                              double *__restrict__ sums)
 {
-    const int p = blockIdx.x * 256 + threadIdx.x;
-    const int slice = blockIdx.y, nslices = gridDim.y;
-    if (p >= P) return;
-    double s = 0.0;
-    constexpr int U = 16; // loads in flight per thread
-    for (int k = slice; k < nparts; k += U * nslices) {
-        float v[U];
+    constexpr int U = 16, GROUPS = 32;
+    __shared__ double red[GROUPS][kReduceEntries + 1];
+    const int stride4 = pair_stride(n) / 4, P = n * (n + 1) / 2;
+    const int col = threadIdx.x & 7, g = threadIdx.x >> 3;
+    const int c4 = (int)blockIdx.x * (kReduceEntries / 4) + col;
+    const f32x4 *src = reinterpret_cast<const f32x4 *>(partials) + (c4 < stride4 ? c4 : stride4 - 1);
+    double s[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int k0 = g; k0 < nparts; k0 += U * GROUPS) {
+        f32x4 v[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) { // unconditional loads (index clamped) issue together
-            const int ku = k + u * nslices;
-            v[u] = partials[(int64_t)(ku < nparts ? ku : nparts - 1) * P + p];
+            const int k = k0 + u * GROUPS;
+            v[u] = src[(int64_t)(k < nparts ? k : nparts - 1) * stride4];
         }
 #pragma unroll
-        for (int u = 0; u < U; ++u) s += (k + u * nslices < nparts) ? (double)v[u] : 0.0;
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) s[c] += (k0 + u * GROUPS < nparts) ? (double)v[u][c] : 0.0;
     }
-    part2[(int64_t)slice * P + p] = s;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) red[g][4 * col + c] = s[c];
+    __syncthreads();
+    // thread (e, part): four of the 32 groups' sums of entry e, then across the eight parts
+    const int e = threadIdx.x >> 3, part = threadIdx.x & 7;
+    double t = 0.0;
+#pragma unroll
+    for (int k = 0; k < GROUPS / 8; ++k) t += red[part * (GROUPS / 8) + k][e];
+    t += dpp_f64<0xB1>(t);
+    t += dpp_f64<0x4E>(t);
+    t += dpp_f64<0x141>(t);
+    const int p = (int)blockIdx.x * kReduceEntries + e;
+    if (part == 0 && p < P) sums[p] = t;
 }
 
 } // namespace svgd

@@ -3,7 +3,6 @@
 
 #include <algorithm>
 #include <cmath>
-#include <cstdlib>
 #include <mutex>
 #include <new>
 #include <unordered_set>
@@ -48,8 +47,8 @@ struct svgd_ctx {
     unsigned sweeps;          // in-place updates with carried sums so far: every other one walks X backwards
     int last_n; // 0 = nothing computed yet
     int last_hip_error;
-    float *partials;  // [kMaxParts][P]
-    double *part2;    // [kSlices][P]
+    float *partials;  // [kMaxParts][pair_stride]
+    double *sums;     // [P], the reduced pair sums
     DevState *state;
     float *coef;      // kCoefFloats
     // optional per-kernel timing (svgd_profile_begin/end): event pairs recorded around launches
@@ -149,25 +148,18 @@ void launch_gram_valu(const float *X, int64_t D, int64_t ld, float *partials, in
         gram_valu_kernel<N, false><<<grid, 256, 0, s>>>(X, D, ld, partials, NoRows{});
 }
 
-template <int N, bool EMIT, bool CARRY>
+template <int N, bool EMIT, bool CARRY, bool FUSED>
 void launch_update_valu(float *X, const float *G, float *PHI, float *coef, DevState *st,
                         int64_t D, int64_t ld, float eps, float *gram_out, int grid, hipStream_t s,
-                        const RowTable *rt, const FusedArgs &ua)
+                        const RowTable *rt, const UpdateArgs &ua)
 {
     if constexpr (!EMIT && !CARRY) {
         if (rt) {
-            update_valu_kernel<N, false, false, true><<<grid, 256, 0, s>>>(X, G, PHI, coef, st, D, ld, eps, gram_out, *rt, ua);
+            update_valu_kernel<N, false, false, true, FUSED><<<grid, 256, 0, s>>>(X, G, PHI, coef, st, D, ld, eps, gram_out, *rt, ua);
             return;
         }
     }
-    update_valu_kernel<N, EMIT, CARRY, false><<<grid, 256, 0, s>>>(X, G, PHI, coef, st, D, ld, eps, gram_out, NoRows{}, ua);
-}
-
-template <int N>
-void launch_update_valu_fused(float *X, const float *G, float *coef, DevState *st, int64_t D, int64_t ld, float eps,
-                              float *gram_out, int grid, hipStream_t s, const FusedArgs &fa)
-{
-    update_valu_kernel<N, false, true, false, true><<<grid, 256, 0, s>>>(X, G, nullptr, coef, st, D, ld, eps, gram_out, NoRows{}, fa);
+    update_valu_kernel<N, EMIT, CARRY, false, FUSED><<<grid, 256, 0, s>>>(X, G, PHI, coef, st, D, ld, eps, gram_out, NoRows{}, ua);
 }
 
 #define SVGD_SWITCH_N(n, CALL)                                                                     \
@@ -193,8 +185,7 @@ int mini(int a, int b) { return a < b ? a : b; }
 // grid whose workgroups write one partial each.
 int max_parts(const svgd_ctx *c, int n)
 {
-    const int64_t P = (int64_t)n * (n + 1) / 2;
-    const int64_t m = c->partials_cap / P;
+    const int64_t m = c->partials_cap / pair_stride(n);
     return (int)(m < kMaxParts ? m : kMaxParts);
 }
 
@@ -223,46 +214,42 @@ bool adjacent_tiles(int n, int64_t ld) { return n > 48 || beyond_cache(n, ld); }
 // 258 -> 241 us; from n = 25 on the gain is below the cost of the longer list of partial sums,
 // with 16 or 32 particles the second workgroup costs 2-5 %, and for an X that cache serves it
 // costs 9 %).
-// The Gram pass splits the tiles the same way.
-int update_workers(const svgd_ctx *c, int n, int64_t D, int64_t ld, bool carry)
+// The Gram pass splits the tiles the same way.  `cap` bounds the grid, the tail's workgroup included.
+int update_workers(const svgd_ctx *c, int n, int64_t D, int64_t ld, int cap)
 {
     const int64_t nfull = D / 64;
     const int per_cu = (n >= 17 && n <= 24 && !has_remainder_rows(n) && beyond_cache(n, ld)) ? 2 : 1;
-    const int max_workers = mini(c->num_cu * per_cu, (carry ? max_parts(c, n) : kMaxParts) - 1);
+    const int max_workers = mini(c->num_cu * per_cu, cap - 1);
     return clampi((nfull + 3) / 4, 1, max_workers);
 }
 
-// Passes 1 and 2: Gram partials -> fp64 reduction -> h, K, coefficient tables (all on `s`).
-// With use_carry the partials the previous update left in c->partials stand in for pass 1.
+// A list of pair-sum partials in the handle's scratch.
+struct PairList {
+    int64_t off; // where it starts (floats)
+    int nparts;
+};
+
+// Pass 1: the pair sums of X, one partial per workgroup, at the start of the scratch.
 // G_next: where the in-place update that follows this call will read its scores (null: none, or
 // an update that writes phi elsewhere); carry_next: that update will carry pair sums.  Both only
-// steer the order in which pass 1 visits X.
-int run_kernel_matrix(svgd_ctx *c, const float *X, int n, int64_t D, int64_t ld, hipStream_t s, bool use_carry,
-                      const RowTable *rt = nullptr, const float *G_next = nullptr, bool carry_next = false)
+// steer the order in which X is visited.
+int run_gram(svgd_ctx *c, const float *X, int n, int64_t D, int64_t ld, hipStream_t s, PairList &list,
+             const RowTable *rt = nullptr, const float *G_next = nullptr, bool carry_next = false)
 {
-    const int P = n * (n + 1) / 2;
     const int cap_parts = max_parts(c, n);
-    int nparts, mode;
-    const float *partials = c->partials; // where the list of partials for pass 2 starts
+    int nparts;
     // streaming loads in pass 1: X well beyond what the memory-side cache could keep for the update
     const bool big_x = (int64_t)n * ld * (int64_t)sizeof(float) > 2 * kMemorySideCacheBytes;
     const bool x_aligned = rt ? rt->aligned != 0 : rows_aligned(X, ld);
-    if (use_carry) {
-        nparts = c->carry_nparts;
-        partials += c->carry_off;
-        mode = (n <= 8) ? kModeDiff : kModeGram; // the update kernels mirror the Gram kernels' formats
-    } else if (n <= kValuMaxN) {
+    KernelTimer t(c, SVGD_KERNEL_GRAM, s);
+    if (n <= kValuMaxN) {
         const int64_t ngroups = (D + 3) / 4;
         nparts = clampi((ngroups + 255) / 256, 1, mini(c->num_cu * 3, cap_parts)); // all resident at once; each ends with a reduction
-        mode = (n <= 8) ? kModeDiff : kModeGram;
         const bool stream_x = big_x;
-        KernelTimer t(c, SVGD_KERNEL_GRAM, s);
 #define CALL(N) launch_gram_valu<N>(X, D, ld, c->partials, nparts, s, rt, stream_x)
         SVGD_SWITCH_N(n, CALL)
 #undef CALL
     } else {
-        KernelTimer t(c, SVGD_KERNEL_GRAM, s);
-        mode = kModeGram;
         const int NB = (n + 15) / 16;
         const int64_t nfull = D / 64;
         nparts = clampi((D + 255) / 256, 1, mini(c->num_cu * 2, cap_parts));
@@ -270,7 +257,7 @@ int run_kernel_matrix(svgd_ctx *c, const float *X, int n, int64_t D, int64_t ld,
         // tiles three quarters of the memory-side cache can hold
         const bool aligned_next = G_next && x_aligned && (rt || rows_aligned(G_next, ld));
         const bool shared_ranges = aligned_next && adjacent_tiles(n, ld);
-        int64_t nranges = (int64_t)update_workers(c, n, D, ld, carry_next) * (shared_ranges ? 1 : 4);
+        int64_t nranges = (int64_t)update_workers(c, n, D, ld, carry_next ? cap_parts : kMaxParts) * (shared_ranges ? 1 : 4);
         int64_t per = (nfull + nranges - 1) / nranges > 0 ? (nfull + nranges - 1) / nranges : 1;
         int64_t hot = (3 * kMemorySideCacheBytes / 4) / ((int64_t)n * 256) / nranges;
         if (shared_ranges) hot &= ~(int64_t)3; // four waves share the start of a range
@@ -301,184 +288,153 @@ int run_kernel_matrix(svgd_ctx *c, const float *X, int n, int64_t D, int64_t ld,
         else GRAM(4);
 #undef GRAM
     }
+    list.off = 0;
+    list.nparts = nparts;
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(c, e);
+    return SVGD_OK;
+}
 
-    // few partials of few pairs: the bandwidth kernel sums them itself
-    const bool direct = P <= kBwThreads && (int64_t)nparts * P <= kDirectMaxFloats;
-    if (!direct) {
-        KernelTimer t(c, SVGD_KERNEL_REDUCE, s);
-        reduce_partials_kernel<<<dim3((P + 255) / 256, kSlices), 256, 0, s>>>(partials, nparts, P, c->part2);
-    }
-    e = hipGetLastError();
+// The list as the source of pass 2: as it is, or - longer than `max_floats` - reduced first.
+int sum_source(svgd_ctx *c, int n, const PairList &list, int max_floats, hipStream_t s, SumSource &src)
+{
+    const int stride = pair_stride(n);
+    src.sums = nullptr;
+    src.partials = c->partials + list.off;
+    src.nparts = list.nparts;
+    if ((int64_t)list.nparts * stride <= max_floats) return SVGD_OK;
+    KernelTimer t(c, SVGD_KERNEL_REDUCE, s);
+    reduce_partials_kernel<<<(stride + kReduceEntries - 1) / kReduceEntries, 256, 0, s>>>(src.partials, list.nparts, n, c->sums);
+    src.sums = c->sums;
+    hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(c, e);
-    {
-        KernelTimer t(c, SVGD_KERNEL_BANDWIDTH, s);
-        bandwidth_kernel<<<1, kBwThreads, 0, s>>>(c->part2, direct ? partials : nullptr, nparts, n, mode, c->h_fixed,
-                                                  c->state, c->coef);
-    }
-    e = hipGetLastError();
+    return SVGD_OK;
+}
+
+// The Gram kernels' format at this particle count (the update kernels with CARRY mirror it).
+int gram_mode(int n) { return n <= 8 ? kModeDiff : kModeGram; }
+
+// Pass 2 as a kernel of its own: list -> h, K, coefficient tables.
+int run_bandwidth(svgd_ctx *c, int n, const PairList &list, hipStream_t s)
+{
+    SumSource src;
+    int rc = sum_source(c, n, list, kDirectMaxFloats, s, src);
+    if (rc) return rc;
+    KernelTimer t(c, SVGD_KERNEL_BANDWIDTH, s);
+    bandwidth_kernel<<<1, kBwThreads, 0, s>>>(src, BwArgs{n, gram_mode(n), c->h_fixed, std::log((double)n + 1.0)}, c->state, c->coef);
+    hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(c, e);
     c->last_n = n;
     return SVGD_OK;
 }
 
-// Pass 3.  EMIT = false: X updated in place; EMIT = true: phi written to PHI.  CARRY (in-place,
-// the update also leaves the Gram partials of the new X in c->partials.
+// Up to kFusedMaxN particles the update kernel does pass 2 itself, in every workgroup, if the list of
+// partials is short: then the whole second half of a step is one launch.  256 threads hold at most
+// 496 pairs comfortably, and every workgroup reads the whole list.  Where the list is long, summing
+// it in a launch of many workgroups and pass 2 in one of its own are faster on the matrix-core path
+// (n = 20, D = 300,007, 110 K floats: 48 us fused, 39 apart); on the vector-ALU path every list a
+// Gram pass or an update leaves is short enough, and fusing wins up to the largest sizes (n = 8,
+// D = 11,173,962: 281 -> 270 us; n = 10, D = 300,001: 31 -> 24; n = 16, D = 8,577: 15.5 -> 12.2).
+constexpr int kFusedMaxN = 32;
+constexpr int kFusedMaxFloatsValu = 64 * 1024;
+constexpr int kFusedMaxFloatsMfma = 48 * 1024;
+
+// Passes 2 and 3.  EMIT = false: X updated in place; EMIT = true: phi written to PHI.  CARRY (in
+// place): the update also leaves the pair-sum partials of the new X in the scratch, described by
+// `list` on return.
 template <bool EMIT, bool CARRY>
 int run_update(svgd_ctx *c, float *X, const float *G, float *PHI, int n, int64_t D, int64_t ld, float eps,
-               hipStream_t s, const RowTable *rt = nullptr)
+               hipStream_t s, PairList &list, const RowTable *rt = nullptr)
 {
+    UpdateArgs ua{};
+    ua.h_fixed = c->h_fixed;
+    ua.log_n1 = std::log((double)n + 1.0);
+    const int64_t list_floats = (int64_t)list.nparts * pair_stride(n);
+    const int64_t half = (c->partials_cap / 2) & ~(int64_t)63; // CARRY: the list is read while the new one is written
+    const bool fused = n <= kFusedMaxN && list_floats <= (n <= kValuMaxN ? kFusedMaxFloatsValu : kFusedMaxFloatsMfma) && (!CARRY || list_floats <= half);
+    int out_cap = max_parts(c, n);
+    int64_t out_off = 0;
+    if (fused) {
+        ua.src = SumSource{nullptr, c->partials + list.off, list.nparts};
+        if (CARRY) {
+            out_off = list.off == 0 ? half : 0;
+            const int64_t m = half / pair_stride(n);
+            out_cap = (int)(m < kMaxParts ? m : kMaxParts);
+        }
+        c->last_n = n;
+    } else {
+        int rc = run_bandwidth(c, n, list, s);
+        if (rc) return rc;
+    }
+    float *gram_out = c->partials + out_off;
     KernelTimer t(c, SVGD_KERNEL_UPDATE, s);
     // With carried sums one update follows the other with nothing but tiny kernels in between:
     // every other one walks X from the far end, so that it starts on what the previous one
     // touched last (the part of X that the memory-side cache still holds).
-    FusedArgs ua{};
     if (!EMIT && CARRY) ua.reverse = (int)(c->sweeps++ & 1u);
     // the four waves of a workgroup on adjacent tiles: always at n > 48; below only for an X beyond
     // the memory-side cache (n = 32, D = 2,000,000, which just fits it, ran 3 % slower that way)
     ua.adjacent = adjacent_tiles(n, ld);
     if (n <= kValuMaxN) {
         const int64_t ngroups = (D + 3) / 4;
-        // fewer, longer-lived workgroups when each one ends with a reduction of its pair sums
-        // (with the pair sums of 9 to 12 particles in registers only one workgroup fits a CU)
-        const int per_cu = CARRY ? (n <= 8 ? 2 : 1) : 8;
-        const int grid = clampi((ngroups + 255) / 256, 1, mini(c->num_cu * per_cu, CARRY ? max_parts(c, n) : kMaxParts));
-        if (CARRY) {
-            c->carry_nparts = grid;
-            c->carry_off = 0;
-        }
-#define CALL(N) launch_update_valu<N, EMIT, CARRY>(X, G, PHI, c->coef, c->state, D, ld, eps, c->partials, grid, s, rt, ua)
+        // All workgroups resident at once, or the prologue (and with CARRY the reduction of the pair
+        // sums at the end) is paid twice.  Two per CU where that leaves each thread's rows enough
+        // registers for loads in flight: plain step at D = 6,000,000, one against two per CU, n = 9
+        // 182 / 168 us, n = 12 235 / 240; at D = 1,000,000 44 / 38 and 57 / 64.
+        const int per_cu = n <= (CARRY ? 8 : 10) ? 2 : 1;
+        const int grid = clampi((ngroups + 255) / 256, 1, mini(c->num_cu * per_cu, CARRY ? out_cap : kMaxParts));
+        if (CARRY) list = PairList{out_off, grid};
+#define CALL(N)                                                                                                      \
+    if (fused) launch_update_valu<N, EMIT, CARRY, true>(X, G, PHI, c->coef, c->state, D, ld, eps, gram_out, grid, s, rt, ua); \
+    else launch_update_valu<N, EMIT, CARRY, false>(X, G, PHI, c->coef, c->state, D, ld, eps, gram_out, grid, s, rt, ua)
         SVGD_SWITCH_N(n, CALL)
 #undef CALL
     } else {
         // workers walk contiguous ranges of full 64-column tiles; one more workgroup does D mod 64
-        const int grid = update_workers(c, n, D, ld, CARRY) + 1;
-        const int NB = (n + 15) / 16;
-        if (CARRY) { // one partial per workgroup, the tail's included
-            c->carry_nparts = grid;
-            c->carry_off = 0;
-        }
+        const int grid = update_workers(c, n, D, ld, CARRY ? out_cap : kMaxParts) + 1;
+        if (CARRY) list = PairList{out_off, grid}; // one partial per workgroup, the tail's included
         // rows that all start on a 128-byte boundary (X's and G's) need no re-aligned stores and
         // can be read with streaming loads
         const bool aligned = !EMIT && (rt ? rt->aligned != 0 : rows_aligned(X, ld) && rows_aligned(G, ld));
-#define UPD(NBV, FULL)                                                                                       \
-    do {                                                                                                     \
-        if (!EMIT && !CARRY && rt && aligned)                                                                \
-            update_mfma_kernel<NBV, false, FULL, false, true, true><<<grid, 256, 0, s>>>(X, G, PHI, c->coef, c->state, n, D, ld, eps, c->partials, *rt, ua); \
-        else if (!EMIT && !CARRY && rt)                                                                      \
-            update_mfma_kernel<NBV, false, FULL, false, false, true><<<grid, 256, 0, s>>>(X, G, PHI, c->coef, c->state, n, D, ld, eps, c->partials, *rt, ua); \
-        else if (!EMIT && aligned)                                                                           \
-            update_mfma_kernel<NBV, false, FULL, CARRY, true, false><<<grid, 256, 0, s>>>(X, G, PHI, c->coef, c->state, n, D, ld, eps, c->partials, NoRows{}, ua); \
-        else if (CARRY && ua.reverse)                                                                        \
-            update_mfma_kernel<NBV, false, FULL, CARRY, false, false, false, CARRY><<<grid, 256, 0, s>>>(X, G, PHI, c->coef, c->state, n, D, ld, eps, c->partials, NoRows{}, ua); \
-        else                                                                                                 \
-            update_mfma_kernel<NBV, EMIT, FULL, CARRY, false, false><<<grid, 256, 0, s>>>(X, G, PHI, c->coef, c->state, n, D, ld, eps, c->partials, NoRows{}, ua); \
+#define UPD_F(NB, FULL, REM, F)                                                                                      \
+    do {                                                                                                             \
+        if (!EMIT && !CARRY && rt && aligned)                                                                        \
+            update_mfma_kernel<NB, false, FULL, false, true, true, F, false, REM><<<grid, 256, 0, s>>>(X, G, PHI, c->coef, c->state, n, D, ld, eps, gram_out, *rt, ua); \
+        else if (!EMIT && !CARRY && rt)                                                                              \
+            update_mfma_kernel<NB, false, FULL, false, false, true, F, false, REM><<<grid, 256, 0, s>>>(X, G, PHI, c->coef, c->state, n, D, ld, eps, gram_out, *rt, ua); \
+        else if (!EMIT && aligned)                                                                                   \
+            update_mfma_kernel<NB, false, FULL, CARRY, true, false, F, false, REM><<<grid, 256, 0, s>>>(X, G, PHI, c->coef, c->state, n, D, ld, eps, gram_out, NoRows{}, ua); \
+        else if (CARRY && ua.reverse)                                                                                \
+            update_mfma_kernel<NB, false, FULL, CARRY, false, false, F, CARRY, REM><<<grid, 256, 0, s>>>(X, G, PHI, c->coef, c->state, n, D, ld, eps, gram_out, NoRows{}, ua); \
+        else                                                                                                         \
+            update_mfma_kernel<NB, EMIT, FULL, CARRY, false, false, F, false, REM><<<grid, 256, 0, s>>>(X, G, PHI, c->coef, c->state, n, D, ld, eps, gram_out, NoRows{}, ua); \
+    } while (0)
+#define UPD(NB, FULL, REM)                                                                                           \
+    do {                                                                                                             \
+        constexpr bool F = NB == 1 || (NB == 2 && !REM); /* n <= kFusedMaxN */                                       \
+        if (F && fused) UPD_F(NB, FULL, REM, F);                                                                     \
+        else UPD_F(NB, FULL, REM, false);                                                                            \
     } while (0)
         // one to four particles beyond a multiple of 16 ride along as remainder rows of the kernel
         // for that multiple
-#define UPD_REM(NBV)                                                                                         \
-    do {                                                                                                     \
-        if (!EMIT && !CARRY && rt && aligned)                                                                \
-            update_mfma_kernel<NBV, false, true, false, true, true, false, false, true><<<grid, 256, 0, s>>>(X, G, PHI, c->coef, c->state, n, D, ld, eps, c->partials, *rt, ua); \
-        else if (!EMIT && !CARRY && rt)                                                                      \
-            update_mfma_kernel<NBV, false, true, false, false, true, false, false, true><<<grid, 256, 0, s>>>(X, G, PHI, c->coef, c->state, n, D, ld, eps, c->partials, *rt, ua); \
-        else if (!EMIT && aligned)                                                                           \
-            update_mfma_kernel<NBV, false, true, CARRY, true, false, false, false, true><<<grid, 256, 0, s>>>(X, G, PHI, c->coef, c->state, n, D, ld, eps, c->partials, NoRows{}, ua); \
-        else if (CARRY && ua.reverse)                                                                        \
-            update_mfma_kernel<NBV, false, true, CARRY, false, false, false, CARRY, true><<<grid, 256, 0, s>>>(X, G, PHI, c->coef, c->state, n, D, ld, eps, c->partials, NoRows{}, ua); \
-        else                                                                                                 \
-            update_mfma_kernel<NBV, EMIT, true, CARRY, false, false, false, false, true><<<grid, 256, 0, s>>>(X, G, PHI, c->coef, c->state, n, D, ld, eps, c->partials, NoRows{}, ua); \
-    } while (0)
         const bool rem = has_remainder_rows(n);
-        if (rem && n < 32) UPD_REM(1);
-        else if (rem && n < 48) UPD_REM(2);
-        else if (rem) UPD_REM(3);
-        else if (n == 16) UPD(1, true);
-        else if (NB == 1) UPD(1, false);
-        else if (n == 32) UPD(2, true);
-        else if (n == 48) UPD(3, true);
-        else if (n == 64) UPD(4, true);
-        else if (NB == 2) UPD(2, false);
-        else if (NB == 3) UPD(3, false);
-        else UPD(4, false);
-#undef UPD_REM
+        const int NB = (n + 15) / 16;
+        if (rem && n < 32) UPD(1, true, true);
+        else if (rem && n < 48) UPD(2, true, true);
+        else if (rem) UPD(3, true, true);
+        else if (n == 16) UPD(1, true, false);
+        else if (NB == 1) UPD(1, false, false);
+        else if (n == 32) UPD(2, true, false);
+        else if (n == 48) UPD(3, true, false);
+        else if (n == 64) UPD(4, true, false);
+        else if (NB == 2) UPD(2, false, false);
+        else if (NB == 3) UPD(3, false, false);
+        else UPD(4, false, false);
 #undef UPD
+#undef UPD_F
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(c, e);
-    return SVGD_OK;
-}
-
-// The fused step: one launch that starts with pass 2 in every workgroup (from the partials the
-// previous update left at carry_off), updates X and leaves the partials of the new X in the other
-// half of the scratch.  For short lists only: every workgroup reads the whole list.
-// Every workgroup sums the whole list with its 256 threads - by groups of threads when there are few
-// pairs (see kernel_matrix_prologue) - so what bounds the prologue is the number of partials one
-// thread adds up, one dependent batch of 16 loads after the other.
-constexpr int kFusedMaxChain = 160;
-
-bool can_fuse(const svgd_ctx *c, int n)
-{
-    const int64_t P = (int64_t)n * (n + 1) / 2, half = (c->partials_cap / 2) & ~(int64_t)63;
-    // On the matrix-core path (n > 12) the prologue runs with one wave per SIMD and measured slower
-    // than the two launches it replaces (n = 16, D = 8,577: 15.1 against 12.4 us per step): only on request.
-    const int max_n = (c->flags & SVGD_FLAG_FUSE_MFMA) ? 32 : kValuMaxN;
-    if (n > max_n || (int64_t)c->carry_nparts * P > half) return false;
-    int64_t chain;
-    if (2 * P <= 256) {
-        const int64_t KL = 256 / P < 32 ? 256 / P : 32;
-        chain = (c->carry_nparts + KL - 1) / KL;
-    } else {
-        chain = (int64_t)c->carry_nparts * ((P + 255) / 256);
-    }
-    return chain <= kFusedMaxChain;
-}
-
-int run_update_fused(svgd_ctx *c, float *X, const float *G, int n, int64_t D, int64_t ld, float eps, hipStream_t s)
-{
-    KernelTimer t(c, SVGD_KERNEL_UPDATE, s);
-    const int64_t P = (int64_t)n * (n + 1) / 2, half = (c->partials_cap / 2) & ~(int64_t)63;
-    const FusedArgs fa{c->partials + c->carry_off, c->carry_nparts, c->h_fixed, (int)(c->sweeps++ & 1u), 0};
-    const int64_t out_off = c->carry_off == 0 ? half : 0;
-    float *gram_out = c->partials + out_off;
-    const int cap = (int)(half / P < kMaxParts ? half / P : kMaxParts); // partials that fit into a half
-    int grid;
-    if (n <= kValuMaxN) {
-        const int64_t ngroups = (D + 3) / 4;
-        // all workgroups resident at once (9 to 12 particles: one per CU), or the prologue is paid twice
-        grid = clampi((ngroups + 255) / 256, 1, mini(c->num_cu * (n <= 8 ? 2 : 1), cap));
-#define CALL(N) launch_update_valu_fused<N>(X, G, c->coef, c->state, D, ld, eps, gram_out, grid, s, fa)
-        SVGD_SWITCH_N(n, CALL)
-#undef CALL
-    } else {
-        const int64_t nfull = D / 64;
-        grid = clampi((nfull + 3) / 4, 1, mini(c->num_cu, cap - 1)) + 1;
-        const bool aligned = rows_aligned(X, ld) && rows_aligned(G, ld);
-#define UPD(NBV, FULL)                                                                                       \
-    do {                                                                                                     \
-        if (aligned)                                                                                         \
-            update_mfma_kernel<NBV, false, FULL, true, true, false, true><<<grid, 256, 0, s>>>(X, G, nullptr, c->coef, c->state, n, D, ld, eps, gram_out, NoRows{}, fa); \
-        else                                                                                                 \
-            update_mfma_kernel<NBV, false, FULL, true, false, false, true><<<grid, 256, 0, s>>>(X, G, nullptr, c->coef, c->state, n, D, ld, eps, gram_out, NoRows{}, fa); \
-    } while (0)
-        if (has_remainder_rows(n)) { // 17..20
-            if (aligned)
-                update_mfma_kernel<1, false, true, true, true, false, true, false, true><<<grid, 256, 0, s>>>(X, G, nullptr, c->coef, c->state, n, D, ld, eps, gram_out, NoRows{}, fa);
-            else
-                update_mfma_kernel<1, false, true, true, false, false, true, false, true><<<grid, 256, 0, s>>>(X, G, nullptr, c->coef, c->state, n, D, ld, eps, gram_out, NoRows{}, fa);
-        }
-        else if (n == 16) UPD(1, true);
-        else if (n < 16) UPD(1, false);
-        else if (n == 32) UPD(2, true);
-        else UPD(2, false);
-#undef UPD
-    }
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return fail(c, e);
-    c->carry_nparts = grid;
-    c->carry_off = out_off;
-    c->last_n = n;
     return SVGD_OK;
 }
 
@@ -491,7 +447,7 @@ int run_tiny(svgd_ctx *c, float *X, const float *G, float *PHI, int n, int64_t D
 {
     {
         KernelTimer t(c, WHAT == kTinyBandwidth ? SVGD_KERNEL_BANDWIDTH : SVGD_KERNEL_UPDATE, s);
-#define TINY(N) step_tiny_kernel<N, WHAT><<<1, kTinyThreads, 0, s>>>(X, G, PHI, D, ld, eps, c->h_fixed, c->state, c->coef)
+#define TINY(N) step_tiny_kernel<N, WHAT><<<1, kTinyThreads, 0, s>>>(X, G, PHI, D, ld, eps, c->h_fixed, std::log(n + 1.0), c->state, c->coef)
         switch (n) {
         case 1: TINY(1); break;
         case 2: TINY(2); break;
@@ -516,11 +472,11 @@ int run_tiny(svgd_ctx *c, float *X, const float *G, float *PHI, int n, int64_t D
 // ---------------------------------------------------------------------------------------------
 constexpr int kStaticMaxParts = 528;                         // partial vectors of n(n+1)/2 <= 2080 floats: 2 * 256 + 1 fit
 constexpr size_t kStaticPartialsBytes = (size_t)kStaticMaxParts * kMaxPairsFull * sizeof(float);
-constexpr size_t kStaticPart2Bytes = (size_t)kSlices * kMaxPairsFull * sizeof(double);
+constexpr size_t kStaticSumsBytes = (size_t)kMaxPairsFull * sizeof(double);
 constexpr size_t kStaticCoefBytes = (size_t)kCoefFloats * sizeof(float);
 constexpr size_t kStaticStateBytes = 256;
-constexpr size_t kStaticBytes = kStaticPartialsBytes + kStaticPart2Bytes + kStaticCoefBytes + kStaticStateBytes;
-static_assert(kStaticPartialsBytes % 256 == 0 && kStaticPart2Bytes % 256 == 0 && kStaticCoefBytes % 256 == 0,
+constexpr size_t kStaticBytes = kStaticPartialsBytes + kStaticSumsBytes + kStaticCoefBytes + kStaticStateBytes;
+static_assert(kStaticPartialsBytes % 256 == 0 && kStaticSumsBytes % 256 == 0 && kStaticCoefBytes % 256 == 0,
               "every part of the scratch starts on a 256-byte boundary");
 static_assert(sizeof(DevState) <= kStaticStateBytes, "state block");
 
@@ -577,9 +533,9 @@ svgd_ctx *static_ctx(int dev, int *rc)
     c.last_hip_error = 0;
     c.partials = reinterpret_cast<float *>(ptr);
     c.partials_cap = (int64_t)kStaticMaxParts * kMaxPairsFull;
-    c.part2 = reinterpret_cast<double *>(ptr + kStaticPartialsBytes);
-    c.coef = reinterpret_cast<float *>(ptr + kStaticPartialsBytes + kStaticPart2Bytes);
-    c.state = reinterpret_cast<DevState *>(ptr + kStaticPartialsBytes + kStaticPart2Bytes + kStaticCoefBytes);
+    c.sums = reinterpret_cast<double *>(ptr + kStaticPartialsBytes);
+    c.coef = reinterpret_cast<float *>(ptr + kStaticPartialsBytes + kStaticSumsBytes);
+    c.state = reinterpret_cast<DevState *>(ptr + kStaticPartialsBytes + kStaticSumsBytes + kStaticCoefBytes);
     c.profiling = false;
     c.profile_kinds = 0;
     sc.ready = true;
@@ -618,7 +574,7 @@ int svgd_create(svgd_handle_t *out, int max_n, int64_t max_D, int device_id, uin
     c->last_n = 0;
     c->last_hip_error = 0;
     c->partials = nullptr;
-    c->part2 = nullptr;
+    c->sums = nullptr;
     c->state = nullptr;
     c->coef = nullptr;
     c->profiling = false;
@@ -640,15 +596,15 @@ int svgd_create(svgd_handle_t *out, int max_n, int64_t max_D, int device_id, uin
     if (e != hipSuccess || cus < 1) { delete c; return SVGD_ERR_DEVICE; }
     c->num_cu = cus > 512 ? 512 : cus; // keeps every persistent grid within kMaxParts workgroups
 
-    const size_t P = (size_t)max_n * (max_n + 1) / 2;
+    const size_t P = (size_t)pair_stride(max_n);
     bool ok = hipMalloc(&c->partials, (size_t)kMaxParts * P * sizeof(float)) == hipSuccess &&
-              hipMalloc(&c->part2, (size_t)kSlices * P * sizeof(double)) == hipSuccess &&
+              hipMalloc(&c->sums, P * sizeof(double)) == hipSuccess &&
               hipMalloc(&c->state, sizeof(DevState)) == hipSuccess &&
               hipMalloc(&c->coef, (size_t)kCoefFloats * sizeof(float)) == hipSuccess;
     if (!ok) {
         (void)hipGetLastError();
         (void)hipFree(c->partials);
-        (void)hipFree(c->part2);
+        (void)hipFree(c->sums);
         (void)hipFree(c->state);
         (void)hipFree(c->coef);
         delete c;
@@ -695,7 +651,9 @@ int svgd_bandwidth_ld(svgd_handle_t c, const float *X, int n, int64_t D, int64_t
         rc = run_tiny<kTinyBandwidth>(c, const_cast<float *>(X), nullptr, nullptr, n, D, ld, 0.f, s);
     } else {
         c->carry_valid = false; // the partials buffer is about to be overwritten
-        rc = run_kernel_matrix(c, X, n, D, ld, s, false);
+        PairList list;
+        rc = run_gram(c, X, n, D, ld, s, list);
+        if (!rc) rc = run_bandwidth(c, n, list, s);
     }
     if (rc) return rc;
     if (h_out_host) {
@@ -729,16 +687,17 @@ int svgd_step_ld(svgd_handle_t c, float *X, const float *G, int n, int64_t D, in
                            c->carry_D == D && c->carry_ld == ld && c->carry_stream == s;
     c->carry_valid = false;
     if (is_tiny(n, D)) return run_tiny<kTinyStep>(c, X, G, nullptr, n, D, ld, eps, s);
-    if (use_carry && can_fuse(c, n)) {
-        rc = run_update_fused(c, X, G, n, D, ld, eps, s); // the whole step in one launch
-    } else {
-        rc = run_kernel_matrix(c, X, n, D, ld, s, use_carry, nullptr, G, carry_mode);
+    PairList list{c->carry_off, c->carry_nparts};
+    if (!use_carry) {
+        rc = run_gram(c, X, n, D, ld, s, list, nullptr, G, carry_mode);
         if (rc) return rc;
-        if (!use_carry) c->sweeps = 0; // a Gram pass ends at the near end of X: the update starts there
-        if (!carry_mode) return run_update<false, false>(c, X, G, nullptr, n, D, ld, eps, s);
-        rc = run_update<false, true>(c, X, G, nullptr, n, D, ld, eps, s);
+        c->sweeps = 0; // a Gram pass ends at the near end of X: the update starts there
     }
+    if (!carry_mode) return run_update<false, false>(c, X, G, nullptr, n, D, ld, eps, s, list);
+    rc = run_update<false, true>(c, X, G, nullptr, n, D, ld, eps, s, list);
     if (rc) return rc;
+    c->carry_off = list.off;
+    c->carry_nparts = list.nparts;
     c->carry_valid = true;
     c->carry_X = X;
     c->carry_n = n;
@@ -790,9 +749,10 @@ int svgd_step_rows(svgd_handle_t c, float *const *X_rows, const float *const *G_
     c->carry_valid = false; // the partials buffer is about to be overwritten; nothing is carried for separate rows
     float *X = X_rows[0];
     const float *G = G_rows[0];
-    rc = run_kernel_matrix(c, X, n, D, D, s, false, &rt);
+    PairList list;
+    rc = run_gram(c, X, n, D, D, s, list, &rt);
     if (rc) return rc;
-    return run_update<false, false>(c, X, G, nullptr, n, D, D, eps, s, &rt);
+    return run_update<false, false>(c, X, G, nullptr, n, D, D, eps, s, list, &rt);
 }
 
 int svgd_phi_ld(svgd_handle_t c, const float *X, const float *G, int n, int64_t D, int64_t ld, float *PHI,
@@ -808,9 +768,10 @@ int svgd_phi_ld(svgd_handle_t c, const float *X, const float *G, int n, int64_t 
     hipStream_t s = (hipStream_t)stream;
     if (is_tiny(n, D)) return run_tiny<kTinyPhi>(c, const_cast<float *>(X), G, PHI, n, D, ld, 0.f, s);
     c->carry_valid = false; // the partials buffer is about to be overwritten
-    rc = run_kernel_matrix(c, X, n, D, ld, s, false);
+    PairList list;
+    rc = run_gram(c, X, n, D, ld, s, list);
     if (rc) return rc;
-    return run_update<true, false>(c, const_cast<float *>(X), G, PHI, n, D, ld, 0.f, s);
+    return run_update<true, false>(c, const_cast<float *>(X), G, PHI, n, D, ld, 0.f, s, list);
 }
 
 int svgd_phi(svgd_handle_t c, const float *X, const float *G, int n, int64_t D, float *PHI, void *stream)
@@ -837,9 +798,10 @@ int svgd_step_static(float *X, const float *G, int n, int64_t D, int64_t ld, flo
     // the coefficient tables by the passes after it): nothing has to start at zero.
     hipStream_t s = (hipStream_t)stream;
     if (is_tiny(n, D)) return run_tiny<kTinyStep>(c, X, G, nullptr, n, D, ld, eps, s);
-    rc = run_kernel_matrix(c, X, n, D, ld, s, false, nullptr, G, false);
+    PairList list;
+    rc = run_gram(c, X, n, D, ld, s, list, nullptr, G, false);
     if (rc) return rc;
-    return run_update<false, false>(c, X, G, nullptr, n, D, ld, eps, s);
+    return run_update<false, false>(c, X, G, nullptr, n, D, ld, eps, s, list);
 }
 
 int svgd_get_last(svgd_handle_t c, double *h_out, float *K_host, void *stream)
@@ -1000,7 +962,7 @@ int svgd_destroy(svgd_handle_t c)
     {
         DeviceGuard guard(c->device);
         if ((t = hipFree(c->partials)) != hipSuccess) e = t;
-        if ((t = hipFree(c->part2)) != hipSuccess) e = t;
+        if ((t = hipFree(c->sums)) != hipSuccess) e = t;
         if ((t = hipFree(c->state)) != hipSuccess) e = t;
         if ((t = hipFree(c->coef)) != hipSuccess) e = t;
         for (hipEvent_t ev : c->ev_pool) (void)hipEventDestroy(ev);

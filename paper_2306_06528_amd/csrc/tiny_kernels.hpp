@@ -24,16 +24,16 @@ template <int N, int WHAT>
 __global__ __launch_bounds__(kTinyThreads) void step_tiny_kernel(float *__restrict__ X,
                                                                const float *__restrict__ G,
                                                                float *__restrict__ PHI, int64_t D, int64_t ld,
-                                                               float eps, double h_fixed,
+                                                               float eps, double h_fixed, double log_n1,
                                                                DevState *__restrict__ st,
                                                                float *__restrict__ coef)
 {
     static_assert(N <= kTinyMaxN, "direct differences only");
     constexpr int P = N * (N + 1) / 2;
-    __shared__ BwShared sh;
+    __shared__ BwShared<kTinyMaxN, kTinyThreads> sh;
     __shared__ float cl[N * N + N]; // C, then rho
+    __shared__ float red[kTinyThreads / 64][P];
     const int tid = threadIdx.x;
-    const int lane = tid & 63, wave = tid >> 6;
     const int64_t ngroups = (D + 3) >> 2;
 
     // pass 1: pair sums over the columns in the format of gram_valu_kernel<N>, lanes = 4-column groups
@@ -48,23 +48,23 @@ __global__ __launch_bounds__(kTinyThreads) void step_tiny_kernel(float *__restri
         for (int j = 0; j < N; ++j) x[j] = load4(X + (int64_t)j * ld, col, D, full);
         pair_accumulate<N>(x, acc);
     }
-    double *red = sh.pr; // [kTinyThreads / 64][P], free until the bandwidth computation's first barrier
-#pragma unroll
-    for (int p = 0; p < P; ++p) {
-        const float v = wave_sum(acc[p]);
-        if (lane == 0) red[wave * P + p] = (double)v;
-    }
+    wave_sums<P>(acc, red[tid >> 6]);
     __syncthreads();
-    if (tid < P) {
-        double s = 0.0;
-        for (int w = 0; w < kTinyThreads / 64; ++w) s += red[w * P + tid];
-        sh.S[tid] = s;
-    }
 
     // pass 2
-    const double h = bandwidth_from_sums<kTinyThreads>(sh, N, kModeDiff, h_fixed, st, coef, cl);
-    __syncthreads();
-    const float c2h = (N == 1) ? 0.f : (float)(2.0 / h);
+    float c2h;
+    kernel_matrix<kTinyThreads, kTinyMaxN, false>(
+        sh, BwArgs{N, kModeDiff, h_fixed, log_n1}, st, coef, WHAT == kTinyBandwidth ? nullptr : cl, true, c2h,
+        [&](auto meanwhile) __attribute__((always_inline)) {
+            meanwhile();
+            if (tid < P) {
+                double s = 0.0;
+#pragma unroll
+                for (int w = 0; w < kTinyThreads / 64; ++w) s += (double)red[w][tid];
+                sh.S[tid] = s;
+            }
+        },
+        NoCall{});
 
     if constexpr (WHAT == kTinyBandwidth) return;
 

@@ -19,18 +19,17 @@
 
 namespace svgd {
 
-// FUSED: the step in ONE launch.  The kernel starts with pass 2 (kernel_matrix_prologue: every
-// workgroup derives h, C and rho for itself from the short list of pair-sum partials that the
-// previous update left behind) and, being a CARRY kernel, ends by leaving the partials of the new
-// X for the next one - in the other half of the scratch, because workgroups that are still in
-// their prologue read the old list.  Used when that list is short (small problems, where two more
-// launches would cost as much as the work).
-struct FusedArgs {
-    const float *partials_in; // [nparts_in][n (n + 1) / 2], format of the Gram kernels
-    int nparts_in;
-    double h_fixed;
-    // Not about fusion, but every update kernel takes this struct: walk the columns from the far
-    // end.  Which thread or wave owns which columns does not change, only the order in which it
+// FUSED: passes 2 and 3 in one launch.  The kernel starts with pass 2 (kernel_matrix: every workgroup
+// derives h, C and rho for itself, from the fully reduced pair sums or from a short list of
+// partials; workgroup 0 records h and K) and needs no tables in device memory.  A CARRY kernel that
+// reads its list of partials from the scratch leaves the partials of the new X in the other half
+// of it, because workgroups still in their prologue read the old list.
+struct UpdateArgs {
+    // FUSED only
+    SumSource src;
+    double h_fixed, log_n1;
+    // all update kernels:
+    // walk the columns from the far end.  Which thread or wave owns which columns does not change, only the order in which it
     // visits them.  A caller that alternates the direction from step to step starts every pass
     // on the part of X that the previous pass touched last, i.e. on what the memory-side cache
     // still holds.
@@ -52,10 +51,9 @@ __global__ __launch_bounds__(256) void update_valu_kernel(float *__restrict__ X,
                                                           DevState *__restrict__ st,
                                                           int64_t D, int64_t ld, float eps,
                                                           float *__restrict__ gram_out,
-                                                          typename RowArg<ROWS>::type rt, FusedArgs fa)
+                                                          typename RowArg<ROWS>::type rt, UpdateArgs ua)
 {
     static_assert(!(ROWS && (EMIT || CARRY)), "separate rows: plain in-place step only");
-    static_assert(!FUSED || (CARRY && !ROWS), "the fused step lives on carried pair sums");
     static_assert(!(CARRY && EMIT), "the pair sums are carried only when X is updated");
     // CARRY: the pair sums of the UPDATED columns, in the format of gram_valu_kernel<N>
     constexpr bool kDiff = (N <= 8);
@@ -91,8 +89,8 @@ __global__ __launch_bounds__(256) void update_valu_kernel(float *__restrict__ X,
     // this thread's groups: grp0 + k * nthreads, k < cnt, visited upwards or (reverse) downwards
     const int64_t grp0 = (int64_t)blockIdx.x * 256 + threadIdx.x;
     const int64_t cnt = (grp0 < ngroups) ? (ngroups - 1 - grp0) / nthreads + 1 : 0;
-    const int64_t gstep = fa.reverse ? -nthreads : nthreads;
-    int64_t grp = fa.reverse ? grp0 + (cnt - 1) * nthreads : grp0;
+    const int64_t gstep = ua.reverse ? -nthreads : nthreads;
+    int64_t grp = ua.reverse ? grp0 + (cnt - 1) * nthreads : grp0;
     // Fused step: the first column group's loads go out in the middle of the prologue, after the
     // list of partial sums has been read, so that they are in flight during the arithmetic on h and K.
     // (only a group that lies wholly inside the row: the masked loads of a ragged last group come
@@ -100,20 +98,22 @@ __global__ __launch_bounds__(256) void update_valu_kernel(float *__restrict__ X,
     const bool early = FUSED && cnt > 0 && ((grp << 2) + 4 <= D);
     float c2h;
     if constexpr (FUSED) {
-        __shared__ BwShared sh;
-        auto first_loads = [&]() __attribute__((always_inline)) {
-            if (early) {
-                const int64_t c = grp << 2;
+        __shared__ BwShared<kValuMaxN, 256> sh;
+        __shared__ __attribute__((aligned(16))) double red_sums[4 * 256];
+        kernel_matrix<256, kValuMaxN, true>(
+            sh, BwArgs{N, kDiff ? kModeDiff : kModeGram, ua.h_fixed, ua.log_n1}, st, coef, C, blockIdx.x == 0, c2h,
+            [&](auto meanwhile) __attribute__((always_inline)) { gather_sums<256>(sh.S, red_sums, ua.src, N, meanwhile); },
+            [&]() __attribute__((always_inline)) {
+                if (early) {
+                    const int64_t c = grp << 2;
 #pragma unroll
-                for (int j = 0; j < N; ++j) {
-                    x[j] = *reinterpret_cast<const f32x4u *>(X + (int64_t)j * ld + c);
-                    z[j] = __builtin_nontemporal_load(reinterpret_cast<const f32x4u *>(G + (int64_t)j * ld + c));
+                    for (int j = 0; j < N; ++j) {
+                        x[j] = *reinterpret_cast<const f32x4u *>(X + (ROWS ? rt.x[ROWS ? j : 0] : (int64_t)j * ld) + c);
+                        z[j] = __builtin_nontemporal_load(
+                            reinterpret_cast<const f32x4u *>(G + (ROWS ? rt.g[ROWS ? j : 0] : (int64_t)j * ld) + c));
+                    }
                 }
-            }
-        };
-        const double h = kernel_matrix_prologue<256>(sh, fa.partials_in, fa.nparts_in, N, kDiff ? kModeDiff : kModeGram,
-                                                     fa.h_fixed, st, coef, C, blockIdx.x == 0, first_loads);
-        c2h = (N == 1) ? 0.f : (float)(2.0 / h);
+            });
     } else {
         c2h = st->two_over_h;
         for (int e = threadIdx.x; e < N * N; e += 256) C[e] = coef[kOffC + e];
@@ -174,15 +174,10 @@ __global__ __launch_bounds__(256) void update_valu_kernel(float *__restrict__ X,
     }
     if constexpr (CARRY) {
         __shared__ float red[4][P];
-        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-        for (int p = 0; p < P; ++p) {
-            const float v = wave_sum(pacc[p]);
-            if (lane == 0) red[wave][p] = v;
-        }
+        wave_sums<P>(pacc, red[threadIdx.x >> 6]);
         __syncthreads();
         for (int p = threadIdx.x; p < P; p += 256)
-            gram_out[(int64_t)blockIdx.x * P + p] = (red[0][p] + red[1][p]) + (red[2][p] + red[3][p]);
+            gram_out[(int64_t)blockIdx.x * pair_stride(N) + p] = (red[0][p] + red[1][p]) + (red[2][p] + red[3][p]);
     }
 }
 
@@ -309,12 +304,12 @@ __attribute__((amdgpu_waves_per_eu((NB <= 2 && !FULLROWS) ? 2 : 1, (NB <= 2 && !
 void update_mfma_kernel(float *__restrict__ X, const float *__restrict__ G, float *__restrict__ PHI,
                         float *__restrict__ coef, DevState *__restrict__ st, int n,
                         int64_t D, int64_t ld, float eps, float *__restrict__ gram_out,
-                        typename RowArg<ROWS>::type rt, FusedArgs fa)
+                        typename RowArg<ROWS>::type rt, UpdateArgs ua)
 {
-    static_assert(!FUSED || (CARRY && !ROWS && NB <= 2), "the fused step: carried pair sums, n <= 32");
+    static_assert(!FUSED || NB <= 2, "pass 2 with 256 threads: n <= 32");
     static_assert(!(CARRY && EMIT), "the Gram is carried only when X is updated");
     static_assert(!(ROWS && (EMIT || CARRY)), "separate rows: plain in-place step");
-    static_assert(!REV || (CARRY && !ALIGNED && !FUSED), "the mirrored walk exists for re-aligned stores with carried sums");
+    static_assert(!REV || (CARRY && !ALIGNED), "the mirrored walk exists for re-aligned stores with carried sums");
     static_assert(!REM || (FULLROWS && NB <= 3), "remainder rows come after full blocks");
     constexpr int NS = 4 * NB; // contraction steps = rows per lane
     constexpr int NBG = NB + (REM ? 1 : 0); // blocks as the pair sums see them
@@ -326,101 +321,13 @@ void update_mfma_kernel(float *__restrict__ X, const float *__restrict__ G, floa
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int q = lane >> 4, c16 = lane & 15;
     float *__restrict__ OUT = EMIT ? PHI : X;
-    // C (n x n) and rho (n): the handle's tables, or - fused step - this workgroup's own copies in
-    // LDS, computed by the prologue in the (still unused) staging area
-    __shared__ float cl[FUSED ? 32 * 32 + 32 : 1];
-    const float *Cm = coef + kOffC, *rhov = coef + kOffRho;
-    float c2h;
-    if constexpr (FUSED) {
-        static_assert(sizeof(BwShared) <= 4 * (kUpdCur + kUpdCarry) * sizeof(float), "pass 2 fits into the staging area");
-        BwShared &sh = *reinterpret_cast<BwShared *>(lds + NB * NB * 64 * 4);
-        const double h = kernel_matrix_prologue<256>(sh, fa.partials_in, fa.nparts_in, n, kModeGram, fa.h_fixed, st, coef,
-                                                     cl, blockIdx.x == 0);
-        c2h = (n == 1) ? 0.f : (float)(2.0 / h);
-        Cm = cl;
-        rhov = cl + n * n;
-    } else {
-        c2h = st->two_over_h;
-    }
-
     const int64_t nfull = D >> 6; // full 64-column tiles
-    if (blockIdx.x == gridDim.x - 1) { // the extra workgroup: ragged tail only
-        float *tail_out = nullptr;
-        if constexpr (CARRY) {
-            const int P = n * (n + 1) / 2;
-            tail_out = gram_out + (int64_t)(gridDim.x - 1) * P; // after the workers' partials
-            if ((nfull << 6) >= D)
-                for (int p = threadIdx.x; p < P; p += 256) tail_out[p] = 0.f;
-        }
-        if ((nfull << 6) < D)
-            update_tail_columns<EMIT, CARRY, ROWS>(X, G, OUT, Cm, rhov, c2h, n, D, ld, nfull << 6, eps, lds, tail_out, rt);
-        return;
-    }
-
-    // With CARRY the staging block doubles as the Gram operand source (lane = row reads), so its
-    // 16-byte granules are XOR-swizzled by the row; without it the block is plain row-major.
-    auto cur_index = [](int rloc, int col) {
-        return CARRY ? rloc * 64 + ((((col >> 2) ^ rloc) & 15) << 2) + (col & 3) : rloc * 64 + col;
-    };
-    f32x4 accg[CARRY ? NPAIR : 1];
-    if constexpr (CARRY) {
-#pragma unroll
-        for (int p = 0; p < NPAIR; ++p) accg[p] = f32x4{0.f, 0.f, 0.f, 0.f};
-    }
-    const float inv_n = 1.0f / (float)n;
-
-    f32x4 *As4 = reinterpret_cast<f32x4 *>(lds);
-    float *cur = lds + NB * NB * 64 * 4 + wave * (kUpdCur + kUpdCarry);
-    float *carry = cur + kUpdCur;
-    // A operands of v_mfma_f32_16x16x4_f32 for output block bi, steps 4sg..4sg+3, as one float4
-    // per lane: for step s = 4sg + k lane (q = l/16, m = l%16) holds C[16bi + m][16sg + 4q + k]
-    // (zero beyond n: rows and columns of the padding take no part)
-    for (int e = threadIdx.x; e < NB * NB * 64; e += 256) {
-        const int l = e & 63, sg = (e >> 6) % NB, bi = (e >> 6) / NB;
-        const int i = 16 * bi + (l & 15), j0 = 16 * sg + 4 * (l >> 4);
-        f32x4 v;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) v[k] = (i < n && j0 + k < n) ? Cm[i * n + j0 + k] : 0.f;
-        As4[e] = v;
-    }
-    float rho[NS];
-#pragma unroll
-    for (int s = 0; s < NS; ++s) {
-        const int row = 16 * (s >> 2) + 4 * q + (s & 3);
-        rho[s] = (FULLROWS || row < n) ? rhov[row] : 0.f;
-    }
-    // remainder rows.  arem: the A operand of their one contraction step for output block bi -
-    // lane (q, m) holds C[16bi + m][16NB + q].  crem: for remainder row r and lane row q the
-    // coefficients C[16NB + r][.] of the rows that a lane of that q holds, in the order of its
-    // registers (NS rows of the full blocks, then row 16NB + q), padded to a multiple of four.
-    constexpr int CREM = NS + 4;
-    __shared__ float arem[REM ? NB * 64 : 1];
-    __shared__ __attribute__((aligned(16))) float crem[REM ? 16 * CREM : 4];
-    float rho_r = 0.f;
-    if constexpr (REM) {
-        for (int e = threadIdx.x; e < NB * 64; e += 256) {
-            const int l = e & 63, bi = e >> 6;
-            arem[e] = ((l >> 4) < R) ? Cm[(16 * bi + (l & 15)) * n + 16 * NB + (l >> 4)] : 0.f;
-        }
-        for (int e = threadIdx.x; e < 16 * CREM; e += 256) {
-            const int s = e % CREM, rq = e / CREM, r = rq >> 2, qq = rq & 3;
-            float v = 0.f;
-            if (r < R) {
-                if (s < NS) v = Cm[(16 * NB + r) * n + 16 * (s >> 2) + 4 * qq + (s & 3)];
-                else if (s == NS && qq < R) v = Cm[(16 * NB + r) * n + 16 * NB + qq];
-            }
-            crem[e] = v;
-        }
-        if (q < R) rho_r = rhov[16 * NB + q];
-    }
-    __syncthreads();
-
     // The tiles of this wave: t0, t0 + TS, ... < t1.  Re-aligned stores hand a row's tail from one
     // tile to the next through the wave's carry, so there each wave walks a contiguous range of
-    // its own (TS = 1).  ALIGNED has nothing to hand over: on request (fa.adjacent, the host's
+    // its own (TS = 1).  ALIGNED has nothing to hand over: on request (ua.adjacent, the host's
     // choice) the workgroup owns a contiguous range and its four waves take adjacent tiles
     // (TS = 4), which makes the workgroup's accesses 1 KiB contiguous per row.
-    const int64_t TS = (ALIGNED && fa.adjacent != 0) ? 4 : 1;
+    const int64_t TS = (ALIGNED && ua.adjacent != 0) ? 4 : 1;
     int64_t t0, t1;
     tile_range(nfull, gridDim.x - 1, blockIdx.x, wave, TS == 4, t0, t1);
     const int64_t c_begin = t0 << 6;
@@ -428,7 +335,7 @@ void update_mfma_kernel(float *__restrict__ X, const float *__restrict__ G, floa
     // at run time; re-aligned stores hand a row's leftover from tile to tile, so their mirror
     // image, which walks right to left, is an instance of its own (REV).
     const int64_t ntiles = (t1 - t0 + TS - 1) / TS;
-    const bool rev = REV || (ALIGNED && fa.reverse != 0);
+    const bool rev = REV || (ALIGNED && ua.reverse != 0);
     const int64_t t_step = rev ? -TS : TS;
     const int64_t t_first = rev ? t0 + (ntiles - 1) * TS : t0;
 
@@ -455,7 +362,7 @@ void update_mfma_kernel(float *__restrict__ X, const float *__restrict__ G, floa
             srow[threadIdx.x] = ((int)threadIdx.x < n) ? rt.x[ROWS ? threadIdx.x : 0] : 0;
             sri[threadIdx.x] = ((int)threadIdx.x < n) ? rt.ri[ROWS ? threadIdx.x : 0] : 0;
         }
-        __syncthreads();
+        block_sync<FUSED>();
     }
 
     // Software pipeline across tiles: the loads of tile t+1 are issued while tile t is being
@@ -523,20 +430,115 @@ void update_mfma_kernel(float *__restrict__ X, const float *__restrict__ G, floa
         }
         load_next_rem(xt, gt);
     };
-    if (t0 < t1) {
-        int64_t in_off = in_lane + (t_first << 6);
-        opaque(in_off);
+    auto first_loads = [&]() __attribute__((always_inline)) {
+        if (t0 < t1) {
+            int64_t in_off = in_lane + (t_first << 6);
+            opaque(in_off);
 #pragma unroll
-        for (int s = 0; s < NS; ++s) {
-            x[s] = f32x4{0.f, 0.f, 0.f, 0.f};
-            z[s] = f32x4{0.f, 0.f, 0.f, 0.f};
-            if constexpr (XBUF) xn[s] = f32x4{0.f, 0.f, 0.f, 0.f};
-            else load_x(X + in_off, s);
-            if constexpr (GBUF) gn[s] = f32x4{0.f, 0.f, 0.f, 0.f};
-            else load_g(G + in_off, s);
+            for (int s = 0; s < NS; ++s) {
+                x[s] = f32x4{0.f, 0.f, 0.f, 0.f};
+                z[s] = f32x4{0.f, 0.f, 0.f, 0.f};
+                if constexpr (XBUF) xn[s] = f32x4{0.f, 0.f, 0.f, 0.f};
+                else load_x(X + in_off, s);
+                if constexpr (GBUF) gn[s] = f32x4{0.f, 0.f, 0.f, 0.f};
+                else load_g(G + in_off, s);
+            }
+            load_next(X + in_off, G + in_off);
         }
-        load_next(X + in_off, G + in_off);
+    };
+
+    // C (n x n) and rho (n): the handle's tables, or - FUSED - this workgroup's own copies in LDS,
+    // computed by the prologue in the (still unused) staging area
+    __shared__ float cl[FUSED ? 32 * 32 + 32 : 1];
+    const float *Cm = coef + kOffC, *rhov = coef + kOffRho;
+    float c2h;
+    if constexpr (FUSED) {
+        typedef BwShared<32, 256> Shared;
+        static_assert(sizeof(Shared) % 16 == 0 && sizeof(Shared) + 4 * 256 * sizeof(double) <= 4 * (kUpdCur + kUpdCarry) * sizeof(float),
+                      "pass 2 fits into the staging area");
+        Shared &sh = *reinterpret_cast<Shared *>(lds + NB * NB * 64 * 4);
+        double *red = reinterpret_cast<double *>(reinterpret_cast<char *>(&sh) + sizeof(Shared));
+        kernel_matrix<256, 32, true>(
+            sh, BwArgs{n, kModeGram, ua.h_fixed, ua.log_n1}, st, coef, cl, blockIdx.x == 0, c2h,
+            [&](auto meanwhile) __attribute__((always_inline)) { gather_sums<256>(sh.S, red, ua.src, n, meanwhile); },
+            first_loads); // the first tile is on its way while h and K are computed
+        Cm = cl;
+        rhov = cl + n * n;
+    } else {
+        c2h = st->two_over_h;
     }
+
+    if (blockIdx.x == gridDim.x - 1) { // the extra workgroup: ragged tail only
+        float *tail_out = nullptr;
+        if constexpr (CARRY) {
+            const int P = n * (n + 1) / 2;
+            tail_out = gram_out + (int64_t)(gridDim.x - 1) * pair_stride(n); // after the workers' partials
+            if ((nfull << 6) >= D)
+                for (int p = threadIdx.x; p < P; p += 256) tail_out[p] = 0.f;
+        }
+        if ((nfull << 6) < D)
+            update_tail_columns<EMIT, CARRY, ROWS>(X, G, OUT, Cm, rhov, c2h, n, D, ld, nfull << 6, eps, lds, tail_out, rt);
+        return;
+    }
+
+    // With CARRY the staging block doubles as the Gram operand source (lane = row reads), so its
+    // 16-byte granules are XOR-swizzled by the row; without it the block is plain row-major.
+    auto cur_index = [](int rloc, int col) {
+        return CARRY ? rloc * 64 + ((((col >> 2) ^ rloc) & 15) << 2) + (col & 3) : rloc * 64 + col;
+    };
+    f32x4 accg[CARRY ? NPAIR : 1];
+    if constexpr (CARRY) {
+#pragma unroll
+        for (int p = 0; p < NPAIR; ++p) accg[p] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    const float inv_n = 1.0f / (float)n;
+
+    f32x4 *As4 = reinterpret_cast<f32x4 *>(lds);
+    float *cur = lds + NB * NB * 64 * 4 + wave * (kUpdCur + kUpdCarry);
+    float *carry = cur + kUpdCur;
+    // A operands of v_mfma_f32_16x16x4_f32 for output block bi, steps 4sg..4sg+3, as one float4
+    // per lane: for step s = 4sg + k lane (q = l/16, m = l%16) holds C[16bi + m][16sg + 4q + k]
+    // (zero beyond n: rows and columns of the padding take no part)
+    for (int e = threadIdx.x; e < NB * NB * 64; e += 256) {
+        const int l = e & 63, sg = (e >> 6) % NB, bi = (e >> 6) / NB;
+        const int i = 16 * bi + (l & 15), j0 = 16 * sg + 4 * (l >> 4);
+        f32x4 v;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] = (i < n && j0 + k < n) ? Cm[i * n + j0 + k] : 0.f;
+        As4[e] = v;
+    }
+    float rho[NS];
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+        const int row = 16 * (s >> 2) + 4 * q + (s & 3);
+        rho[s] = (FULLROWS || row < n) ? rhov[row] : 0.f;
+    }
+    // remainder rows.  arem: the A operand of their one contraction step for output block bi -
+    // lane (q, m) holds C[16bi + m][16NB + q].  crem: for remainder row r and lane row q the
+    // coefficients C[16NB + r][.] of the rows that a lane of that q holds, in the order of its
+    // registers (NS rows of the full blocks, then row 16NB + q), padded to a multiple of four.
+    constexpr int CREM = NS + 4;
+    __shared__ float arem[REM ? NB * 64 : 1];
+    __shared__ __attribute__((aligned(16))) float crem[REM ? 16 * CREM : 4];
+    float rho_r = 0.f;
+    if constexpr (REM) {
+        for (int e = threadIdx.x; e < NB * 64; e += 256) {
+            const int l = e & 63, bi = e >> 6;
+            arem[e] = ((l >> 4) < R) ? Cm[(16 * bi + (l & 15)) * n + 16 * NB + (l >> 4)] : 0.f;
+        }
+        for (int e = threadIdx.x; e < 16 * CREM; e += 256) {
+            const int s = e % CREM, rq = e / CREM, r = rq >> 2, qq = rq & 3;
+            float v = 0.f;
+            if (r < R) {
+                if (s < NS) v = Cm[(16 * NB + r) * n + 16 * (s >> 2) + 4 * qq + (s & 3)];
+                else if (s == NS && qq < R) v = Cm[(16 * NB + r) * n + 16 * NB + qq];
+            }
+            crem[e] = v;
+        }
+        if (q < R) rho_r = rhov[16 * NB + q];
+    }
+    block_sync<FUSED>(); // (does not wait for the first tile's loads)
+    if constexpr (!FUSED) first_loads();
 
     auto process_tile = [&](auto first_tag, int64_t tile, bool last) __attribute__((always_inline)) {
         constexpr bool FIRST = decltype(first_tag)::value;
@@ -788,8 +790,7 @@ void update_mfma_kernel(float *__restrict__ X, const float *__restrict__ G, floa
         }
         __syncthreads();
         const float *all = lds + NB * NB * 64 * 4;
-        const int P = n * (n + 1) / 2;
-        float *out = gram_out + (int64_t)blockIdx.x * P;
+        float *out = gram_out + (int64_t)blockIdx.x * pair_stride(n);
         int p = 0;
 #pragma unroll
         for (int b = 0; b < NBG; ++b) {

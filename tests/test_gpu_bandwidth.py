@@ -1,0 +1,55 @@
+"""Pass 2 (bandwidth and kernel matrix) where its rule can go wrong: the median of sets that are all
+equal, that crowd into one bucket of the selection, or that hold infinities, at the particle counts
+where the way it is computed changes - by the kernel of its own (svgd_bandwidth) and as the prologue
+of the update (svgd_step, which up to 32 particles derives h and K in every workgroup)."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import svgd_oracle as orc
+from parity_checks import TOL_H, TOL_K
+
+pytestmark = pytest.mark.gpu
+
+
+def _particles(kind, n, D):
+    g = torch.Generator().manual_seed(97 * n + D)
+    X = torch.zeros(n, D)
+    if kind == "equal":            # every distance the same
+        X[torch.arange(n), torch.arange(n)] = 1.5
+    elif kind == "crowded":        # two far outliers; all other distances within 1/256 of the range
+        X[torch.arange(n), torch.arange(n)] = 1.0 + 1e-3 * torch.rand(n, generator=g)
+        X[0, 0], X[n - 1, n - 1] = 40.0, 25.0
+    elif kind == "infinite":       # one particle so far off that its squared distances overflow
+        X = torch.randn(n, D, generator=g)
+        X[n // 2] = 1e30
+    else:
+        X = torch.randn(n, D, generator=g)
+    return X
+
+
+@pytest.mark.parametrize("kind", ["equal", "crowded", "random"])
+@pytest.mark.parametrize("n", [2, 8, 9, 11, 12, 13, 16, 17, 32, 33, 64])
+def test_median_of_awkward_sets(n, kind):
+    _check(n, 3001, kind)
+
+
+@pytest.mark.parametrize("n,D", [(4, 100), (8, 3001)])   # direct differences: infinite d2, not inf - inf
+def test_median_with_infinite_distances(n, D):
+    _check(n, D, "infinite")
+
+
+def _check(n, D, kind):
+    from paper_2306_06528_amd import svgd
+    Xh = _particles(kind, n, D)
+    ref = orc.step(Xh.numpy(), np.zeros((n, D), np.float32), 0.0, want_phi=False, want_xnew=False)
+    X, G = Xh.cuda(), torch.zeros(n, D, device="cuda")
+    with svgd.Svgd(n, D) as eng:
+        eng.bandwidth(X)
+        got = [eng.get_last(n)]
+        eng.step(X, G, 0.0)
+        got.append(eng.get_last(n))
+    for h, K in got:
+        assert abs(h - ref["h"]) <= TOL_H * ref["h"]
+        assert np.abs(K - ref["K"]).max() <= TOL_K
+        assert np.array_equal(K, K.T) and np.all(np.diag(K) == 1.0)
