@@ -483,7 +483,7 @@ __device__ inline void gather_sums(double *S, double *red, const SumSource &src,
 
 // Lists of at most this many floats are summed by the bandwidth kernel itself; longer ones by
 // reduce_partials_kernel first.
-constexpr int kDirectMaxFloats = 96 * 1024;
+constexpr int kDirectMaxFloats = 48 * 1024;
 
 __global__ __launch_bounds__(kBwThreads) void bandwidth_kernel(SumSource src, BwArgs ba, DevState *__restrict__ st,
                                                                float *__restrict__ coef)

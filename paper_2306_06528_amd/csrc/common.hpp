@@ -17,6 +17,10 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // rows of X start at i*D floats, so a 4-column group is only 4-byte aligned in general
 typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+
 // Partial-sum formats written by the Gram kernels, both indexed by tri(i, j), i <= j.
 enum GramMode : int {
     kModeDiff = 0, // entry (i<j) holds sum_k (x_ik - x_jk)^2; diagonal entries are 0
@@ -120,6 +124,10 @@ __device__ inline void tile_range(int64_t nfull, int64_t nwg, int64_t wg, int wa
     }
 }
 
+// keeps the compiler from turning per-row addresses into 2 x 16 loop-carried pointer pairs
+// (an integer offset is laundered, not the pointer, so the accesses stay global_load/store)
+__device__ inline void opaque(int64_t &v) { asm volatile("" : "+v"(v)); }
+
 // rows that all start on a 128-byte boundary
 __host__ inline bool rows_aligned(const void *base, int64_t ld)
 {
@@ -136,6 +144,48 @@ __device__ inline void store4(float *__restrict__ row, int64_t col, int64_t D, b
     if (col + 1 < D) row[col + 1] = v.y;
     if (col + 2 < D) row[col + 2] = v.z;
     if (col + 3 < D) row[col + 3] = v.w;
+}
+
+// Eight fp32 values as three bf16 operands of the matrix instructions: v = h + m + l EXACTLY - h is v
+// rounded to bf16's eight bits, m the (exact) rest rounded, l what then remains, at most eight bits.
+// A product of two such triples is hh + (hm + mh) + (mm + hl + lh) + terms below 2^-25 of it, whose
+// signs are as random as those of rounding errors (the parts are rounded to nearest, not cut off).
+// A pair's rests are one instruction each: a dot product of the packed pair with (-1, 0) or (0, -1),
+// exact because the rest is representable; with shifts, masks and subtractions the split takes
+// 5.5 instructions per value, so 3.5.  Finite values beyond 2^64 or so can overflow in products
+// of different signs (h h and h m), which fp32 products do not: the caller looks at its sums.
+struct SplitConst {
+    unsigned neg_lo, neg_hi; // bf16 pairs (-1, 0) and (0, -1), in registers: as literals they would be broadcast
+};
+__device__ __forceinline__ SplitConst split_const()
+{
+    SplitConst c{0x0000BF80u, 0xBF800000u};
+    asm volatile("" : "+s"(c.neg_lo), "+s"(c.neg_hi));
+    return c;
+}
+struct Split3 {
+    bf16x8 h, m, l;
+};
+__device__ __forceinline__ Split3 split3(f32x4 a, f32x4 b, const SplitConst &sc)
+{
+    const bf16x2 neg_lo = __builtin_bit_cast(bf16x2, sc.neg_lo), neg_hi = __builtin_bit_cast(bf16x2, sc.neg_hi);
+    Split3 r;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        f32x2 v = k < 2 ? f32x2{a[2 * k], a[2 * k + 1]} : f32x2{b[2 * k - 4], b[2 * k - 3]};
+        const bf16x2 h = __builtin_convertvector(v, bf16x2);
+        v = f32x2{__builtin_amdgcn_fdot2_f32_bf16(h, neg_lo, v[0], false), __builtin_amdgcn_fdot2_f32_bf16(h, neg_hi, v[1], false)};
+        const bf16x2 m = __builtin_convertvector(v, bf16x2);
+        v = f32x2{__builtin_amdgcn_fdot2_f32_bf16(m, neg_lo, v[0], false), __builtin_amdgcn_fdot2_f32_bf16(m, neg_hi, v[1], false)};
+        const bf16x2 l = __builtin_convertvector(v, bf16x2);
+        r.h[2 * k] = h[0];
+        r.h[2 * k + 1] = h[1];
+        r.m[2 * k] = m[0];
+        r.m[2 * k + 1] = m[1];
+        r.l[2 * k] = l[0];
+        r.l[2 * k + 1] = l[1];
+    }
+    return r;
 }
 
 // Sum over the 16 lanes of each row of a wave, in every lane: quad swap, quad-pair swap, half-row

@@ -117,11 +117,12 @@ __global__ __launch_bounds__(256) void gram_valu_kernel(const float *__restrict_
 //      quarter-wave), rows {4i + lane/16}, columns 4*(lane%16)..+3,
 //   2. centres the columns (own rows in registers, two cross-lane adds for the other rows),
 //   3. writes the slab to a wave-private LDS region with a 16-byte-granule XOR swizzle,
-//   4. reads it back as v_mfma_f32_16x16x4_f32 operands: lane (q = lane/16, rr = lane%16) takes
-//      row 16b+rr, 4 columns per read; the 4 k-slots of one MFMA are columns {16s+4q+c, q=0..3},
+//   4. reads it back row-wise, eight columns per lane and step - lane (q = lane/16, rr = lane%16)
+//      takes row 16b+rr - and splits each value into three bf16 parts that add up to it exactly
+//      (split3); v_mfma_f32_16x16x32_bf16 wants 32 columns as its k-slots, eight per lane
 //      (the loads of the next slab are issued here, before the multiply phase),
-//   5. issues one MFMA per unordered block pair (b <= b'), fp32 accumulators in registers:
-//      lane (q, c), register r of pair (b, b') holds S[16b + 4q + r][16b' + c].
+//   5. issues six MFMAs per unordered block pair b < b' and four per b = b' (see acc), fp32 accumulators in
+//      registers: lane (q, c), register r of pair (b, b') holds S[16b + 4q + r][16b' + c].
 // Any assignment of columns to k-slots is valid because every column is summed exactly once.
 // ---------------------------------------------------------------------------------------------
 // Order of the slabs.  The update re-reads X right after this pass, every wave (or workgroup) of it
@@ -132,11 +133,16 @@ __global__ __launch_bounds__(256) void gram_valu_kernel(const float *__restrict_
 //     [I1, I1 + I2)  the hot tiles, range after range,
 //     I1 + I2        the partial slab after the last full tile, if D mod 64 != 0,
 // with I1 = nranges * (per - hot), I2 = nranges * hot (indices that fall beyond a short last range
-// are empty slabs), and wave w of workgroup b takes the indices 4 (b + k * gridDim.x) + w: the
-// workgroups sweep the index space together, the four waves of one on adjacent slabs.
-constexpr int kGramWaves = 4; // waves per workgroup, as in the update kernel
+// are empty slabs), and wave w of workgroup b takes the indices W (b + k * gridDim.x) + w: the
+// workgroups sweep the index space together, the W waves of one on adjacent slabs.
 
-// (a wave's indices are `stride` = 4 * gridDim.x apart; its quotient and remainder by the lengths
+// Waves per workgroup (template argument W): eight, one workgroup per CU and two waves per SIMD - half
+// as many partial sums as with two workgroups of four -, or four for an X of so few slabs that
+// every wave has one anyway and more CUs can share them.
+constexpr int kGramWaves = 8;
+constexpr int kGramWavesSmall = 4;
+
+// (a wave's indices are `stride` = W * gridDim.x apart; its quotient and remainder by the lengths
 // of a range's cold and hot parts come from the host, so that stepping from one index to the next
 // needs no division; everything fits 32 bits, the host sees to that)
 struct GramOrder {
@@ -152,33 +158,52 @@ struct GramOrder {
 //   way in) - for rows on 128-byte boundaries (nothing is shared between the slabs of neighbouring
 //   waves).  The pass itself then runs 5 % (n = 64, D = 11.2 M) to 28 % (n = 16, same D) faster.
 // The host takes ORDER 1 or 2 when X is larger than twice the memory-side cache.
-template <int NB, bool ROWS = false, int ORDER = 0>
-__global__ __launch_bounds__(64 * kGramWaves) void gram_mfma_kernel(const float *__restrict__ X, int n,
+// What bounds the pass: at n = 64 the matrix pipe and power, below that memory.  In fp32
+// (v_mfma_f32_16x16x4_f32, 160 per slab) the multiplies took 32 cycles each during which the vector
+// ALU stood still - the fp32 matrix instructions share its multipliers, measured with both in one
+// wave and in two - and 1.07 M cycles per launch; 104 bf16 instructions of 17 cycles beside 224
+// instructions for the split are 0.55 M cycles, of which some of the gain goes to a lower clock (1.7
+// against 2.1 GHz).  n = 64, D = 11,173,962: 568 -> 460 us on padded rows (6.2 TB/s), 583 -> 537 on dense
+// ones, whose slabs share lines that are fetched twice; n = 33, D = 5 M 153 -> 117 (5.6 TB/s);
+// n = 48, D = 1 M 44 -> 38; n = 16, D = 11.2 M 115 -> 112 (6.4 TB/s).  h against 64 bits, n = 64, D =
+// 3 M: relative error 2.6e-8 -> 2e-9 (slab sums instead of one long chain); n = 16, D = 8,577: 5e-9, as before.
+template <int NB, int W, bool ROWS = false, int ORDER = 0>
+__global__ __launch_bounds__(64 * W) void gram_mfma_kernel(const float *__restrict__ X, int n,
                                                                     int64_t D, int64_t ld, float *__restrict__ partials,
                                                                     typename RowArg<ROWS>::type rt, GramOrder go)
 {
     constexpr int NROW = 16 * NB;
     constexpr int RPL = 4 * NB; // rows per lane while loading
     constexpr int NPAIR = NB * (NB + 1) / 2;
-    __shared__ float lds[kGramWaves][NROW * 64];
+    __shared__ float lds[W][NROW * 64];
 
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int q = lane >> 4, c16 = lane & 15;
     float *my = lds[wave];
     const float inv_n = 1.0f / (float)n;
 
-    f32x4 acc[NPAIR];
+    // acc: the sums of the block pairs.  Of a diagonal pair (b, b) only hh + mm is in it; hm + hl, whose
+    // transpose is mh + lh, is in acct and added both ways round at the end: four matrix
+    // instructions instead of six.
+    f32x4 acc[NPAIR], acct[NB];
+    auto clear = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int p = 0; p < NPAIR; ++p) acc[p] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int p = 0; p < NPAIR; ++p) acc[p] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int b = 0; b < NB; ++b) acct[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+    };
+    const SplitConst sc = split_const();
 
     constexpr bool ORDERED = ORDER != 0, STREAM = ORDER == 2;
+    constexpr bool F32 = W == kGramWavesSmall; // one slab per wave: the shorter code counts, not the matrix pipe
     const int64_t nfull = D >> 6;
     const uint32_t uper = go.per, uhot = go.hot, ucold = uper - uhot, unfull = (uint32_t)nfull;
     const uint32_t I1 = ORDERED ? go.nranges * ucold : 0u, I2 = ORDERED ? go.nranges * uhot : unfull;
     const uint32_t nidx = I1 + I2 + (((nfull << 6) < D) ? 1u : 0u);
-    const uint32_t lo = 4u * blockIdx.x + (uint32_t)__builtin_amdgcn_readfirstlane(wave), stride = 4u * gridDim.x;
+    const uint32_t first = (uint32_t)W * blockIdx.x + (uint32_t)__builtin_amdgcn_readfirstlane(wave);
+    const uint32_t stride = (uint32_t)W * gridDim.x;
     // the walk: index `at` is tile r * per + o (+ hot while cold), or the partial slab (phase 2)
-    uint32_t at = lo, phase = 0, r = 0, o = 0;
+    uint32_t at, phase, r, o;
     auto enter = [&]() { // state at index `at`, by division: once per wave and phase
         if (at < I1) {
             phase = 0;
@@ -208,7 +233,11 @@ __global__ __launch_bounds__(64 * kGramWaves) void gram_mfma_kernel(const float 
             }
         }
     };
-    if constexpr (ORDERED) enter();
+    auto start = [&]() {
+        at = first;
+        phase = r = o = 0;
+        if constexpr (ORDERED) enter();
+    };
     f32x4 x[RPL];
     int64_t xro[ROWS ? RPL : 1]; // where this lane's rows start (separate rows only)
     if constexpr (ROWS) {
@@ -238,15 +267,18 @@ __global__ __launch_bounds__(64 * kGramWaves) void gram_mfma_kernel(const float 
     };
     auto rows = [&](auto how) __attribute__((always_inline)) {
         constexpr int HOW = decltype(how)::value;
+        int64_t at0 = (int64_t)q * ld + col; // this lane's place in row q; row 4i + q is a uniform distance on
+        opaque(at0);
 #pragma unroll
         for (int i = 0; i < RPL; ++i) {
             const int row = 4 * i + q;
-            const float *xr = X + (ROWS ? xro[ROWS ? i : 0] : (int64_t)row * ld);
+            const float *xr = ROWS ? X + xro[ROWS ? i : 0] + col : X + at0 + (int64_t)(4 * i) * ld;
             f32x4 v = {0.f, 0.f, 0.f, 0.f}; // rows beyond n, and empty slabs, add nothing to any sum
-            if (HOW != 3 && row < n) {
-                if constexpr (HOW == 0) v = *reinterpret_cast<const f32x4u *>(xr + col);
-                else if constexpr (HOW == 1) v = __builtin_nontemporal_load(reinterpret_cast<const f32x4u *>(xr + col));
-                else v = load4(xr, col, D, false);
+            // (only the last block of 16 rows can reach beyond n)
+            if (HOW != 3 && (i < RPL - 4 || row < n)) {
+                if constexpr (HOW == 0) v = *reinterpret_cast<const f32x4u *>(xr);
+                else if constexpr (HOW == 1) v = __builtin_nontemporal_load(reinterpret_cast<const f32x4u *>(xr));
+                else v = load4(xr - col, col, D, false);
             }
             x[i] = v;
         }
@@ -279,14 +311,61 @@ __global__ __launch_bounds__(64 * kGramWaves) void gram_mfma_kernel(const float 
     };
     // steps 4 and 5 on the slab in `buf`
     auto multiply = [&](const float *buf) __attribute__((always_inline)) {
+        // A slab's sums start from zero and are added to the running ones in fp32 at its end.  Straight
+        // into a large running sum, squares of eight-bit values leave remainders that are not evenly
+        // spread - odd squares are 1 modulo 8 - and the rounding errors do not cancel (measured: d2
+        // 6e-8 too large after 30 steps).
+        f32x4 t[NPAIR];
+#pragma unroll
+        for (int p = 0; p < NPAIR; ++p) t[p] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int st = 0; st < 2; ++st) { // 32 columns each
+            Split3 a[NB];
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+                const float *row = buf + (16 * b + c16) * 64; // here c16 plays the role of rr (matrix row)
+                a[b] = split3(*reinterpret_cast<const f32x4 *>(&row[((8 * st + q) ^ c16) << 2]),
+                              *reinterpret_cast<const f32x4 *>(&row[((8 * st + 4 + q) ^ c16) << 2]), sc);
+            }
+            // one kind of product after the other over the pairs of blocks: a dependent matrix
+            // instruction can issue after some 44 cycles, an independent one after 17
+            auto products = [&](auto left, auto right, bool diagonal) __attribute__((always_inline)) {
+                int p = 0;
+#pragma unroll
+                for (int b = 0; b < NB; ++b) {
+#pragma unroll
+                    for (int b2 = b; b2 < NB; ++b2) {
+                        if (diagonal || b != b2)
+                            t[p] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[b].*left, a[b2].*right, t[p], 0, 0, 0);
+                        ++p;
+                    }
+                }
+            };
+            auto half_products = [&](auto right) __attribute__((always_inline)) {
+#pragma unroll
+                for (int b = 0; b < NB; ++b)
+                    acct[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[b].h, a[b].*right, acct[b], 0, 0, 0);
+            };
+            half_products(&Split3::l);
+            products(&Split3::h, &Split3::l, false);
+            products(&Split3::l, &Split3::h, false);
+            products(&Split3::m, &Split3::m, true);
+            half_products(&Split3::m);
+            products(&Split3::h, &Split3::m, false);
+            products(&Split3::m, &Split3::h, false);
+            products(&Split3::h, &Split3::h, true);
+        }
+#pragma unroll
+        for (int p = 0; p < NPAIR; ++p) acc[p] += t[p];
+    };
+    // the same in fp32: v_mfma_f32_16x16x4_f32, four k-slots (columns {16s + 4q + c, q = 0..3}) at a time
+    auto multiply_f32 = [&](const float *buf) __attribute__((always_inline)) {
 #pragma unroll
         for (int st = 0; st < 4; ++st) {
             f32x4 a[NB];
 #pragma unroll
-            for (int b = 0; b < NB; ++b) {
-                const int row = 16 * b + c16; // here c16 plays the role of rr (matrix row)
-                a[b] = *reinterpret_cast<const f32x4 *>(&buf[row * 64 + (((4 * st + q) ^ c16) << 2)]);
-            }
+            for (int b = 0; b < NB; ++b)
+                a[b] = *reinterpret_cast<const f32x4 *>(&buf[(16 * b + c16) * 64 + (((4 * st + q) ^ c16) << 2)]);
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
                 int p = 0;
@@ -301,46 +380,73 @@ __global__ __launch_bounds__(64 * kGramWaves) void gram_mfma_kernel(const float 
             }
         }
     };
-    // Two workgroups per CU, i.e. two waves per SIMD, take turns at the matrix pipe.  (One wave per
-    // SIMD that overlaps the steps itself - two slabs in its LDS region; slab t multiplied while
-    // slab t+1 is centred and staged and the loads of slab t+2 go out, all in one basic block -
-    // was slower: 632 against 566 us at n = 64, D = 11.2 M.)
-    if (lo < nidx) load_slab();
-    for (uint32_t idx = lo; idx < nidx; idx += stride) {
-        centre_and_stage(my);
-        // the next slab's loads are in flight while this one is multiplied
-        if (idx + stride < nidx) load_slab();
-        multiply(my);
-    }
-
-    // combine the waves through LDS, then store the upper triangle in tri(i, j) order
-    __syncthreads();
-    float *xch = &lds[0][0]; // [wave-1][pair][r][lane], NPAIR*256 floats per wave (<= NROW*64)
-    if (wave > 0) {
+    // Two waves per SIMD: one's vector instructions run beside the other's matrix instructions (the
+    // bf16 ones; fp32 matrix instructions and the vector ALU exclude each other).
+    auto sweep = [&](auto f32) __attribute__((always_inline)) {
+        clear();
+        start();
+        if (first < nidx) load_slab();
+        for (uint32_t idx = first; idx < nidx; idx += stride) {
+            centre_and_stage(my);
+            // the next slab's loads are in flight while this one is multiplied
+            if (idx + stride < nidx) load_slab();
+            if constexpr (decltype(f32)::value) multiply_f32(my);
+            else multiply(my);
+        }
+    };
+    if constexpr (F32) {
+        sweep(std::true_type{});
+    } else {
+        sweep(std::false_type{});
+        // Sums that are not finite - a product overflowed, or X is not finite - are taken again in fp32,
+        // whose infinities and NaNs do not depend on how the values were split.
+        float odd = 0.f;
 #pragma unroll
         for (int p = 0; p < NPAIR; ++p)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) xch[((wave - 1) * NPAIR * 4 + p * 4 + r) * 64 + lane] = acc[p][r];
+            for (int r = 0; r < 4; ++r) odd += 0.f * acc[p][r]; // 0, or NaN
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) odd += 0.f * acct[b][r];
+        if (__ballot(odd != 0.f) != 0) sweep(std::true_type{});
     }
+
+    // The waves meet in LDS, each with its sums in its own region (free by now); wave w adds up and
+    // stores the block pairs w, w + 8, ... of the upper triangle in tri(i, j) order.
+    static_assert((NPAIR + NB) * 256 <= NROW * 64, "a wave's sums fit its region");
+#pragma unroll
+    for (int p = 0; p < NPAIR; ++p)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) my[(p * 4 + r) * 64 + lane] = acc[p][r];
+#pragma unroll
+    for (int b = 0; !F32 && b < NB; ++b)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) my[((NPAIR + b) * 4 + r) * 64 + lane] = acct[b][r];
     __syncthreads();
-    if (wave == 0) {
-        float *out = partials + (int64_t)blockIdx.x * pair_stride(n);
-        int p = 0;
+    float *out = partials + (int64_t)blockIdx.x * pair_stride(n);
+    int p = 0;
 #pragma unroll
-        for (int b = 0; b < NB; ++b) {
+    for (int b = 0; b < NB; ++b) {
 #pragma unroll
-            for (int b2 = b; b2 < NB; ++b2) {
+        for (int b2 = b; b2 < NB; ++b2) {
+            if (p % W == wave) {
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     const int i = 16 * b + 4 * q + r;
                     const int j = 16 * b2 + c16;
-                    float v = acc[p][r];
+                    double v = 0.0;
 #pragma unroll
-                    for (int w = 1; w < kGramWaves; ++w) v += xch[((w - 1) * NPAIR * 4 + p * 4 + r) * 64 + lane];
-                    if (i <= j && j < n) out[tri(i, j, n)] = v;
+                    for (int w = 0; w < W; ++w) {
+                        v += (double)lds[w][(p * 4 + r) * 64 + lane];
+                        if (!F32 && b == b2) // entry (4q + r, c16) of acct and its mirror image
+                            v += (double)lds[w][((NPAIR + b) * 4 + r) * 64 + lane] +
+                                 (double)lds[w][((NPAIR + b) * 4 + (c16 & 3)) * 64 + 16 * (c16 >> 2) + 4 * q + r];
+                    }
+                    if (i <= j && j < n) out[tri(i, j, n)] = (float)v;
                 }
-                ++p;
             }
+            ++p;
         }
     }
 }

@@ -252,7 +252,9 @@ int run_gram(svgd_ctx *c, const float *X, int n, int64_t D, int64_t ld, hipStrea
     } else {
         const int NB = (n + 15) / 16;
         const int64_t nfull = D / 64;
-        nparts = clampi((D + 255) / 256, 1, mini(c->num_cu * 2, cap_parts));
+        const bool small = nfull < (int64_t)kGramWavesSmall * mini(c->num_cu, cap_parts); // a slab per wave, the partial one included
+        const int waves = small ? kGramWavesSmall : kGramWaves;
+        nparts = clampi((D + 64 * waves - 1) / (64 * waves), 1, mini(c->num_cu, cap_parts));
         // the ranges of the update that follows (tile_range) and how many of each range's first
         // tiles three quarters of the memory-side cache can hold
         const bool aligned_next = G_next && x_aligned && (rt || rows_aligned(G_next, ld));
@@ -268,25 +270,29 @@ int run_gram(svgd_ctx *c, const float *X, int n, int64_t D, int64_t ld, hipStrea
             hot = 0;
         }
         const bool stream_x = big_x && x_aligned; // slabs of unaligned rows share lines
-        const uint32_t stride = 4u * (uint32_t)nparts, cold = (uint32_t)(per - hot);
+        const uint32_t stride = (uint32_t)kGramWaves * (uint32_t)nparts, cold = (uint32_t)(per - hot);
         GramOrder go{(uint32_t)nranges, (uint32_t)per, (uint32_t)hot, 0, 0, 0, 0};
         if (cold) { go.q_cold = stride / cold; go.r_cold = stride % cold; }
         if (hot) { go.q_hot = stride / (uint32_t)hot; go.r_hot = stride % (uint32_t)hot; }
         // (the order is only worth its bookkeeping for an X well beyond the memory-side cache)
-#define GRAM(NBV)                                                                                            \
+#define GRAM_W(NB, W, ROWS, ORDER, rows) gram_mfma_kernel<NB, W, ROWS, ORDER><<<nparts, 64 * W, 0, s>>>(X, n, D, ld, c->partials, rows, go)
+#define GRAM(NB)                                                                                             \
     do {                                                                                                     \
-        if (rt && stream_x) gram_mfma_kernel<NBV, true, 2><<<nparts, 64 * kGramWaves, 0, s>>>(X, n, D, ld, c->partials, *rt, go); \
-        else if (rt && big_x) gram_mfma_kernel<NBV, true, 1><<<nparts, 64 * kGramWaves, 0, s>>>(X, n, D, ld, c->partials, *rt, go); \
-        else if (rt) gram_mfma_kernel<NBV, true, 0><<<nparts, 64 * kGramWaves, 0, s>>>(X, n, D, ld, c->partials, *rt, go); \
-        else if (stream_x) gram_mfma_kernel<NBV, false, 2><<<nparts, 64 * kGramWaves, 0, s>>>(X, n, D, ld, c->partials, NoRows{}, go); \
-        else if (big_x) gram_mfma_kernel<NBV, false, 1><<<nparts, 64 * kGramWaves, 0, s>>>(X, n, D, ld, c->partials, NoRows{}, go); \
-        else gram_mfma_kernel<NBV, false, 0><<<nparts, 64 * kGramWaves, 0, s>>>(X, n, D, ld, c->partials, NoRows{}, go); \
+        if (rt && small) GRAM_W(NB, kGramWavesSmall, true, 0, *rt);                                          \
+        else if (rt && stream_x) GRAM_W(NB, kGramWaves, true, 2, *rt);                                       \
+        else if (rt && big_x) GRAM_W(NB, kGramWaves, true, 1, *rt);                                          \
+        else if (rt) GRAM_W(NB, kGramWaves, true, 0, *rt);                                                   \
+        else if (small) GRAM_W(NB, kGramWavesSmall, false, 0, NoRows{});                                     \
+        else if (stream_x) GRAM_W(NB, kGramWaves, false, 2, NoRows{});                                       \
+        else if (big_x) GRAM_W(NB, kGramWaves, false, 1, NoRows{});                                          \
+        else GRAM_W(NB, kGramWaves, false, 0, NoRows{});                                                     \
     } while (0)
         if (NB == 1) GRAM(1);
         else if (NB == 2) GRAM(2);
         else if (NB == 3) GRAM(3);
         else GRAM(4);
 #undef GRAM
+#undef GRAM_W
     }
     list.off = 0;
     list.nparts = nparts;

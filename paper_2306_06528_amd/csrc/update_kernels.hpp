@@ -269,10 +269,6 @@ __device__ inline void update_tail_columns(float *__restrict__ X, const float *_
     }
 }
 
-// keeps the compiler from turning per-row addresses into 2 x 16 loop-carried pointer pairs
-// (an integer offset is laundered, not the pointer, so the accesses stay global_load/store)
-__device__ inline void opaque(int64_t &v) { asm volatile("" : "+v"(v)); }
-
 // CARRY: additionally accumulate the Gram of the UPDATED columns, centred by the pre-update column
 // mean (any per-column shift common to all particles leaves every d2 unchanged), and write one
 // partial per workgroup (the last one is the tail's) to gram_out in the format of

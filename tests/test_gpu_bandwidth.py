@@ -39,6 +39,27 @@ def test_median_with_infinite_distances(n, D):
     _check(n, D, "infinite")
 
 
+@pytest.mark.parametrize("n,D", [(13, 2001), (16, 200_001), (33, 200_001), (64, 100_001)])
+def test_pair_sums_that_overflow(n, D):
+    """One particle is far enough off in one column for its squares to overflow fp32 sums, at both ends of
+    the range where products of its parts overflow to different signs.  The pair sums then have to be
+    those of the fp32 products: infinite distances to that particle (K exactly 0), never NaN."""
+    from paper_2306_06528_amd import svgd
+    for big in (2.5e19, 1e30):
+        X = torch.randn(n, D, generator=torch.Generator().manual_seed(n)).cuda()
+        X[3, D // 2] = big
+        G = torch.randn(n, D, device="cuda")
+        with svgd.Svgd(n, D) as eng:
+            eng.set_bandwidth(float(2 * D))
+            eng.bandwidth(X)
+            h, K = eng.get_last(n)
+            assert np.isfinite(K).all() and np.all(np.diag(K) == 1.0) and np.array_equal(K, K.T)
+            off = np.arange(n) != 3
+            assert np.all(K[3, off] == 0.0)
+            eng.step(X, G, 1e-3)
+            assert bool(torch.isfinite(X[torch.tensor(off)]).all())
+
+
 def _check(n, D, kind):
     from paper_2306_06528_amd import svgd
     Xh = _particles(kind, n, D)
