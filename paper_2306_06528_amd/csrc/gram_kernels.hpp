@@ -240,9 +240,12 @@ __global__ __launch_bounds__(64 * W) void gram_mfma_kernel(const float *__restri
     };
     f32x4 x[RPL];
     int64_t xro[ROWS ? RPL : 1]; // where this lane's rows start (separate rows only)
-    if constexpr (ROWS) {
+    if constexpr (ROWS) { // from the kernel's arguments to LDS in one coalesced read (entries beyond n repeat row 0)
+        __shared__ int64_t srow[ROWS ? kMaxN : 1];
+        if (threadIdx.x < kMaxN) srow[threadIdx.x] = rt.x[ROWS ? threadIdx.x : 0];
+        __syncthreads();
 #pragma unroll
-        for (int i = 0; i < RPL; ++i) xro[i] = (4 * i + q < n) ? rt.x[ROWS ? 4 * i + q : 0] : 0;
+        for (int i = 0; i < RPL; ++i) xro[i] = srow[ROWS ? 4 * i + q : 0];
     }
     // The slab at `at` (then on to the next index): where it lies and how it is to be loaded -
     // 0: plain 16-byte loads, 1: streaming ones, 2: the partial slab, 3: an empty slab.  One

@@ -399,17 +399,17 @@ int run_update(svgd_ctx *c, float *X, const float *G, float *PHI, int n, int64_t
         // workers walk contiguous ranges of full 64-column tiles; one more workgroup does D mod 64
         const int grid = update_workers(c, n, D, ld, CARRY ? out_cap : kMaxParts) + 1;
         if (CARRY) list = PairList{out_off, grid}; // one partial per workgroup, the tail's included
-        // rows that all start on a 128-byte boundary (X's and G's) need no re-aligned stores and
+        // rows that all start on a 128-byte boundary (X's and G's, and PHI's) need no re-aligned stores and
         // can be read with streaming loads
-        const bool aligned = !EMIT && (rt ? rt->aligned != 0 : rows_aligned(X, ld) && rows_aligned(G, ld));
+        const bool aligned = rt ? rt->aligned != 0 : rows_aligned(X, ld) && rows_aligned(G, ld) && (!EMIT || rows_aligned(PHI, ld));
 #define UPD_F(NB, FULL, REM, F)                                                                                      \
     do {                                                                                                             \
         if (!EMIT && !CARRY && rt && aligned)                                                                        \
             update_mfma_kernel<NB, false, FULL, false, true, true, F, false, REM><<<grid, 256, 0, s>>>(X, G, PHI, c->coef, c->state, n, D, ld, eps, gram_out, *rt, ua); \
         else if (!EMIT && !CARRY && rt)                                                                              \
             update_mfma_kernel<NB, false, FULL, false, false, true, F, false, REM><<<grid, 256, 0, s>>>(X, G, PHI, c->coef, c->state, n, D, ld, eps, gram_out, *rt, ua); \
-        else if (!EMIT && aligned)                                                                                   \
-            update_mfma_kernel<NB, false, FULL, CARRY, true, false, F, false, REM><<<grid, 256, 0, s>>>(X, G, PHI, c->coef, c->state, n, D, ld, eps, gram_out, NoRows{}, ua); \
+        else if (aligned)                                                                                            \
+            update_mfma_kernel<NB, EMIT, FULL, CARRY, true, false, F, false, REM><<<grid, 256, 0, s>>>(X, G, PHI, c->coef, c->state, n, D, ld, eps, gram_out, NoRows{}, ua); \
         else if (CARRY && ua.reverse)                                                                                \
             update_mfma_kernel<NB, false, FULL, CARRY, false, false, F, CARRY, REM><<<grid, 256, 0, s>>>(X, G, PHI, c->coef, c->state, n, D, ld, eps, gram_out, NoRows{}, ua); \
         else                                                                                                         \

@@ -224,7 +224,7 @@ __device__ inline void update_tail_columns(float *__restrict__ X, const float *_
                                            float *__restrict__ OUT, const float *Cm, const float *rhov,
                                            float c2h, int n, int64_t D, int64_t ld, int64_t col0, float eps,
                                            float *__restrict__ lds, float *__restrict__ gram_out,
-                                           const typename RowArg<ROWS>::type &rt)
+                                           const int64_t *xrow, const int64_t *grow)
 {
     // plain per-column evaluation for the < 64 columns after the last full tile
     float *zs = lds, *xs = lds + 64 * 64, *yn = lds + 2 * 64 * 64;
@@ -233,8 +233,8 @@ __device__ inline void update_tail_columns(float *__restrict__ X, const float *_
     for (int j = part; j < n; j += 4) {
         float xv = 0.f, gv = 0.f;
         if (ok) {
-            xv = X[(ROWS ? rt.x[ROWS ? j : 0] : (int64_t)j * ld) + col0 + col];
-            gv = G[(ROWS ? rt.g[ROWS ? j : 0] : (int64_t)j * ld) + col0 + col];
+            xv = X[(ROWS ? xrow[j] : (int64_t)j * ld) + col0 + col];
+            gv = G[(ROWS ? grow[j] : (int64_t)j * ld) + col0 + col];
         }
         xs[j * 64 + col] = xv;
         zs[j * 64 + col] = gv - c2h * xv;
@@ -251,7 +251,7 @@ __device__ inline void update_tail_columns(float *__restrict__ X, const float *_
         const float xv = xs[i * 64 + col];
         const float phi = fmaf(rhov[i], xv, acc);
         const float out = EMIT ? phi : fmaf(eps, phi, xv);
-        if (ok) OUT[(ROWS ? rt.x[ROWS ? i : 0] : (int64_t)i * ld) + col0 + col] = out;
+        if (ok) OUT[(ROWS ? xrow[i] : (int64_t)i * ld) + col0 + col] = out;
         if constexpr (CARRY) yn[i * 64 + col] = ok ? out - m : 0.f;
     }
     if constexpr (CARRY) {
@@ -342,23 +342,26 @@ void update_mfma_kernel(float *__restrict__ X, const float *__restrict__ G, floa
     const int64_t out_lane = ROWS ? (int64_t)(4 * c16) : (int64_t)q * ld + 4 * c16;
     const uint32_t dm = (uint32_t)ld & 31u;
     const uint32_t a0 = (uint32_t)(reinterpret_cast<uintptr_t>(OUT) >> 2) & 31u;
-    // separate rows: where this lane's rows of X and G start (loads), and for every row where it
-    // starts and how it is aligned (stores; in LDS, read per store group)
+    // separate rows: where every row of X and of G starts, and X's alignment.  The table goes from the
+    // kernel's arguments to LDS first, one coalesced read: read by every lane where it needs
+    // an entry, the arguments (in host memory) took 5.5 us of each workgroup's start (n = 24, D =
+    // 1,500,001: 125.8 -> 123.8 us per step; n = 13, D = 1,001: 27.3 -> 22.4 with pass 2 fused).
     int64_t xro[ROWS ? NS : 1], gro[ROWS ? NS : 1];
-    __shared__ int64_t srow[ROWS ? kMaxN : 1];
+    __shared__ int64_t srow[ROWS ? kMaxN : 1], sgrow[ROWS ? kMaxN : 1];
     __shared__ int sri[ROWS ? kMaxN : 1];
     if constexpr (ROWS) {
+        if (threadIdx.x < kMaxN) { // (entries beyond n repeat row 0)
+            srow[threadIdx.x] = rt.x[ROWS ? threadIdx.x : 0];
+            sgrow[threadIdx.x] = rt.g[ROWS ? threadIdx.x : 0];
+            sri[threadIdx.x] = rt.ri[ROWS ? threadIdx.x : 0];
+        }
+        __syncthreads();
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
             const int row = 16 * (s >> 2) + (s & 3) + 4 * q;
-            xro[s] = (row < n) ? rt.x[ROWS ? row : 0] : 0;
-            gro[s] = (row < n) ? rt.g[ROWS ? row : 0] : 0;
+            xro[s] = srow[ROWS ? row : 0];
+            gro[s] = sgrow[ROWS ? row : 0];
         }
-        if (threadIdx.x < kMaxN) {
-            srow[threadIdx.x] = ((int)threadIdx.x < n) ? rt.x[ROWS ? threadIdx.x : 0] : 0;
-            sri[threadIdx.x] = ((int)threadIdx.x < n) ? rt.ri[ROWS ? threadIdx.x : 0] : 0;
-        }
-        block_sync<FUSED>();
     }
 
     // Software pipeline across tiles: the loads of tile t+1 are issued while tile t is being
@@ -380,8 +383,8 @@ void update_mfma_kernel(float *__restrict__ X, const float *__restrict__ G, floa
     f32x4 xr = {0.f, 0.f, 0.f, 0.f}, zr = xr, xrn = xr, grn = xr;
     int64_t rem_x, rem_g; // row 16NB + q relative to in_lane (which has 4q ld on one array)
     if constexpr (ROWS) {
-        rem_x = (REM && q < R) ? rt.x[ROWS ? 16 * NB + q : 0] : 0;
-        rem_g = (REM && q < R) ? rt.g[ROWS ? 16 * NB + q : 0] : 0;
+        rem_x = (REM && q < R) ? srow[ROWS ? 16 * NB + q : 0] : 0;
+        rem_g = (REM && q < R) ? sgrow[ROWS ? 16 * NB + q : 0] : 0;
     } else {
         rem_x = rem_g = (int64_t)(16 * NB - 3 * q) * ld;
     }
@@ -473,7 +476,7 @@ void update_mfma_kernel(float *__restrict__ X, const float *__restrict__ G, floa
                 for (int p = threadIdx.x; p < P; p += 256) tail_out[p] = 0.f;
         }
         if ((nfull << 6) < D)
-            update_tail_columns<EMIT, CARRY, ROWS>(X, G, OUT, Cm, rhov, c2h, n, D, ld, nfull << 6, eps, lds, tail_out, rt);
+            update_tail_columns<EMIT, CARRY, ROWS>(X, G, OUT, Cm, rhov, c2h, n, D, ld, nfull << 6, eps, lds, tail_out, srow, sgrow);
         return;
     }
 
