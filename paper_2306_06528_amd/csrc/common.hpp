@@ -61,14 +61,17 @@ struct NoRows {
 template <bool ROWS> struct RowArg { typedef NoRows type; };
 template <> struct RowArg<true> { typedef RowTable type; };
 
-// Offsets (in floats) into the handle's coefficient block.
+// Offsets (in floats) into the handle's coefficient block, which lies kStateBytes behind its DevState:
+// h and K are one piece of memory, so that svgd_get_last is one copy.
+//   K   [n*n]   K_ij (kept for svgd_get_last)
 //   C   [n*n]   C_ij = K_ij / n
 //   RHO [n]     rho_i = (2/h) * (sum_j K_ij) / n
-//   K   [n*n]   K_ij (kept for svgd_get_last)
-constexpr int kOffC = 0;
+constexpr int kStateBytes = 256;
+static_assert(sizeof(DevState) <= kStateBytes, "state block");
+constexpr int kOffK = 0;
+constexpr int kOffC = kOffK + kMaxN * kMaxN;
 constexpr int kOffRho = kOffC + kMaxN * kMaxN;
-constexpr int kOffK = kOffRho + kMaxN;
-constexpr int kCoefFloats = kOffK + kMaxN * kMaxN;
+constexpr int kCoefFloats = kOffRho + kMaxN;
 
 __device__ inline f32x4 load4(const float *__restrict__ row, int64_t col, int64_t D, bool full)
 {

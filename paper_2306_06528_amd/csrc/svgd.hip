@@ -3,6 +3,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <cstring>
 #include <mutex>
 #include <new>
 #include <unordered_set>
@@ -50,7 +51,7 @@ struct svgd_ctx {
     float *partials;  // [kMaxParts][pair_stride]
     double *sums;     // [P], the reduced pair sums
     DevState *state;
-    float *coef;      // kCoefFloats
+    float *coef;      // kCoefFloats, kStateBytes behind `state` in one allocation
     // optional per-kernel timing (svgd_profile_begin/end): event pairs recorded around launches
     bool profiling;
     unsigned profile_kinds; // bit k set: kernels of kind k are timed
@@ -480,11 +481,9 @@ constexpr int kStaticMaxParts = 528;                         // partial vectors 
 constexpr size_t kStaticPartialsBytes = (size_t)kStaticMaxParts * kMaxPairsFull * sizeof(float);
 constexpr size_t kStaticSumsBytes = (size_t)kMaxPairsFull * sizeof(double);
 constexpr size_t kStaticCoefBytes = (size_t)kCoefFloats * sizeof(float);
-constexpr size_t kStaticStateBytes = 256;
-constexpr size_t kStaticBytes = kStaticPartialsBytes + kStaticSumsBytes + kStaticCoefBytes + kStaticStateBytes;
+constexpr size_t kStaticBytes = kStaticPartialsBytes + kStaticSumsBytes + kStaticCoefBytes + kStateBytes;
 static_assert(kStaticPartialsBytes % 256 == 0 && kStaticSumsBytes % 256 == 0 && kStaticCoefBytes % 256 == 0,
               "every part of the scratch starts on a 256-byte boundary");
-static_assert(sizeof(DevState) <= kStaticStateBytes, "state block");
 
 // In host code this name is only a stand-in for the symbol: the memory is reached through the
 // address that hipGetSymbolAddress returns for the current device (static_ctx below).
@@ -540,8 +539,8 @@ svgd_ctx *static_ctx(int dev, int *rc)
     c.partials = reinterpret_cast<float *>(ptr);
     c.partials_cap = (int64_t)kStaticMaxParts * kMaxPairsFull;
     c.sums = reinterpret_cast<double *>(ptr + kStaticPartialsBytes);
-    c.coef = reinterpret_cast<float *>(ptr + kStaticPartialsBytes + kStaticSumsBytes);
-    c.state = reinterpret_cast<DevState *>(ptr + kStaticPartialsBytes + kStaticSumsBytes + kStaticCoefBytes);
+    c.state = reinterpret_cast<DevState *>(ptr + kStaticPartialsBytes + kStaticSumsBytes);
+    c.coef = reinterpret_cast<float *>(ptr + kStaticPartialsBytes + kStaticSumsBytes + kStateBytes);
     c.profiling = false;
     c.profile_kinds = 0;
     sc.ready = true;
@@ -605,17 +604,16 @@ int svgd_create(svgd_handle_t *out, int max_n, int64_t max_D, int device_id, uin
     const size_t P = (size_t)pair_stride(max_n);
     bool ok = hipMalloc(&c->partials, (size_t)kMaxParts * P * sizeof(float)) == hipSuccess &&
               hipMalloc(&c->sums, P * sizeof(double)) == hipSuccess &&
-              hipMalloc(&c->state, sizeof(DevState)) == hipSuccess &&
-              hipMalloc(&c->coef, (size_t)kCoefFloats * sizeof(float)) == hipSuccess;
+              hipMalloc(&c->state, kStateBytes + (size_t)kCoefFloats * sizeof(float)) == hipSuccess;
     if (!ok) {
         (void)hipGetLastError();
         (void)hipFree(c->partials);
         (void)hipFree(c->sums);
         (void)hipFree(c->state);
-        (void)hipFree(c->coef);
         delete c;
         return SVGD_ERR_ALLOC;
     }
+    c->coef = reinterpret_cast<float *>(reinterpret_cast<char *>(c->state) + kStateBytes);
     c->partials_cap = (int64_t)kMaxParts * (int64_t)P;
     c->magic = kMagic;
     {
@@ -817,12 +815,20 @@ int svgd_get_last(svgd_handle_t c, double *h_out, float *K_host, void *stream)
     if (c->last_n < 1) return SVGD_ERR_INVALID_ARG;
     DeviceGuard guard(c->device);
     hipStream_t s = (hipStream_t)stream;
+    // h and K lie in one piece (DevState, K): one copy - a copy to pageable memory is a round trip of
+    // its own, some 15 us - and the host takes apart what arrived
     hipError_t e = hipSuccess;
-    if (h_out) e = hipMemcpyAsync(h_out, &c->state->h, sizeof(double), hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess && K_host)
-        e = hipMemcpyAsync(K_host, c->coef + kOffK, (size_t)c->last_n * c->last_n * sizeof(float),
-                           hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (h_out || K_host) {
+        alignas(DevState) char buf[kStateBytes + sizeof(float) * kMaxN * kMaxN];
+        const size_t kbytes = K_host ? (size_t)c->last_n * c->last_n * sizeof(float) : 0;
+        e = hipMemcpyAsync(buf, c->state, kStateBytes + kbytes, hipMemcpyDeviceToHost, s);
+        if (e == hipSuccess) e = hipStreamSynchronize(s);
+        if (e != hipSuccess) return fail(c, e);
+        if (h_out) *h_out = reinterpret_cast<const DevState *>(buf)->h;
+        if (K_host) std::memcpy(K_host, buf + kStateBytes, kbytes);
+        return SVGD_OK;
+    }
+    e = hipStreamSynchronize(s);
     if (e != hipSuccess) return fail(c, e);
     return SVGD_OK;
 }
@@ -970,7 +976,6 @@ int svgd_destroy(svgd_handle_t c)
         if ((t = hipFree(c->partials)) != hipSuccess) e = t;
         if ((t = hipFree(c->sums)) != hipSuccess) e = t;
         if ((t = hipFree(c->state)) != hipSuccess) e = t;
-        if ((t = hipFree(c->coef)) != hipSuccess) e = t;
         for (hipEvent_t ev : c->ev_pool) (void)hipEventDestroy(ev);
     }
     delete c;

@@ -8,6 +8,7 @@ import ctypes
 import os
 
 import torch
+from torch._C import _cuda_getCurrentRawStream, _cuda_getDevice
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libsvgd.so")
@@ -70,6 +71,8 @@ for _f in ("svgd_create", "svgd_set_bandwidth", "svgd_bandwidth", "svgd_step", "
            "svgd_profile_end"):
     getattr(_lib, _f).restype = ctypes.c_int
 
+_step_ld, _step_static, _Tensor, _float32 = _lib.svgd_step_ld, _lib.svgd_step_static, torch.Tensor, torch.float32
+
 SVGD_OK = 0
 FLAG_CARRY_GRAM = 1
 FLAG_FUSE_MFMA = 2
@@ -92,9 +95,11 @@ def status_string(status: int) -> str:
 
 
 def _stream_ptr(stream):
+    # the current stream of the current device as an integer: torch.cuda.current_stream() builds an
+    # object around it first, which costs as much as the rest of this module's part of a call
     if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+        return _cuda_getCurrentRawStream(_cuda_getDevice())
+    return stream.cuda_stream
 
 
 def _dev_matrix(t: torch.Tensor, name: str):
@@ -168,8 +173,11 @@ def step_static(X: torch.Tensor, G: torch.Tensor, eps: float, stream=None):
     if _rows_of(G, "G") != shape:
         raise ValueError("G must have the shape and row stride of X")
     n, D, ld = shape
-    with torch.cuda.device(X.device):
-        rc = _lib.svgd_step_static(X.data_ptr(), G.data_ptr(), n, D, ld, float(eps), _stream_ptr(stream))
+    if X.get_device() == _cuda_getDevice():
+        rc = _step_static(X.data_ptr(), G.data_ptr(), n, D, ld, float(eps), _stream_ptr(stream))
+    else:
+        with torch.cuda.device(X.device):
+            rc = _step_static(X.data_ptr(), G.data_ptr(), n, D, ld, float(eps), _stream_ptr(stream))
     if rc != SVGD_OK:
         raise SvgdError(rc)
 
@@ -202,14 +210,18 @@ class Svgd:
         """Checks a matrix argument (2-D float32, rows contiguous, on the handle's device - a
         pointer of another GPU would fault) and returns (n, D, ld).  Kept short: at small sizes
         a step costs less than these checks."""
-        if not isinstance(t, torch.Tensor) or t.dtype is not torch.float32 or not t.is_cuda or t.dim() != 2:
+        if not isinstance(t, _Tensor) or t.dtype is not _float32 or not t.is_cuda:
             raise TypeError(f"{name} must be a 2-D float32 CUDA tensor")
-        (n, D), st = t.shape, t.stride()
-        if (D != 1 and st[1] != 1) or (n != 1 and st[0] < D):
+        st = t.stride()
+        if len(st) != 2:
+            raise TypeError(f"{name} must be a 2-D float32 CUDA tensor")
+        n, D = t.shape
+        ld, s1 = st
+        if (D != 1 and s1 != 1) or (n != 1 and ld < D):
             raise TypeError(f"{name} must have contiguous rows, at least D elements apart")
         if t.get_device() != self._device:
             raise ValueError(f"{name} is on cuda:{t.get_device()}, the handle on cuda:{self._device}")
-        return n, D, (st[0] if n != 1 else D)
+        return n, D, (ld if n != 1 else D)
 
     def _same(self, a, b, name):
         if a != b:
@@ -237,10 +249,13 @@ class Svgd:
         """X <- X + eps * phi(X, G) in place.  X and G: (n, D) with contiguous rows and the same
         row stride (dense, or views like buf[:, :D] of an (n, ld) buffer, see padded_rows)."""
         shape = self._rows(X, "X")
-        self._same(shape, self._rows(G, "G"), "G")
+        other = self._rows(G, "G")
+        if other != shape:
+            self._same(shape, other, "G")
         n, D, ld = shape
-        self._check(_lib.svgd_step_ld(self._h, X.data_ptr(), G.data_ptr(), n, D, ld, float(eps),
-                                      _stream_ptr(stream)))
+        rc = _step_ld(self._h, X.data_ptr(), G.data_ptr(), n, D, ld, float(eps), _stream_ptr(stream))
+        if rc:
+            self._check(rc)
         self._last_n = n
 
     def step_rows(self, X_rows, G_rows, eps: float, stream=None):
@@ -250,12 +265,13 @@ class Svgd:
         if n < 1 or len(G_rows) != n:
             raise ValueError("X_rows and G_rows must be non-empty sequences of the same length")
         D = X_rows[0].numel()
+        size, device = (D,), self._device
         for name, rows in (("X_rows", X_rows), ("G_rows", G_rows)):
             for t in rows:
-                if not (isinstance(t, torch.Tensor) and t.dtype is torch.float32 and t.is_cuda and t.dim() == 1
-                        and t.numel() == D and (D == 1 or t.stride(0) == 1)):
+                if not (isinstance(t, _Tensor) and t.dtype is _float32 and t.is_cuda and t.shape == size
+                        and (D == 1 or t.stride(0) == 1)):
                     raise TypeError(f"{name} must hold contiguous 1-D float32 CUDA tensors of one length")
-                if t.get_device() != self._device:
+                if t.get_device() != device:
                     raise ValueError(f"a row of {name} is on cuda:{t.get_device()}, the handle on cuda:{self._device}")
         xp = (ctypes.c_void_p * n)(*[t.data_ptr() for t in X_rows])
         gp = (ctypes.c_void_p * n)(*[t.data_ptr() for t in G_rows])
