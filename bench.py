@@ -157,8 +157,8 @@ def main():
                     help="run the pairwise-d2 pass as its own kernel every step instead of carrying "
                          "the sums over from the previous update (SVGD_FLAG_CARRY_GRAM)")
     ap.add_argument("--fuse", action="store_true",
-                    help="SVGD_FLAG_FUSE_MFMA: the single-launch fused step also for 13 <= n <= 32 "
-                         "(measured slower than two launches there; for the record)")
+                    help="pass SVGD_FLAG_FUSE_MFMA (without effect: the single-launch step is the default "
+                         "wherever the list of carried sums is short)")
     ap.add_argument("--dense-rows", action="store_true",
                     help="rows D floats apart (ld = D) instead of ld = D rounded up to 32 floats")
     ap.add_argument("--swag", action="store_true",

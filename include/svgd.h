@@ -74,7 +74,7 @@ enum svgd_status {
 /*
  * Accepted for compatibility and without effect: it used to ask for the single-launch step on carried
  * sums at 13 <= n <= 32.  That step is now the default wherever the list of carried partial sums is
- * short, at every n <= 32 (n = 16, D = 8,577: 12.4 us in two launches, 9.6 in one).
+ * short, at every n <= 32 (n = 16, D = 8,577: 12.4 us per step in two launches, 10.4 in one).
  */
 #define SVGD_FLAG_FUSE_MFMA 2u
 
@@ -259,7 +259,7 @@ int swag_update_moments(float *mean, float *sqmean, const float *X, int n, int64
 /*
  * svgd_step_ld for callers that cannot allocate: code under HIP graph capture, tight serving
  * loops, harnesses that forbid hipMalloc.  No handle: the scratch (partial sums, their reduction,
- * h, K and the coefficient tables, 4.6 MB) is a static device array inside the library, one copy
+ * h, K and the coefficient tables, 4.5 MB) is a static device array inside the library, one copy
  * per GPU, held until the process ends.  Plain step on the current device: median-heuristic
  * bandwidth, pair sums recomputed from X every call (nothing is carried), X updated in place;
  * same kernels and results as svgd_step_ld on a handle created with flags = 0.  Calls no

@@ -482,8 +482,9 @@ __device__ inline void gather_sums(double *S, double *red, const SumSource &src,
 }
 
 // Lists of at most this many floats are summed by the bandwidth kernel itself; longer ones by
-// reduce_partials_kernel first.
-constexpr int kDirectMaxFloats = 48 * 1024;
+// reduce_partials_kernel first: one CU reads what others have just written at some 60 GB/s (41,600
+// floats at n = 64: step 48.5 us, 45.3 with the reduction; 20,480 at n = 40: 29.4 and 29.0).
+constexpr int kDirectMaxFloats = 16 * 1024;
 
 __global__ __launch_bounds__(kBwThreads) void bandwidth_kernel(SumSource src, BwArgs ba, DevState *__restrict__ st,
                                                                float *__restrict__ coef)

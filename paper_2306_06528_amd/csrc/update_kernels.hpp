@@ -219,6 +219,12 @@ __global__ __launch_bounds__(256) void update_valu_kernel(float *__restrict__ X,
 constexpr int kUpdCur = 16 * 64;    // floats per wave
 constexpr int kUpdCarry = 64 * 32;  // floats per wave
 
+// The < 64 columns after the last full tile, by one workgroup of 256 threads.  Everything is staged in
+// LDS (n * 64 floats each of z, x and - CARRY - the centred new values, n * n4 of C transposed, n4 = n
+// rounded up to 4: at most the 16384 floats the kernel has) and a thread computes a 4 x 4 tile, two
+// 16-byte LDS reads for sixteen multiply-adds.  At small D this workgroup is the last to finish:
+// with a row and a column per thread and C read from memory, n = 64, D = 1,003 took 48.9 us per
+// step, D = 20,003 43.9.
 template <bool EMIT, bool CARRY, bool ROWS>
 __device__ inline void update_tail_columns(float *__restrict__ X, const float *__restrict__ G,
                                            float *__restrict__ OUT, const float *Cm, const float *rhov,
@@ -226,45 +232,105 @@ __device__ inline void update_tail_columns(float *__restrict__ X, const float *_
                                            float *__restrict__ lds, float *__restrict__ gram_out,
                                            const int64_t *xrow, const int64_t *grow)
 {
-    // plain per-column evaluation for the < 64 columns after the last full tile
-    float *zs = lds, *xs = lds + 64 * 64, *yn = lds + 2 * 64 * 64;
-    const int col = threadIdx.x & 63, part = threadIdx.x >> 6;
-    const bool ok = (col0 + col < D);
-    for (int j = part; j < n; j += 4) {
-        float xv = 0.f, gv = 0.f;
-        if (ok) {
-            xv = X[(ROWS ? xrow[j] : (int64_t)j * ld) + col0 + col];
-            gv = G[(ROWS ? grow[j] : (int64_t)j * ld) + col0 + col];
+    const int n4 = (n + 3) & ~3;
+    float *zs = lds, *xs = zs + n * 64, *yn = xs + n * 64, *Ct = yn + (CARRY ? n * 64 : 0);
+    constexpr int U = 8; // loads in flight per array and thread
+    {
+        const int col = threadIdx.x & 63, part = threadIdx.x >> 6;
+        const int64_t at = col0 + col < D ? col0 + col : D - 1;
+        for (int j0 = part; j0 < n; j0 += 4 * U) {
+            float xv[U], gv[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) { // clamped, not guarded: all of them go out together
+                const int j = j0 + 4 * u < n ? j0 + 4 * u : n - 1;
+                xv[u] = X[(ROWS ? xrow[ROWS ? j : 0] : (int64_t)j * ld) + at];
+                gv[u] = G[(ROWS ? grow[ROWS ? j : 0] : (int64_t)j * ld) + at];
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (j0 + 4 * u < n) {
+                    const float x = col0 + col < D ? xv[u] : 0.f, g = col0 + col < D ? gv[u] : 0.f;
+                    xs[(j0 + 4 * u) * 64 + col] = x;
+                    zs[(j0 + 4 * u) * 64 + col] = g - c2h * x;
+                }
+            }
         }
-        xs[j * 64 + col] = xv;
-        zs[j * 64 + col] = gv - c2h * xv;
+        for (int e0 = threadIdx.x; e0 < n * n; e0 += 256 * U) {
+            float c[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) c[u] = Cm[e0 + 256 * u < n * n ? e0 + 256 * u : n * n - 1];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int e = e0 + 256 * u, i = e / n;
+                if (e < n * n) Ct[(e - i * n) * n4 + i] = c[u];
+            }
+        }
     }
     __syncthreads();
-    float m = 0.f;
-    if constexpr (CARRY) {
-        for (int j = 0; j < n; ++j) m += xs[j * 64 + col];
+    const int cg = 4 * (threadIdx.x & 15), i0 = 4 * (threadIdx.x >> 4); // 4 columns, 4 rows
+    if (i0 < n) {
+        f32x4 acc[4], m = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[r] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+        for (int j = 0; j < n; ++j) {
+            const f32x4 z = *reinterpret_cast<const f32x4 *>(&zs[j * 64 + cg]);
+            const f32x4 c = *reinterpret_cast<const f32x4 *>(&Ct[j * n4 + i0]); // (rows n .. n4 - 1 hold anything: not stored)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[r] += c[r] * z;
+            if constexpr (CARRY) m += *reinterpret_cast<const f32x4 *>(&xs[j * 64 + cg]);
+        }
         m *= 1.0f / (float)n;
-    }
-    for (int i = part; i < n; i += 4) {
-        float acc = 0.f;
-        for (int j = 0; j < n; ++j) acc = fmaf(Cm[i * n + j], zs[j * 64 + col], acc);
-        const float xv = xs[i * 64 + col];
-        const float phi = fmaf(rhov[i], xv, acc);
-        const float out = EMIT ? phi : fmaf(eps, phi, xv);
-        if (ok) OUT[(ROWS ? xrow[i] : (int64_t)i * ld) + col0 + col] = out;
-        if constexpr (CARRY) yn[i * 64 + col] = ok ? out - m : 0.f;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int i = i0 + r;
+            if (i < n) {
+                const f32x4 x = *reinterpret_cast<const f32x4 *>(&xs[i * 64 + cg]);
+                f32x4 out;
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    const float phi = fmaf(rhov[i], x[c], acc[r][c]);
+                    out[c] = EMIT ? phi : fmaf(eps, phi, x[c]);
+                    if (col0 + cg + c < D) OUT[(ROWS ? xrow[ROWS ? i : 0] : (int64_t)i * ld) + col0 + cg + c] = out[c];
+                    if (CARRY) out[c] = col0 + cg + c < D ? out[c] - m[c] : 0.f;
+                }
+                if constexpr (CARRY) *reinterpret_cast<f32x4 *>(&yn[i * 64 + cg]) = out;
+            }
+        }
     }
     if constexpr (CARRY) {
-        // Gram of the updated, column-centred tail columns, in tri(i, j) order
+        // Gram of the updated, column-centred tail columns, in tri(i, j) order: thread t takes the t-th
+        // pair of groups of four rows, at most 136; the columns are walked from a different start
+        // by every thread, or all would read the same LDS banks
         __syncthreads();
-        const int P = n * (n + 1) / 2;
-        for (int p = threadIdx.x; p < P; p += 256) {
-            int i = 0, rem = p;
-            while (rem >= n - i) { rem -= n - i; ++i; }
-            const int j = i + rem;
-            float acc = 0.f;
-            for (int c = 0; c < 64; ++c) acc = fmaf(yn[i * 64 + c], yn[j * 64 + c], acc);
-            gram_out[p] = acc;
+        const int ng = n4 / 4;
+        int bi = 0, rem = threadIdx.x;
+        while (bi < ng && rem >= ng - bi) rem -= ng - bi++;
+        const int bj = bi + rem;
+        if (bi < ng) {
+            float acc[4][4] = {};
+            for (int k = 0; k < 16; ++k) {
+                const int c = 4 * ((k + threadIdx.x) & 15);
+                f32x4 a[4], b[4];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    a[r] = *reinterpret_cast<const f32x4 *>(&yn[(4 * bi + r < n ? 4 * bi + r : 0) * 64 + c]);
+                    b[r] = *reinterpret_cast<const f32x4 *>(&yn[(4 * bj + r < n ? 4 * bj + r : 0) * 64 + c]);
+                }
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+#pragma unroll
+                    for (int t = 0; t < 4; ++t)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) acc[r][t] = fmaf(a[r][e], b[t][e], acc[r][t]);
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    const int i = 4 * bi + r, j = 4 * bj + t;
+                    if (i <= j && j < n) gram_out[tri(i, j, n)] = acc[r][t];
+                }
         }
     }
 }
@@ -498,19 +564,37 @@ void update_mfma_kernel(float *__restrict__ X, const float *__restrict__ G, floa
     // A operands of v_mfma_f32_16x16x4_f32 for output block bi, steps 4sg..4sg+3, as one float4
     // per lane: for step s = 4sg + k lane (q = l/16, m = l%16) holds C[16bi + m][16sg + 4q + k]
     // (zero beyond n: rows and columns of the padding take no part)
-    for (int e = threadIdx.x; e < NB * NB * 64; e += 256) {
+    // FULLROWS: all loads go out before the first result is used - one trip to memory, where a loop made
+    // four at n = 64 (3.4 us, now 1.1).  Padded blocks keep guarded loads: with clamped ones the
+    // whole kernel came out slower (separate rows, n = 24, D = 1,500,001: 124.8 -> 132.4 us per step).
+    constexpr int NA = (NB * NB * 64 + 255) / 256;
+    f32x4 av[NA];
+#pragma unroll
+    for (int it = 0; it < NA; ++it) {
+        const int e0 = (int)threadIdx.x + 256 * it, e = e0 < NB * NB * 64 ? e0 : 0;
         const int l = e & 63, sg = (e >> 6) % NB, bi = (e >> 6) / NB;
         const int i = 16 * bi + (l & 15), j0 = 16 * sg + 4 * (l >> 4);
-        f32x4 v;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) v[k] = (i < n && j0 + k < n) ? Cm[i * n + j0 + k] : 0.f;
-        As4[e] = v;
+        if constexpr (FULLROWS) {
+            av[it] = *reinterpret_cast<const f32x4u *>(Cm + i * n + j0);
+        }
     }
     float rho[NS];
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
         const int row = 16 * (s >> 2) + 4 * q + (s & 3);
         rho[s] = (FULLROWS || row < n) ? rhov[row] : 0.f;
+    }
+#pragma unroll
+    for (int it = 0; it < NA; ++it) {
+        const int e = (int)threadIdx.x + 256 * it;
+        if constexpr (!FULLROWS) {
+            const int l = e & 63, sg = (e >> 6) % NB, bi = (e >> 6) / NB;
+            const int i = 16 * bi + (l & 15), j0 = 16 * sg + 4 * (l >> 4);
+            if (e < NB * NB * 64)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) av[it][k] = (i < n && j0 + k < n) ? Cm[i * n + j0 + k] : 0.f;
+        }
+        if (e < NB * NB * 64) As4[e] = av[it];
     }
     // remainder rows.  arem: the A operand of their one contraction step for output block bi -
     // lane (q, m) holds C[16bi + m][16NB + q].  crem: for remainder row r and lane row q the
