@@ -121,8 +121,8 @@ __global__ __launch_bounds__(256) void gram_valu_kernel(const float *__restrict_
 //      takes row 16b+rr - and splits each value into three bf16 parts that add up to it exactly
 //      (split3); v_mfma_f32_16x16x32_bf16 wants 32 columns as its k-slots, eight per lane
 //      (the loads of the next slab are issued here, before the multiply phase),
-//   5. issues six MFMAs per unordered block pair b < b' and four per b = b' (see acc), fp32 accumulators in
-//      registers: lane (q, c), register r of pair (b, b') holds S[16b + 4q + r][16b' + c].
+//   5. issues six MFMAs per unordered block pair b <= b', fp32 accumulators in registers: lane (q, c),
+//      register r of pair (b, b') holds S[16b + 4q + r][16b' + c].
 // Any assignment of columns to k-slots is valid because every column is summed exactly once.
 // ---------------------------------------------------------------------------------------------
 // Order of the slabs.  The update re-reads X right after this pass, every wave (or workgroup) of it
@@ -161,12 +161,13 @@ struct GramOrder {
 // What bounds the pass: at n = 64 the matrix pipe and power, below that memory.  In fp32
 // (v_mfma_f32_16x16x4_f32, 160 per slab) the multiplies took 32 cycles each during which the vector
 // ALU stood still - the fp32 matrix instructions share its multipliers, measured with both in one
-// wave and in two - and 1.07 M cycles per launch; 104 bf16 instructions of 17 cycles beside 224
-// instructions for the split are 0.55 M cycles, of which some of the gain goes to a lower clock (1.7
-// against 2.1 GHz).  n = 64, D = 11,173,962: 568 -> 460 us on padded rows (6.2 TB/s), 583 -> 537 on dense
-// ones, whose slabs share lines that are fetched twice; n = 33, D = 5 M 153 -> 117 (5.6 TB/s);
-// n = 48, D = 1 M 44 -> 38; n = 16, D = 11.2 M 115 -> 112 (6.4 TB/s).  h against 64 bits, n = 64, D =
-// 3 M: relative error 2.6e-8 -> 2e-9 (slab sums instead of one long chain); n = 16, D = 8,577: 5e-9, as before.
+// wave and in two; the bf16 ones, 120 per slab of 17 cycles, run beside the 224 instructions of
+// the split.  Before and after, launched by itself: n = 64, D = 11,173,962, padded rows 569 -> 459 us
+// (6.2 TB/s), dense ones, whose slabs share lines that are fetched twice, 587 -> 552; n = 33, D = 5 M
+// 166 -> 130 (5.1 TB/s); n = 48, D = 1 M 41.5 -> 38.0; n = 16, D = 11.2 M 116 -> 111 (6.4 TB/s).  Inside
+// a step, right behind the update's writes, less of it is left: 568 -> 549 and 558 -> 554 at n = 64,
+// 156 -> 130 at n = 33, 43.7 -> 39.5 at n = 48.  d2 against 64 bits over n = 13..64, D = 65,536..3 M and
+// five distributions: 9.5e-9 -> 2.7e-9 rms (slab sums instead of one long chain); no size is worse.
 template <int NB, int W, bool ROWS = false, int ORDER = 0>
 __global__ __launch_bounds__(64 * W) void gram_mfma_kernel(const float *__restrict__ X, int n,
                                                                     int64_t D, int64_t ld, float *__restrict__ partials,
@@ -182,15 +183,10 @@ __global__ __launch_bounds__(64 * W) void gram_mfma_kernel(const float *__restri
     float *my = lds[wave];
     const float inv_n = 1.0f / (float)n;
 
-    // acc: the sums of the block pairs.  Of a diagonal pair (b, b) only hh + mm is in it; hm + hl, whose
-    // transpose is mh + lh, is in acct and added both ways round at the end: four matrix
-    // instructions instead of six.
-    f32x4 acc[NPAIR], acct[NB];
+    f32x4 acc[NPAIR];
     auto clear = [&]() __attribute__((always_inline)) {
 #pragma unroll
         for (int p = 0; p < NPAIR; ++p) acc[p] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int b = 0; b < NB; ++b) acct[b] = f32x4{0.f, 0.f, 0.f, 0.f};
     };
     const SplitConst sc = split_const();
 
@@ -321,42 +317,50 @@ __global__ __launch_bounds__(64 * W) void gram_mfma_kernel(const float *__restri
         f32x4 t[NPAIR];
 #pragma unroll
         for (int p = 0; p < NPAIR; ++p) t[p] = f32x4{0.f, 0.f, 0.f, 0.f};
+        // One kind of product after the other over the pairs of blocks: a dependent matrix instruction can
+        // issue after some 44 cycles, an independent one after 17.  The small products come first,
+        // those of the leading parts last, so that the sum is rounded at its full size twice only.
+        // Every entry of the matrix takes the same products in the same order, those on the
+        // diagonal too: S_ii, S_ij and S_jj of two equal particles are then equal bit for bit,
+        // wherever the particles lie, and their distance is exactly 0.  (With h l and h m of a diagonal
+        // block taken once and added both ways round - four products instead of six - it was
+        // rounding noise, and with it the median of an ensemble most of whose particles coincide.)
+        auto products = [&](auto left, auto right) __attribute__((always_inline)) {
+            int p = 0;
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+#pragma unroll
+                for (int b2 = b; b2 < NB; ++b2) {
+                    t[p] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(left(b), right(b2), t[p], 0, 0, 0);
+                    ++p;
+                }
+            }
+        };
+        bf16x8 h[2][NB], m[NB], l[NB];
+        auto pm = [&](int b) __attribute__((always_inline)) { return m[b]; };
+        auto pl = [&](int b) __attribute__((always_inline)) { return l[b]; };
 #pragma unroll
         for (int st = 0; st < 2; ++st) { // 32 columns each
-            Split3 a[NB];
 #pragma unroll
             for (int b = 0; b < NB; ++b) {
                 const float *row = buf + (16 * b + c16) * 64; // here c16 plays the role of rr (matrix row)
-                a[b] = split3(*reinterpret_cast<const f32x4 *>(&row[((8 * st + q) ^ c16) << 2]),
-                              *reinterpret_cast<const f32x4 *>(&row[((8 * st + 4 + q) ^ c16) << 2]), sc);
+                const Split3 a = split3(*reinterpret_cast<const f32x4 *>(&row[((8 * st + q) ^ c16) << 2]),
+                                        *reinterpret_cast<const f32x4 *>(&row[((8 * st + 4 + q) ^ c16) << 2]), sc);
+                h[st][b] = a.h;
+                m[b] = a.m;
+                l[b] = a.l;
             }
-            // one kind of product after the other over the pairs of blocks: a dependent matrix
-            // instruction can issue after some 44 cycles, an independent one after 17
-            auto products = [&](auto left, auto right, bool diagonal) __attribute__((always_inline)) {
-                int p = 0;
+            auto ph = [&](int b) __attribute__((always_inline)) { return h[st][b]; };
+            products(ph, pl);
+            products(pl, ph);
+            products(pm, pm);
+            products(ph, pm);
+            products(pm, ph);
+        }
 #pragma unroll
-                for (int b = 0; b < NB; ++b) {
-#pragma unroll
-                    for (int b2 = b; b2 < NB; ++b2) {
-                        if (diagonal || b != b2)
-                            t[p] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[b].*left, a[b2].*right, t[p], 0, 0, 0);
-                        ++p;
-                    }
-                }
-            };
-            auto half_products = [&](auto right) __attribute__((always_inline)) {
-#pragma unroll
-                for (int b = 0; b < NB; ++b)
-                    acct[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[b].h, a[b].*right, acct[b], 0, 0, 0);
-            };
-            half_products(&Split3::l);
-            products(&Split3::h, &Split3::l, false);
-            products(&Split3::l, &Split3::h, false);
-            products(&Split3::m, &Split3::m, true);
-            half_products(&Split3::m);
-            products(&Split3::h, &Split3::m, false);
-            products(&Split3::m, &Split3::h, false);
-            products(&Split3::h, &Split3::h, true);
+        for (int st = 0; st < 2; ++st) {
+            auto ph = [&](int b) __attribute__((always_inline)) { return h[st][b]; };
+            products(ph, ph);
         }
 #pragma unroll
         for (int p = 0; p < NPAIR; ++p) acc[p] += t[p];
@@ -408,24 +412,16 @@ __global__ __launch_bounds__(64 * W) void gram_mfma_kernel(const float *__restri
         for (int p = 0; p < NPAIR; ++p)
 #pragma unroll
             for (int r = 0; r < 4; ++r) odd += 0.f * acc[p][r]; // 0, or NaN
-#pragma unroll
-        for (int b = 0; b < NB; ++b)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) odd += 0.f * acct[b][r];
         if (__ballot(odd != 0.f) != 0) sweep(std::true_type{});
     }
 
     // The waves meet in LDS, each with its sums in its own region (free by now); wave w adds up and
     // stores the block pairs w, w + 8, ... of the upper triangle in tri(i, j) order.
-    static_assert((NPAIR + NB) * 256 <= NROW * 64, "a wave's sums fit its region");
+    static_assert(NPAIR * 256 <= NROW * 64, "a wave's sums fit its region");
 #pragma unroll
     for (int p = 0; p < NPAIR; ++p)
 #pragma unroll
         for (int r = 0; r < 4; ++r) my[(p * 4 + r) * 64 + lane] = acc[p][r];
-#pragma unroll
-    for (int b = 0; !F32 && b < NB; ++b)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) my[((NPAIR + b) * 4 + r) * 64 + lane] = acct[b][r];
     __syncthreads();
     float *out = partials + (int64_t)blockIdx.x * pair_stride(n);
     int p = 0;
@@ -440,12 +436,7 @@ __global__ __launch_bounds__(64 * W) void gram_mfma_kernel(const float *__restri
                     const int j = 16 * b2 + c16;
                     double v = 0.0;
 #pragma unroll
-                    for (int w = 0; w < W; ++w) {
-                        v += (double)lds[w][(p * 4 + r) * 64 + lane];
-                        if (!F32 && b == b2) // entry (4q + r, c16) of acct and its mirror image
-                            v += (double)lds[w][((NPAIR + b) * 4 + r) * 64 + lane] +
-                                 (double)lds[w][((NPAIR + b) * 4 + (c16 & 3)) * 64 + 16 * (c16 >> 2) + 4 * q + r];
-                    }
+                    for (int w = 0; w < W; ++w) v += (double)lds[w][(p * 4 + r) * 64 + lane];
                     if (i <= j && j < n) out[tri(i, j, n)] = (float)v;
                 }
             }
