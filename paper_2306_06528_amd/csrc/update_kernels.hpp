@@ -233,6 +233,9 @@ __device__ inline void update_tail_columns(float *__restrict__ X, const float *_
                                            const int64_t *xrow, const int64_t *grow)
 {
     const int n4 = (n + 3) & ~3;
+    // yn: groups of four rows keep their 16-byte granules in orders of their own, so that the pair sums can
+    // read different groups at the same column without meeting in the LDS banks
+    auto yn_index = [](int i, int c) { return i * 64 + (c ^ (((i >> 2) & 15) << 2)); };
     float *zs = lds, *xs = zs + n * 64, *yn = xs + n * 64, *Ct = yn + (CARRY ? n * 64 : 0);
     constexpr int U = 8; // loads in flight per array and thread
     {
@@ -294,14 +297,14 @@ __device__ inline void update_tail_columns(float *__restrict__ X, const float *_
                     if (col0 + cg + c < D) OUT[(ROWS ? xrow[ROWS ? i : 0] : (int64_t)i * ld) + col0 + cg + c] = out[c];
                     if (CARRY) out[c] = col0 + cg + c < D ? out[c] - m[c] : 0.f;
                 }
-                if constexpr (CARRY) *reinterpret_cast<f32x4 *>(&yn[i * 64 + cg]) = out;
+                if constexpr (CARRY) *reinterpret_cast<f32x4 *>(&yn[yn_index(i, cg)]) = out;
             }
         }
     }
     if constexpr (CARRY) {
         // Gram of the updated, column-centred tail columns, in tri(i, j) order: thread t takes the t-th
-        // pair of groups of four rows, at most 136; the columns are walked from a different start
-        // by every thread, or all would read the same LDS banks
+        // pair of groups of four rows, at most 136.  Every pair adds its columns in the same order,
+        // so that equal particles stay at distance exactly 0.
         __syncthreads();
         const int ng = n4 / 4;
         int bi = 0, rem = threadIdx.x;
@@ -309,13 +312,12 @@ __device__ inline void update_tail_columns(float *__restrict__ X, const float *_
         const int bj = bi + rem;
         if (bi < ng) {
             float acc[4][4] = {};
-            for (int k = 0; k < 16; ++k) {
-                const int c = 4 * ((k + threadIdx.x) & 15);
+            for (int c = 0; c < 64; c += 4) {
                 f32x4 a[4], b[4];
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    a[r] = *reinterpret_cast<const f32x4 *>(&yn[(4 * bi + r < n ? 4 * bi + r : 0) * 64 + c]);
-                    b[r] = *reinterpret_cast<const f32x4 *>(&yn[(4 * bj + r < n ? 4 * bj + r : 0) * 64 + c]);
+                    a[r] = *reinterpret_cast<const f32x4 *>(&yn[yn_index(4 * bi + r < n ? 4 * bi + r : 0, c)]);
+                    b[r] = *reinterpret_cast<const f32x4 *>(&yn[yn_index(4 * bj + r < n ? 4 * bj + r : 0, c)]);
                 }
 #pragma unroll
                 for (int r = 0; r < 4; ++r)
