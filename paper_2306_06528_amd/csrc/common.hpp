@@ -191,14 +191,15 @@ __device__ __forceinline__ Split3 split3(f32x4 a, f32x4 b, const SplitConst &sc)
     return r;
 }
 
-// Sum over the 16 lanes of each row of a wave, in every lane: quad swap, quad-pair swap, half-row
-// mirror, row mirror.
+// Sum over the 16 lanes of each row of a wave (or over aligned groups of L = 1, 2, 4 or 8 lanes), in
+// every lane: quad swap, quad-pair swap, half-row mirror, row mirror.
+template <int L = 16>
 __device__ inline float row_sum(float v)
 {
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xF, 0xF, false));  // quad_perm [1,0,3,2]
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4E, 0xF, 0xF, false));  // quad_perm [2,3,0,1]
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x141, 0xF, 0xF, false)); // row_half_mirror
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x140, 0xF, 0xF, false)); // row_mirror
+    if constexpr (L > 1) v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xF, 0xF, false)); // quad_perm [1,0,3,2]
+    if constexpr (L > 2) v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4E, 0xF, 0xF, false)); // quad_perm [2,3,0,1]
+    if constexpr (L > 4) v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x141, 0xF, 0xF, false)); // row_half_mirror
+    if constexpr (L > 8) v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x140, 0xF, 0xF, false)); // row_mirror
     return v;
 }
 

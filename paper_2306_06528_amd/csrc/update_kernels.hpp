@@ -225,7 +225,7 @@ constexpr int kUpdCarry = 64 * 32;  // floats per wave
 // 16-byte LDS reads for sixteen multiply-adds.  At small D this workgroup is the last to finish:
 // with a row and a column per thread and C read from memory, n = 64, D = 1,003 took 48.9 us per
 // step, D = 20,003 43.9.
-template <bool EMIT, bool CARRY, bool ROWS>
+template <int NMAX, bool EMIT, bool CARRY, bool ROWS> // n <= NMAX, a multiple of 4
 __device__ inline void update_tail_columns(float *__restrict__ X, const float *__restrict__ G,
                                            float *__restrict__ OUT, const float *Cm, const float *rhov,
                                            float c2h, int n, int64_t D, int64_t ld, int64_t col0, float eps,
@@ -302,17 +302,21 @@ __device__ inline void update_tail_columns(float *__restrict__ X, const float *_
         }
     }
     if constexpr (CARRY) {
-        // Gram of the updated, column-centred tail columns, in tri(i, j) order: thread t takes the t-th
-        // pair of groups of four rows, at most 136.  Every pair adds its columns in the same order,
-        // so that equal particles stay at distance exactly 0.
-        __syncthreads();
-        const int ng = n4 / 4;
-        int bi = 0, rem = threadIdx.x;
+        // Gram of the updated, column-centred tail columns, in tri(i, j) order: a 4 x 4 tile of pairs, at
+        // most 136 tiles, belongs to PARTS neighbouring threads that share its columns - as many as
+        // the workgroup has for it.  (With one thread per tile ten of them walked all columns at n = 16
+        // while the others waited: D = 1,003, 15.8 us per step, now 12.1.)  Every pair adds its columns
+        // in the same order, so that equal particles stay at distance exactly 0.
+        constexpr int kTiles = (NMAX / 4) * (NMAX / 4 + 1) / 2;
+        constexpr int PARTS = kTiles * 16 <= 256 ? 16 : (kTiles * 4 <= 256 ? 4 : (kTiles * 2 <= 256 ? 2 : 1));
+        block_sync<true>(); // (LDS only: nothing waits for the stores of the new columns)
+        const int ng = n4 / 4, part = threadIdx.x % PARTS;
+        int bi = 0, rem = threadIdx.x / PARTS;
         while (bi < ng && rem >= ng - bi) rem -= ng - bi++;
         const int bj = bi + rem;
         if (bi < ng) {
             float acc[4][4] = {};
-            for (int c = 0; c < 64; c += 4) {
+            for (int c = 4 * part; c < 64; c += 4 * PARTS) {
                 f32x4 a[4], b[4];
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
@@ -330,8 +334,9 @@ __device__ inline void update_tail_columns(float *__restrict__ X, const float *_
             for (int r = 0; r < 4; ++r)
 #pragma unroll
                 for (int t = 0; t < 4; ++t) {
+                    const float v = row_sum<PARTS>(acc[r][t]);
                     const int i = 4 * bi + r, j = 4 * bj + t;
-                    if (i <= j && j < n) gram_out[tri(i, j, n)] = acc[r][t];
+                    if ((4 * r + t) % PARTS == part && i <= j && j < n) gram_out[tri(i, j, n)] = v;
                 }
         }
     }
@@ -544,7 +549,7 @@ void update_mfma_kernel(float *__restrict__ X, const float *__restrict__ G, floa
                 for (int p = threadIdx.x; p < P; p += 256) tail_out[p] = 0.f;
         }
         if ((nfull << 6) < D)
-            update_tail_columns<EMIT, CARRY, ROWS>(X, G, OUT, Cm, rhov, c2h, n, D, ld, nfull << 6, eps, lds, tail_out, srow, sgrow);
+            update_tail_columns<16 * NB + (REM ? 4 : 0), EMIT, CARRY, ROWS>(X, G, OUT, Cm, rhov, c2h, n, D, ld, nfull << 6, eps, lds, tail_out, srow, sgrow);
         return;
     }
 
