@@ -585,11 +585,21 @@ void update_mfma_kernel(float *__restrict__ X, const float *__restrict__ G, floa
             av[it] = *reinterpret_cast<const f32x4u *>(Cm + i * n + j0);
         }
     }
-    float rho[NS];
+    // rho of this lane's rows: in registers, or (RHO_LDS) in LDS, four of a block at a time, where the registers
+    // do not suffice: with two waves per SIMD there are 256, and a spilled one read back in every tile
+    // waits for all loads of the next tile, which are older (n = 24, D = 3,000,001, dense rows:
+    // 203 us per step with three spilled, 188 now; n = 21 194 -> 172, n = 30, D = 1,000,003 88 -> 82).
+    constexpr bool RHO_LDS = CARRY && !ALIGNED && !FULLROWS && NB == 2;
+    __shared__ __attribute__((aligned(16))) float rho_lds[RHO_LDS ? 16 * NB : 4];
+    float rho[RHO_LDS ? 1 : NS];
+    if constexpr (RHO_LDS) {
+        if (threadIdx.x < 16 * NB) rho_lds[threadIdx.x] = (int)threadIdx.x < n ? rhov[threadIdx.x] : 0.f;
+    } else {
 #pragma unroll
-    for (int s = 0; s < NS; ++s) {
-        const int row = 16 * (s >> 2) + 4 * q + (s & 3);
-        rho[s] = (FULLROWS || row < n) ? rhov[row] : 0.f;
+        for (int s = 0; s < NS; ++s) {
+            const int row = 16 * (s >> 2) + 4 * q + (s & 3);
+            rho[s] = (FULLROWS || row < n) ? rhov[row] : 0.f;
+        }
     }
 #pragma unroll
     for (int it = 0; it < NA; ++it) {
@@ -778,13 +788,15 @@ void update_mfma_kernel(float *__restrict__ X, const float *__restrict__ G, floa
             }
             if (!ALIGNED && bi > 0) carry_copy(bi - 1);
             // epilogue for rows 16bi + 4q + r, then stage the block in LDS
+            f32x4 rho4;
+            if constexpr (RHO_LDS) rho4 = *reinterpret_cast<const f32x4 *>(&rho_lds[16 * bi + 4 * q]);
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int s = 4 * bi + r;
                 f32x4 o;
 #pragma unroll
                 for (int t = 0; t < 4; ++t) {
-                    const float phi = fmaf(rho[s], x[s][t], acc[t][r]);
+                    const float phi = fmaf(RHO_LDS ? rho4[r] : rho[RHO_LDS ? 0 : s], x[s][t], acc[t][r]);
                     o[t] = EMIT ? phi : fmaf(eps, phi, x[s][t]);
                 }
                 if constexpr (ALIGNED) { // the lane's 16 bytes lie where it loaded x from: whole lines per quarter-wave
