@@ -235,13 +235,19 @@ __global__ __launch_bounds__(64 * W) void gram_mfma_kernel(const float *__restri
         if constexpr (ORDERED) enter();
     };
     f32x4 x[RPL];
-    int64_t xro[ROWS ? RPL : 1]; // where this lane's rows start (separate rows only)
-    if constexpr (ROWS) { // from the kernel's arguments to LDS in one coalesced read (entries beyond n repeat row 0)
-        __shared__ int64_t srow[ROWS ? kMaxN : 1];
+    // Where this lane's rows start (separate rows only): in LDS, and - RREG - in registers from there.  With four
+    // blocks there are none left for them: 47 were spilled, and the pass took 304 us at n = 64, D =
+    // 5,000,000 (262 in fp32, 256 now; n = 49, D = 3,000,001 146 -> 116).
+    constexpr bool RREG = ROWS && (NB < 4 || F32);
+    __shared__ int64_t srow[ROWS ? kMaxN : 1];
+    int64_t xro[RREG ? RPL : 1];
+    if constexpr (ROWS) { // from the kernel's arguments in one coalesced read (entries beyond n repeat row 0)
         if (threadIdx.x < kMaxN) srow[threadIdx.x] = rt.x[ROWS ? threadIdx.x : 0];
         __syncthreads();
+    }
+    if constexpr (RREG) {
 #pragma unroll
-        for (int i = 0; i < RPL; ++i) xro[i] = srow[ROWS ? 4 * i + q : 0];
+        for (int i = 0; i < RPL; ++i) xro[i] = srow[4 * i + q];
     }
     // The slab at `at` (then on to the next index): where it lies and how it is to be loaded -
     // 0: plain 16-byte loads, 1: streaming ones, 2: the partial slab, 3: an empty slab.  One
@@ -268,10 +274,12 @@ __global__ __launch_bounds__(64 * W) void gram_mfma_kernel(const float *__restri
         constexpr int HOW = decltype(how)::value;
         int64_t at0 = (int64_t)q * ld + col; // this lane's place in row q; row 4i + q is a uniform distance on
         opaque(at0);
+        int qv = q;
+        if constexpr (ROWS && !RREG) asm volatile("" : "+v"(qv)); // (or the reads would be hoisted out of the loop)
 #pragma unroll
         for (int i = 0; i < RPL; ++i) {
             const int row = 4 * i + q;
-            const float *xr = ROWS ? X + xro[ROWS ? i : 0] + col : X + at0 + (int64_t)(4 * i) * ld;
+            const float *xr = RREG ? X + xro[RREG ? i : 0] + col : (ROWS ? X + srow[ROWS ? 4 * i + qv : 0] + col : X + at0 + (int64_t)(4 * i) * ld);
             f32x4 v = {0.f, 0.f, 0.f, 0.f}; // rows beyond n, and empty slabs, add nothing to any sum
             // (only the last block of 16 rows can reach beyond n)
             if (HOW != 3 && (i < RPL - 4 || row < n)) {
