@@ -422,8 +422,9 @@ struct SumSource {
 };
 
 // Reads them into S [n (n + 1) / 2].  Thread (kk, pp) = (tid / P4, tid % P4), kk < KL, sums four
-// consecutive entries of the partials kk, kk + KL, ... sixteen 16-byte loads in flight; the KL
+// consecutive entries of the partials kk, kk + KL, ... kSumLoads 16-byte loads in flight; the KL
 // sums of an entry meet in `red` [KL * P4 * 4 <= 4 * THREADS].
+constexpr int kSumLoads = 16;
 template <int THREADS, class Meanwhile>
 __device__ inline void gather_sums(double *S, double *red, const SumSource &src, int n, Meanwhile meanwhile)
 {
@@ -443,7 +444,7 @@ __device__ inline void gather_sums(double *S, double *red, const SumSource &src,
     const int P4 = (P + 3) / 4;
     const int KL = THREADS / P4 < 32 ? THREADS / P4 : 32; // capped: the KL sums are added serially
     const int kk = tid / P4, pp = tid - kk * P4;
-    constexpr int U = 16;
+    constexpr int U = kSumLoads;
     const f32x4 *base = reinterpret_cast<const f32x4 *>(src.partials) + pp;
     double s[4] = {0.0, 0.0, 0.0, 0.0};
     bool first = true;

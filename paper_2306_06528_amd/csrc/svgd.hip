@@ -216,6 +216,7 @@ bool adjacent_tiles(int n, int64_t ld) { return n > 48 || beyond_cache(n, ld); }
 // with 16 or 32 particles the second workgroup costs 2-5 %, and for an X that cache serves it
 // costs 9 %).
 // The Gram pass splits the tiles the same way.  `cap` bounds the grid, the tail's workgroup included.
+// (D mod 64 = 0: no workgroup for the tail.)
 int update_workers(const svgd_ctx *c, int n, int64_t D, int64_t ld, int cap)
 {
     const int64_t nfull = D / 64;
@@ -335,16 +336,45 @@ int run_bandwidth(svgd_ctx *c, int n, const PairList &list, hipStream_t s)
     return SVGD_OK;
 }
 
-// Up to kFusedMaxN particles the update kernel does pass 2 itself, in every workgroup, if the list of
-// partials is short: then the whole second half of a step is one launch.  256 threads hold at most
-// 496 pairs comfortably, and every workgroup reads the whole list.  Where the list is long, summing
-// it in a launch of many workgroups and pass 2 in one of its own are faster on the matrix-core path
-// (n = 20, D = 300,007, 110 K floats: 48 us fused, 39 apart); on the vector-ALU path every list a
-// Gram pass or an update leaves is short enough, and fusing wins up to the largest sizes (n = 8,
-// D = 11,173,962: 281 -> 270 us; n = 10, D = 300,001: 31 -> 24; n = 16, D = 8,577: 15.5 -> 12.2).
+// Up to kFusedMaxN particles the update kernel does pass 2 itself, in every workgroup, if that costs
+// less than the launches it saves: 256 threads hold at most 496 pairs comfortably, and every
+// workgroup reads the whole list, in batches of sixteen 16-byte loads per thread, one after the
+// other (gather_sums).  Up to four batches it wins, from five on the list is better summed by a
+// launch of many workgroups: us per step on dense rows, in one launch and apart, n = 16, D =
+// 300,007 (3 batches) 25.3 and 30.1; n = 24, D = 40,003 (4) 21.5 and 22.0, D = 50,001 (5) 23.4 and 22.7;
+// n = 32, D = 12,289 (4) 21.1 and 21.8, D = 20,001 (5) 24.0 and 22.1, D = 65,000 (16) 40.7 and 24.1.
+// On the vector-ALU path every list is that short, and one launch wins up to the largest sizes (n =
+// 8, D = 11,173,962: 281 -> 270 us; n = 10, D = 300,001: 31 -> 24).
 constexpr int kFusedMaxN = 32;
-constexpr int kFusedMaxFloatsValu = 64 * 1024;
-constexpr int kFusedMaxFloatsMfma = 48 * 1024;
+constexpr int kFusedMaxBatches = 4;
+
+int sum_batches(int n, int nparts)
+{
+    const int p4 = pair_stride(n) / 4, groups = mini(256 / p4, 32);
+    return (nparts + kSumLoads * groups - 1) / (kSumLoads * groups);
+}
+
+// And only if all its workgroups are resident at once, or pass 2 is paid for twice: the instances
+// whose blocks are full take a CU's registers for one workgroup, the others for half of one.  Where
+// the tail's workgroup comes on top of a worker for every CU, one worker less makes room for it if
+// no wave gets a tile more by that - also where two workgroups fit a CU, and the two there would
+// slow each other (257 and 256 workgroups: n = 16, D = 300,007 35 and 25 us per step; n = 13, D =
+// 100,003, padded rows, carried sums 16.1 and 13.8).  Returns the number of workers, 0: not as one launch.
+int fused_workers(const svgd_ctx *c, int n, int64_t D, int64_t ld, int workers)
+{
+    const bool full_rows = (n & 15) == 0 || has_remainder_rows(n);
+    const int64_t nfull = D / 64, ranges = adjacent_tiles(n, ld) ? 1 : 4; // per workgroup
+    auto tiles_per_wave = [&](int64_t w) {
+        const int64_t per = (nfull + w * ranges - 1) / (w * ranges);
+        return ranges == 1 ? (per + 3) / 4 : per;
+    };
+    for (int per_cu = 1; per_cu <= (full_rows ? 1 : 2); ++per_cu) {
+        const int room = c->num_cu * per_cu - ((D & 63) ? 1 : 0);
+        if (workers <= room) return workers;
+        if (room > 0 && tiles_per_wave(room) == tiles_per_wave(workers)) return room;
+    }
+    return 0;
+}
 
 // Passes 2 and 3.  EMIT = false: X updated in place; EMIT = true: phi written to PHI.  CARRY (in
 // place): the update also leaves the pair-sum partials of the new X in the scratch, described by
@@ -357,17 +387,19 @@ int run_update(svgd_ctx *c, float *X, const float *G, float *PHI, int n, int64_t
     ua.h_fixed = c->h_fixed;
     ua.log_n1 = std::log((double)n + 1.0);
     const int64_t list_floats = (int64_t)list.nparts * pair_stride(n);
-    const int64_t half = (c->partials_cap / 2) & ~(int64_t)63; // CARRY: the list is read while the new one is written
-    const bool fused = n <= kFusedMaxN && list_floats <= (n <= kValuMaxN ? kFusedMaxFloatsValu : kFusedMaxFloatsMfma) && (!CARRY || list_floats <= half);
-    int out_cap = max_parts(c, n);
+    const int64_t half = (c->partials_cap / 2) & ~(int64_t)63; // CARRY: a list may be read while the new one is written
+    const int out_cap = CARRY ? (int)std::min<int64_t>(half / pair_stride(n), kMaxParts) : kMaxParts;
+    int workers = n > kValuMaxN ? update_workers(c, n, D, ld, out_cap) : 0;
+    bool fused = n <= kFusedMaxN && sum_batches(n, list.nparts) <= kFusedMaxBatches && (!CARRY || list_floats <= half);
+    if (fused && n > kValuMaxN) {
+        const int w = fused_workers(c, n, D, ld, workers);
+        fused = w > 0;
+        if (fused) workers = w;
+    }
     int64_t out_off = 0;
     if (fused) {
         ua.src = SumSource{nullptr, c->partials + list.off, list.nparts};
-        if (CARRY) {
-            out_off = list.off == 0 ? half : 0;
-            const int64_t m = half / pair_stride(n);
-            out_cap = (int)(m < kMaxParts ? m : kMaxParts);
-        }
+        if (CARRY) out_off = list.off == 0 ? half : 0;
         c->last_n = n;
     } else {
         int rc = run_bandwidth(c, n, list, s);
@@ -389,7 +421,7 @@ int run_update(svgd_ctx *c, float *X, const float *G, float *PHI, int n, int64_t
         // registers for loads in flight: plain step at D = 6,000,000, one against two per CU, n = 9
         // 182 / 168 us, n = 12 235 / 240; at D = 1,000,000 44 / 38 and 57 / 64.
         const int per_cu = n <= (CARRY ? 8 : 10) ? 2 : 1;
-        const int grid = clampi((ngroups + 255) / 256, 1, mini(c->num_cu * per_cu, CARRY ? out_cap : kMaxParts));
+        const int grid = clampi((ngroups + 255) / 256, 1, mini(c->num_cu * per_cu, out_cap));
         if (CARRY) list = PairList{out_off, grid};
 #define CALL(N)                                                                                                      \
     if (fused) launch_update_valu<N, EMIT, CARRY, true>(X, G, PHI, c->coef, c->state, D, ld, eps, gram_out, grid, s, rt, ua); \
@@ -398,7 +430,7 @@ int run_update(svgd_ctx *c, float *X, const float *G, float *PHI, int n, int64_t
 #undef CALL
     } else {
         // workers walk contiguous ranges of full 64-column tiles; one more workgroup does D mod 64
-        const int grid = update_workers(c, n, D, ld, CARRY ? out_cap : kMaxParts) + 1;
+        const int grid = workers + ((D & 63) ? 1 : 0);
         if (CARRY) list = PairList{out_off, grid}; // one partial per workgroup, the tail's included
         // rows that all start on a 128-byte boundary (X's and G's, and PHI's) need no re-aligned stores and
         // can be read with streaming loads

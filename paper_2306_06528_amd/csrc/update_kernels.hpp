@@ -398,7 +398,9 @@ void update_mfma_kernel(float *__restrict__ X, const float *__restrict__ G, floa
     // (TS = 4), which makes the workgroup's accesses 1 KiB contiguous per row.
     const int64_t TS = (ALIGNED && ua.adjacent != 0) ? 4 : 1;
     int64_t t0, t1;
-    tile_range(nfull, gridDim.x - 1, blockIdx.x, wave, TS == 4, t0, t1);
+    const bool has_tail = (nfull << 6) < D; // the last workgroup does the columns after the last full tile
+    const int nwork = (int)gridDim.x - (has_tail ? 1 : 0);
+    tile_range(nfull, nwork, blockIdx.x, wave, TS == 4, t0, t1);
     const int64_t c_begin = t0 << 6;
     // visiting order: tiles t_first + k * t_step, k < ntiles.  ALIGNED kernels take the direction
     // at run time; re-aligned stores hand a row's leftover from tile to tile, so their mirror
@@ -540,16 +542,10 @@ void update_mfma_kernel(float *__restrict__ X, const float *__restrict__ G, floa
         c2h = st->two_over_h;
     }
 
-    if (blockIdx.x == gridDim.x - 1) { // the extra workgroup: ragged tail only
+    if (has_tail && (int)blockIdx.x == nwork) { // the extra workgroup: ragged tail only
         float *tail_out = nullptr;
-        if constexpr (CARRY) {
-            const int P = n * (n + 1) / 2;
-            tail_out = gram_out + (int64_t)(gridDim.x - 1) * pair_stride(n); // after the workers' partials
-            if ((nfull << 6) >= D)
-                for (int p = threadIdx.x; p < P; p += 256) tail_out[p] = 0.f;
-        }
-        if ((nfull << 6) < D)
-            update_tail_columns<16 * NB + (REM ? 4 : 0), EMIT, CARRY, ROWS>(X, G, OUT, Cm, rhov, c2h, n, D, ld, nfull << 6, eps, lds, tail_out, srow, sgrow);
+        if constexpr (CARRY) tail_out = gram_out + (int64_t)nwork * pair_stride(n); // after the workers' partials
+        update_tail_columns<16 * NB + (REM ? 4 : 0), EMIT, CARRY, ROWS>(X, G, OUT, Cm, rhov, c2h, n, D, ld, nfull << 6, eps, lds, tail_out, srow, sgrow);
         return;
     }
 

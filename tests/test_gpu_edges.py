@@ -40,3 +40,50 @@ def test_moments_at_the_edges(total):
     tol = 2.0 ** -22
     assert bool(((md.cpu().double() - ref_m).abs() <= tol * (m.abs() + x.abs())).all())
     assert bool(((sd.cpu().double() - ref_s).abs() <= tol * (s + x * x)).all())
+
+
+def _counts(svgd, eng, calls):
+    """Launches per kernel kind (gram, reduce, bandwidth, update) that `calls` make."""
+    eng.profile_begin()
+    calls()
+    prof = eng.profile_end()
+    return [prof[k][1] for k in svgd.KERNEL_KINDS]
+
+
+@pytest.mark.parametrize("flags", ["carry", "carry_and_fuse"])
+@pytest.mark.parametrize("n,D,fused", [
+    (8, 100_003, True), (12, 300_007, True),          # vector ALU: always
+    (13, 5_001, True), (16, 8_577, True), (24, 40_003, True), (24, 50_001, False),
+    (32, 12_289, True), (32, 20_001, False), (33, 5_001, False),
+    (16, 300_007, True),                              # 255 workers and the tail's workgroup fill the chip
+    (16, 131_100, False),                             # 255 workers would need a third tile per wave
+    (20, 131_072, True), (16, 131_072, True),         # no columns after the last tile, no workgroup for them
+])
+def test_where_pass_2_is_part_of_the_update(n, D, fused, flags):
+    """The launches of a plain step, phi, separate rows and a carried step on both sides of the rule that
+    makes pass 2 part of the update (a device of 256 CUs), and their results on either side: phi
+    and a chain of steps against the oracle.  SVGD_FLAG_FUSE_MFMA changes nothing."""
+    from paper_2306_06528_amd import svgd
+    assert torch.cuda.get_device_properties(0).multi_processor_count == 256
+    g = torch.Generator().manual_seed(n + D)
+    X, G = (0.3 * torch.randn(n, D, generator=g)).cuda(), torch.randn(n, D, generator=g).cuda()
+    PHI = torch.empty_like(X)
+    one = lambda gram: [gram, 0, 0, 1]
+    def expect(got, gram):
+        if fused:
+            assert got == one(gram)
+        else:
+            assert got[0] == gram and got[2:] == [1, 1]
+    with svgd.Svgd(n, D) as eng:
+        expect(_counts(svgd, eng, lambda: eng.phi(X, G, PHI)), 1)
+        expect(_counts(svgd, eng, lambda: eng.step(X.clone(), G, 0.05)), 1)
+        rows, grows = [X[i].clone() for i in range(n)], [G[i].clone() for i in range(n)]
+        expect(_counts(svgd, eng, lambda: eng.step_rows(rows, grows, 0.05)), 1)
+    f = svgd.FLAG_CARRY_GRAM | (svgd.FLAG_FUSE_MFMA if flags == "carry_and_fuse" else 0)
+    with svgd.Svgd(n, D, flags=f) as eng:
+        Xc = X.clone()
+        expect(_counts(svgd, eng, lambda: eng.step(Xc, G, 0.05)), 1)
+        expect(_counts(svgd, eng, lambda: eng.step(Xc, G, 0.05)), 0)
+    if flags == "carry":
+        for padded in (False, True):
+            check_carried_chain(svgd, X, G, 0.05, padded=padded, steps=3)
