@@ -356,11 +356,15 @@ int sum_batches(int n, int nparts)
 
 // And only if all its workgroups are resident at once, or pass 2 is paid for twice: the instances
 // whose blocks are full take a CU's registers for one workgroup, the others for half of one.  Where
-// the tail's workgroup comes on top of a worker for every CU, one worker less makes room for it if
-// no wave gets a tile more by that - also where two workgroups fit a CU, and the two there would
-// slow each other (257 and 256 workgroups: n = 16, D = 300,007 35 and 25 us per step; n = 13, D =
-// 100,003, padded rows, carried sums 16.1 and 13.8).  Returns the number of workers, 0: not as one launch.
-int fused_workers(const svgd_ctx *c, int n, int64_t D, int64_t ld, int workers)
+// the tail's workgroup comes on top of a worker for every CU, one worker less makes room for it
+// (257 and 256 workgroups: n = 16, D = 300,007 35 and 25 us per step; n = 13, D = 100,003, padded rows,
+// carried sums 16.1 and 13.8).  That may give the waves a tile more, which is still the faster way
+// with full blocks (n = 16, D = 131,100, two tiles per wave or three: 32 us in 257 workgroups, 22.9
+// in launches of their own, 21.9) and, carrying sums, where the tail's workgroup takes longer, up to 15
+// particles (n = 15, same D, padded: 17.8 and 14.2); otherwise two workgroups share a CU (n = 15,
+// plain step: 17.5, 21.1 with a tile more; n = 21, carried: 23.8 and 27.3).
+// Returns the number of workers, 0: not as one launch.
+int fused_workers(const svgd_ctx *c, int n, int64_t D, int64_t ld, int workers, bool carry)
 {
     const bool full_rows = (n & 15) == 0 || has_remainder_rows(n);
     const int64_t nfull = D / 64, ranges = adjacent_tiles(n, ld) ? 1 : 4; // per workgroup
@@ -371,7 +375,7 @@ int fused_workers(const svgd_ctx *c, int n, int64_t D, int64_t ld, int workers)
     for (int per_cu = 1; per_cu <= (full_rows ? 1 : 2); ++per_cu) {
         const int room = c->num_cu * per_cu - ((D & 63) ? 1 : 0);
         if (workers <= room) return workers;
-        if (room > 0 && tiles_per_wave(room) == tiles_per_wave(workers)) return room;
+        if (room > 0 && (full_rows || (carry && n < 16) || tiles_per_wave(room) == tiles_per_wave(workers))) return room;
     }
     return 0;
 }
@@ -392,7 +396,7 @@ int run_update(svgd_ctx *c, float *X, const float *G, float *PHI, int n, int64_t
     int workers = n > kValuMaxN ? update_workers(c, n, D, ld, out_cap) : 0;
     bool fused = n <= kFusedMaxN && sum_batches(n, list.nparts) <= kFusedMaxBatches && (!CARRY || list_floats <= half);
     if (fused && n > kValuMaxN) {
-        const int w = fused_workers(c, n, D, ld, workers);
+        const int w = fused_workers(c, n, D, ld, workers, CARRY);
         fused = w > 0;
         if (fused) workers = w;
     }

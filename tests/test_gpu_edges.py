@@ -56,7 +56,7 @@ def _counts(svgd, eng, calls):
     (13, 5_001, True), (16, 8_577, True), (24, 40_003, True), (24, 50_001, False),
     (32, 12_289, True), (32, 20_001, False), (33, 5_001, False),
     (16, 300_007, True),                              # 255 workers and the tail's workgroup fill the chip
-    (16, 131_100, False),                             # 255 workers would need a third tile per wave
+    (16, 131_100, True), (15, 131_100, True),         # 255 workers with a third tile per wave; 257 workgroups, two a CU
     (20, 131_072, True), (16, 131_072, True),         # no columns after the last tile, no workgroup for them
 ])
 def test_where_pass_2_is_part_of_the_update(n, D, fused, flags):
