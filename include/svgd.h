@@ -69,6 +69,11 @@ enum svgd_status {
  * the same either way), so that each starts on the part of X that is still in the memory-side
  * cache; the direction is chosen when the call is made.  A caller who captures steps into a HIP
  * graph keeps that benefit by capturing an even number of consecutive steps per graph.
+ * Captured steps read the sums that the last replay or eager step on the handle has left: replays of
+ * graphs captured on this handle and eager steps mix freely on the stream of the capture (same X, n, D).  From
+ * the first captured step on the handle keeps its sums in one place for that, which costs steps
+ * that run as one launch a second, small one (n <= 32).  After touching X, replay only graphs
+ * whose first step recomputes: those captured right after svgd_forget_carry.
  */
 #define SVGD_FLAG_CARRY_GRAM 1u
 /*

@@ -453,6 +453,13 @@ __global__ __launch_bounds__(64 * W) void gram_mfma_kernel(const float *__restri
     }
 }
 
+// A list of partials from one half of the scratch to the other.
+__global__ __launch_bounds__(256) void copy_list_kernel(const f32x4 *__restrict__ src, f32x4 *__restrict__ dst, int n4)
+{
+    const int i = (int)(blockIdx.x * 256 + threadIdx.x);
+    if (i < n4) dst[i] = src[i];
+}
+
 // Sum the per-workgroup fp32 partials in fp64: sums[p] = sum_k partials[k][p].  A workgroup takes 32
 // entries, eight lanes of four next to each other, and thread group g of 32 the partials g, g + 32,
 // ... with sixteen 16-byte loads in flight: the 512 partials of a large problem are one batch of

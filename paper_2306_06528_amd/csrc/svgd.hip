@@ -43,6 +43,8 @@ struct svgd_ctx {
     int64_t carry_ld;
     int carry_nparts;
     int64_t carry_off;        // where in `partials` the carried list starts (floats): 0 or the upper half
+    bool captured;            // a step on carried sums has been captured into a graph (svgd_step_ld):
+    int64_t home;             // from then on every carried list ends up here
     hipStream_t carry_stream; // the stream the carried sums were produced on
     int64_t partials_cap;     // floats available in `partials`
     unsigned sweeps;          // in-place updates with carried sums so far: every other one walks X backwards
@@ -182,13 +184,17 @@ void launch_update_valu(float *X, const float *G, float *PHI, float *coef, DevSt
 int clampi(int64_t v, int lo, int hi) { return (int)(v < lo ? lo : (v > hi ? hi : v)); }
 int mini(int a, int b) { return a < b ? a : b; }
 
-// How many partial vectors of n(n+1)/2 floats the handle's scratch holds: the upper bound on every
-// grid whose workgroups write one partial each.
-int max_parts(const svgd_ctx *c, int n)
+// How many partial vectors of n(n+1)/2 floats the handle's scratch holds from `off` on: the upper bound on
+// every grid whose workgroups write one partial each.
+int max_parts(const svgd_ctx *c, int n, int64_t off)
 {
-    const int64_t m = c->partials_cap / pair_stride(n);
+    const int64_t m = (c->partials_cap - off) / pair_stride(n);
     return (int)(m < kMaxParts ? m : kMaxParts);
 }
+
+// The scratch in two halves: a list may be read while the new one is written.
+int64_t half_scratch(const svgd_ctx *c) { return (c->partials_cap / 2) & ~(int64_t)63; }
+int64_t other_half(const svgd_ctx *c, int64_t off) { return off == 0 ? half_scratch(c) : 0; }
 
 // An X that the memory-side cache cannot hold (with a margin: n = 32, D = 2,000,000 just fits and
 // behaves like a cached problem).
@@ -231,14 +237,17 @@ struct PairList {
     int nparts;
 };
 
-// Pass 1: the pair sums of X, one partial per workgroup, at the start of the scratch.
+// Pass 1: the pair sums of X, one partial per workgroup, at the start of the scratch - or, once a step on
+// carried sums has been captured, where the graph expects a list (carry_next), or out of its way.
 // G_next: where the in-place update that follows this call will read its scores (null: none, or
 // an update that writes phi elsewhere); carry_next: that update will carry pair sums.  Both only
 // steer the order in which X is visited.
 int run_gram(svgd_ctx *c, const float *X, int n, int64_t D, int64_t ld, hipStream_t s, PairList &list,
              const RowTable *rt = nullptr, const float *G_next = nullptr, bool carry_next = false)
 {
-    const int cap_parts = max_parts(c, n);
+    list.off = !c->captured ? 0 : (carry_next ? c->home : other_half(c, c->home));
+    float *const partials = c->partials + list.off;
+    const int cap_parts = max_parts(c, n, list.off);
     int nparts;
     // streaming loads in pass 1: X well beyond what the memory-side cache could keep for the update
     const bool big_x = (int64_t)n * ld * (int64_t)sizeof(float) > 2 * kMemorySideCacheBytes;
@@ -248,7 +257,7 @@ int run_gram(svgd_ctx *c, const float *X, int n, int64_t D, int64_t ld, hipStrea
         const int64_t ngroups = (D + 3) / 4;
         nparts = clampi((ngroups + 255) / 256, 1, mini(c->num_cu * 3, cap_parts)); // all resident at once; each ends with a reduction
         const bool stream_x = big_x;
-#define CALL(N) launch_gram_valu<N>(X, D, ld, c->partials, nparts, s, rt, stream_x)
+#define CALL(N) launch_gram_valu<N>(X, D, ld, partials, nparts, s, rt, stream_x)
         SVGD_SWITCH_N(n, CALL)
 #undef CALL
     } else {
@@ -277,7 +286,7 @@ int run_gram(svgd_ctx *c, const float *X, int n, int64_t D, int64_t ld, hipStrea
         if (cold) { go.q_cold = stride / cold; go.r_cold = stride % cold; }
         if (hot) { go.q_hot = stride / (uint32_t)hot; go.r_hot = stride % (uint32_t)hot; }
         // (the order is only worth its bookkeeping for an X well beyond the memory-side cache)
-#define GRAM_W(NB, W, ROWS, ORDER, rows) gram_mfma_kernel<NB, W, ROWS, ORDER><<<nparts, 64 * W, 0, s>>>(X, n, D, ld, c->partials, rows, go)
+#define GRAM_W(NB, W, ROWS, ORDER, rows) gram_mfma_kernel<NB, W, ROWS, ORDER><<<nparts, 64 * W, 0, s>>>(X, n, D, ld, partials, rows, go)
 #define GRAM(NB)                                                                                             \
     do {                                                                                                     \
         if (rt && small) GRAM_W(NB, kGramWavesSmall, true, 0, *rt);                                          \
@@ -296,7 +305,6 @@ int run_gram(svgd_ctx *c, const float *X, int n, int64_t D, int64_t ld, hipStrea
 #undef GRAM
 #undef GRAM_W
     }
-    list.off = 0;
     list.nparts = nparts;
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(c, e);
@@ -348,7 +356,7 @@ int run_bandwidth(svgd_ctx *c, int n, const PairList &list, hipStream_t s)
 constexpr int kFusedMaxN = 32;
 constexpr int kFusedMaxBatches = 4;
 
-int sum_batches(int n, int nparts)
+int sum_batches(int n, int nparts) // n <= kFusedMaxN
 {
     const int p4 = pair_stride(n) / 4, groups = mini(256 / p4, 32);
     return (nparts + kSumLoads * groups - 1) / (kSumLoads * groups);
@@ -391,19 +399,23 @@ int run_update(svgd_ctx *c, float *X, const float *G, float *PHI, int n, int64_t
     ua.h_fixed = c->h_fixed;
     ua.log_n1 = std::log((double)n + 1.0);
     const int64_t list_floats = (int64_t)list.nparts * pair_stride(n);
-    const int64_t half = (c->partials_cap / 2) & ~(int64_t)63; // CARRY: a list may be read while the new one is written
+    const int64_t half = half_scratch(c);
     const int out_cap = CARRY ? (int)std::min<int64_t>(half / pair_stride(n), kMaxParts) : kMaxParts;
-    int workers = n > kValuMaxN ? update_workers(c, n, D, ld, out_cap) : 0;
     bool fused = n <= kFusedMaxN && sum_batches(n, list.nparts) <= kFusedMaxBatches && (!CARRY || list_floats <= half);
-    if (fused && n > kValuMaxN) {
-        const int w = fused_workers(c, n, D, ld, workers, CARRY);
-        fused = w > 0;
-        if (fused) workers = w;
+    int workers = 0;
+    if (n > kValuMaxN) {
+        workers = update_workers(c, n, D, ld, out_cap);
+        const int w = n <= kFusedMaxN ? fused_workers(c, n, D, ld, workers, CARRY) : 0;
+        // CARRY: the number of workgroups, which is that of the carried partial sums, depends on the
+        // problem only, not on the list that is read: a captured step reads what any other one left
+        const bool adapt = w > 0 && (CARRY ? sum_batches(n, w + ((D & 63) ? 1 : 0)) <= kFusedMaxBatches : fused);
+        if (adapt) workers = w;
+        fused = fused && workers == w;
     }
-    int64_t out_off = 0;
+    int64_t out_off = c->captured ? c->home : 0;
     if (fused) {
         ua.src = SumSource{nullptr, c->partials + list.off, list.nparts};
-        if (CARRY) out_off = list.off == 0 ? half : 0;
+        if (CARRY) out_off = other_half(c, list.off);
         c->last_n = n;
     } else {
         int rc = run_bandwidth(c, n, list, s);
@@ -476,9 +488,26 @@ int run_update(svgd_ctx *c, float *X, const float *G, float *PHI, int n, int64_t
 #undef UPD
 #undef UPD_F
     }
+    if (CARRY && c->captured && list.off != c->home) {
+        const int n4 = list.nparts * (pair_stride(n) / 4);
+        copy_list_kernel<<<(n4 + 255) / 256, 256, 0, s>>>(reinterpret_cast<const f32x4 *>(c->partials + list.off),
+                                                          reinterpret_cast<f32x4 *>(c->partials + c->home), n4);
+        list.off = c->home;
+    }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(c, e);
     return SVGD_OK;
+}
+
+// Whether what is launched on the stream goes into a graph.
+bool is_capturing(hipStream_t s)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &st) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return st == hipStreamCaptureStatusActive;
 }
 
 // The single-launch path: sizes at which one workgroup does the whole step faster than three
@@ -568,6 +597,8 @@ svgd_ctx *static_ctx(int dev, int *rc)
     c.carry_D = c.carry_ld = 0;
     c.carry_nparts = 0;
     c.carry_off = 0;
+    c.captured = false;
+    c.home = 0;
     c.carry_stream = nullptr;
     c.sweeps = 0;
     c.last_n = 0;
@@ -609,6 +640,8 @@ int svgd_create(svgd_handle_t *out, int max_n, int64_t max_D, int device_id, uin
     c->carry_ld = 0;
     c->carry_nparts = 0;
     c->carry_off = 0;
+    c->captured = false;
+    c->home = 0;
     c->carry_stream = nullptr;
     c->sweeps = 0;
     c->partials_cap = 0;
@@ -728,6 +761,13 @@ int svgd_step_ld(svgd_handle_t c, float *X, const float *G, int n, int64_t D, in
     c->carry_valid = false;
     if (is_tiny(n, D)) return run_tiny<kTinyStep>(c, X, G, nullptr, n, D, ld, eps, s);
     PairList list{c->carry_off, c->carry_nparts};
+    // A step that reads one half of the scratch and writes the other cannot be replayed: the next replay
+    // would read the old sums again.  From the first captured step on, every list on this handle
+    // ends up where that step found its own.
+    if (carry_mode && !c->captured && is_capturing(s)) {
+        c->captured = true;
+        c->home = use_carry ? list.off : 0;
+    }
     if (!use_carry) {
         rc = run_gram(c, X, n, D, ld, s, list, nullptr, G, carry_mode);
         if (rc) return rc;
