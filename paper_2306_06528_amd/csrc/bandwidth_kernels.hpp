@@ -383,8 +383,8 @@ __device__ inline double kernel_matrix(BwShared<MAXN, THREADS> &sh, const BwArgs
     }
 
 #pragma unroll
-    for (int u = 0; u < VPT; ++u) // K per pair, reusing S (last read before the barriers above)
-        if (tid + u * THREADS < Pp) sh.S[tid + u * THREADS] = exp(-d2[u] * inv_h);
+    for (int u = 0; u < VPT; ++u) // K per pair, reusing S (last read before the barriers above); 1 / h may be infinite
+        if (tid + u * THREADS < Pp) sh.S[tid + u * THREADS] = d2[u] > 0.0 ? exp(-d2[u] * inv_h) : 1.0;
     block_sync<LO>();
     // K, C, row sums: 16 lanes per row.  K_ij and K_ji are the same LDS entry, so K is exactly
     // symmetric; the diagonal is exactly 1.

@@ -60,6 +60,22 @@ def test_pair_sums_that_overflow(n, D):
             assert bool(torch.isfinite(X[torch.tensor(off)]).all())
 
 
+@pytest.mark.parametrize("n,D", [(4, 100), (8, 3001), (16, 3001), (33, 3001)])
+def test_equal_particles_under_a_tiny_fixed_bandwidth(n, D):
+    """K = exp(-d2 / h) of equal particles is 1 at every h, also where 1 / h overflows; of others it is 0."""
+    from paper_2306_06528_amd import svgd
+    X = torch.randn(n, D, generator=torch.Generator().manual_seed(n))
+    X[1] = X[n - 1]
+    want = np.eye(n, dtype=np.float32)
+    want[1, n - 1] = want[n - 1, 1] = 1.0
+    with svgd.Svgd(n, D) as eng:
+        for h in (1e-300, 1e-310, 5e-324):
+            eng.set_bandwidth(h)
+            eng.bandwidth(X.cuda())
+            got_h, K = eng.get_last(n)
+            assert got_h == h and np.array_equal(K, want), h
+
+
 def _check(n, D, kind):
     from paper_2306_06528_amd import svgd
     Xh = _particles(kind, n, D)
