@@ -8,7 +8,14 @@ import ctypes
 import os
 
 import torch
-from torch._C import _cuda_getCurrentRawStream, _cuda_getDevice
+
+try:  # the current stream as an integer, without an object around it
+    from torch._C import _cuda_getCurrentRawStream, _cuda_getDevice
+except ImportError:  # (names that torch does not promise to keep)
+    _cuda_getDevice = torch.cuda.current_device
+
+    def _cuda_getCurrentRawStream(device):
+        return torch.cuda.current_stream(device).cuda_stream
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libsvgd.so")
