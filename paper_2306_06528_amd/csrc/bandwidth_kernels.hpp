@@ -414,48 +414,52 @@ __device__ inline double kernel_matrix(BwShared<MAXN, THREADS> &sh, const BwArgs
 }
 
 // Where the pair sums of pass 2 come from: fully reduced sums (reduce_partials_kernel), or - sums
-// null - a list of nparts fp32 partials, pair_stride(n) floats apart, summed here in fp64.
+// null - a list of nparts fp32 partials, pair_stride(n) floats apart.
 struct SumSource {
     const double *sums;
     const float *partials;
     int nparts;
 };
 
-// Reads them into S [n (n + 1) / 2].  Thread (kk, pp) = (tid / P4, tid % P4), kk < KL, sums four
-// consecutive entries of the partials kk, kk + KL, ... kSumLoads 16-byte loads in flight; the KL
-// sums of an entry meet in `red` [KL * P4 * 4 <= 4 * THREADS].
+// Reads reduced sums into S [n (n + 1) / 2 <= 2080].
+template <int THREADS, class Meanwhile>
+__device__ inline void copy_sums(double *S, const double *sums, int n, Meanwhile meanwhile)
+{
+    constexpr int U = (kMaxPairsFull + THREADS - 1) / THREADS;
+    const int tid = threadIdx.x, P = n * (n + 1) / 2;
+    double v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = sums[tid + u * THREADS < P ? tid + u * THREADS : 0];
+    meanwhile();
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+        if (tid + u * THREADS < P) S[tid + u * THREADS] = v[u];
+}
+
+// Sums a list of partials in fp64 into S [n (n + 1) / 2].  Thread (kk, pp) = (tid / P4, tid % P4), kk <
+// KL, sums four consecutive entries of the partials kk, kk + KL, ... kSumLoads 16-byte loads in
+// flight; the KL sums of an entry meet in `red` [KL * P4 * 4 <= 4 * THREADS].
 constexpr int kSumLoads = 16;
 template <int THREADS, class Meanwhile>
-__device__ inline void gather_sums(double *S, double *red, const SumSource &src, int n, Meanwhile meanwhile)
+__device__ inline void gather_sums(double *S, double *red, const float *partials, int nparts, int n, Meanwhile meanwhile)
 {
     const int tid = threadIdx.x;
     const int P = n * (n + 1) / 2;
-    if (src.sums != nullptr) {
-        constexpr int U = 3; // P <= 2080 with 1024 threads, 528 with 256
-        double v[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) v[u] = src.sums[tid + u * THREADS < P ? tid + u * THREADS : 0];
-        meanwhile();
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-            if (tid + u * THREADS < P) S[tid + u * THREADS] = v[u];
-        return;
-    }
     const int P4 = (P + 3) / 4;
     const int KL = THREADS / P4 < 32 ? THREADS / P4 : 32; // capped: the KL sums are added serially
     const int kk = tid / P4, pp = tid - kk * P4;
     constexpr int U = kSumLoads;
-    const f32x4 *base = reinterpret_cast<const f32x4 *>(src.partials) + pp;
+    const f32x4 *base = reinterpret_cast<const f32x4 *>(partials) + pp;
     double s[4] = {0.0, 0.0, 0.0, 0.0};
     bool first = true;
-    for (int k0 = 0; k0 < src.nparts; k0 += U * KL) { // trip count uniform over the workgroup
+    for (int k0 = 0; k0 < nparts; k0 += U * KL) { // trip count uniform over the workgroup
         f32x4 v[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             v[u] = f32x4{0.f, 0.f, 0.f, 0.f};
-            if (k0 + u * KL < src.nparts) { // uniform: whole loads beyond the list are left out, single lanes read its last entry again
+            if (k0 + u * KL < nparts) { // uniform: whole loads beyond the list are left out, single lanes read its last entry again
                 int k = k0 + kk + u * KL;
-                k = k < src.nparts ? k : src.nparts - 1;
+                k = k < nparts ? k : nparts - 1;
                 v[u] = base[(int64_t)k * P4];
             }
         }
@@ -463,7 +467,7 @@ __device__ inline void gather_sums(double *S, double *red, const SumSource &src,
         first = false;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const bool in = k0 + kk + u * KL < src.nparts;
+            const bool in = k0 + kk + u * KL < nparts;
 #pragma unroll
             for (int c = 0; c < 4; ++c) s[c] += in ? (double)v[u][c] : 0.0;
         }
@@ -495,7 +499,10 @@ __global__ __launch_bounds__(kBwThreads) void bandwidth_kernel(SumSource src, Bw
     float c2h;
     kernel_matrix<kBwThreads, kMaxN, false>(
         sh, ba, st, coef, nullptr, true, c2h,
-        [&](auto meanwhile) __attribute__((always_inline)) { gather_sums<kBwThreads>(sh.S, red, src, ba.n, meanwhile); },
+        [&](auto meanwhile) __attribute__((always_inline)) {
+            if (src.sums != nullptr) copy_sums<kBwThreads>(sh.S, src.sums, ba.n, meanwhile);
+            else gather_sums<kBwThreads>(sh.S, red, src.partials, src.nparts, ba.n, meanwhile);
+        },
         NoCall{});
 }
 

@@ -31,7 +31,7 @@ __host__ __device__ inline int tri(int i, int j, int n) { return i * n - (i * (i
 
 // Partial-sum vectors lie this many floats apart, so that every one starts on 16 bytes and is read
 // four entries at a time (the up to three floats after the last entry are never used).
-__host__ __device__ inline int pair_stride(int n) { return (n * (n + 1) / 2 + 3) & ~3; }
+__host__ __device__ constexpr int pair_stride(int n) { return (n * (n + 1) / 2 + 3) & ~3; }
 
 // Everything the update kernels need from the bandwidth kernel, in device memory.
 struct DevState {

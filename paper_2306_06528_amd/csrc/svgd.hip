@@ -23,6 +23,7 @@ namespace {
 
 constexpr uint32_t kMagic = 0x53564744u; // "SVGD"
 constexpr int kMaxParts = 2048;          // upper bound on Gram workgroups (= partial vectors)
+constexpr int kMaxCu = 256;              // CUs of this part
 constexpr int64_t kMemorySideCacheBytes = (int64_t)256 << 20; // this part's memory-side cache (between L2 and HBM)
 
 } // namespace
@@ -151,18 +152,18 @@ void launch_gram_valu(const float *X, int64_t D, int64_t ld, float *partials, in
         gram_valu_kernel<N, false><<<grid, 256, 0, s>>>(X, D, ld, partials, NoRows{});
 }
 
-template <int N, bool EMIT, bool CARRY, bool FUSED>
+template <int N, bool EMIT, bool CARRY>
 void launch_update_valu(float *X, const float *G, float *PHI, float *coef, DevState *st,
                         int64_t D, int64_t ld, float eps, float *gram_out, int grid, hipStream_t s,
                         const RowTable *rt, const UpdateArgs &ua)
 {
     if constexpr (!EMIT && !CARRY) {
         if (rt) {
-            update_valu_kernel<N, false, false, true, FUSED><<<grid, 256, 0, s>>>(X, G, PHI, coef, st, D, ld, eps, gram_out, *rt, ua);
+            update_valu_kernel<N, false, false, true><<<grid, 256, 0, s>>>(X, G, PHI, coef, st, D, ld, eps, gram_out, *rt, ua);
             return;
         }
     }
-    update_valu_kernel<N, EMIT, CARRY, false, FUSED><<<grid, 256, 0, s>>>(X, G, PHI, coef, st, D, ld, eps, gram_out, NoRows{}, ua);
+    update_valu_kernel<N, EMIT, CARRY, false><<<grid, 256, 0, s>>>(X, G, PHI, coef, st, D, ld, eps, gram_out, NoRows{}, ua);
 }
 
 #define SVGD_SWITCH_N(n, CALL)                                                                     \
@@ -231,6 +232,28 @@ int update_workers(const svgd_ctx *c, int n, int64_t D, int64_t ld, int cap)
     return clampi((nfull + 3) / 4, 1, max_workers);
 }
 
+// Up to kFusedMaxN particles the update kernel does pass 2 itself, in every workgroup, if that costs
+// less than the launches it saves: 256 threads hold at most 496 pairs comfortably, and every
+// workgroup reads the whole list, in batches of sixteen 16-byte loads per thread, one after the
+// other (gather_sums).  Up to four batches it wins, from five on the list is better summed by a
+// launch of many workgroups: us per step on dense rows, in one launch and apart, n = 16, D =
+// 300,007 (3 batches) 25.3 and 30.1; n = 24, D = 40,003 (4) 21.5 and 22.0, D = 50,001 (5) 23.4 and 22.7;
+// n = 32, D = 12,289 (4) 21.1 and 21.8, D = 20,001 (5) 24.0 and 22.1, D = 65,000 (16) 40.7 and 24.1.
+// On the vector-ALU path every list is that short (run_gram sees to it), and one launch wins up to the
+// largest sizes (n = 8, D = 11,173,962: 281 -> 270 us; n = 10, D = 300,001: 31 -> 24).
+constexpr int kFusedMaxN = 32;
+constexpr int kFusedMaxBatches = 4;
+
+constexpr int fused_max_parts(int n) // n <= kFusedMaxN
+{
+    const int groups = 256 / (pair_stride(n) / 4);
+    return kFusedMaxBatches * kSumLoads * (groups < 32 ? groups : 32);
+}
+// Up to 20 particles (one block of rows, remainder rows included) no list is longer: the grids whose workgroups
+// leave a partial each have one per CU on the matrix-core path, the tail's workgroup included.
+constexpr int kFusedAlwaysN = 20;
+static_assert(fused_max_parts(kFusedAlwaysN) >= kMaxCu, "one partial per CU is a short list");
+
 // A list of pair-sum partials in the handle's scratch.
 struct PairList {
     int64_t off; // where it starts (floats)
@@ -240,7 +263,7 @@ struct PairList {
 // Pass 1: the pair sums of X, one partial per workgroup, at the start of the scratch - or, once a step on
 // carried sums has been captured, where the graph expects a list (carry_next), or out of its way.
 // G_next: where the update that follows this call will read its scores (null: none, or one that writes
-// phi to unaligned rows); carry_next: that update will carry pair sums.  Both only steer the order in
+// phi to unaligned rows); carry_next: that update will carry pair sums.  They steer the order in
 // which X is visited, so that the pass ends on the tiles the update starts with (n = 32, D = 9,000,000:
 // separate rows 888 -> 865 us per step, phi on aligned rows 856 -> 836).
 int run_gram(svgd_ctx *c, const float *X, int n, int64_t D, int64_t ld, hipStream_t s, PairList &list,
@@ -256,7 +279,9 @@ int run_gram(svgd_ctx *c, const float *X, int n, int64_t D, int64_t ld, hipStrea
     KernelTimer t(c, SVGD_KERNEL_GRAM, s);
     if (n <= kValuMaxN) {
         const int64_t ngroups = (D + 3) / 4;
-        nparts = clampi((ngroups + 255) / 256, 1, mini(c->num_cu * 3, cap_parts)); // all resident at once; each ends with a reduction
+        // all resident at once; each ends with a reduction; the update sums the list (three per CU of
+        // 256 are just what it takes at n = 12)
+        nparts = clampi((ngroups + 255) / 256, 1, mini(mini(c->num_cu * 3, cap_parts), mini(fused_max_parts(n), (int)(half_scratch(c) / pair_stride(n)))));
         const bool stream_x = big_x;
 #define CALL(N) launch_gram_valu<N>(X, D, ld, partials, nparts, s, rt, stream_x)
         SVGD_SWITCH_N(n, CALL)
@@ -345,24 +370,6 @@ int run_bandwidth(svgd_ctx *c, int n, const PairList &list, hipStream_t s)
     return SVGD_OK;
 }
 
-// Up to kFusedMaxN particles the update kernel does pass 2 itself, in every workgroup, if that costs
-// less than the launches it saves: 256 threads hold at most 496 pairs comfortably, and every
-// workgroup reads the whole list, in batches of sixteen 16-byte loads per thread, one after the
-// other (gather_sums).  Up to four batches it wins, from five on the list is better summed by a
-// launch of many workgroups: us per step on dense rows, in one launch and apart, n = 16, D =
-// 300,007 (3 batches) 25.3 and 30.1; n = 24, D = 40,003 (4) 21.5 and 22.0, D = 50,001 (5) 23.4 and 22.7;
-// n = 32, D = 12,289 (4) 21.1 and 21.8, D = 20,001 (5) 24.0 and 22.1, D = 65,000 (16) 40.7 and 24.1.
-// On the vector-ALU path every list is that short, and one launch wins up to the largest sizes (n =
-// 8, D = 11,173,962: 281 -> 270 us; n = 10, D = 300,001: 31 -> 24).
-constexpr int kFusedMaxN = 32;
-constexpr int kFusedMaxBatches = 4;
-
-int sum_batches(int n, int nparts) // n <= kFusedMaxN
-{
-    const int p4 = pair_stride(n) / 4, groups = mini(256 / p4, 32);
-    return (nparts + kSumLoads * groups - 1) / (kSumLoads * groups);
-}
-
 // And only if all its workgroups are resident at once, or pass 2 is paid for twice: the instances
 // whose blocks are full take a CU's registers for one workgroup, the others for half of one.  Where
 // the tail's workgroup comes on top of a worker for every CU, one worker less makes room for it
@@ -372,7 +379,7 @@ int sum_batches(int n, int nparts) // n <= kFusedMaxN
 // in launches of their own, 21.9) and, carrying sums, where the tail's workgroup takes longer, up to 15
 // particles (n = 15, same D, padded: 17.8 and 14.2); otherwise two workgroups share a CU (n = 15,
 // plain step: 17.5, 21.1 with a tile more; n = 21, carried: 23.8 and 27.3).
-// Returns the number of workers, 0: not as one launch.
+// Returns the number of workers, 0: not as one launch (21 particles or more only).
 int fused_workers(const svgd_ctx *c, int n, int64_t D, int64_t ld, int workers, bool carry)
 {
     const bool full_rows = (n & 15) == 0 || has_remainder_rows(n);
@@ -382,9 +389,9 @@ int fused_workers(const svgd_ctx *c, int n, int64_t D, int64_t ld, int workers, 
         return ranges == 1 ? (per + 3) / 4 : per;
     };
     for (int per_cu = 1; per_cu <= (full_rows ? 1 : 2); ++per_cu) {
-        const int room = c->num_cu * per_cu - ((D & 63) ? 1 : 0);
+        const int room = std::max(c->num_cu * per_cu - ((D & 63) ? 1 : 0), 1);
         if (workers <= room) return workers;
-        if (room > 0 && (full_rows || (carry && n < 16) || tiles_per_wave(room) == tiles_per_wave(workers))) return room;
+        if (full_rows || (carry && n < 16) || tiles_per_wave(room) == tiles_per_wave(workers)) return room;
     }
     return 0;
 }
@@ -399,23 +406,24 @@ int run_update(svgd_ctx *c, float *X, const float *G, float *PHI, int n, int64_t
     UpdateArgs ua{};
     ua.h_fixed = c->h_fixed;
     ua.log_n1 = std::log((double)n + 1.0);
-    const int64_t list_floats = (int64_t)list.nparts * pair_stride(n);
     const int64_t half = half_scratch(c);
-    const int out_cap = CARRY ? (int)std::min<int64_t>(half / pair_stride(n), kMaxParts) : kMaxParts;
-    bool fused = n <= kFusedMaxN && sum_batches(n, list.nparts) <= kFusedMaxBatches && (!CARRY || list_floats <= half);
+    int out_cap = CARRY ? (int)std::min<int64_t>(half / pair_stride(n), kMaxParts) : kMaxParts;
+    if (CARRY && n <= kValuMaxN) out_cap = mini(out_cap, fused_max_parts(n));
+    bool fused = n <= kFusedAlwaysN || (n <= kFusedMaxN && list.nparts <= fused_max_parts(n) && (!CARRY || (int64_t)list.nparts * pair_stride(n) <= half));
     int workers = 0;
     if (n > kValuMaxN) {
         workers = update_workers(c, n, D, ld, out_cap);
         const int w = n <= kFusedMaxN ? fused_workers(c, n, D, ld, workers, CARRY) : 0;
         // CARRY: the number of workgroups, which is that of the carried partial sums, depends on the
         // problem only, not on the list that is read: a captured step reads what any other one left
-        const bool adapt = w > 0 && (CARRY ? sum_batches(n, w + ((D & 63) ? 1 : 0)) <= kFusedMaxBatches : fused);
+        const bool adapt = w > 0 && (CARRY ? w + ((D & 63) ? 1 : 0) <= fused_max_parts(n) : fused);
         if (adapt) workers = w;
         fused = fused && workers == w;
     }
     int64_t out_off = c->captured ? c->home : 0;
     if (fused) {
-        ua.src = SumSource{nullptr, c->partials + list.off, list.nparts};
+        ua.partials = c->partials + list.off;
+        ua.nparts = list.nparts;
         if (CARRY) out_off = other_half(c, list.off);
         c->last_n = n;
     } else {
@@ -440,9 +448,7 @@ int run_update(svgd_ctx *c, float *X, const float *G, float *PHI, int n, int64_t
         const int per_cu = n <= (CARRY ? 8 : 10) ? 2 : 1;
         const int grid = clampi((ngroups + 255) / 256, 1, mini(c->num_cu * per_cu, out_cap));
         if (CARRY) list = PairList{out_off, grid};
-#define CALL(N)                                                                                                      \
-    if (fused) launch_update_valu<N, EMIT, CARRY, true>(X, G, PHI, c->coef, c->state, D, ld, eps, gram_out, grid, s, rt, ua); \
-    else launch_update_valu<N, EMIT, CARRY, false>(X, G, PHI, c->coef, c->state, D, ld, eps, gram_out, grid, s, rt, ua)
+#define CALL(N) launch_update_valu<N, EMIT, CARRY>(X, G, PHI, c->coef, c->state, D, ld, eps, gram_out, grid, s, rt, ua)
         SVGD_SWITCH_N(n, CALL)
 #undef CALL
     } else {
@@ -467,9 +473,11 @@ int run_update(svgd_ctx *c, float *X, const float *G, float *PHI, int n, int64_t
     } while (0)
 #define UPD(NB, FULL, REM)                                                                                           \
     do {                                                                                                             \
-        constexpr bool F = NB == 1 || (NB == 2 && !REM); /* n <= kFusedMaxN */                                       \
-        if (F && fused) UPD_F(NB, FULL, REM, F);                                                                     \
-        else UPD_F(NB, FULL, REM, false);                                                                            \
+        if constexpr (NB == 1) UPD_F(NB, FULL, REM, true); /* n <= kFusedAlwaysN */                                  \
+        else if constexpr (NB == 2 && !REM) { /* n <= kFusedMaxN */                                                  \
+            if (fused) UPD_F(NB, FULL, REM, true);                                                                   \
+            else UPD_F(NB, FULL, REM, false);                                                                        \
+        } else UPD_F(NB, FULL, REM, false);                                                                          \
     } while (0)
         // one to four particles beyond a multiple of 16 ride along as remainder rows of the kernel
         // for that multiple
@@ -589,7 +597,7 @@ svgd_ctx *static_ctx(int dev, int *rc)
     c.device = dev;
     c.max_n = SVGD_MAX_PARTICLES;
     c.max_D = SVGD_STATIC_MAX_D;
-    c.num_cu = cus > 256 ? 256 : cus; // keeps the Gram grid (2 workgroups per CU, one for the tail) within kStaticMaxParts
+    c.num_cu = cus > kMaxCu ? kMaxCu : cus; // keeps the Gram grid (one workgroup per CU at n > 12) within kStaticMaxParts
     c.flags = 0;
     c.h_fixed = 0.0;
     c.carry_valid = false;
@@ -669,7 +677,7 @@ int svgd_create(svgd_handle_t *out, int max_n, int64_t max_D, int device_id, uin
     int cus = 0;
     e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     if (e != hipSuccess || cus < 1) { delete c; return SVGD_ERR_DEVICE; }
-    c->num_cu = cus > 512 ? 512 : cus; // keeps every persistent grid within kMaxParts workgroups
+    c->num_cu = cus > kMaxCu ? kMaxCu : cus; // keeps every persistent grid within kMaxParts workgroups
 
     const size_t P = (size_t)pair_stride(max_n);
     bool ok = hipMalloc(&c->partials, (size_t)kMaxParts * P * sizeof(float)) == hipSuccess &&

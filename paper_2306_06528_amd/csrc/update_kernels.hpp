@@ -19,14 +19,15 @@
 
 namespace svgd {
 
-// FUSED: passes 2 and 3 in one launch.  The kernel starts with pass 2 (kernel_matrix: every workgroup
-// derives h, C and rho for itself, from the fully reduced pair sums or from a short list of
-// partials; workgroup 0 records h and K) and needs no tables in device memory.  A CARRY kernel that
-// reads its list of partials from the scratch leaves the partials of the new X in the other half
-// of it, because workgroups still in their prologue read the old list.
+// Passes 2 and 3 in one launch: always on the vector ALU, FUSED on the matrix cores.  The kernel starts
+// with pass 2 (kernel_matrix: every workgroup derives h, C and rho for itself from a short list
+// of partials; workgroup 0 records h and K) and needs no tables in device memory.  A CARRY kernel
+// leaves the partials of the new X in the other half of the scratch, because workgroups still in their
+// prologue read the old list.
 struct UpdateArgs {
-    // FUSED only
-    SumSource src;
+    // passes 2 and 3 in one launch only
+    const float *partials;
+    int nparts;
     double h_fixed, log_n1;
     // all update kernels:
     // walk the columns from the far end.  Which thread or wave owns which columns does not change, only the order in which it
@@ -43,7 +44,7 @@ struct UpdateArgs {
 // n <= kValuMaxN (12): vector ALU, lanes = columns, 4 consecutive columns per thread (16-byte
 // loads, 1 KiB contiguous per row per wave).  C and rho are wave-uniform: LDS broadcasts.
 // ---------------------------------------------------------------------------------------------
-template <int N, bool EMIT, bool CARRY, bool ROWS = false, bool FUSED = false>
+template <int N, bool EMIT, bool CARRY, bool ROWS = false>
 __global__ __launch_bounds__(256) void update_valu_kernel(float *__restrict__ X,
                                                           const float *__restrict__ G,
                                                           float *__restrict__ PHI,
@@ -63,9 +64,7 @@ __global__ __launch_bounds__(256) void update_valu_kernel(float *__restrict__ X,
 #pragma unroll
         for (int p = 0; p < P; ++p) pacc[p] = 0.f;
     }
-    // C and rho are wave-uniform.  They are staged in LDS and read back as broadcasts: a chain of
-    // dependent scalar loads from global memory costs microseconds per wave, which is all there
-    // is to hide behind when D is small.
+    // C and rho: wave-uniform, read back as LDS broadcasts
     __shared__ __attribute__((aligned(16))) float C[N * N + N];
     float *rho = C + N * N;
     const int64_t ngroups = (D + 3) >> 2;
@@ -91,35 +90,28 @@ __global__ __launch_bounds__(256) void update_valu_kernel(float *__restrict__ X,
     const int64_t cnt = (grp0 < ngroups) ? (ngroups - 1 - grp0) / nthreads + 1 : 0;
     const int64_t gstep = ua.reverse ? -nthreads : nthreads;
     int64_t grp = ua.reverse ? grp0 + (cnt - 1) * nthreads : grp0;
-    // Fused step: the first column group's loads go out in the middle of the prologue, after the
+    // The first column group's loads go out in the middle of the prologue, after the
     // list of partial sums has been read, so that they are in flight during the arithmetic on h and K.
     // (only a group that lies wholly inside the row: the masked loads of a ragged last group come
     // with branches and waits of their own and are left to the loop)
-    const bool early = FUSED && cnt > 0 && ((grp << 2) + 4 <= D);
+    const bool early = cnt > 0 && ((grp << 2) + 4 <= D);
     float c2h;
-    if constexpr (FUSED) {
-        __shared__ BwShared<kValuMaxN, 256> sh;
-        __shared__ __attribute__((aligned(16))) double red_sums[4 * 256];
-        kernel_matrix<256, kValuMaxN, true>(
-            sh, BwArgs{N, kDiff ? kModeDiff : kModeGram, ua.h_fixed, ua.log_n1}, st, coef, C, blockIdx.x == 0, c2h,
-            [&](auto meanwhile) __attribute__((always_inline)) { gather_sums<256>(sh.S, red_sums, ua.src, N, meanwhile); },
-            [&]() __attribute__((always_inline)) {
-                if (early) {
-                    const int64_t c = grp << 2;
+    __shared__ BwShared<kValuMaxN, 256> sh;
+    __shared__ __attribute__((aligned(16))) double red_sums[4 * 256];
+    kernel_matrix<256, kValuMaxN, true>(
+        sh, BwArgs{N, kDiff ? kModeDiff : kModeGram, ua.h_fixed, ua.log_n1}, st, coef, C, blockIdx.x == 0, c2h,
+        [&](auto meanwhile) __attribute__((always_inline)) { gather_sums<256>(sh.S, red_sums, ua.partials, ua.nparts, N, meanwhile); },
+        [&]() __attribute__((always_inline)) {
+            if (early) {
+                const int64_t c = grp << 2;
 #pragma unroll
-                    for (int j = 0; j < N; ++j) {
-                        x[j] = *reinterpret_cast<const f32x4u *>(X + (ROWS ? rt.x[ROWS ? j : 0] : (int64_t)j * ld) + c);
-                        z[j] = __builtin_nontemporal_load(
-                            reinterpret_cast<const f32x4u *>(G + (ROWS ? rt.g[ROWS ? j : 0] : (int64_t)j * ld) + c));
-                    }
+                for (int j = 0; j < N; ++j) {
+                    x[j] = *reinterpret_cast<const f32x4u *>(X + (ROWS ? rt.x[ROWS ? j : 0] : (int64_t)j * ld) + c);
+                    z[j] = __builtin_nontemporal_load(
+                        reinterpret_cast<const f32x4u *>(G + (ROWS ? rt.g[ROWS ? j : 0] : (int64_t)j * ld) + c));
                 }
-            });
-    } else {
-        c2h = st->two_over_h;
-        for (int e = threadIdx.x; e < N * N; e += 256) C[e] = coef[kOffC + e];
-        if (threadIdx.x < N) rho[threadIdx.x] = coef[kOffRho + threadIdx.x];
-        __syncthreads();
-    }
+            }
+        });
     if constexpr (PREFETCH) {
         if (cnt > 0 && !early) load_group(grp);
     }
@@ -534,7 +526,7 @@ void update_mfma_kernel(float *__restrict__ X, const float *__restrict__ G, floa
         double *red = reinterpret_cast<double *>(reinterpret_cast<char *>(&sh) + sizeof(Shared));
         kernel_matrix<256, 32, true>(
             sh, BwArgs{n, kModeGram, ua.h_fixed, ua.log_n1}, st, coef, cl, blockIdx.x == 0, c2h,
-            [&](auto meanwhile) __attribute__((always_inline)) { gather_sums<256>(sh.S, red, ua.src, n, meanwhile); },
+            [&](auto meanwhile) __attribute__((always_inline)) { gather_sums<256>(sh.S, red, ua.partials, ua.nparts, n, meanwhile); },
             first_loads); // the first tile is on its way while h and K are computed
         Cm = cl;
         rhov = cl + n * n;
