@@ -137,8 +137,11 @@ __global__ __launch_bounds__(256) void gram_valu_kernel(const float *__restrict_
 // workgroups sweep the index space together, the W waves of one on adjacent slabs.
 
 // Waves per workgroup (template argument W): eight, one workgroup per CU and two waves per SIMD - half
-// as many partial sums as with two workgroups of four -, or four for an X of so few slabs that
-// every wave has one anyway and more CUs can share them.
+// as many partial sums as with two workgroups of four -, or four for an X of fewer slabs than four
+// waves per CU take, which more CUs can share then.  (From there to eight slabs per CU every wave has
+// one at most as well, and some CUs have none, but the shorter list pays: us per step at D = 65,000 in
+// 254 workgroups of four and D = 65,600 in 129 of eight, n = 16 15.7 and 13.5, n = 24 23.2 and 20.0, n = 32
+// 24.1 and 22.0.)
 constexpr int kGramWaves = 8;
 constexpr int kGramWavesSmall = 4;
 
@@ -158,16 +161,18 @@ struct GramOrder {
 //   way in) - for rows on 128-byte boundaries (nothing is shared between the slabs of neighbouring
 //   waves).  The pass itself then runs 5 % (n = 64, D = 11.2 M) to 28 % (n = 16, same D) faster.
 // The host takes ORDER 1 or 2 when X is larger than twice the memory-side cache.
-// What bounds the pass: at n = 64 the matrix pipe and power, below that memory.  In fp32
-// (v_mfma_f32_16x16x4_f32, 160 per slab) the multiplies took 32 cycles each during which the vector
-// ALU stood still - the fp32 matrix instructions share its multipliers, measured with both in one
-// wave and in two; the bf16 ones, 120 per slab of 17 cycles, run beside the 224 instructions of
-// the split.  Before and after, launched by itself: n = 64, D = 11,173,962, padded rows 569 -> 459 us
+// What bounds the pass is memory, since the multiplies are in bf16: at n = 64 the matrix pipe is busy for
+// 27 % of the cycles (120 instructions of 16 per slab) and the vector ALU for 32.  In fp32
+// (v_mfma_f32_16x16x4_f32, 160 per slab) they took 32 cycles each during which the vector ALU stood
+// still - the fp32 matrix instructions share its multipliers, measured with both in one wave and in
+// two; the bf16 ones run beside the 224 instructions of the split.  Before and after, launched by itself: n = 64, D = 11,173,962, padded rows 569 -> 459 us
 // (6.2 TB/s), dense ones, whose slabs share lines that are fetched twice, 587 -> 552; n = 33, D = 5 M
 // 166 -> 130 (5.1 TB/s); n = 48, D = 1 M 41.5 -> 38.0; n = 16, D = 11.2 M 116 -> 111 (6.4 TB/s).  Inside
 // a step, right behind the update's writes, less of it is left: 568 -> 549 and 558 -> 554 at n = 64,
-// 156 -> 130 at n = 33, 43.7 -> 39.5 at n = 48.  d2 against 64 bits over n = 13..64, D = 65,536..3 M and
-// five distributions: 9.5e-9 -> 2.7e-9 rms (slab sums instead of one long chain); no size is worse.
+// 156 -> 130 at n = 33, 43.7 -> 39.5 at n = 48.  d2 against 64 bits, n = 13..64, D = 65,536..3 M, unit
+// normal values, small ones and small ones around a large common part: 9.4e-9 -> 2.7e-9 rms on
+// average (slab sums instead of one long chain: 3e-8 -> 3e-9 at 3 M; up to D = 300,007 both are at
+// 3e-9); inside clusters 1e-3 wide 4.1e-3 -> 1.8e-3 of the small distances.
 template <int NB, int W, bool ROWS = false, int ORDER = 0>
 __global__ __launch_bounds__(64 * W) void gram_mfma_kernel(const float *__restrict__ X, int n,
                                                                     int64_t D, int64_t ld, float *__restrict__ partials,
@@ -462,8 +467,8 @@ __global__ __launch_bounds__(256) void copy_list_kernel(const f32x4 *__restrict_
 
 // Sum the per-workgroup fp32 partials in fp64: sums[p] = sum_k partials[k][p].  A workgroup takes 32
 // entries, eight lanes of four next to each other, and thread group g of 32 the partials g, g + 32,
-// ... with sixteen 16-byte loads in flight: the 512 partials of a large problem are one batch of
-// loads and one LDS exchange, and the result is the sums themselves, not slices for the next kernel
+// ... with sixteen 16-byte loads in flight: up to 512 partials - 256 are usual, a carried step at 21 to
+// 24 particles may leave 513 - are one batch of loads and one LDS exchange, and the result is the sums themselves, not slices for the next kernel
 // to add.  3.7 us at n = 20, 4.7 at n = 32 and 64 (4.9, 4.9 and 4.8 with eight slices read four
 // bytes at a time): the launch, one trip to memory the partials were just written to, the exchange.
 constexpr int kReduceEntries = 32;
