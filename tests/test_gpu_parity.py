@@ -509,9 +509,10 @@ def test_particle_counts_just_above_a_multiple_of_16(svgd, n, D, padded):
 
 @pytest.mark.parametrize("n,D", [(16, 8577), (13, 4099), (24, 20_011), (32, 8577), (32, 4096), (17, 1531), (8, 100_003)])
 def test_fused_single_launch_step_on_request(svgd, n, D):
-    """SVGD_FLAG_FUSE_MFMA: with a short list of carried sums the step is one launch also on the
-    matrix-core path (13 <= n <= 32) - seen in the launch counts - and its results match the oracle
-    like every other path."""
+    """With a short list of carried sums the step is one launch also on the matrix-core path (13 <= n <=
+    32) - seen in the launch counts - and its results match the oracle like every other path.
+    SVGD_FLAG_FUSE_MFMA, which used to ask for it, is still accepted (without it, and the other side of the
+    rule: test_gpu_edges.py)."""
     X, G = _random_problem(n, D, 7 * n + D, x_std=0.3)
     eps = 0.05
     with svgd.Svgd(n, D, flags=svgd.FLAG_CARRY_GRAM | svgd.FLAG_FUSE_MFMA) as eng:
