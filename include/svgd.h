@@ -79,7 +79,7 @@ enum svgd_status {
 /*
  * Accepted for compatibility and without effect: it used to ask for the single-launch step on carried
  * sums at 13 <= n <= 32.  That step is now the default wherever the list of carried partial sums is
- * short, at every n <= 32 (n = 16, D = 8,577: 12.4 us per step in two launches, 10.4 in one).
+ * short, at every n <= 32 (n = 16, D = 8,577: 12.4 us per step in two launches, 10.8 in one).
  */
 #define SVGD_FLAG_FUSE_MFMA 2u
 
