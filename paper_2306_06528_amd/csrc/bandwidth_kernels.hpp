@@ -4,6 +4,8 @@
 // is spent here).  Nothing returns to the host: the paper's routine (App. B.2) reads each kernel
 // value back to the host, one synchronisation per pair; here K stays on the device.
 #pragma once
+#include <type_traits>
+
 #include "common.hpp"
 
 namespace svgd {
@@ -63,14 +65,35 @@ __device__ inline void wave_minmax(double &mn, double &mx)
     mx = fmax(fmax(readlane_f64(mx, 0), readlane_f64(mx, 16)), fmax(readlane_f64(mx, 32), readlane_f64(mx, 48)));
 }
 
-// Sum over the 16 lanes of each row of a wave, in every lane.
+// Sum over the 16 lanes of each row of a wave (or over aligned groups of L = 8 lanes), in every lane.
+template <int L = 16>
 __device__ inline double row_sum_f64(double v)
 {
     v += dpp_f64<0xB1>(v);
     v += dpp_f64<0x4E>(v);
     v += dpp_f64<0x141>(v);
-    v += dpp_f64<0x140>(v);
+    if constexpr (L > 8) v += dpp_f64<0x140>(v);
     return v;
+}
+
+// The value of lane l ^ M, M = 16 or 32, in lane l: the row-swap instructions, no LDS.
+template <int M>
+__device__ inline double swap_f64(double v)
+{
+    static_assert(M == 16 || M == 32, "whole rows of lanes");
+    const unsigned lo = (unsigned)__double2loint(v), hi = (unsigned)__double2hiint(v);
+    const bool upper = (threadIdx.x & M) != 0;
+    unsigned l, h;
+    if constexpr (M == 16) {
+        const auto a = __builtin_amdgcn_permlane16_swap(lo, lo, false, false), b = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+        l = upper ? a[0] : a[1];
+        h = upper ? b[0] : b[1];
+    } else {
+        const auto a = __builtin_amdgcn_permlane32_swap(lo, lo, false, false), b = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+        l = upper ? a[0] : a[1];
+        h = upper ? b[0] : b[1];
+    }
+    return __hiloint2double((int)h, (int)l);
 }
 
 // Inclusive prefix sum over the 64 lanes of a wave: four DPP shift-adds inside each row of 16
@@ -483,6 +506,234 @@ __device__ inline void gather_sums(double *S, double *red, const float *partials
 #pragma unroll 4
         for (int q = 0; q < KL; ++q) t += red[q * P4 * 4 + p];
         S[p] = t;
+    }
+}
+
+// ---------------------------------------------------------------------------------------------
+// Pass 2 for at most kValuMaxN particles, inside the vector-ALU update and the single-workgroup step: EVERY
+// wave of the workgroup does all of it by itself.  66 pairs are at most two per lane, so nothing has
+// to be shared, and apart from the one barrier behind which the waves' sums meet (the caller's)
+// there is none: with the pairs dealt to all threads of the workgroup five barriers and as many
+// trips through LDS were half of the prologue (with that and the cheaper last column group, RaggedGroup,
+// us per step at D = 100,003 before and now: n = 8, padded, carried sums 10.0 and 7.2, n = 10, plain 16.8
+// and 12.0, n = 12 18.9 and 14.5; in the single-workgroup step n = 8, D = 1,003 9.5 and 6.0).  The rank of a value is the number of smaller ones, counted
+// against a broadcast of the whole list; a value of rank r is one whose count is r, or with ties the
+// largest count below r.
+// ---------------------------------------------------------------------------------------------
+template <int N>
+struct WaveShared { // LDS, one per wave
+    static constexpr int P = N * (N + 1) / 2, Pp = N * (N - 1) / 2;
+    static constexpr int kList = Pp > 1 ? (Pp + 1) & ~1 : 2;
+    __attribute__((aligned(16))) double pr[kList]; // d2 per pair, then K
+    double S[N > 8 ? P : 1];                       // centred Gram sums
+    // the result: row i is C_i0 .. C_i,N-1, then rho_i; read 16 bytes at a time
+    static constexpr int kRow = (N + 1 + 3) & ~3;
+    __attribute__((aligned(16))) float C[N * kRow];
+    // Row i.  `at` is 0, but unknown to the compiler (opaque_zero): what is read through it stays where it is
+    // needed - hoisted out of the loop over the columns C and rho would take N^2 + N registers.
+    __device__ void row(int i, int at, float (&c)[N], float &rho) const
+    {
+        const f32x4 *src = reinterpret_cast<const f32x4 *>(C) + at + i * (kRow / 4);
+#pragma unroll
+        for (int k = 0; k < kRow / 4; ++k) {
+            const f32x4 v = src[k];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                if (4 * k + e < N) c[4 * k + e < N ? 4 * k + e : 0] = v[e];
+                if (4 * k + e == N) rho = v[e];
+            }
+        }
+    }
+};
+__device__ inline int opaque_zero()
+{
+    int z = 0;
+    asm volatile("" : "+v"(z));
+    return z;
+}
+
+// sum(e): the reduced pair sum tri(i, j) = e (direct differences up to N = 8, centred Gram above).
+// write_global: this wave also leaves h and K in st and coef.  Returns 2 / h (0 for one particle).
+template <int N, class Sum>
+__device__ inline float wave_kernel_matrix(WaveShared<N> &sh, double h_fixed, double log_n1, DevState *__restrict__ st,
+                                           float *__restrict__ coef, bool write_global, Sum sum)
+{
+    constexpr int P = WaveShared<N>::P, Pp = WaveShared<N>::Pp, kList = WaveShared<N>::kList;
+    constexpr int VPL = Pp > kWave ? 2 : 1; // pairs per lane
+    const int lane = threadIdx.x & 63;
+    const double inf = __builtin_huge_val();
+    if constexpr (N > 8) {
+#pragma unroll
+        for (int u = 0; u < (P + kWave - 1) / kWave; ++u) {
+            const int e = lane + kWave * u;
+            if (e < P) sh.S[e] = sum(e);
+        }
+    }
+    double d2[VPL];
+#pragma unroll
+    for (int u = 0; u < VPL; ++u) {
+        const int p = lane + kWave * u;
+        int i = 0;
+#pragma unroll
+        for (int k = 1; k < N - 1; ++k) i += p >= pair_index(k, k + 1, N) ? 1 : 0;
+        const int j = i + 1 + p - pair_index(i, i + 1, N);
+        double d = inf;
+        if (p < Pp) {
+            if constexpr (N > 8) d = sh.S[tri(i, i, N)] + sh.S[tri(j, j, N)] - 2.0 * sh.S[tri(i, j, N)];
+            else d = sum(tri(i, j, N));
+            if (!(d > 0.0)) d = 0.0; // clamps rounding negatives (and -0.0, and NaN)
+        }
+        d2[u] = d;
+        if (p < kList) sh.pr[p] = d;
+    }
+    // the two middle order statistics of all n * n entries, see kernel_matrix
+    constexpr int t_lo = (N * N - 1) / 2, t_hi = (N * N) / 2;
+    double med = 0.0;
+    if constexpr (N > 1) {
+        constexpr int r_hi = (t_hi - N) / 2, r_lo = t_lo >= N ? (t_lo - N) / 2 : r_hi;
+        if (h_fixed <= 0.0) {
+            int cnt[VPL];
+#pragma unroll
+            for (int u = 0; u < VPL; ++u) cnt[u] = lane + kWave * u < Pp ? 0 : Pp;
+#pragma unroll
+            for (int k = 0; k < kList; k += 2) {
+                const double2 w = *reinterpret_cast<const double2 *>(&sh.pr[k]);
+#pragma unroll
+                for (int u = 0; u < VPL; ++u) {
+                    cnt[u] += w.x < d2[u] ? 1 : 0;
+                    cnt[u] += w.y < d2[u] ? 1 : 0;
+                }
+            }
+            auto value_at = [&](int r) __attribute__((always_inline)) {
+                for (;; --r) { // (count 0 exists: the smallest value)
+                    const unsigned long long m0 = __ballot(cnt[0] == r);
+                    if (m0) return readlane_f64(d2[0], __ffsll(m0) - 1);
+                    if constexpr (VPL > 1) {
+                        const unsigned long long m1 = __ballot(cnt[VPL - 1] == r);
+                        if (m1) return readlane_f64(d2[VPL - 1], __ffsll(m1) - 1);
+                    }
+                }
+            };
+            const double hi = value_at(r_hi);
+            med = 0.5 * ((t_lo >= N ? (r_lo == r_hi ? hi : value_at(r_lo)) : 0.0) + hi);
+        }
+    }
+    // h = num / den and 1 / h = den / num: two divisions side by side
+    const double num = (h_fixed > 0.0) ? h_fixed : med, den = (h_fixed > 0.0) ? 1.0 : log_n1;
+    double h = num / den, inv_h = den / num;
+    if (!(h > 0.0)) {
+        h = 1.0;
+        inv_h = 1.0;
+    }
+    // a single particle has no repulsive term at all: make that exact (phi = g)
+    const double c2h = (N == 1) ? 0.0 : 2.0 * inv_h;
+    if (write_global && lane == 0) {
+        st->h = h;
+        st->med = med;
+        st->two_over_h = (float)c2h;
+        st->n = N;
+    }
+#pragma unroll
+    for (int u = 0; u < VPL; ++u) // K per pair; 1 / h may be infinite
+        if (lane + kWave * u < Pp) sh.pr[lane + kWave * u] = d2[u] > 0.0 ? exp(-d2[u] * inv_h) : 1.0;
+    // K, C, row sums: 8 or 16 lanes per row.  K_ij and K_ji are the same LDS entry, so K is exactly
+    // symmetric; the diagonal is exactly 1.
+    constexpr int L = N <= 8 ? 8 : 16;
+    constexpr double inv_n = 1.0 / (double)N;
+#pragma unroll
+    for (int i0 = 0; i0 < N; i0 += kWave / L) {
+        const int i = i0 + lane / L, j = lane % L;
+        const bool in = i < N && j < N;
+        double k = in ? 1.0 : 0.0;
+        if (in && i != j) k = sh.pr[i < j ? pair_index(i, j, N) : pair_index(j, i, N)];
+        const double r = row_sum_f64<L>(k); // row sum of K
+        if (in) {
+            if (write_global) coef[kOffK + i * N + j] = (float)k;
+            sh.C[i * WaveShared<N>::kRow + j] = (float)(k * inv_n);
+            if (j == 0) sh.C[i * WaveShared<N>::kRow + N] = (float)(c2h * r * inv_n);
+        }
+    }
+    return (float)c2h;
+}
+
+// Sums a list of partials in fp64 for wave_kernel_matrix, every wave a part of it: G neighbouring lanes read one
+// partial, 16 bytes each, R partials side by side and up to kSumLoads of them one after the other in flight.
+// Then the wave's R sums are added, up to seven particles across the lanes (a partial then takes 4 or 8
+// lanes), above by way of the wave's part of `scratch`, where G is exactly what a partial takes (at n = 8, nine lanes: with
+// sixteen for each, a list of 512 took 1.7 times the loads), and go to red[wave].
+// `last` is called when the last loads of the list have been sent off: the place for the caller to send
+// off loads of its own, which are then in flight while the list is summed (a wave's loads complete in
+// order: earlier, the sums would wait behind them).
+template <int N>
+struct GatherShared {
+    static constexpr int P4 = pair_stride(N) / 4;
+    static constexpr bool kLanes = N <= 7;
+    static constexpr int G = kLanes ? (P4 <= 4 ? 4 : 8) : P4;
+    static constexpr int R = kWave / G;
+    __attribute__((aligned(16))) double red[4][4 * P4];
+    __attribute__((aligned(16))) double scratch[kLanes ? 1 : 4][kLanes ? 1 : R][4 * P4];
+    __device__ double sum(int e) const { return (red[0][e] + red[1][e]) + (red[2][e] + red[3][e]); }
+};
+template <int N, class Last>
+__device__ inline void gather_wave_sums(GatherShared<N> &sh, const float *partials, int nparts, Last last)
+{
+    typedef GatherShared<N> Sh;
+    constexpr int P4 = Sh::P4, G = Sh::G, R = Sh::R, STEP = 4 * R;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int row = lane / G;
+    const bool idle = row >= R; // (lanes that no whole partial is left for)
+    const int pp = lane % G < P4 ? lane % G : P4 - 1, kk = wave * R + (idle ? 0 : row);
+    const f32x4 *base = reinterpret_cast<const f32x4 *>(partials) + pp;
+    double s[4] = {0.0, 0.0, 0.0, 0.0};
+    int k0 = 0;
+    // U loads in a row, clamped and not guarded: with a number of loads that is not known the first wait would be
+    // for everything in flight, the caller's loads included
+    auto batch = [&](auto loads, auto then) __attribute__((always_inline)) {
+        constexpr int U = decltype(loads)::value;
+        f32x4 v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int k = k0 + kk + u * STEP;
+            v[u] = base[(k < nparts ? k : nparts - 1) * P4];
+        }
+        then();
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const bool in = k0 + kk + u * STEP < nparts;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) s[c] += in ? (double)v[u][c] : 0.0;
+        }
+    };
+    for (; nparts - k0 > kSumLoads * STEP; k0 += kSumLoads * STEP) batch(std::integral_constant<int, kSumLoads>{}, [] {});
+    if (nparts - k0 > kSumLoads / 2 * STEP) batch(std::integral_constant<int, kSumLoads>{}, last);
+    else if (nparts - k0 > kSumLoads / 4 * STEP) batch(std::integral_constant<int, kSumLoads / 2>{}, last);
+    else batch(std::integral_constant<int, kSumLoads / 4>{}, last);
+    if constexpr (Sh::kLanes) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            if constexpr (G == 4) s[c] += dpp_f64<0x124>(s[c]); // row_ror:4
+            s[c] += dpp_f64<0x128>(s[c]);                       // row_ror:8
+            s[c] += swap_f64<16>(s[c]);
+            s[c] += swap_f64<32>(s[c]);
+        }
+        if (lane < P4) {
+            double2 *dst = reinterpret_cast<double2 *>(&sh.red[wave][4 * lane]);
+            dst[0] = double2{s[0], s[1]};
+            dst[1] = double2{s[2], s[3]};
+        }
+    } else {
+        if (!idle) {
+            double2 *dst = reinterpret_cast<double2 *>(&sh.scratch[wave][row][4 * pp]);
+            dst[0] = double2{s[0], s[1]};
+            dst[1] = double2{s[2], s[3]};
+        }
+        // (one wave's LDS operations execute in order)
+        for (int e = lane; e < 4 * P4; e += kWave) {
+            double t = sh.scratch[wave][0][e];
+#pragma unroll
+            for (int r = 1; r < R; ++r) t += sh.scratch[wave][r][e];
+            sh.red[wave][e] = t;
+        }
     }
 }
 

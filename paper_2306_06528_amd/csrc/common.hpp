@@ -84,12 +84,63 @@ __device__ inline f32x4 load4(const float *__restrict__ row, int64_t col, int64_
     return v;
 }
 
-// streaming variant for data that is read exactly once (G)
+// streaming variant for data that is read exactly once
 __device__ inline f32x4 load4_stream(const float *__restrict__ row, int64_t col, int64_t D, bool full)
 {
     if (full) return __builtin_nontemporal_load(reinterpret_cast<const f32x4u *>(row + col));
     return load4(row, col, D, false);
 }
+
+// A row's 4-column groups, the last of which may be ragged, without a branch around any load: the group
+// at column col is loaded at min(col, D - 4), always inside the row, and `fix` then moves what was
+// loaded into place and sets the columns beyond D to 0 (a group wholly beyond D becomes 0).  With
+// guarded loads of single columns the one wave that has the ragged group went through 4 N loads one
+// after the other and was the last of its launch to end (n = 8, D = 100,003: 20.8 thousand
+// cycles, all others 15).  Rows of fewer than four columns are one group and go through load_narrow,
+// outside the loop over the groups: a choice inside it makes every load wait for the one before.
+struct RaggedGroup {
+    int64_t at; // column to load from
+    int s;      // how far that is to the left of the group
+    __device__ RaggedGroup(int64_t col, int64_t D)
+    {
+        at = D < 4 || col < D - 4 ? col : D - 4;
+        s = (int)(col - at < 4 ? col - at : 4);
+    }
+    template <bool STREAM>
+    __device__ f32x4 load(const float *__restrict__ row) const // rows of four columns or more
+    {
+        if constexpr (STREAM) return __builtin_nontemporal_load(reinterpret_cast<const f32x4u *>(row + at));
+        else return *reinterpret_cast<const f32x4u *>(row + at);
+    }
+    __device__ f32x4 fix(f32x4 v) const
+    {
+        if (s & 1) v = f32x4{v.y, v.z, v.w, 0.f};
+        if (s & 2) v = f32x4{v.z, v.w, 0.f, 0.f};
+        if (s & 4) v = f32x4{0.f, 0.f, 0.f, 0.f};
+        return v;
+    }
+};
+
+// A row of fewer than four columns, the rest 0.
+__device__ inline f32x4 load_narrow(const float *__restrict__ row, int64_t D)
+{
+    f32x4 v;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        v[e] = row[e < D ? e : 0];
+        if (e >= D) v[e] = 0.f;
+    }
+    return v;
+}
+
+// How the column groups are dealt to the threads of a grid: thread t visits the groups t + k * stride,
+// k < count(t).  Quotient and remainder of the number of groups come from the host: as a 64-bit division
+// in every thread they took 0.3 us of each launch.
+struct GroupSplit {
+    int q, r;
+    __host__ GroupSplit(int64_t ngroups, int64_t stride) : q((int)(ngroups / stride)), r((int)(ngroups % stride)) {}
+    __device__ int count(int t) const { return q + (t < r ? 1 : 0); }
+};
 
 // Sum of v over the four lanes l, l ^ 16, l ^ 32, l ^ 48 (the four 16-lane rows of a wave), in every
 // lane, as (v[l] + v[l ^ 16]) + (the same of l ^ 32): the gfx950 row-swap instructions exchange

@@ -64,11 +64,16 @@ __device__ __forceinline__ void pair_accumulate(f32x4 (&x)[N], float (&acc)[N * 
     }
 }
 
-// STREAM: loads with the streaming hint, see gram_mfma_kernel (here also for unaligned rows: a
+// Workgroups per CU, all resident at once; as registers per wave, too, so that no CU takes more of them than another.
+constexpr int kGramPerCu = 3;
+// Column groups per iteration: two when the registers allow, for twice the loads in flight.
+template <int N> constexpr int kGramGroups = N <= 8 ? 2 : 1;
+
+// STREAM: loads with the streaming hint, but for the `hot` iterations walked last, see gram_mfma_kernel (here also for unaligned rows: a
 // wave covers 1 KiB of a row, the one line it shares with its neighbour matters little).
 template <int N, bool ROWS = false, bool STREAM = false>
-__global__ __launch_bounds__(256) void gram_valu_kernel(const float *__restrict__ X, int64_t D, int64_t ld,
-                                                        float *__restrict__ partials,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kGramPerCu, kGramPerCu))) void gram_valu_kernel(const float *__restrict__ X, int64_t D, int64_t ld,
+                                                        float *__restrict__ partials, GroupSplit split, int hot,
                                                         typename RowArg<ROWS>::type rt)
 {
     constexpr int P = N * (N + 1) / 2;
@@ -76,30 +81,44 @@ __global__ __launch_bounds__(256) void gram_valu_kernel(const float *__restrict_
 #pragma unroll
     for (int p = 0; p < P; ++p) acc[p] = 0.f;
 
-    const int64_t ngroups = (D + 3) >> 2;
     const int64_t nthreads = (int64_t)gridDim.x * 256;
-    // two column groups per iteration when the registers allow: twice the loads in flight
-    constexpr int U = (N <= 8) ? 2 : 1;
+    constexpr int U = kGramGroups<N>;
     // The columns are walked from the far end: the update that follows walks them from the near
     // end, so each pass starts on the part of X that the pass before it touched last and that the
     // memory-side cache still holds.
-    const int64_t grp0 = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    const int64_t cnt = (grp0 < ngroups) ? (ngroups - 1 - grp0) / (U * nthreads) + 1 : 0;
-    for (int64_t k = cnt - 1; k >= 0; --k) {
-        const int64_t grp = grp0 + k * U * nthreads;
+    const int grp0 = (int)(blockIdx.x * 256 + threadIdx.x);
+    auto row = [&](int j) __attribute__((always_inline)) { return X + (ROWS ? rt.x[ROWS ? j : 0] : (int64_t)j * ld); };
+    const int cnt = split.count(grp0);
+    auto groups = [&](int k, auto stream) __attribute__((always_inline)) { // the U groups of iteration k
+        const int64_t grp = grp0 + (int64_t)k * U * nthreads;
         f32x4 x[U][N];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int64_t col = (grp + u * nthreads) << 2; // past the end: every load is masked to 0
-            const bool full = (col + 4 <= D);
+            const RaggedGroup rg((grp + u * nthreads) << 2, D);
 #pragma unroll
-            for (int j = 0; j < N; ++j) {
-                const float *xr = X + (ROWS ? rt.x[ROWS ? j : 0] : (int64_t)j * ld);
-                x[u][j] = STREAM ? load4_stream(xr, col, D, full) : load4(xr, col, D, full);
-            }
+            for (int j = 0; j < N; ++j) x[u][j] = rg.template load<decltype(stream)::value>(row(j));
         }
 #pragma unroll
-        for (int u = 0; u < U; ++u) pair_accumulate<N>(x[u], acc);
+        for (int u = 0; u < U; ++u) {
+            const RaggedGroup rg((grp + u * nthreads) << 2, D);
+            if (rg.s) { // (a group past the end becomes 0)
+#pragma unroll
+                for (int j = 0; j < N; ++j) x[u][j] = rg.fix(x[u][j]);
+            }
+            pair_accumulate<N>(x[u], acc);
+        }
+    };
+    if (D >= 4) {
+        int k = cnt - 1;
+        if constexpr (STREAM) {
+            for (; k >= hot; --k) groups(k, std::true_type{});
+        }
+        for (; k >= 0; --k) groups(k, std::false_type{});
+    } else if (cnt > 0) {
+        f32x4 x[N];
+#pragma unroll
+        for (int j = 0; j < N; ++j) x[j] = load_narrow(row(j), D);
+        pair_accumulate<N>(x, acc);
     }
 
     __shared__ float red[4][P];

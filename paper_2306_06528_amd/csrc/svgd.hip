@@ -142,14 +142,17 @@ bool overlaps(const float *a, const float *b, int n, int64_t D, int64_t ld)
 // rt != nullptr: the particles are separate rows (svgd_step_rows); the table goes along by value
 template <int N>
 void launch_gram_valu(const float *X, int64_t D, int64_t ld, float *partials, int grid, hipStream_t s,
-                      const RowTable *rt, bool stream_x)
+                      const RowTable *rt, bool stream_x, int64_t hot_bytes)
 {
+    const int64_t stride = (int64_t)grid * 256 * kGramGroups<N>;
+    const GroupSplit split((D + 3) / 4, stride);
+    const int hot = (int)(hot_bytes / (stride * 16 * N));
     if (rt)
-        gram_valu_kernel<N, true><<<grid, 256, 0, s>>>(X, D, ld, partials, *rt);
+        gram_valu_kernel<N, true><<<grid, 256, 0, s>>>(X, D, ld, partials, split, 0, *rt);
     else if (stream_x)
-        gram_valu_kernel<N, false, true><<<grid, 256, 0, s>>>(X, D, ld, partials, NoRows{});
+        gram_valu_kernel<N, false, true><<<grid, 256, 0, s>>>(X, D, ld, partials, split, hot, NoRows{});
     else
-        gram_valu_kernel<N, false><<<grid, 256, 0, s>>>(X, D, ld, partials, NoRows{});
+        gram_valu_kernel<N, false><<<grid, 256, 0, s>>>(X, D, ld, partials, split, 0, NoRows{});
 }
 
 template <int N, bool EMIT, bool CARRY>
@@ -157,13 +160,14 @@ void launch_update_valu(float *X, const float *G, float *PHI, float *coef, DevSt
                         int64_t D, int64_t ld, float eps, float *gram_out, int grid, hipStream_t s,
                         const RowTable *rt, const UpdateArgs &ua)
 {
+    const GroupSplit split((D + 3) / 4, (int64_t)grid * 256);
     if constexpr (!EMIT && !CARRY) {
         if (rt) {
-            update_valu_kernel<N, false, false, true><<<grid, 256, 0, s>>>(X, G, PHI, coef, st, D, ld, eps, gram_out, *rt, ua);
+            update_valu_kernel<N, false, false, true><<<grid, 256, 0, s>>>(X, G, PHI, coef, st, D, ld, eps, gram_out, split, *rt, ua);
             return;
         }
     }
-    update_valu_kernel<N, EMIT, CARRY, false><<<grid, 256, 0, s>>>(X, G, PHI, coef, st, D, ld, eps, gram_out, NoRows{}, ua);
+    update_valu_kernel<N, EMIT, CARRY, false><<<grid, 256, 0, s>>>(X, G, PHI, coef, st, D, ld, eps, gram_out, split, NoRows{}, ua);
 }
 
 #define SVGD_SWITCH_N(n, CALL)                                                                     \
@@ -282,8 +286,15 @@ int run_gram(svgd_ctx *c, const float *X, int n, int64_t D, int64_t ld, hipStrea
         // all resident at once; each ends with a reduction; the update sums the list (three per CU of
         // 256 are just what it takes at n = 12)
         nparts = clampi((ngroups + 255) / 256, 1, mini(mini(c->num_cu * 3, cap_parts), mini(fused_max_parts(n), (int)(half_scratch(c) / pair_stride(n)))));
-        const bool stream_x = big_x;
-#define CALL(N) launch_gram_valu<N>(X, D, ld, partials, nparts, s, rt, stream_x)
+        const int64_t x_bytes = (int64_t)n * D * (int64_t)sizeof(float);
+        // An X that outgrows the memory-side cache is loaded with the streaming hint, above 8 particles up to
+        // the three quarters of that cache which the update reads first (walked last, loaded plainly): n = 12,
+        // D = 11,173,962 432 -> 416 us per step, D = 6,000,002 235 -> 226.  At n = 8 that pass is 4 us faster, too, but
+        // the update finds less of X and the step is slower by as much (271 -> 274): there, up to twice the cache all loads
+        // are plain.
+        const bool stream_x = x_bytes > (n > 8 ? 1 : 2) * kMemorySideCacheBytes;
+        const int64_t hot_bytes = n > 8 ? 3 * kMemorySideCacheBytes / 4 : 0;
+#define CALL(N) launch_gram_valu<N>(X, D, ld, partials, nparts, s, rt, stream_x, hot_bytes)
         SVGD_SWITCH_N(n, CALL)
 #undef CALL
     } else {
@@ -441,11 +452,7 @@ int run_update(svgd_ctx *c, float *X, const float *G, float *PHI, int n, int64_t
     ua.adjacent = adjacent_tiles(n, ld);
     if (n <= kValuMaxN) {
         const int64_t ngroups = (D + 3) / 4;
-        // All workgroups resident at once, or the prologue (and with CARRY the reduction of the pair
-        // sums at the end) is paid twice.  Two per CU where that leaves each thread's rows enough
-        // registers for loads in flight: plain step at D = 6,000,000, one against two per CU, n = 9
-        // 182 / 168 us, n = 12 235 / 240; at D = 1,000,000 44 / 38 and 57 / 64.
-        const int per_cu = n <= (CARRY ? 8 : 10) ? 2 : 1;
+        const int per_cu = n <= (CARRY ? 8 : 10) ? 2 : 1; // kUpdatePerCu
         const int grid = clampi((ngroups + 255) / 256, 1, mini(c->num_cu * per_cu, out_cap));
         if (CARRY) list = PairList{out_off, grid};
 #define CALL(N) launch_update_valu<N, EMIT, CARRY>(X, G, PHI, c->coef, c->state, D, ld, eps, gram_out, grid, s, rt, ua)

@@ -44,14 +44,22 @@ struct UpdateArgs {
 // n <= kValuMaxN (12): vector ALU, lanes = columns, 4 consecutive columns per thread (16-byte
 // loads, 1 KiB contiguous per row per wave).  C and rho are wave-uniform: LDS broadcasts.
 // ---------------------------------------------------------------------------------------------
+// Workgroups per CU, all resident at once, or the prologue (and with CARRY the reduction of the pair sums at
+// the end) is paid twice.  Two where that leaves each thread's rows enough registers for loads in flight: plain
+// step at D = 6,000,000, one against two per CU, n = 9 182 / 168 us, n = 12 235 / 240; at D = 1,000,000
+// 44 / 38 and 57 / 64.  The kernel claims the registers of that many waves, so that no CU takes more
+// workgroups than another.
+template <int N, bool CARRY> constexpr int kUpdatePerCu = N <= (CARRY ? 8 : 10) ? 2 : 1;
+
 template <int N, bool EMIT, bool CARRY, bool ROWS = false>
-__global__ __launch_bounds__(256) void update_valu_kernel(float *__restrict__ X,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kUpdatePerCu<N, CARRY>, kUpdatePerCu<N, CARRY>)))
+void update_valu_kernel(float *__restrict__ X,
                                                           const float *__restrict__ G,
                                                           float *__restrict__ PHI,
                                                           float *__restrict__ coef,
                                                           DevState *__restrict__ st,
                                                           int64_t D, int64_t ld, float eps,
-                                                          float *__restrict__ gram_out,
+                                                          float *__restrict__ gram_out, GroupSplit split,
                                                           typename RowArg<ROWS>::type rt, UpdateArgs ua)
 {
     static_assert(!(ROWS && (EMIT || CARRY)), "separate rows: plain in-place step only");
@@ -64,64 +72,61 @@ __global__ __launch_bounds__(256) void update_valu_kernel(float *__restrict__ X,
 #pragma unroll
         for (int p = 0; p < P; ++p) pacc[p] = 0.f;
     }
-    // C and rho: wave-uniform, read back as LDS broadcasts
-    __shared__ __attribute__((aligned(16))) float C[N * N + N];
-    float *rho = C + N * N;
-    const int64_t ngroups = (D + 3) >> 2;
     const int64_t nthreads = (int64_t)gridDim.x * 256;
-    // PREFETCH (carried pair sums of 9 to 12 particles, where the registers allow a single wave per
-    // SIMD anyway): the loads of a thread's next column group are issued as soon as this group's
-    // results are stored, before its pair sums are accumulated, so that arithmetic runs while the
-    // loads are in flight (88.6 instead of 94.3 us per step at n = 12, D = 3,000,000).  At n <= 8
-    // the longer live ranges cost a resident wave and the kernel gets slower.
-    constexpr bool PREFETCH = CARRY && N > 8;
+    // PREFETCH (carried pair sums of 6 particles and more): the loads of a thread's next column group are issued as
+    // soon as this group's results are stored, before its pair sums are accumulated, so that arithmetic
+    // runs while the loads are in flight (88.6 instead of 94.3 us per step at n = 12, D = 3,000,000; 15.8 and
+    // 15.1 at n = 7, D = 1,000,000; at n <= 5 no difference).
+    constexpr bool PREFETCH = CARRY && N > 5;
     f32x4 x[N], z[N];
     auto load_group = [&](int64_t g) __attribute__((always_inline)) {
-        const int64_t c = g << 2;
-        const bool fl = (c + 4 <= D);
+        const RaggedGroup rg(g << 2, D);
 #pragma unroll
         for (int j = 0; j < N; ++j) {
-            x[j] = load4(X + (ROWS ? rt.x[ROWS ? j : 0] : (int64_t)j * ld), c, D, fl);
-            z[j] = load4_stream(G + (ROWS ? rt.g[ROWS ? j : 0] : (int64_t)j * ld), c, D, fl);
+            x[j] = rg.load<false>(X + (ROWS ? rt.x[ROWS ? j : 0] : (int64_t)j * ld));
+            z[j] = rg.load<true>(G + (ROWS ? rt.g[ROWS ? j : 0] : (int64_t)j * ld));
         }
     };
     // this thread's groups: grp0 + k * nthreads, k < cnt, visited upwards or (reverse) downwards
-    const int64_t grp0 = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    const int64_t cnt = (grp0 < ngroups) ? (ngroups - 1 - grp0) / nthreads + 1 : 0;
+    const int64_t grp0 = (int)(blockIdx.x * 256 + threadIdx.x);
+    const int cnt = split.count((int)grp0);
     const int64_t gstep = ua.reverse ? -nthreads : nthreads;
     int64_t grp = ua.reverse ? grp0 + (cnt - 1) * nthreads : grp0;
-    // The first column group's loads go out in the middle of the prologue, after the
-    // list of partial sums has been read, so that they are in flight during the arithmetic on h and K.
-    // (only a group that lies wholly inside the row: the masked loads of a ragged last group come
-    // with branches and waits of their own and are left to the loop)
-    const bool early = cnt > 0 && ((grp << 2) + 4 <= D);
-    float c2h;
-    __shared__ BwShared<kValuMaxN, 256> sh;
-    __shared__ __attribute__((aligned(16))) double red_sums[4 * 256];
-    kernel_matrix<256, kValuMaxN, true>(
-        sh, BwArgs{N, kDiff ? kModeDiff : kModeGram, ua.h_fixed, ua.log_n1}, st, coef, C, blockIdx.x == 0, c2h,
-        [&](auto meanwhile) __attribute__((always_inline)) { gather_sums<256>(sh.S, red_sums, ua.partials, ua.nparts, N, meanwhile); },
-        [&]() __attribute__((always_inline)) {
-            if (early) {
-                const int64_t c = grp << 2;
+    // Pass 2: the list of partial sums by all waves together, everything else by every wave for itself.  C and
+    // rho are wave-uniform, read back as LDS broadcasts from the wave's own copy.
+    __shared__ WaveShared<N> shw[4];
+    __shared__ GatherShared<N> gather;
+    WaveShared<N> &sh = shw[threadIdx.x >> 6];
+    gather_wave_sums<N>(gather, ua.partials, ua.nparts, [&]() __attribute__((always_inline)) {
+        if (cnt > 0 && D >= 4) load_group(grp); // the first column group is on its way while h and K are computed
+    });
+    block_sync<true>();
+    const float c2h = wave_kernel_matrix<N>(
+        sh, ua.h_fixed, ua.log_n1, st, coef, blockIdx.x == 0 && threadIdx.x < kWave,
+        [&](int e) __attribute__((always_inline)) { return gather.sum(e); });
+    if (cnt > 0 && D < 4) {
 #pragma unroll
-                for (int j = 0; j < N; ++j) {
-                    x[j] = *reinterpret_cast<const f32x4u *>(X + (ROWS ? rt.x[ROWS ? j : 0] : (int64_t)j * ld) + c);
-                    z[j] = __builtin_nontemporal_load(
-                        reinterpret_cast<const f32x4u *>(G + (ROWS ? rt.g[ROWS ? j : 0] : (int64_t)j * ld) + c));
-                }
-            }
-        });
-    if constexpr (PREFETCH) {
-        if (cnt > 0 && !early) load_group(grp);
+        for (int j = 0; j < N; ++j) {
+            x[j] = load_narrow(X + (ROWS ? rt.x[ROWS ? j : 0] : (int64_t)j * ld), D);
+            z[j] = load_narrow(G + (ROWS ? rt.g[ROWS ? j : 0] : (int64_t)j * ld), D);
+        }
     }
-    for (int64_t k = 0; k < cnt; ++k, grp += gstep) {
+    for (int k = 0; k < cnt; ++k, grp += gstep) {
         const int64_t col = grp << 2;
         const bool full = (col + 4 <= D);
         if constexpr (!PREFETCH) {
-            if (k > 0 || !early) load_group(grp);
+            if (k > 0) load_group(grp);
+        }
+        if (!full) {
+            const RaggedGroup rg(col, D);
+#pragma unroll
+            for (int j = 0; j < N; ++j) {
+                x[j] = rg.fix(x[j]);
+                z[j] = rg.fix(z[j]);
+            }
         }
 
+        const int c0 = opaque_zero();
         f32x4 m = f32x4{0.f, 0.f, 0.f, 0.f};
         if constexpr (CARRY && !kDiff) { // centre by the pre-update column mean
 #pragma unroll
@@ -130,19 +135,27 @@ __global__ __launch_bounds__(256) void update_valu_kernel(float *__restrict__ X,
         }
 #pragma unroll
         for (int j = 0; j < N; ++j) z[j] -= c2h * x[j];
-        f32x4 y[CARRY ? N : 1];
+        f32x4 y[N]; // the results; CARRY: then the centred new values
+        float *__restrict__ OUT = EMIT ? PHI : X;
+        auto rows = [&](auto whole) __attribute__((always_inline)) {
 #pragma unroll
-        for (int i = 0; i < N; ++i) {
-            f32x4 acc = rho[i] * x[i];
+            for (int i = 0; i < N; ++i) {
+                float C[N], rho;
+                sh.row(i, c0, C, rho);
+                f32x4 acc = rho * x[i];
 #pragma unroll
-            for (int j = 0; j < N; ++j) acc += C[i * N + j] * z[j];
-            if constexpr (EMIT) {
-                store4(PHI + (int64_t)i * ld, col, D, full, acc);
-            } else {
-                const f32x4 xn = x[i] + eps * acc;
-                store4(X + (ROWS ? rt.x[ROWS ? i : 0] : (int64_t)i * ld), col, D, full, xn);
-                if constexpr (CARRY) y[i] = xn - m; // columns beyond D: x = g = 0 -> xn = 0, m = 0
+                for (int j = 0; j < N; ++j) acc += C[j] * z[j];
+                if constexpr (EMIT) y[i] = acc;
+                else y[i] = x[i] + eps * acc;
+                store4(OUT + (ROWS ? rt.x[ROWS ? i : 0] : (int64_t)i * ld), col, D, decltype(whole)::value || full, y[i]);
             }
+        };
+        // one decision per wave: with a branch around every row's store no row's coefficients were read ahead
+        if (__ballot(!full) == 0) rows(std::true_type{});
+        else rows(std::false_type{});
+        if constexpr (CARRY) {
+#pragma unroll
+            for (int i = 0; i < N; ++i) y[i] -= m; // columns beyond D: x = g = 0 -> 0
         }
         if constexpr (CARRY) {
             if constexpr (PREFETCH) {
