@@ -298,7 +298,7 @@ struct BwArgs {
 // on the sums is done there.  after_sums() is called between the sums and the arithmetic that needs
 // no memory: the place for the caller to send off loads of its own (issued earlier they would only
 // make the sums wait behind them - a wave's loads complete in order).
-// coef_lds, if not null, receives C [n*n] and rho [n] (LDS of the caller; barrier included);
+// coef_lds, if not null, receives C, its rows padded with zeros to a multiple of four, and rho [n] (LDS of the caller; barrier included);
 // otherwise they go to coef (device memory).  write_global = false: st and K are left alone - for
 // workgroups that repeat the computation of another one.  Returns h; c2h = 2 / h (0 for one particle).
 //
@@ -412,6 +412,7 @@ __device__ inline double kernel_matrix(BwShared<MAXN, THREADS> &sh, const BwArgs
     // K, C, row sums: 16 lanes per row.  K_ij and K_ji are the same LDS entry, so K is exactly
     // symmetric; the diagonal is exactly 1.
     const double inv_n = 1.0 / (double)n;
+    const int n4 = (n + 3) & ~3; // rows of C in LDS
     for (int i = tid >> 4; i < n; i += THREADS / 16) {
         double r = 0.0;
 #pragma unroll
@@ -421,14 +422,16 @@ __device__ inline double kernel_matrix(BwShared<MAXN, THREADS> &sh, const BwArgs
                 const double k = (i == j) ? 1.0 : sh.S[i < j ? pair_index(i, j, n) : pair_index(j, i, n)];
                 r += k;
                 if (write_global) coef[kOffK + i * n + j] = (float)k;
-                if (coef_lds) coef_lds[i * n + j] = (float)(k * inv_n);
+                if (coef_lds) coef_lds[i * n4 + j] = (float)(k * inv_n);
                 else coef[kOffC + i * n + j] = (float)(k * inv_n);
+            } else if (coef_lds && j < n4) {
+                coef_lds[i * n4 + j] = 0.f;
             }
         }
         r = row_sum_f64(r); // row sum of K
         if ((tid & 15) == 0) {
             const float rho = (float)(c2h * r * inv_n);
-            if (coef_lds) coef_lds[n * n + i] = rho;
+            if (coef_lds) coef_lds[n * n4 + i] = rho;
             else coef[kOffRho + i] = rho;
         }
     }
@@ -742,7 +745,7 @@ __device__ inline void gather_wave_sums(GatherShared<N> &sh, const float *partia
 // floats at n = 64: step 48.5 us, 45.3 with the reduction; 20,480 at n = 40: 29.4 and 29.0).
 constexpr int kDirectMaxFloats = 16 * 1024;
 
-__global__ __launch_bounds__(kBwThreads) void bandwidth_kernel(SumSource src, BwArgs ba, DevState *__restrict__ st,
+static __global__ __launch_bounds__(kBwThreads) void bandwidth_kernel(SumSource src, BwArgs ba, DevState *__restrict__ st,
                                                                float *__restrict__ coef)
 {
     __shared__ BwShared<kMaxN, kBwThreads> sh;

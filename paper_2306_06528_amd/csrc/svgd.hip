@@ -15,7 +15,7 @@
 #include "gram_kernels.hpp"
 #include "swag_kernels.hpp"
 #include "tiny_kernels.hpp"
-#include "update_kernels.hpp"
+#include "update_launch.hpp"
 
 using namespace svgd;
 
@@ -207,10 +207,6 @@ bool beyond_cache(int n, int64_t ld)
 {
     return (int64_t)n * ld * (int64_t)sizeof(float) > kMemorySideCacheBytes + kMemorySideCacheBytes / 4;
 }
-
-// Particle counts one to four above a multiple of 16: the matrix-core update treats the extra
-// particles as remainder rows (template argument REM of update_mfma_kernel).
-bool has_remainder_rows(int n) { return n > 16 && (n & 15) >= 1 && (n & 15) <= 4; }
 
 // Whether the matrix-core update on aligned rows lets the waves of a workgroup share a range.
 bool adjacent_tiles(int n, int64_t ld) { return n > 48 || beyond_cache(n, ld); }
@@ -407,6 +403,21 @@ int fused_workers(const svgd_ctx *c, int n, int64_t D, int64_t ld, int workers, 
     return 0;
 }
 
+// Rows that do not start on 128-byte boundaries: whether the update stores its tiles where they lie all the same
+// (kStoreDirect).  Staged, a tile is some three thousand cycles longer, and a wave's first tile and the end of
+// its range more than that; direct, a line that two tiles share is written twice, which costs little while the caches
+// hold what is in use, and most where phi is a third array.  The lines lie where the two cross (MiB of X; dense rows,
+// us per step staged and direct): plain n = 16 192 163.9 / 161.3, n = 24 58 62.7 / 61.4 and 96 94.5 / 96.2, n = 47
+// 56 71.4 / 71.0 and 94 98.8 / 106.8, n = 64 128 137.5 / 127.3 and 256 234.5 / 247.3; phi n = 20 24 34.2 / 32.2 and
+// 48 51.6 / 53.5, n = 48 38 55.2 / 54.1 and 58 73.3 / 76.8, n = 64 77 100.2 / 93.5; carried sums n = 16 64 40.9 / 39.9
+// and 128 68.7 / 70.7, n = 24 96 72.8 / 68.2 and 192 131.0 / 135.2, n = 64 256 201.3 / 186.5.  At small sizes:
+// n = 33, D = 20,001 25.6 / 22.2, n = 64, D = 8,577 33.1 / 28.4.
+bool store_directly(int n, int64_t D, bool emit, bool carry)
+{
+    const int mib = emit ? (n <= 32 ? 24 : (n <= 48 ? 40 : 76)) : (carry ? (n <= 48 ? 92 : 256) : (n <= 16 ? 184 : (n <= 48 ? 56 : 144)));
+    return (int64_t)n * D * (int64_t)sizeof(float) <= ((int64_t)mib << 20);
+}
+
 // Passes 2 and 3.  EMIT = false: X updated in place; EMIT = true: phi written to PHI.  CARRY (in
 // place): the update also leaves the pair-sum partials of the new X in the scratch, described by
 // `list` on return.
@@ -465,44 +476,11 @@ int run_update(svgd_ctx *c, float *X, const float *G, float *PHI, int n, int64_t
         // rows that all start on a 128-byte boundary (X's and G's, and PHI's) need no re-aligned stores and
         // can be read with streaming loads
         const bool aligned = rt ? rt->aligned != 0 : rows_aligned(X, ld) && rows_aligned(G, ld) && (!EMIT || rows_aligned(PHI, ld));
-#define UPD_F(NB, FULL, REM, F)                                                                                      \
-    do {                                                                                                             \
-        if (!EMIT && !CARRY && rt && aligned)                                                                        \
-            update_mfma_kernel<NB, false, FULL, false, true, true, F, false, REM><<<grid, 256, 0, s>>>(X, G, PHI, c->coef, c->state, n, D, ld, eps, gram_out, *rt, ua); \
-        else if (!EMIT && !CARRY && rt)                                                                              \
-            update_mfma_kernel<NB, false, FULL, false, false, true, F, false, REM><<<grid, 256, 0, s>>>(X, G, PHI, c->coef, c->state, n, D, ld, eps, gram_out, *rt, ua); \
-        else if (aligned)                                                                                            \
-            update_mfma_kernel<NB, EMIT, FULL, CARRY, true, false, F, false, REM><<<grid, 256, 0, s>>>(X, G, PHI, c->coef, c->state, n, D, ld, eps, gram_out, NoRows{}, ua); \
-        else if (CARRY && ua.reverse)                                                                                \
-            update_mfma_kernel<NB, false, FULL, CARRY, false, false, F, CARRY, REM><<<grid, 256, 0, s>>>(X, G, PHI, c->coef, c->state, n, D, ld, eps, gram_out, NoRows{}, ua); \
-        else                                                                                                         \
-            update_mfma_kernel<NB, EMIT, FULL, CARRY, false, false, F, false, REM><<<grid, 256, 0, s>>>(X, G, PHI, c->coef, c->state, n, D, ld, eps, gram_out, NoRows{}, ua); \
-    } while (0)
-#define UPD(NB, FULL, REM)                                                                                           \
-    do {                                                                                                             \
-        if constexpr (NB == 1) UPD_F(NB, FULL, REM, true); /* n <= kFusedAlwaysN */                                  \
-        else if constexpr (NB == 2 && !REM) { /* n <= kFusedMaxN */                                                  \
-            if (fused) UPD_F(NB, FULL, REM, true);                                                                   \
-            else UPD_F(NB, FULL, REM, false);                                                                        \
-        } else UPD_F(NB, FULL, REM, false);                                                                          \
-    } while (0)
-        // one to four particles beyond a multiple of 16 ride along as remainder rows of the kernel
-        // for that multiple
-        const bool rem = has_remainder_rows(n);
-        const int NB = (n + 15) / 16;
-        if (rem && n < 32) UPD(1, true, true);
-        else if (rem && n < 48) UPD(2, true, true);
-        else if (rem) UPD(3, true, true);
-        else if (n == 16) UPD(1, true, false);
-        else if (NB == 1) UPD(1, false, false);
-        else if (n == 32) UPD(2, true, false);
-        else if (n == 48) UPD(3, true, false);
-        else if (n == 64) UPD(4, true, false);
-        else if (NB == 2) UPD(2, false, false);
-        else if (NB == 3) UPD(3, false, false);
-        else UPD(4, false, false);
-#undef UPD
-#undef UPD_F
+        const bool direct = !rt && store_directly(n, D, EMIT, CARRY);
+        const UpdateCall call{X, G, PHI, c->coef, c->state, n, D, ld, eps, gram_out, rt, ua, grid, s,
+                              aligned ? kStoreLines : (direct ? kStoreDirect : kStoreStaged), fused};
+        if (n <= kFusedMaxN) launch_update_low<EMIT, CARRY>(call);
+        else launch_update_high<EMIT, CARRY>(call);
     }
     if (CARRY && c->captured && list.off != c->home) {
         const int n4 = list.nparts * (pair_stride(n) / 4);

@@ -215,137 +215,178 @@ void update_valu_kernel(float *__restrict__ X,
 // 32 floats, base pointer aligned).  Then r_i = 0 for all rows, the windows are the tiles, and
 // the results are stored straight from the registers that computed them - no staging at all
 // unless the Gram operands need it.
-// Columns beyond the last full tile (D mod 64) are done by one extra workgroup with a plain
-// loop.  Rows >= n (n not a multiple of 16) are neither loaded nor stored; their A entries are
+// Columns beyond the last full tile (D mod 64) are done by one extra workgroup (TailColumns).  Rows >= n (n not a multiple of 16) are neither loaded nor stored; their A entries are
 // zero (their contraction steps still run: skipping them behind wave-uniform branches cost more
 // than it saved, see below).  One to four rows beyond a multiple of 16 do not get a block of
 // their own at all (REM, below).
 // ---------------------------------------------------------------------------------------------
+enum StoreMode : int {
+    kStoreStaged = 0, // re-aligned through LDS, as described above
+    kStoreLines = 1,  // every row starts on a 128-byte boundary: straight from the registers, G streamed (ALIGNED)
+    kStoreDirect = 2  // straight from the registers to wherever the row starts, all accesses plain: for an X
+                      // that the caches hold, where lines written in two parts meet again before they leave
+};
 constexpr int kUpdCur = 16 * 64;    // floats per wave
 constexpr int kUpdCarry = 64 * 32;  // floats per wave
 
-// The < 64 columns after the last full tile, by one workgroup of 256 threads.  Everything is staged in
-// LDS (n * 64 floats each of z, x and - CARRY - the centred new values, n * n4 of C transposed, n4 = n
-// rounded up to 4: at most the 16384 floats the kernel has) and a thread computes a 4 x 4 tile, two
-// 16-byte LDS reads for sixteen multiply-adds.  At small D this workgroup is the last to finish:
-// with a row and a column per thread and C read from memory, n = 64, D = 1,003 took 48.9 us per
-// step, D = 20,003 43.9.
-template <int NMAX, bool EMIT, bool CARRY, bool ROWS> // n <= NMAX, a multiple of 4
-__device__ inline void update_tail_columns(float *__restrict__ X, const float *__restrict__ G,
-                                           float *__restrict__ OUT, const float *Cm, const float *rhov,
-                                           float c2h, int n, int64_t D, int64_t ld, int64_t col0, float eps,
-                                           float *__restrict__ lds, float *__restrict__ gram_out,
-                                           const int64_t *xrow, const int64_t *grow)
-{
-    const int n4 = (n + 3) & ~3;
-    // yn: groups of four rows keep their 16-byte granules in orders of their own, so that the pair sums can
-    // read different groups at the same column without meeting in the LDS banks
-    auto yn_index = [](int i, int c) { return i * 64 + (c ^ (((i >> 2) & 15) << 2)); };
-    float *zs = lds, *xs = zs + n * 64, *yn = xs + n * 64, *Ct = yn + (CARRY ? n * 64 : 0);
-    constexpr int U = 8; // loads in flight per array and thread
+// The < 64 columns after the last full tile, by one workgroup of 256 threads.  x, z and - CARRY - the centred new
+// values are staged in LDS, z and C with rows padded to a multiple of four, and a thread computes 4 columns
+// of every sixteenth row, four rows of z at a time: 16 RT multiply-adds for RT + 4 reads of 16 bytes.  At small
+// D this workgroup is the last to finish, so its loads go out with the other workgroups' first ones, all of
+// them together, and every particle count has all 256 threads at work.  (Loaded after pass 2, and with 4 x 4
+// tiles that left 192 threads idle at n = 16 and took C transposed, it ended 3.3 thousand cycles after the
+// others at n = 16, D = 8,577, and 5 at n = 33, D = 20,001.  As one more tile on the matrix cores it cost the loop over
+// the full tiles registers: n = 14, D = 4,000,003, padded, carried sums 110 -> 126 us.)
+template <int NMAX, bool EMIT, bool CARRY, bool ROWS, bool FUSED> // n <= NMAX, a multiple of 4
+struct TailColumns {
+    static constexpr int RT = (NMAX + 15) / 16; // rows per thread
+    static constexpr int U = NMAX / 4;          // loads per array and thread
+    static constexpr int UC = FUSED ? 1 : (NMAX * NMAX + 255) / 256;
+    float xv[U], gv[U];
+
+    // column tid % 64 of the rows tid / 64, + 4, + 8 ...; clamped, not guarded: all of them go out together
+    __device__ __forceinline__ void load(int n, int64_t D, int64_t ld, const float *X, const float *G, const int64_t *xrow, const int64_t *grow)
     {
-        const int col = threadIdx.x & 63, part = threadIdx.x >> 6;
-        const int64_t at = col0 + col < D ? col0 + col : D - 1;
-        for (int j0 = part; j0 < n; j0 += 4 * U) {
-            float xv[U], gv[U];
+        const int64_t col = (D & ~(int64_t)63) + (threadIdx.x & 63), at = col < D ? col : D - 1;
 #pragma unroll
-            for (int u = 0; u < U; ++u) { // clamped, not guarded: all of them go out together
-                const int j = j0 + 4 * u < n ? j0 + 4 * u : n - 1;
-                xv[u] = X[(ROWS ? xrow[ROWS ? j : 0] : (int64_t)j * ld) + at];
-                gv[u] = G[(ROWS ? grow[ROWS ? j : 0] : (int64_t)j * ld) + at];
-            }
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                if (j0 + 4 * u < n) {
-                    const float x = col0 + col < D ? xv[u] : 0.f, g = col0 + col < D ? gv[u] : 0.f;
-                    xs[(j0 + 4 * u) * 64 + col] = x;
-                    zs[(j0 + 4 * u) * 64 + col] = g - c2h * x;
-                }
-            }
-        }
-        for (int e0 = threadIdx.x; e0 < n * n; e0 += 256 * U) {
-            float c[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u) c[u] = Cm[e0 + 256 * u < n * n ? e0 + 256 * u : n * n - 1];
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int e = e0 + 256 * u, i = e / n;
-                if (e < n * n) Ct[(e - i * n) * n4 + i] = c[u];
-            }
+        for (int u = 0; u < U; ++u) {
+            const int r = (int)(threadIdx.x >> 6) + 4 * u, j = r < n ? r : n - 1;
+            xv[u] = X[(ROWS ? xrow[ROWS ? j : 0] : (int64_t)j * ld) + at];
+            gv[u] = G[(ROWS ? grow[ROWS ? j : 0] : (int64_t)j * ld) + at];
         }
     }
-    __syncthreads();
-    const int cg = 4 * (threadIdx.x & 15), i0 = 4 * (threadIdx.x >> 4); // 4 columns, 4 rows
-    if (i0 < n) {
-        f32x4 acc[4], m = {0.f, 0.f, 0.f, 0.f};
+
+    // Cm: rows `cs` floats apart - FUSED: in LDS, padded with zeros to a multiple of four; else in memory, n.
+    __device__ __forceinline__ void run(float *__restrict__ OUT, const float *Cm, int cs, const float *rhov, float c2h, int n, int64_t D,
+                                        int64_t ld, float eps, float *__restrict__ lds, float *__restrict__ gram_out, const int64_t *xrow)
+    {
+        const int n4 = (n + 3) & ~3, tid = threadIdx.x;
+        const int64_t col0 = D & ~(int64_t)63;
+        // yn: groups of four rows keep their 16-byte granules in orders of their own, so that the pair sums can
+        // read different groups at the same column without meeting in the LDS banks
+        auto yn_index = [](int i, int c) { return i * 64 + (c ^ (((i >> 2) & 15) << 2)); };
+        float *zs = lds, *xs = zs + n4 * 64, *yn = xs + n * 64, *Cs = yn + (CARRY ? n * 64 : 0);
+        __shared__ __attribute__((aligned(16))) float means[CARRY ? 4 * 64 : 4]; // the waves' shares of the column sums
+        float cv[UC];
+        if constexpr (!FUSED) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) acc[r] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll 4
-        for (int j = 0; j < n; ++j) {
-            const f32x4 z = *reinterpret_cast<const f32x4 *>(&zs[j * 64 + cg]);
-            const f32x4 c = *reinterpret_cast<const f32x4 *>(&Ct[j * n4 + i0]); // (rows n .. n4 - 1 hold anything: not stored)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) acc[r] += c[r] * z;
-            if constexpr (CARRY) m += *reinterpret_cast<const f32x4 *>(&xs[j * 64 + cg]);
+            for (int u = 0; u < UC; ++u) cv[u] = Cm[tid + 256 * u < n * n ? tid + 256 * u : n * n - 1];
         }
-        m *= 1.0f / (float)n;
+        float rho[RT];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int i = i0 + r;
+        for (int k = 0; k < RT; ++k) rho[k] = rhov[16 * k + (tid >> 4) < n ? 16 * k + (tid >> 4) : 0];
+        {
+            const int col = tid & 63;
+            const bool in = col0 + col < D;
+            float s = 0.f;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int r = (tid >> 6) + 4 * u;
+                const float x = in ? xv[u] : 0.f, g = in ? gv[u] : 0.f;
+                if (r < n) {
+                    xs[r * 64 + col] = x;
+                    s += x;
+                }
+                if (r < n4) zs[r * 64 + col] = r < n ? g - c2h * x : 0.f;
+            }
+            if constexpr (CARRY) means[tid] = s;
+        }
+        if constexpr (!FUSED) {
+#pragma unroll
+            for (int u = 0; u < UC; ++u) {
+                const int e = tid + 256 * u, i = e / n;
+                if (e < n * n) Cs[i * n4 + e - i * n] = cv[u];
+            }
+            if (n4 > n) // the padding
+                for (int e = tid; e < n * 4; e += 256)
+                    if (n4 - 4 + (e & 3) >= n) Cs[(e >> 2) * n4 + n4 - 4 + (e & 3)] = 0.f;
+        }
+        block_sync<true>();
+        const float *C = FUSED ? Cm : Cs;
+        const int st = FUSED ? cs : n4;
+        const int cg = 4 * (tid & 15), i0 = tid >> 4; // 4 columns, rows i0 + 16 k
+        f32x4 acc[RT];
+#pragma unroll
+        for (int k = 0; k < RT; ++k) acc[k] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 2
+        for (int j = 0; j < n4; j += 4) {
+            f32x4 z[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) z[r] = *reinterpret_cast<const f32x4 *>(&zs[(j + r) * 64 + cg]);
+#pragma unroll
+            for (int k = 0; k < RT; ++k) {
+                const int i = i0 + 16 * k < n ? i0 + 16 * k : n - 1;
+                const f32x4 c = *reinterpret_cast<const f32x4 *>(&C[i * st + j]);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) acc[k] += c[r] * z[r];
+            }
+        }
+        f32x4 m = {0.f, 0.f, 0.f, 0.f};
+        if constexpr (CARRY) {
+#pragma unroll
+            for (int w = 0; w < 4; ++w) m += *reinterpret_cast<const f32x4 *>(&means[64 * w + cg]);
+            m *= 1.0f / (float)n;
+        }
+#pragma unroll
+        for (int k = 0; k < RT; ++k) {
+            const int i = i0 + 16 * k;
             if (i < n) {
                 const f32x4 x = *reinterpret_cast<const f32x4 *>(&xs[i * 64 + cg]);
                 f32x4 out;
 #pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    const float phi = fmaf(rhov[i], x[c], acc[r][c]);
-                    out[c] = EMIT ? phi : fmaf(eps, phi, x[c]);
-                    if (col0 + cg + c < D) OUT[(ROWS ? xrow[ROWS ? i : 0] : (int64_t)i * ld) + col0 + cg + c] = out[c];
-                    if (CARRY) out[c] = col0 + cg + c < D ? out[c] - m[c] : 0.f;
+                for (int e = 0; e < 4; ++e) {
+                    const float phi = fmaf(rho[k], x[e], acc[k][e]);
+                    out[e] = EMIT ? phi : fmaf(eps, phi, x[e]);
                 }
-                if constexpr (CARRY) *reinterpret_cast<f32x4 *>(&yn[yn_index(i, cg)]) = out;
+                store4(OUT + (ROWS ? xrow[ROWS ? i : 0] : (int64_t)i * ld), col0 + cg, D, col0 + cg + 4 <= D, out);
+                if constexpr (CARRY) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) out[e] = col0 + cg + e < D ? out[e] - m[e] : 0.f;
+                    *reinterpret_cast<f32x4 *>(&yn[yn_index(i, cg)]) = out;
+                }
             }
         }
-    }
-    if constexpr (CARRY) {
-        // Gram of the updated, column-centred tail columns, in tri(i, j) order: a 4 x 4 tile of pairs, at
-        // most 136 tiles, belongs to PARTS neighbouring threads that share its columns - as many as
-        // the workgroup has for it.  (With one thread per tile ten of them walked all columns at n = 16
-        // while the others waited: D = 1,003, 15.8 us per step, now 12.1.)  Every pair adds its columns
-        // in the same order, so that equal particles stay at distance exactly 0.
-        constexpr int kTiles = (NMAX / 4) * (NMAX / 4 + 1) / 2;
-        constexpr int PARTS = kTiles * 16 <= 256 ? 16 : (kTiles * 4 <= 256 ? 4 : (kTiles * 2 <= 256 ? 2 : 1));
-        block_sync<true>(); // (LDS only: nothing waits for the stores of the new columns)
-        const int ng = n4 / 4, part = threadIdx.x % PARTS;
-        int bi = 0, rem = threadIdx.x / PARTS;
-        while (bi < ng && rem >= ng - bi) rem -= ng - bi++;
-        const int bj = bi + rem;
-        if (bi < ng) {
-            float acc[4][4] = {};
-            for (int c = 4 * part; c < 64; c += 4 * PARTS) {
-                f32x4 a[4], b[4];
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    a[r] = *reinterpret_cast<const f32x4 *>(&yn[yn_index(4 * bi + r < n ? 4 * bi + r : 0, c)]);
-                    b[r] = *reinterpret_cast<const f32x4 *>(&yn[yn_index(4 * bj + r < n ? 4 * bj + r : 0, c)]);
+        if constexpr (CARRY) {
+            // Gram of the updated, column-centred tail columns, in tri(i, j) order: a 4 x 4 tile of pairs, at
+            // most 136 tiles, belongs to PARTS neighbouring threads that share its columns - as many as
+            // the workgroup has for it.  (With one thread per tile ten of them walked all columns at n = 16
+            // while the others waited: D = 1,003, 15.8 us per step, now 12.1.)  Every pair adds its columns
+            // in the same order, so that equal particles stay at distance exactly 0.
+            constexpr int kTiles = (NMAX / 4) * (NMAX / 4 + 1) / 2;
+            constexpr int PARTS = kTiles * 16 <= 256 ? 16 : (kTiles * 4 <= 256 ? 4 : (kTiles * 2 <= 256 ? 2 : 1));
+            block_sync<true>(); // (LDS only: nothing waits for the stores of the new columns)
+            const int ng = n4 / 4, part = threadIdx.x % PARTS;
+            int bi = 0, rem = threadIdx.x / PARTS;
+            while (bi < ng && rem >= ng - bi) rem -= ng - bi++;
+            const int bj = bi + rem;
+            if (bi < ng) {
+                float acc[4][4] = {};
+                for (int c = 4 * part; c < 64; c += 4 * PARTS) {
+                    f32x4 a[4], b[4];
+    #pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        a[r] = *reinterpret_cast<const f32x4 *>(&yn[yn_index(4 * bi + r < n ? 4 * bi + r : 0, c)]);
+                        b[r] = *reinterpret_cast<const f32x4 *>(&yn[yn_index(4 * bj + r < n ? 4 * bj + r : 0, c)]);
+                    }
+    #pragma unroll
+                    for (int r = 0; r < 4; ++r)
+    #pragma unroll
+                        for (int t = 0; t < 4; ++t)
+    #pragma unroll
+                            for (int e = 0; e < 4; ++e) acc[r][t] = fmaf(a[r][e], b[t][e], acc[r][t]);
                 }
-#pragma unroll
+    #pragma unroll
                 for (int r = 0; r < 4; ++r)
-#pragma unroll
-                    for (int t = 0; t < 4; ++t)
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) acc[r][t] = fmaf(a[r][e], b[t][e], acc[r][t]);
+    #pragma unroll
+                    for (int t = 0; t < 4; ++t) {
+                        const float v = row_sum<PARTS>(acc[r][t]);
+                        const int i = 4 * bi + r, j = 4 * bj + t;
+                        if ((4 * r + t) % PARTS == part && i <= j && j < n) gram_out[tri(i, j, n)] = v;
+                    }
             }
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-#pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    const float v = row_sum<PARTS>(acc[r][t]);
-                    const int i = 4 * bi + r, j = 4 * bj + t;
-                    if ((4 * r + t) % PARTS == part && i <= j && j < n) gram_out[tri(i, j, n)] = v;
-                }
         }
     }
-}
+};
 
 // CARRY: additionally accumulate the Gram of the UPDATED columns, centred by the pre-update column
 // mean (any per-column shift common to all particles leaves every d2 unchanged), and write one
@@ -371,7 +412,7 @@ __device__ inline void update_tail_columns(float *__restrict__ X, const float *_
 // is summed on the vector ALU (each lane over its own rows, then across the wave's four rows of
 // lanes); they are stored as one more store group, and their pair sums (CARRY) are accumulated
 // like those of a further block whose rows R..15 are zero.
-template <int NB, bool EMIT, bool FULLROWS, bool CARRY, bool ALIGNED = false, bool ROWS = false, bool FUSED = false,
+template <int NB, bool EMIT, bool FULLROWS, bool CARRY, int STORE = kStoreStaged, bool ROWS = false, bool FUSED = false,
           bool REV = false, bool REM = false>
 __global__ __launch_bounds__(256)
 __attribute__((amdgpu_waves_per_eu((NB <= 2 && !FULLROWS) ? 2 : 1, (NB <= 2 && !FULLROWS) ? 2 : 1)))
@@ -380,6 +421,7 @@ void update_mfma_kernel(float *__restrict__ X, const float *__restrict__ G, floa
                         int64_t D, int64_t ld, float eps, float *__restrict__ gram_out,
                         typename RowArg<ROWS>::type rt, UpdateArgs ua)
 {
+    constexpr bool ALIGNED = STORE != kStoreStaged, STREAM = STORE == kStoreLines;
     static_assert(!FUSED || NB <= 2, "pass 2 with 256 threads: n <= 32");
     static_assert(!(CARRY && EMIT), "the Gram is carried only when X is updated");
     static_assert(!(ROWS && (EMIT || CARRY)), "separate rows: plain in-place step");
@@ -479,7 +521,7 @@ void update_mfma_kernel(float *__restrict__ X, const float *__restrict__ G, floa
         return *reinterpret_cast<const f32x4u *>(p);
     };
     auto load16g = [](const float *p) __attribute__((always_inline)) -> f32x4 {
-        if constexpr (ALIGNED) return __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(p));
+        if constexpr (STREAM) return __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(p));
         else return *reinterpret_cast<const f32x4u *>(p);
     };
     auto load_x = [&](const float *xt, int s) __attribute__((always_inline)) {
@@ -509,7 +551,16 @@ void update_mfma_kernel(float *__restrict__ X, const float *__restrict__ G, floa
         }
         load_next_rem(xt, gt);
     };
+    // the extra workgroup: ragged tail only
+    // (staged stores with two blocks of rows have no register to spare for loads across pass 2: three to five were
+    // spilled in the loop)
+    constexpr bool TAIL_EARLY = FUSED && (NB == 1 || ALIGNED);
+    const bool in_tail = has_tail && (int)blockIdx.x == nwork;
+    TailColumns<16 * NB + (REM ? 4 : 0), EMIT, CARRY, ROWS, FUSED> tail;
     auto first_loads = [&]() __attribute__((always_inline)) {
+        if constexpr (TAIL_EARLY) {
+            if (in_tail) tail.load(n, D, ld, X, G, srow, sgrow);
+        }
         if (t0 < t1) {
             int64_t in_off = in_lane + (t_first << 6);
             opaque(in_off);
@@ -528,8 +579,9 @@ void update_mfma_kernel(float *__restrict__ X, const float *__restrict__ G, floa
 
     // C (n x n) and rho (n): the handle's tables, or - FUSED - this workgroup's own copies in LDS,
     // computed by the prologue in the (still unused) staging area
-    __shared__ float cl[FUSED ? 32 * 32 + 32 : 1];
+    __shared__ __attribute__((aligned(16))) float cl[FUSED ? 32 * 32 + 32 : 1];
     const float *Cm = coef + kOffC, *rhov = coef + kOffRho;
+    const int cs = FUSED ? (n + 3) & ~3 : n; // rows of C (kernel_matrix pads its own with zeros)
     float c2h;
     if constexpr (FUSED) {
         typedef BwShared<32, 256> Shared;
@@ -542,15 +594,16 @@ void update_mfma_kernel(float *__restrict__ X, const float *__restrict__ G, floa
             [&](auto meanwhile) __attribute__((always_inline)) { gather_sums<256>(sh.S, red, ua.partials, ua.nparts, n, meanwhile); },
             first_loads); // the first tile is on its way while h and K are computed
         Cm = cl;
-        rhov = cl + n * n;
+        rhov = cl + n * cs;
     } else {
         c2h = st->two_over_h;
     }
 
-    if (has_tail && (int)blockIdx.x == nwork) { // the extra workgroup: ragged tail only
+    if (in_tail) {
+        if constexpr (!TAIL_EARLY) tail.load(n, D, ld, X, G, srow, sgrow);
         float *tail_out = nullptr;
         if constexpr (CARRY) tail_out = gram_out + (int64_t)nwork * pair_stride(n); // after the workers' partials
-        update_tail_columns<16 * NB + (REM ? 4 : 0), EMIT, CARRY, ROWS>(X, G, OUT, Cm, rhov, c2h, n, D, ld, nfull << 6, eps, lds, tail_out, srow, sgrow);
+        tail.run(OUT, Cm, cs, rhov, c2h, n, D, ld, eps, lds, tail_out, srow);
         return;
     }
 
@@ -583,7 +636,7 @@ void update_mfma_kernel(float *__restrict__ X, const float *__restrict__ G, floa
         const int l = e & 63, sg = (e >> 6) % NB, bi = (e >> 6) / NB;
         const int i = 16 * bi + (l & 15), j0 = 16 * sg + 4 * (l >> 4);
         if constexpr (FULLROWS) {
-            av[it] = *reinterpret_cast<const f32x4u *>(Cm + i * n + j0);
+            av[it] = *reinterpret_cast<const f32x4u *>(Cm + i * cs + j0);
         }
     }
     // rho of this lane's rows: in registers, or (RHO_LDS) in LDS, four of a block at a time, where the registers
@@ -610,7 +663,7 @@ void update_mfma_kernel(float *__restrict__ X, const float *__restrict__ G, floa
             const int i = 16 * bi + (l & 15), j0 = 16 * sg + 4 * (l >> 4);
             if (e < NB * NB * 64)
 #pragma unroll
-            for (int k = 0; k < 4; ++k) av[it][k] = (i < n && j0 + k < n) ? Cm[i * n + j0 + k] : 0.f;
+            for (int k = 0; k < 4; ++k) av[it][k] = (i < n && j0 + k < n) ? Cm[i * cs + j0 + k] : 0.f;
         }
         if (e < NB * NB * 64) As4[e] = av[it];
     }
@@ -625,14 +678,14 @@ void update_mfma_kernel(float *__restrict__ X, const float *__restrict__ G, floa
     if constexpr (REM) {
         for (int e = threadIdx.x; e < NB * 64; e += 256) {
             const int l = e & 63, bi = e >> 6;
-            arem[e] = ((l >> 4) < R) ? Cm[(16 * bi + (l & 15)) * n + 16 * NB + (l >> 4)] : 0.f;
+            arem[e] = ((l >> 4) < R) ? Cm[(16 * bi + (l & 15)) * cs + 16 * NB + (l >> 4)] : 0.f;
         }
         for (int e = threadIdx.x; e < 16 * CREM; e += 256) {
             const int s = e % CREM, rq = e / CREM, r = rq >> 2, qq = rq & 3;
             float v = 0.f;
             if (r < R) {
-                if (s < NS) v = Cm[(16 * NB + r) * n + 16 * (s >> 2) + 4 * qq + (s & 3)];
-                else if (s == NS && qq < R) v = Cm[(16 * NB + r) * n + 16 * NB + qq];
+                if (s < NS) v = Cm[(16 * NB + r) * cs + 16 * (s >> 2) + 4 * qq + (s & 3)];
+                else if (s == NS && qq < R) v = Cm[(16 * NB + r) * cs + 16 * NB + qq];
             }
             crem[e] = v;
         }
@@ -668,6 +721,12 @@ void update_mfma_kernel(float *__restrict__ X, const float *__restrict__ G, floa
             zr = grn;
             load_next_rem(xt, gt);
         }
+        // the lane's 16 bytes of a row: where it loaded x from
+        auto store_direct = [&](int64_t row_off, f32x4 v) __attribute__((always_inline)) {
+            float *dst = OUT + in_lane + base + row_off;
+            if constexpr (STREAM) __builtin_nontemporal_store(v, reinterpret_cast<f32x4 *>(dst));
+            else *reinterpret_cast<f32x4u *>(dst) = v;
+        };
 
         f32x4 mg[CARRY ? 4 : 1];      // pre-update column means in the Gram operand layout
         f32x4 ag[CARRY ? NBG : 1][4]; // Gram operands of the blocks finished so far
@@ -800,9 +859,8 @@ void update_mfma_kernel(float *__restrict__ X, const float *__restrict__ G, floa
                     const float phi = fmaf(RHO_LDS ? rho4[r] : rho[RHO_LDS ? 0 : s], x[s][t], acc[t][r]);
                     o[t] = EMIT ? phi : fmaf(eps, phi, x[s][t]);
                 }
-                if constexpr (ALIGNED) { // the lane's 16 bytes lie where it loaded x from: whole lines per quarter-wave
-                    if (FULLROWS || 16 * bi + 4 * q + r < n)
-                        __builtin_nontemporal_store(o, reinterpret_cast<f32x4 *>(OUT + in_lane + base + (ROWS ? xro[ROWS ? s : 0] : (int64_t)(16 * bi + r) * ld)));
+                if constexpr (ALIGNED) {
+                    if (FULLROWS || 16 * bi + 4 * q + r < n) store_direct(ROWS ? xro[ROWS ? s : 0] : (int64_t)(16 * bi + r) * ld, o);
                 }
                 if constexpr (!ALIGNED || CARRY) // staged for the re-aligned stores and/or as Gram operands
                     *reinterpret_cast<f32x4 *>(&cur[cur_index(4 * q + r, 4 * c16)]) = o;
@@ -838,7 +896,7 @@ void update_mfma_kernel(float *__restrict__ X, const float *__restrict__ G, floa
                 o[t] = EMIT ? phi : fmaf(eps, phi, xr[t]);
             }
             if constexpr (ALIGNED) {
-                if (q < R) __builtin_nontemporal_store(o, reinterpret_cast<f32x4 *>(OUT + in_lane + base + rem_x));
+                if (q < R) store_direct(rem_x, o);
             }
             if constexpr (!ALIGNED || CARRY) *reinterpret_cast<f32x4 *>(&cur[cur_index(q, 4 * c16)]) = o;
             if constexpr (CARRY) {

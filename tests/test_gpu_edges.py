@@ -4,7 +4,7 @@ carried sums) and the last, partly filled round of the streaming moments kernel.
 import pytest
 import torch
 
-from parity_checks import check_carried_chain
+from parity_checks import check_carried_chain, ulp_diff_device
 
 pytestmark = pytest.mark.gpu
 
@@ -87,3 +87,41 @@ def test_where_pass_2_is_part_of_the_update(n, D, fused, flags):
     if flags == "carry":
         for padded in (False, True):
             check_carried_chain(svgd, X, G, 0.05, padded=padded, steps=3)
+
+
+# (MiB of X up to which rows off the 128-byte boundaries are stored directly: 24, 40, 76 for phi; 184, 56, 144 for a
+# plain step; 92, 256 on carried sums)
+@pytest.mark.parametrize("n,mib", [(16, 184), (16, 92), (20, 24), (24, 56), (33, 40), (48, 56), (51, 76), (64, 76)])
+def test_direct_and_staged_stores(n, mib):
+    """One column less and one more than the size at which the stores change, and odd row starts: what both leave
+    is the oracle's (through phi of the same sizes), nothing between the rows is touched."""
+    from paper_2306_06528_amd import svgd
+    D0 = (mib << 20) // (4 * n)
+    for D in (D0 - 1, D0 + 1):
+        g = torch.Generator(device="cuda").manual_seed(D)
+        buf, G = torch.full((n, D + 3), 7.0, device="cuda"), torch.randn(n, D + 3, device="cuda", generator=g)
+        X = buf[:, 1:D + 1]
+        X.copy_(0.3 * torch.randn(n, D, device="cuda", generator=g))
+        old, Gv = X.clone(), G[:, 1:D + 1]
+        pbuf = torch.full((n, D + 3), 7.0, device="cuda")
+        PHI = pbuf[:, 1:D + 1]
+        with svgd.Svgd(n, D) as eng:
+            eng.phi(X, Gv, PHI)
+            h, K = eng.get_last(n)
+            Kd = torch.from_numpy(K).cuda().double()
+            ref = Kd @ (Gv.double() - (2.0 / h) * old.double()) / n + (2.0 / h) * Kd.sum(1, keepdim=True) / n * old.double()
+            assert float((PHI.double() - ref).abs().max()) <= 1e-5 * float(ref.abs().max())
+            eng.step(X, Gv, 0.05)
+        assert ulp_diff_device(X, old, PHI, 0.05) <= 1.0
+        with svgd.Svgd(n, D, flags=svgd.FLAG_CARRY_GRAM) as eng:
+            X.copy_(old)
+            eng.step(X, Gv, 0.05)
+            assert ulp_diff_device(X, old, PHI, 0.05) <= 1.0
+            now = X.clone()
+            with svgd.Svgd(n, D) as plain:
+                plain.phi(X, Gv, PHI)
+            eng.step(X, Gv, 0.05)  # walks the other way
+            assert ulp_diff_device(X, now, PHI, 0.05) <= 1.0
+        for b in (buf, pbuf):
+            assert bool((b[:, 0] == 7.0).all()) and bool((b[:, D + 1:] == 7.0).all())
+        del buf, G, X, Gv, PHI, pbuf, old, now, ref
