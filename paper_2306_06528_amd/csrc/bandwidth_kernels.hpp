@@ -22,7 +22,7 @@ __device__ inline int pair_index(int i, int j, int n) { return i * n - (i * (i +
 template <int MAXN, int THREADS>
 struct BwShared {
     static constexpr int kPairs = MAXN * (MAXN - 1) / 2;
-    static constexpr int kPr = (kPairs > kSelDirect) ? kPairs : kSelDirect;
+    static constexpr int kPr = (kPairs > 2 * kWave) ? kPairs : 2 * kWave; // (wave_select reads whole registers)
     double S[MAXN * (MAXN + 1) / 2]; // reduced pair sums, later K per pair
     double pr[kPr];                  // d2 per unordered pair i < j
     double list[kSelDirect];         // the final short list
@@ -284,6 +284,66 @@ __device__ inline void select_two_ranks(Shared &sh, const double (&v)[VPT], int 
     }
 }
 
+// The same by one wave, for at most 64 V values, lane l holding the values l + 64 u: no LDS and no barrier, so
+// every wave of a workgroup does it for itself.  A pivot among the candidates, two ballots per register
+// to count what lies below it and what does not lie above it, and the candidates are what is left on the wanted
+// side; the pivot's place among the candidates changes from round to round, so that an order in the data (particles
+// on a line) does not make it the smallest each time.  Values: not NaN.  r_hi = r_lo or r_lo + 1.
+template <int V>
+__device__ inline void wave_select(const double (&v)[V], int count, int r_lo, int r_hi, double &lo, double &hi)
+{
+    unsigned long long m[V]; // the candidates
+#pragma unroll
+    for (int u = 0; u < V; ++u) {
+        const int left = count - kWave * u;
+        m[u] = left >= kWave ? ~0ull : (left > 0 ? (1ull << left) - 1ull : 0ull);
+    }
+    int r = r_lo; // among the candidates
+    unsigned rot = 29;
+    for (;;) {
+        double from = v[V - 1];
+        unsigned long long mu = m[V - 1];
+#pragma unroll
+        for (int u = V - 2; u >= 0; --u) {
+            if (m[u]) {
+                from = v[u];
+                mu = m[u];
+            }
+        }
+        const unsigned long long turned = (mu >> rot) | (mu << (64 - rot)); // (rot is odd: 1 .. 63)
+        const int lane = (__ffsll(turned) - 1 + (int)rot) & 63;
+        const double p = readlane_f64(from, __builtin_amdgcn_readfirstlane(lane));
+        unsigned long long lt[V], le[V];
+        int c_lt = 0, c_le = 0;
+#pragma unroll
+        for (int u = 0; u < V; ++u) {
+            lt[u] = __ballot(v[u] < p) & m[u];
+            le[u] = __ballot(v[u] <= p) & m[u];
+            c_lt += __popcll(lt[u]);
+            c_le += __popcll(le[u]);
+        }
+        if (r < c_lt) {
+#pragma unroll
+            for (int u = 0; u < V; ++u) m[u] = lt[u];
+        } else if (r >= c_le) {
+            r -= c_le;
+#pragma unroll
+            for (int u = 0; u < V; ++u) m[u] &= ~le[u];
+        } else {
+            lo = hi = p;
+            if (r + (r_hi - r_lo) >= c_le) { // the next one is the smallest of all that lie above
+                double mn = __builtin_huge_val(), mx = 0.0;
+#pragma unroll
+                for (int u = 0; u < V; ++u) mn = fmin(mn, (v[u] > p && (int)(threadIdx.x & 63) + kWave * u < count) ? v[u] : __builtin_huge_val());
+                wave_minmax(mn, mx);
+                hi = mn;
+            }
+            return;
+        }
+        rot = (rot + 22) & 63;
+    }
+}
+
 // What pass 2 is asked for.
 struct BwArgs {
     int n;
@@ -295,9 +355,7 @@ struct BwArgs {
 // Pass 2: h, K and the coefficient tables from the pair sums.  Called by all THREADS threads of a
 // workgroup.  fill(meanwhile) leaves the reduced pair sums in sh.S (a barrier follows here); it
 // calls meanwhile() once, at the point where it waits for memory: everything that does not depend
-// on the sums is done there.  after_sums() is called between the sums and the arithmetic that needs
-// no memory: the place for the caller to send off loads of its own (issued earlier they would only
-// make the sums wait behind them - a wave's loads complete in order).
+// on the sums is done there.
 // coef_lds, if not null, receives C, its rows padded with zeros to a multiple of four, and rho [n] (LDS of the caller; barrier included);
 // otherwise they go to coef (device memory).  write_global = false: st and K are left alone - for
 // workgroups that repeat the computation of another one.  Returns h; c2h = 2 / h (0 for one particle).
@@ -310,10 +368,10 @@ struct BwArgs {
 struct NoCall {
     __device__ void operator()() const {}
 };
-template <int THREADS, int MAXN, bool LO, class Fill, class AfterSums>
+template <int THREADS, int MAXN, bool LO, class Fill>
 __device__ inline double kernel_matrix(BwShared<MAXN, THREADS> &sh, const BwArgs &ba, DevState *__restrict__ st,
                                        float *__restrict__ coef, float *coef_lds, bool write_global, float &c2h_out,
-                                       Fill fill, AfterSums after_sums)
+                                       Fill fill)
 {
     static_assert(THREADS % 64 == 0 && THREADS >= 256 && THREADS <= 1024, "whole waves");
     constexpr int kPairs = MAXN * (MAXN - 1) / 2;
@@ -321,17 +379,20 @@ __device__ inline double kernel_matrix(BwShared<MAXN, THREADS> &sh, const BwArgs
     const int tid = threadIdx.x, n = ba.n;
     const int Pp = n * (n - 1) / 2;
     const bool select = ba.h_fixed <= 0.0 && Pp > 0;
-    const bool buckets = kPairs > kSelDirect && select && Pp > kSelDirect;
+    // Above kWaveSelect pairs (17 particles and more) the selection spreads them over buckets; up to there every
+    // wave selects by itself.  (us per step by buckets and by waves: n = 13, D = 8,577, padded, carried sums 8.9
+    // and 7.6, n = 16 8.7 and 8.2, with four values per lane n = 18 10.1 and 10.7, n = 22 11.2 and 12.3.)
+    constexpr int kWaveSelect = 2 * kWave;
+    const bool buckets = kPairs > kWaveSelect && select && Pp > kWaveSelect;
     const double inf = __builtin_huge_val();
     int pi[VPT], pj[VPT];
     fill([&]() __attribute__((always_inline)) {
         // the selection's scratch in its initial state
-        if (tid < 2) sh.sel[tid] = 0.0;
-        if (tid < kSelDirect) {
-            sh.counters[tid] = 0;
-            sh.list[tid] = inf;
-        }
-        if (kPairs > kSelDirect) {
+        if (buckets) {
+            if (tid < kSelDirect) {
+                sh.counters[tid] = 0;
+                sh.list[tid] = inf;
+            }
             for (int e = tid; e < kBuckets; e += THREADS) sh.hist[e] = 0;
             if (tid < 4) {
                 sh.misc[tid] = 0;
@@ -353,7 +414,6 @@ __device__ inline double kernel_matrix(BwShared<MAXN, THREADS> &sh, const BwArgs
         }
     });
     block_sync<LO>();
-    after_sums();
 
     // d2 per pair: direct sums, or S_ii + S_jj - 2 S_ij (clamped at 0) from the centred Gram
     double d2[VPT];
@@ -380,14 +440,21 @@ __device__ inline double kernel_matrix(BwShared<MAXN, THREADS> &sh, const BwArgs
     // pair value otherwise; an even count averages positions n*n/2 - 1 and n*n/2.  So what is
     // needed are the pair values of rank r_lo and r_hi (equal or adjacent), not a sorted list.
     const int t_lo = (n * n - 1) / 2, t_hi = (n * n) / 2; // t_hi >= n for every n >= 2
+    double lo = 0.0, hi = 0.0;
     if (select) {
         // n = 2: position t_lo is one of the diagonal zeros - the other rank is selected twice
         const int r_lo = (t_lo >= n) ? (t_lo - n) / 2 : (t_hi - n) / 2, r_hi = (t_hi - n) / 2;
-        if (buckets) select_two_ranks<THREADS, VPT, LO>(sh, d2, Pp, r_lo, r_hi);
-        else rank_directly<THREADS, LO>(sh.pr, Pp, 0, r_lo, r_hi, sh.sel, sh.counters);
-        block_sync<LO>();
+        if (buckets) {
+            select_two_ranks<THREADS, VPT, LO>(sh, d2, Pp, r_lo, r_hi);
+            block_sync<LO>();
+            lo = sh.sel[0];
+            hi = sh.sel[1];
+        } else {
+            const double v[2] = {sh.pr[tid & 63], sh.pr[(tid & 63) + kWave]};
+            wave_select<2>(v, Pp, r_lo, r_hi, lo, hi);
+        }
     }
-    const double med = select ? 0.5 * ((t_lo >= n ? sh.sel[0] : 0.0) + sh.sel[1]) : 0.0;
+    const double med = select ? 0.5 * ((t_lo >= n ? lo : 0.0) + hi) : 0.0;
     // h = num / den and 1 / h = den / num: two divisions side by side
     const double num = (ba.h_fixed > 0.0) ? ba.h_fixed : med, den = (ba.h_fixed > 0.0) ? 1.0 : ba.log_n1;
     double h = num / den, inv_h = den / num;
@@ -463,47 +530,59 @@ __device__ inline void copy_sums(double *S, const double *sums, int n, Meanwhile
 }
 
 // Sums a list of partials in fp64 into S [n (n + 1) / 2].  Thread (kk, pp) = (tid / P4, tid % P4), kk <
-// KL, sums four consecutive entries of the partials kk, kk + KL, ... kSumLoads 16-byte loads in
-// flight; the KL sums of an entry meet in `red` [KL * P4 * 4 <= 4 * THREADS].
+// KL, sums four consecutive entries of the partials kk, kk + KL, ..., up to MAXU 16-byte loads in
+// flight (as the registers allow); the KL sums of an entry meet in `red` [KL * P4 * 4 <= 4 * THREADS].  meanwhile() and then last() are called
+// when the last loads of the list have been sent off (see gather_wave_sums).  With sixteen loads in flight and the
+// next kernel's first loads sent off after the sums a list of 256 at n = 20 took 7.3 us (four rounds).
 constexpr int kSumLoads = 16;
-template <int THREADS, class Meanwhile>
-__device__ inline void gather_sums(double *S, double *red, const float *partials, int nparts, int n, Meanwhile meanwhile)
+template <int THREADS, bool LO, int MAXU, class Meanwhile, class Last>
+__device__ inline void gather_sums(double *S, double *red, const float *partials, int nparts, int n, Meanwhile meanwhile, Last last)
 {
     const int tid = threadIdx.x;
     const int P = n * (n + 1) / 2;
     const int P4 = (P + 3) / 4;
-    const int KL = THREADS / P4 < 32 ? THREADS / P4 : 32; // capped: the KL sums are added serially
-    const int kk = tid / P4, pp = tid - kk * P4;
-    constexpr int U = kSumLoads;
+    // (quotients of small integers: half a unit off the next one, far more than the reciprocal's error)
+    const float inv = __builtin_amdgcn_rcpf((float)P4);
+    const int per_wg = (int)(((float)THREADS + 0.5f) * inv);
+    const int KL = per_wg < 32 ? per_wg : 32; // capped: the KL sums are added serially
+    const int kk = (int)(((float)tid + 0.5f) * inv), pp = tid - kk * P4;
     const f32x4 *base = reinterpret_cast<const f32x4 *>(partials) + pp;
     double s[4] = {0.0, 0.0, 0.0, 0.0};
-    bool first = true;
-    for (int k0 = 0; k0 < nparts; k0 += U * KL) { // trip count uniform over the workgroup
+    int k0 = 0;
+    auto batch = [&](auto loads, auto then) __attribute__((always_inline)) { // clamped, not guarded: the number of loads is known
+        constexpr int U = decltype(loads)::value;
         f32x4 v[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            v[u] = f32x4{0.f, 0.f, 0.f, 0.f};
-            if (k0 + u * KL < nparts) { // uniform: whole loads beyond the list are left out, single lanes read its last entry again
-                int k = k0 + kk + u * KL;
-                k = k < nparts ? k : nparts - 1;
-                v[u] = base[(int64_t)k * P4];
-            }
+            const int k = k0 + kk + u * KL;
+            v[u] = base[(int64_t)(k < nparts ? k : nparts - 1) * P4];
         }
-        if (first) meanwhile();
-        first = false;
+        then();
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const bool in = k0 + kk + u * KL < nparts;
 #pragma unroll
             for (int c = 0; c < 4; ++c) s[c] += in ? (double)v[u][c] : 0.0;
         }
+    };
+    auto both = [&]() __attribute__((always_inline)) {
+        meanwhile();
+        last();
+    };
+    for (; nparts - k0 > MAXU * KL; k0 += MAXU * KL) batch(std::integral_constant<int, MAXU>{}, NoCall{});
+    if (MAXU > kSumLoads && nparts - k0 > kSumLoads * KL) {
+        batch(std::integral_constant<int, MAXU>{}, both);
+    } else if (nparts - k0 > kSumLoads / 4 * KL) {
+        batch(std::integral_constant<int, kSumLoads>{}, both);
+    } else {
+        batch(std::integral_constant<int, kSumLoads / 4>{}, both);
     }
     if (kk < KL) {
         double2 *dst = reinterpret_cast<double2 *>(red + (kk * P4 + pp) * 4);
         dst[0] = double2{s[0], s[1]};
         dst[1] = double2{s[2], s[3]};
     }
-    __syncthreads();
+    block_sync<LO>();
     for (int p = tid; p < P; p += THREADS) {
         double t = 0.0;
 #pragma unroll 4
@@ -755,9 +834,8 @@ static __global__ __launch_bounds__(kBwThreads) void bandwidth_kernel(SumSource 
         sh, ba, st, coef, nullptr, true, c2h,
         [&](auto meanwhile) __attribute__((always_inline)) {
             if (src.sums != nullptr) copy_sums<kBwThreads>(sh.S, src.sums, ba.n, meanwhile);
-            else gather_sums<kBwThreads>(sh.S, red, src.partials, src.nparts, ba.n, meanwhile);
-        },
-        NoCall{});
+            else gather_sums<kBwThreads, false, kSumLoads>(sh.S, red, src.partials, src.nparts, ba.n, meanwhile, NoCall{});
+        });
 }
 
 } // namespace svgd

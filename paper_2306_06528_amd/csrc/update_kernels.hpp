@@ -591,8 +591,8 @@ void update_mfma_kernel(float *__restrict__ X, const float *__restrict__ G, floa
         double *red = reinterpret_cast<double *>(reinterpret_cast<char *>(&sh) + sizeof(Shared));
         kernel_matrix<256, 32, true>(
             sh, BwArgs{n, kModeGram, ua.h_fixed, ua.log_n1}, st, coef, cl, blockIdx.x == 0, c2h,
-            [&](auto meanwhile) __attribute__((always_inline)) { gather_sums<256>(sh.S, red, ua.partials, ua.nparts, n, meanwhile); },
-            first_loads); // the first tile is on its way while h and K are computed
+            [&](auto meanwhile) __attribute__((always_inline)) { gather_sums<256, true, (NB == 1 || FULLROWS) && !ROWS ? 2 * kSumLoads : kSumLoads>(sh.S, red, ua.partials, ua.nparts, n, meanwhile, first_loads); });
+        // (the first tile is on its way while the list is summed and h and K are computed)
         Cm = cl;
         rhov = cl + n * cs;
     } else {

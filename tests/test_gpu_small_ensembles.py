@@ -70,3 +70,26 @@ def test_equal_distances(n, D):
         assert abs(h - ref["h"]) <= TOL_H * ref["h"], second
         assert float(np.abs(K - ref["K"]).max()) <= TOL_K
         assert_x_new(X.cpu().numpy(), ref, 0.05, f"second {second}")
+
+
+@pytest.mark.parametrize("kind", ["line", "line_reversed", "two_places", "half_equal", "one_far", "random"])
+@pytest.mark.parametrize("n", [13, 14, 15, 16])
+def test_selection_by_a_wave(n, kind):
+    """13 to 16 particles, whose middle distances every wave finds by itself: orders in the data, ties on either
+    side of the wanted ranks, all sizes of what is left above them."""
+    from paper_2306_06528_amd import svgd
+    D = 600
+    base = _inputs(n, D, n)[0]
+    at = {"line": torch.arange(n), "line_reversed": torch.arange(n).flip(0), "two_places": torch.arange(n) % 2,
+          "half_equal": torch.clamp(torch.arange(n) - n // 2, min=0), "one_far": (torch.arange(n) == 3) * 50,
+          "random": torch.zeros(n)}[kind].float().cuda()
+    X = base if kind == "random" else at[:, None] * base[0][None, :] / 8 + base[1][None, :]
+    X = X.contiguous()
+    G = torch.ones_like(X)
+    ref = orc.step(X.cpu().numpy(), G.cpu().numpy(), 0.05)
+    with svgd.Svgd(n, D) as eng:
+        eng.step(X, G, 0.05)
+        h, K = eng.get_last(n)
+    # sums of squares in fp32 around the mean: a distance is good to some 2^-22 of the largest square
+    assert abs(h - ref["h"]) <= TOL_H * ref["h"]
+    assert float(np.abs(K - ref["K"]).max()) <= TOL_K
