@@ -2,6 +2,7 @@
 #include "../../include/svgd.h"
 
 #include <algorithm>
+#include <chrono>
 #include <cmath>
 #include <cstring>
 #include <mutex>
@@ -55,6 +56,8 @@ struct svgd_ctx {
     double *sums;     // [P], the reduced pair sums
     DevState *state;
     float *coef;      // kCoefFloats, kStateBytes behind `state` in one allocation
+    Mirror *mirror;   // page-locked host memory (read_back)
+    unsigned ticket;
     // optional per-kernel timing (svgd_profile_begin/end): event pairs recorded around launches
     bool profiling;
     unsigned profile_kinds; // bit k set: kernels of kind k are timed
@@ -123,6 +126,39 @@ struct KernelTimer {
         if (slot != (size_t)-1) (void)hipEventRecord(c->ev_pool[2 * slot + 1], s);
     }
 };
+
+// Whether what is launched on the stream goes into a graph.
+bool is_capturing(hipStream_t s)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &st) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return st == hipStreamCaptureStatusActive;
+}
+
+// The first `bytes` bytes of the handle's state (DevState, then K) as they are when the work enqueued on the stream
+// is done, in c->mirror->data.  A kernel writes them to page-locked memory and the host watches for its ticket;
+// if that does not come within a few milliseconds the stream is waited for as usual, which also
+// reports what went wrong.
+int read_back(svgd_ctx *c, size_t bytes, hipStream_t s)
+{
+    if (is_capturing(s)) return fail(c, hipErrorStreamCaptureUnsupported); // nothing can be read while nothing runs
+    const unsigned ticket = ++c->ticket;
+    mirror_kernel<<<1, 256, 0, s>>>(reinterpret_cast<const unsigned *>(c->state), c->mirror, (int)((bytes + 3) / 4), ticket);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return fail(c, e);
+    const auto until = std::chrono::steady_clock::now() + std::chrono::milliseconds(5);
+    for (unsigned k = 0;; ++k) {
+        if (__atomic_load_n(&c->mirror->ticket, __ATOMIC_ACQUIRE) == ticket) return SVGD_OK;
+        if ((k & 63) == 63 && std::chrono::steady_clock::now() > until) break;
+        __builtin_ia32_pause();
+    }
+    e = hipStreamSynchronize(s);
+    if (e != hipSuccess) return fail(c, e);
+    return SVGD_OK;
+}
 
 int check_shape(svgd_ctx *c, int n, int64_t D, int64_t ld)
 {
@@ -493,17 +529,6 @@ int run_update(svgd_ctx *c, float *X, const float *G, float *PHI, int n, int64_t
     return SVGD_OK;
 }
 
-// Whether what is launched on the stream goes into a graph.
-bool is_capturing(hipStream_t s)
-{
-    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(s, &st) != hipSuccess) {
-        (void)hipGetLastError();
-        return false;
-    }
-    return st == hipStreamCaptureStatusActive;
-}
-
 // The single-launch path: sizes at which one workgroup does the whole step faster than three
 // dependent launches.  It neither reads nor leaves carried pair sums.
 bool is_tiny(int n, int64_t D) { return n <= kTinyMaxN && (int64_t)n * D <= kTinyMaxElems; }
@@ -645,6 +670,8 @@ int svgd_create(svgd_handle_t *out, int max_n, int64_t max_D, int device_id, uin
     c->sums = nullptr;
     c->state = nullptr;
     c->coef = nullptr;
+    c->mirror = nullptr;
+    c->ticket = 0;
     c->profiling = false;
     c->profile_kinds = ~0u;
 
@@ -667,15 +694,18 @@ int svgd_create(svgd_handle_t *out, int max_n, int64_t max_D, int device_id, uin
     const size_t P = (size_t)pair_stride(max_n);
     bool ok = hipMalloc(&c->partials, (size_t)kMaxParts * P * sizeof(float)) == hipSuccess &&
               hipMalloc(&c->sums, P * sizeof(double)) == hipSuccess &&
-              hipMalloc(&c->state, kStateBytes + (size_t)kCoefFloats * sizeof(float)) == hipSuccess;
+              hipMalloc(&c->state, kStateBytes + (size_t)kCoefFloats * sizeof(float)) == hipSuccess &&
+              hipHostMalloc((void **)&c->mirror, sizeof(Mirror), hipHostMallocMapped | hipHostMallocCoherent) == hipSuccess;
     if (!ok) {
         (void)hipGetLastError();
         (void)hipFree(c->partials);
         (void)hipFree(c->sums);
         (void)hipFree(c->state);
+        (void)hipHostFree(c->mirror);
         delete c;
         return SVGD_ERR_ALLOC;
     }
+    c->mirror->ticket = 0;
     c->coef = reinterpret_cast<float *>(reinterpret_cast<char *>(c->state) + kStateBytes);
     c->partials_cap = (int64_t)kMaxParts * (int64_t)P;
     c->magic = kMagic;
@@ -724,9 +754,9 @@ int svgd_bandwidth_ld(svgd_handle_t c, const float *X, int n, int64_t D, int64_t
     }
     if (rc) return rc;
     if (h_out_host) {
-        hipError_t e = hipMemcpyAsync(h_out_host, &c->state->h, sizeof(double), hipMemcpyDeviceToHost, s);
-        if (e == hipSuccess) e = hipStreamSynchronize(s);
-        if (e != hipSuccess) return fail(c, e);
+        rc = read_back(c, sizeof(DevState), s);
+        if (rc) return rc;
+        *h_out_host = reinterpret_cast<const DevState *>(c->mirror->data)->h;
     }
     return SVGD_OK;
 }
@@ -885,20 +915,15 @@ int svgd_get_last(svgd_handle_t c, double *h_out, float *K_host, void *stream)
     if (c->last_n < 1) return SVGD_ERR_INVALID_ARG;
     DeviceGuard guard(c->device);
     hipStream_t s = (hipStream_t)stream;
-    // h and K lie in one piece (DevState, K): one copy - a copy to pageable memory is a round trip of
-    // its own, some 15 us - and the host takes apart what arrived
-    hipError_t e = hipSuccess;
-    if (h_out || K_host) {
-        alignas(DevState) char buf[kStateBytes + sizeof(float) * kMaxN * kMaxN];
+    if (h_out || K_host) { // h and K lie in one piece (DevState, K)
         const size_t kbytes = K_host ? (size_t)c->last_n * c->last_n * sizeof(float) : 0;
-        e = hipMemcpyAsync(buf, c->state, kStateBytes + kbytes, hipMemcpyDeviceToHost, s);
-        if (e == hipSuccess) e = hipStreamSynchronize(s);
-        if (e != hipSuccess) return fail(c, e);
-        if (h_out) *h_out = reinterpret_cast<const DevState *>(buf)->h;
-        if (K_host) std::memcpy(K_host, buf + kStateBytes, kbytes);
+        rc = read_back(c, kStateBytes + kbytes, s);
+        if (rc) return rc;
+        if (h_out) *h_out = reinterpret_cast<const DevState *>(c->mirror->data)->h;
+        if (K_host) std::memcpy(K_host, c->mirror->data + kStateBytes, kbytes);
         return SVGD_OK;
     }
-    e = hipStreamSynchronize(s);
+    hipError_t e = hipStreamSynchronize(s);
     if (e != hipSuccess) return fail(c, e);
     return SVGD_OK;
 }
@@ -1050,6 +1075,7 @@ int svgd_destroy(svgd_handle_t c)
         if ((t = hipFree(c->partials)) != hipSuccess) e = t;
         if ((t = hipFree(c->sums)) != hipSuccess) e = t;
         if ((t = hipFree(c->state)) != hipSuccess) e = t;
+        if ((t = hipHostFree(c->mirror)) != hipSuccess) e = t;
         for (hipEvent_t ev : c->ev_pool) (void)hipEventDestroy(ev);
     }
     delete c;

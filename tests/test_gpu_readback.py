@@ -1,0 +1,59 @@
+"""svgd_get_last and svgd_bandwidth read h and K through page-locked memory: what arrives belongs to the last call,
+also behind more work than the host watches for, and nothing is read while a stream is captured."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n,D", [(1, 7), (4, 1024), (12, 5001), (16, 5001), (64, 5001)])
+def test_every_call_reads_its_own(n, D):
+    from paper_2306_06528_amd import svgd
+    g = torch.Generator(device="cuda").manual_seed(n)
+    with svgd.Svgd(n, D) as eng, svgd.Svgd(n, D) as other:
+        for k in range(20):
+            X = (k + 1) * torch.randn(n, D, device="cuda", generator=g)
+            h = eng.bandwidth(X)
+            h2, K = eng.get_last(n)
+            other.bandwidth(X, want_h=False)
+            h3, K3 = other.get_last(n)
+            assert h == h2 == h3 and np.array_equal(K, K3)
+            assert np.all(np.diag(K) == 1.0)
+
+
+def test_behind_more_work_than_the_host_watches_for():
+    from paper_2306_06528_amd import svgd
+    n, D = 64, 1_000_003
+    g = torch.Generator(device="cuda").manual_seed(1)
+    X, G = (torch.randn(n, D, device="cuda", generator=g) for _ in range(2))
+    want = None
+    with svgd.Svgd(n, D) as eng:
+        for wait in (True, False):
+            Y = X.clone()
+            for _ in range(100):  # some 20 ms
+                eng.step(Y, G, 1e-3)
+                if wait:
+                    torch.cuda.synchronize()
+            h, K = eng.get_last(n)
+            if want is None:
+                want = h, K
+            assert h == want[0] and np.array_equal(K, want[1])
+
+
+def test_not_under_capture():
+    from paper_2306_06528_amd import svgd
+    n, D = 8, 5001
+    X, G = torch.randn(n, D, device="cuda"), torch.randn(n, D, device="cuda")
+    with svgd.Svgd(n, D) as eng:
+        eng.step(X, G, 1e-3)
+        h, K = eng.get_last(n)
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            eng.step(X, G, 1e-3)
+            with pytest.raises(svgd.SvgdError):
+                eng.get_last(n)
+        graph.replay()
+        torch.cuda.synchronize()
+        h2, _ = eng.get_last(n)
+        assert np.isfinite(h2)
