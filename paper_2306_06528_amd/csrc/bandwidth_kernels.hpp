@@ -22,15 +22,16 @@ __device__ inline int pair_index(int i, int j, int n) { return i * n - (i * (i +
 template <int MAXN, int THREADS>
 struct BwShared {
     static constexpr int kPairs = MAXN * (MAXN - 1) / 2;
-    static constexpr int kPr = (kPairs > 2 * kWave) ? kPairs : 2 * kWave; // (wave_select reads whole registers)
+    static constexpr int kPr = (kPairs > 2 * kWave) ? kPairs : 2 * kWave; // (count_ranks reads that many)
     double S[MAXN * (MAXN + 1) / 2]; // reduced pair sums, later K per pair
-    double pr[kPr];                  // d2 per unordered pair i < j
+    __attribute__((aligned(16))) double pr[kPr]; // d2 per unordered pair i < j
     double list[kSelDirect];         // the final short list
     double sel[2];
     unsigned long long mm[4];        // min / max bit patterns, two alternating slots
     __attribute__((aligned(16))) unsigned hist[kBuckets];
     unsigned counters[kSelDirect];   // partial ranks of the list elements
     unsigned misc[4];                // 0: length of the list
+    __attribute__((aligned(16))) unsigned short counts[THREADS / kWave][2 * kWave]; // count_ranks
 };
 
 // A double moved across lanes by a DPP control word (both halves).
@@ -284,64 +285,53 @@ __device__ inline void select_two_ranks(Shared &sh, const double (&v)[VPT], int 
     }
 }
 
-// The same by one wave, for at most 64 V values, lane l holding the values l + 64 u: no LDS and no barrier, so
-// every wave of a workgroup does it for itself.  A pivot among the candidates, two ballots per register
-// to count what lies below it and what does not lie above it, and the candidates are what is left on the wanted
-// side; the pivot's place among the candidates changes from round to round, so that an order in the data (particles
-// on a line) does not make it the smallest each time.  Values: not NaN.  r_hi = r_lo or r_lo + 1.
-template <int V>
-__device__ inline void wave_select(const double (&v)[V], int count, int r_lo, int r_hi, double &lo, double &hi)
+// The same for at most kCounted values: every wave counts, for all of them (two per lane), the smaller ones in its
+// share of the list; the shares meet in LDS, and behind one barrier every wave has all counts and picks the values
+// by itself - one of rank r is one whose count is r, or with ties the largest count below r.  The
+// buckets above take six barriers for it (120 values: 3.2 thousand cycles of a prologue of 14; us per step,
+// padded, carried sums, n = 13, D = 1,003 8.7 -> 7.4, n = 16 8.4 -> 7.4, the list's loads in one trip included).  Choosing
+// pivots and counting them by ballots, without LDS, took 4.4 thousand.  sh.pr holds kCounted values, +inf behind the last.
+constexpr int kCounted = 2 * kWave;
+template <int THREADS, bool LO, class Shared>
+__device__ inline void count_ranks(Shared &sh, int Pp, int r_lo, int r_hi, double &lo, double &hi)
 {
-    unsigned long long m[V]; // the candidates
+    constexpr int WAVES = THREADS / kWave, SHARE = kCounted / WAVES;
+    static_assert(SHARE % 2 == 0, "two values per read");
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    double v[2];
+    int cnt[2] = {0, 0};
 #pragma unroll
-    for (int u = 0; u < V; ++u) {
-        const int left = count - kWave * u;
-        m[u] = left >= kWave ? ~0ull : (left > 0 ? (1ull << left) - 1ull : 0ull);
-    }
-    int r = r_lo; // among the candidates
-    unsigned rot = 29;
-    for (;;) {
-        double from = v[V - 1];
-        unsigned long long mu = m[V - 1];
+    for (int u = 0; u < 2; ++u) v[u] = sh.pr[lane + kWave * u];
+    if (wave * SHARE < Pp) {
 #pragma unroll
-        for (int u = V - 2; u >= 0; --u) {
-            if (m[u]) {
-                from = v[u];
-                mu = m[u];
+        for (int k = 0; k < SHARE; k += 2) {
+            const double2 w = *reinterpret_cast<const double2 *>(&sh.pr[wave * SHARE + k]);
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                cnt[u] += w.x < v[u] ? 1 : 0;
+                cnt[u] += w.y < v[u] ? 1 : 0;
             }
         }
-        const unsigned long long turned = (mu >> rot) | (mu << (64 - rot)); // (rot is odd: 1 .. 63)
-        const int lane = (__ffsll(turned) - 1 + (int)rot) & 63;
-        const double p = readlane_f64(from, __builtin_amdgcn_readfirstlane(lane));
-        unsigned long long lt[V], le[V];
-        int c_lt = 0, c_le = 0;
-#pragma unroll
-        for (int u = 0; u < V; ++u) {
-            lt[u] = __ballot(v[u] < p) & m[u];
-            le[u] = __ballot(v[u] <= p) & m[u];
-            c_lt += __popcll(lt[u]);
-            c_le += __popcll(le[u]);
-        }
-        if (r < c_lt) {
-#pragma unroll
-            for (int u = 0; u < V; ++u) m[u] = lt[u];
-        } else if (r >= c_le) {
-            r -= c_le;
-#pragma unroll
-            for (int u = 0; u < V; ++u) m[u] &= ~le[u];
-        } else {
-            lo = hi = p;
-            if (r + (r_hi - r_lo) >= c_le) { // the next one is the smallest of all that lie above
-                double mn = __builtin_huge_val(), mx = 0.0;
-#pragma unroll
-                for (int u = 0; u < V; ++u) mn = fmin(mn, (v[u] > p && (int)(threadIdx.x & 63) + kWave * u < count) ? v[u] : __builtin_huge_val());
-                wave_minmax(mn, mx);
-                hi = mn;
-            }
-            return;
-        }
-        rot = (rot + 22) & 63;
     }
+#pragma unroll
+    for (int u = 0; u < 2; ++u) sh.counts[wave][lane + kWave * u] = (unsigned short)cnt[u];
+    block_sync<LO>();
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        cnt[u] = 0;
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) cnt[u] += sh.counts[w][lane + kWave * u];
+        if (lane + kWave * u >= Pp) cnt[u] = kCounted;
+    }
+    auto value_at = [&](int r) __attribute__((always_inline)) {
+        for (;; --r) { // (count 0 exists: the smallest value)
+            const unsigned long long m0 = __ballot(cnt[0] == r), m1 = __ballot(cnt[1] == r);
+            if (m0) return readlane_f64(v[0], __ffsll(m0) - 1);
+            if (m1) return readlane_f64(v[1], __ffsll(m1) - 1);
+        }
+    };
+    lo = value_at(r_lo);
+    hi = r_hi == r_lo ? lo : value_at(r_hi);
 }
 
 // What pass 2 is asked for.
@@ -379,11 +369,7 @@ __device__ inline double kernel_matrix(BwShared<MAXN, THREADS> &sh, const BwArgs
     const int tid = threadIdx.x, n = ba.n;
     const int Pp = n * (n - 1) / 2;
     const bool select = ba.h_fixed <= 0.0 && Pp > 0;
-    // Above kWaveSelect pairs (17 particles and more) the selection spreads them over buckets; up to there every
-    // wave selects by itself.  (us per step by buckets and by waves: n = 13, D = 8,577, padded, carried sums 8.9
-    // and 7.6, n = 16 8.7 and 8.2, with four values per lane n = 18 10.1 and 10.7, n = 22 11.2 and 12.3.)
-    constexpr int kWaveSelect = 2 * kWave;
-    const bool buckets = kPairs > kWaveSelect && select && Pp > kWaveSelect;
+    const bool buckets = kPairs > kCounted && select && Pp > kCounted; // 17 particles and more
     const double inf = __builtin_huge_val();
     int pi[VPT], pj[VPT];
     fill([&]() __attribute__((always_inline)) {
@@ -450,8 +436,7 @@ __device__ inline double kernel_matrix(BwShared<MAXN, THREADS> &sh, const BwArgs
             lo = sh.sel[0];
             hi = sh.sel[1];
         } else {
-            const double v[2] = {sh.pr[tid & 63], sh.pr[(tid & 63) + kWave]};
-            wave_select<2>(v, Pp, r_lo, r_hi, lo, hi);
+            count_ranks<THREADS, LO>(sh, Pp, r_lo, r_hi, lo, hi);
         }
     }
     const double med = select ? 0.5 * ((t_lo >= n ? lo : 0.0) + hi) : 0.0;
@@ -549,7 +534,7 @@ __device__ inline void gather_sums(double *S, double *red, const float *partials
     const f32x4 *base = reinterpret_cast<const f32x4 *>(partials) + pp;
     double s[4] = {0.0, 0.0, 0.0, 0.0};
     int k0 = 0;
-    auto batch = [&](auto loads, auto then) __attribute__((always_inline)) { // clamped, not guarded: the number of loads is known
+    auto batch = [&](auto loads, auto whole, auto then) __attribute__((always_inline)) { // clamped, not guarded: the number of loads is known
         constexpr int U = decltype(loads)::value;
         f32x4 v[U];
 #pragma unroll
@@ -560,22 +545,22 @@ __device__ inline void gather_sums(double *S, double *red, const float *partials
         then();
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const bool in = k0 + kk + u * KL < nparts;
+            const bool in = decltype(whole)::value || k0 + kk + u * KL < nparts; // (a choice between floats: half the price of one between doubles)
 #pragma unroll
-            for (int c = 0; c < 4; ++c) s[c] += in ? (double)v[u][c] : 0.0;
+            for (int c = 0; c < 4; ++c) s[c] += (double)(in ? v[u][c] : 0.f);
         }
     };
     auto both = [&]() __attribute__((always_inline)) {
         meanwhile();
         last();
     };
-    for (; nparts - k0 > MAXU * KL; k0 += MAXU * KL) batch(std::integral_constant<int, MAXU>{}, NoCall{});
+    for (; nparts - k0 > MAXU * KL; k0 += MAXU * KL) batch(std::integral_constant<int, MAXU>{}, std::true_type{}, NoCall{});
     if (MAXU > kSumLoads && nparts - k0 > kSumLoads * KL) {
-        batch(std::integral_constant<int, MAXU>{}, both);
+        batch(std::integral_constant<int, MAXU>{}, std::false_type{}, both);
     } else if (nparts - k0 > kSumLoads / 4 * KL) {
-        batch(std::integral_constant<int, kSumLoads>{}, both);
+        batch(std::integral_constant<int, kSumLoads>{}, std::false_type{}, both);
     } else {
-        batch(std::integral_constant<int, kSumLoads / 4>{}, both);
+        batch(std::integral_constant<int, kSumLoads / 4>{}, std::false_type{}, both);
     }
     if (kk < KL) {
         double2 *dst = reinterpret_cast<double2 *>(red + (kk * P4 + pp) * 4);
@@ -783,7 +768,7 @@ __device__ inline void gather_wave_sums(GatherShared<N> &sh, const float *partia
         for (int u = 0; u < U; ++u) {
             const bool in = k0 + kk + u * STEP < nparts;
 #pragma unroll
-            for (int c = 0; c < 4; ++c) s[c] += in ? (double)v[u][c] : 0.0;
+            for (int c = 0; c < 4; ++c) s[c] += (double)(in ? v[u][c] : 0.f);
         }
     };
     for (; nparts - k0 > kSumLoads * STEP; k0 += kSumLoads * STEP) batch(std::integral_constant<int, kSumLoads>{}, [] {});

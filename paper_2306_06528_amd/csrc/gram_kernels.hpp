@@ -163,6 +163,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kGramPerCu,
 // 24.1 and 22.0.)
 constexpr int kGramWaves = 8;
 constexpr int kGramWavesSmall = 4;
+// With one slab per wave the shorter code of the fp32 multiply counts, up to two blocks of rows; three and four are six
+// and ten pairs of blocks, 3 and 5 thousand cycles in fp32 (step at D = 1,003, n = 40 23.5 -> 21.8 us, n = 64
+// 29.9 -> 27.6; D = 20,001 24.4 -> 24.3 and 30.8 -> 30.0).
+constexpr int kGramF32Blocks = 2;
 
 // (a wave's indices are `stride` = W * gridDim.x apart; its quotient and remainder by the lengths
 // of a range's cold and hot parts come from the host, so that stepping from one index to the next
@@ -215,7 +219,7 @@ __global__ __launch_bounds__(64 * W) void gram_mfma_kernel(const float *__restri
     const SplitConst sc = split_const();
 
     constexpr bool ORDERED = ORDER != 0, STREAM = ORDER == 2;
-    constexpr bool F32 = W == kGramWavesSmall; // one slab per wave: the shorter code counts, not the matrix pipe
+    constexpr bool F32 = W == kGramWavesSmall && NB <= kGramF32Blocks;
     const int64_t nfull = D >> 6;
     const uint32_t uper = go.per, uhot = go.hot, ucold = uper - uhot, unfull = (uint32_t)nfull;
     const uint32_t I1 = ORDERED ? go.nranges * ucold : 0u, I2 = ORDERED ? go.nranges * uhot : unfull;

@@ -513,6 +513,7 @@ int run_update(svgd_ctx *c, float *X, const float *G, float *PHI, int n, int64_t
         // can be read with streaming loads
         const bool aligned = rt ? rt->aligned != 0 : rows_aligned(X, ld) && rows_aligned(G, ld) && (!EMIT || rows_aligned(PHI, ld));
         const bool direct = !rt && store_directly(n, D, EMIT, CARRY);
+        ua.per = tiles_per_range(D / 64, workers, ua.adjacent && (aligned || direct)); // (staged stores: a range per wave)
         const UpdateCall call{X, G, PHI, c->coef, c->state, n, D, ld, eps, gram_out, rt, ua, grid, s,
                               aligned ? kStoreLines : (direct ? kStoreDirect : kStoreStaged), fused};
         if (n <= kFusedMaxN) launch_update_low<EMIT, CARRY>(call);

@@ -38,6 +38,7 @@ struct UpdateArgs {
     // ALIGNED matrix-core kernels: the four waves of a workgroup take adjacent tiles of one range
     // instead of a range each (see tile_range).
     int adjacent;
+    int64_t per; // matrix-core kernels: tiles_per_range for the mode they take
 };
 
 // ---------------------------------------------------------------------------------------------
@@ -447,7 +448,7 @@ void update_mfma_kernel(float *__restrict__ X, const float *__restrict__ G, floa
     int64_t t0, t1;
     const bool has_tail = (nfull << 6) < D; // the last workgroup does the columns after the last full tile
     const int nwork = (int)gridDim.x - (has_tail ? 1 : 0);
-    tile_range(nfull, nwork, blockIdx.x, wave, TS == 4, t0, t1);
+    tile_range(nfull, ua.per, blockIdx.x, wave, TS == 4, t0, t1);
     const int64_t c_begin = t0 << 6;
     // visiting order: tiles t_first + k * t_step, k < ntiles.  ALIGNED kernels take the direction
     // at run time; re-aligned stores hand a row's leftover from tile to tile, so their mirror
