@@ -11,8 +11,8 @@
 namespace svgd {
 
 constexpr int kBwThreads = 1024;
-// A set of at most kSelDirect values is ranked directly, a larger one spread over kBuckets buckets by
-// value first.  With 256 threads ranking 120 values (n = 16) took 4.9 us, the buckets take 1.4.
+// Selection among more than kCounted values: they are spread over kBuckets buckets by value, and a bucket of at
+// most kSelDirect values is ranked directly.
 constexpr int kSelDirect = 64;
 constexpr int kBuckets = 256;
 
@@ -141,9 +141,7 @@ __device__ inline void block_sync()
 // kSelDirect values, +inf in the entries from len to kSelDirect; the elements of the wanted ranks
 // are stored to sel.  E >= len threads take an element each and THREADS / E of them share one, each
 // comparing it with a slice of the list; the partial ranks meet in `counters`, which must be zero
-// on entry.  E and with it the slice follow len (28 pairs at n = 8 are four comparisons per
-// thread): with slices sized for 128 values the ranking was half of the fused step's prologue
-// (n = 8, D = 100,003: 3.3 us of 6.5, now 0.5).  A barrier lies between the writes of the list and this call.
+// on entry.  E and with it the slice follow len.  A barrier lies between the writes of the list and this call.
 template <int THREADS, bool LO>
 __device__ inline void rank_directly(const double *list, int len, int below, int r_lo, int r_hi, double *sel,
                                      unsigned *counters)
@@ -181,10 +179,10 @@ __device__ inline void rank_directly(const double *list, int len, int below, int
 // into the first and the last bucket and infinities into the last, so the set shrinks at every
 // level until all of it is equal; 2016 values (n = 64) take one level and a short list.  Ranks that
 // fall into two different buckets are the maximum of the one and the minimum of the other.
-// Contract: called by all THREADS threads with kSelDirect < Pp <= VPT * THREADS and values that are
+// Contract: called by all THREADS threads with kCounted < Pp <= VPT * THREADS and values that are
 // not negative and not NaN, after a barrier behind which
 //   - sh.mm[0] / mm[1] hold the bit patterns of a / b, mm[2] = ~0, mm[3] = 0,
-//   - sh.hist, sh.counters and sh.misc are zero, sh.list is +inf
+//   - sh.hist, sh.counters and sh.misc are zero, sh.list is +inf (kSelDirect entries each)
 // (pass 2 prepares all of this on its way).
 template <int THREADS, int VPT, bool LO, class Shared>
 __device__ inline void select_two_ranks(Shared &sh, const double (&v)[VPT], int Pp, int r_lo, int r_hi)
@@ -517,8 +515,9 @@ __device__ inline void copy_sums(double *S, const double *sums, int n, Meanwhile
 // Sums a list of partials in fp64 into S [n (n + 1) / 2].  Thread (kk, pp) = (tid / P4, tid % P4), kk <
 // KL, sums four consecutive entries of the partials kk, kk + KL, ..., up to MAXU 16-byte loads in
 // flight (as the registers allow); the KL sums of an entry meet in `red` [KL * P4 * 4 <= 4 * THREADS].  meanwhile() and then last() are called
-// when the last loads of the list have been sent off (see gather_wave_sums).  With sixteen loads in flight and the
-// next kernel's first loads sent off after the sums a list of 256 at n = 20 took 7.3 us (four rounds).
+// when the last loads of the list have been sent off (see gather_wave_sums).  With sixteen loads in flight, selects
+// for every value and the caller's first loads sent off after the sums, a list of 256 at n = 20 took 7.3 us (four
+// rounds; phi at D = 300,007 32.1 us, now 30.4).
 constexpr int kSumLoads = 16;
 template <int THREADS, bool LO, int MAXU, class Meanwhile, class Last>
 __device__ inline void gather_sums(double *S, double *red, const float *partials, int nparts, int n, Meanwhile meanwhile, Last last)

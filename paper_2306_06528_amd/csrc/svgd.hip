@@ -272,8 +272,8 @@ int update_workers(const svgd_ctx *c, int n, int64_t D, int64_t ld, int cap)
 // less than the launches it saves: 256 threads hold at most 496 pairs comfortably, and every
 // workgroup reads the whole list, in batches of sixteen 16-byte loads per thread, one after the
 // other (gather_sums).  Up to four batches it wins, from five on the list is better summed by a
-// launch of many workgroups: us per step on dense rows, in one launch and apart, n = 16, D =
-// 300,007 (3 batches) 25.3 and 30.1; n = 24, D = 40,003 (4) 21.5 and 22.0, D = 50,001 (5) 23.4 and 22.7;
+// launch of many workgroups: us per step on dense rows (before the loads of a list went out in known numbers; both
+// sides have gained since), in one launch and apart, n = 16, D = 300,007 (3 batches) 25.3 and 30.1; n = 24, D = 40,003 (4) 21.5 and 22.0, D = 50,001 (5) 23.4 and 22.7;
 // n = 32, D = 12,289 (4) 21.1 and 21.8, D = 20,001 (5) 24.0 and 22.1, D = 65,000 (16) 40.7 and 24.1.
 // On the vector-ALU path every list is that short (run_gram sees to it), and one launch wins up to the
 // largest sizes (n = 8, D = 11,173,962: 281 -> 270 us; n = 10, D = 300,001: 31 -> 24).
