@@ -107,8 +107,10 @@ int svgd_forget_carry(svgd_handle_t h);
 /*
  * Compute d2, h, K and the row sums of K for X (device, n x D) and keep them in the handle
  * (App. B.2: the radius^2 / exp step of the per-pair kernel, done once for all pairs).
- * If h_out_host is non-NULL the stream is synchronised and *h_out_host (HOST memory) receives h;
- * with NULL nothing is copied and the call does not synchronise.
+ * If h_out_host is non-NULL the call waits for the work enqueued on `stream` so far, its own included, and
+ * *h_out_host (HOST memory) receives h; while the stream is being captured it is then refused with a
+ * DEVICE error before anything is launched or changed.  With NULL nothing is copied and the call does
+ * not wait.
  */
 int svgd_bandwidth(svgd_handle_t h, const float *X, int n, int64_t D, double *h_out_host,
                    void *stream);

@@ -138,13 +138,19 @@ bool is_capturing(hipStream_t s)
     return st == hipStreamCaptureStatusActive;
 }
 
+// For calls that read back: nothing can be read while nothing runs.  To be asked before anything is launched or
+// changed, or the graph would keep what the refused call has left in it.
+int refuse_capture(svgd_ctx *c, hipStream_t s)
+{
+    return is_capturing(s) ? fail(c, hipErrorStreamCaptureUnsupported) : SVGD_OK;
+}
+
 // The first `bytes` bytes of the handle's state (DevState, then K) as they are when the work enqueued on the stream
 // is done, in c->mirror->data.  A kernel writes them to page-locked memory and the host watches for its ticket;
 // if that does not come within a few milliseconds the stream is waited for as usual, which also
-// reports what went wrong.
+// reports what went wrong.  Not for a stream that is being captured: the caller has looked (refuse_capture).
 int read_back(svgd_ctx *c, size_t bytes, hipStream_t s)
 {
-    if (is_capturing(s)) return fail(c, hipErrorStreamCaptureUnsupported); // nothing can be read while nothing runs
     const unsigned ticket = ++c->ticket;
     mirror_kernel<<<1, 256, 0, s>>>(reinterpret_cast<const unsigned *>(c->state), c->mirror, (int)((bytes + 3) / 4), ticket);
     hipError_t e = hipGetLastError();
@@ -745,6 +751,7 @@ int svgd_bandwidth_ld(svgd_handle_t c, const float *X, int n, int64_t D, int64_t
     if (rc) return rc;
     DeviceGuard guard(c->device);
     hipStream_t s = (hipStream_t)stream;
+    if (h_out_host && (rc = refuse_capture(c, s))) return rc;
     if (is_tiny(n, D)) {
         rc = run_tiny<kTinyBandwidth>(c, const_cast<float *>(X), nullptr, nullptr, n, D, ld, 0.f, s);
     } else {
@@ -917,6 +924,7 @@ int svgd_get_last(svgd_handle_t c, double *h_out, float *K_host, void *stream)
     DeviceGuard guard(c->device);
     hipStream_t s = (hipStream_t)stream;
     if (h_out || K_host) { // h and K lie in one piece (DevState, K)
+        if ((rc = refuse_capture(c, s))) return rc;
         const size_t kbytes = K_host ? (size_t)c->last_n * c->last_n * sizeof(float) : 0;
         rc = read_back(c, kStateBytes + kbytes, s);
         if (rc) return rc;

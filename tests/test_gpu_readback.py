@@ -57,3 +57,26 @@ def test_not_under_capture():
         torch.cuda.synchronize()
         h2, _ = eng.get_last(n)
         assert np.isfinite(h2)
+
+
+def test_bandwidth_with_h_not_under_capture():
+    """Refused before anything is launched or changed: nothing of it is in the graph, and the carried sums stay."""
+    from paper_2306_06528_amd import svgd
+    n, D = 8, 5001
+    X, G = torch.randn(n, D, device="cuda"), torch.randn(n, D, device="cuda")
+    y = torch.zeros(4, device="cuda")
+    with svgd.Svgd(n, D, flags=svgd.FLAG_CARRY_GRAM) as eng:
+        eng.step(X, G, 1e-3)
+        h, K = eng.get_last(n)
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            y.add_(1.0)
+            with pytest.raises(svgd.SvgdError):
+                eng.bandwidth(X)
+        graph.replay()
+        h2, K2 = eng.get_last(n)  # X has moved since: the step's, not those of X as it is now
+        assert h2 == h and np.array_equal(K2, K)
+        assert bool((y == 1.0).all())
+        eng.profile_begin()
+        eng.step(X, G, 1e-3)
+        assert eng.profile_end()["gram"][1] == 0
