@@ -90,7 +90,8 @@ enum svgd_status {
  * arguments of the top-level SVGD inference call; its `lengthscale` is svgd_set_bandwidth, its
  * `lr` the eps of svgd_step).  `flags`: 0 or an OR of the SVGD_FLAG_* values above.  Allocates the handle's
  * device scratch: 8192 * max_n * (max_n + 1) / 2 bytes of partial sums (17 MB at max_n = 64; each of
- * the 2048 vectors rounded up to 16 bytes) and about 0.1 MB of tables.  On success *out receives the handle.
+ * the 2048 vectors rounded up to 16 bytes) and about 0.1 MB of tables, and 17 KB of page-locked host memory (up to
+ * four such pieces stay with the library for later handles).  On success *out receives the handle.
  */
 int svgd_create(svgd_handle_t *out, int max_n, int64_t max_D, int device_id, uint32_t flags);
 

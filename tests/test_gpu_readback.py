@@ -1,5 +1,8 @@
 """svgd_get_last and svgd_bandwidth read h and K through page-locked memory: what arrives belongs to the last call,
 also behind more work than the host watches for, and nothing is read while a stream is captured."""
+import time
+from concurrent.futures import ThreadPoolExecutor
+
 import numpy as np
 import pytest
 import torch
@@ -80,3 +83,55 @@ def test_bandwidth_with_h_not_under_capture():
         eng.profile_begin()
         eng.step(X, G, 1e-3)
         assert eng.profile_end()["gram"][1] == 0
+
+
+def _h_of(svgd, X):
+    with svgd.Svgd(*X.shape) as eng:
+        h = eng.bandwidth(X)
+        h2, K = eng.get_last(X.shape[0])
+    assert h == h2
+    return h, K
+
+
+def test_handles_one_after_another_and_side_by_side():
+    """The page-locked buffer of a handle that is gone serves the next one: more handles than are kept, alive
+    together and not, from several threads with streams of their own, each read their own h and K."""
+    from paper_2306_06528_amd import svgd
+    n, D = 16, 2003
+    g = torch.Generator(device="cuda").manual_seed(5)
+    Xs = [(k + 1) * torch.randn(n, D, device="cuda", generator=g) for k in range(7)]
+    want = [_h_of(svgd, X) for X in Xs]
+    torch.cuda.synchronize()
+    for _ in range(3):
+        engs = [svgd.Svgd(n, D) for _ in Xs]
+        for eng, X in zip(engs, Xs):
+            eng.bandwidth(X, want_h=False)
+        for eng, (h, K) in reversed(list(zip(engs, want))):
+            got = eng.get_last(n)
+            assert got[0] == h and np.array_equal(got[1], K)
+        for eng in engs:
+            eng.close()
+
+    def work(k):
+        with torch.cuda.stream(torch.cuda.Stream()):
+            return all(_h_of(svgd, Xs[k])[0] == want[k][0] for _ in range(50))
+
+    with ThreadPoolExecutor(4) as pool:
+        assert all(pool.map(work, range(4)))
+
+
+def test_a_handle_is_cheap_to_make():
+    """No page-locked memory is allocated and freed for each handle (27 and 35 us; all else is some 5 us)."""
+    from paper_2306_06528_amd import svgd
+    X = torch.randn(16, 2003, device="cuda")
+    best = float("inf")
+    for _ in range(100):
+        t0 = time.perf_counter()
+        eng = svgd.Svgd(16, 2003)
+        t1 = time.perf_counter()
+        eng.bandwidth(X)
+        torch.cuda.synchronize()
+        t2 = time.perf_counter()
+        eng.close()
+        best = min(best, time.perf_counter() - t2 + t1 - t0)
+    assert best < 25e-6
