@@ -634,6 +634,7 @@ __device__ inline float wave_kernel_matrix(WaveShared<N> &sh, double h_fixed, do
             const int e = lane + kWave * u;
             if (e < P) sh.S[e] = sum(e);
         }
+        wave_sync();
     }
     double d2[VPL];
 #pragma unroll
@@ -652,6 +653,7 @@ __device__ inline float wave_kernel_matrix(WaveShared<N> &sh, double h_fixed, do
         d2[u] = d;
         if (p < kList) sh.pr[p] = d;
     }
+    wave_sync();
     // the two middle order statistics of all n * n entries, see kernel_matrix
     constexpr int t_lo = (N * N - 1) / 2, t_hi = (N * N) / 2;
     double med = 0.0;
@@ -699,9 +701,11 @@ __device__ inline float wave_kernel_matrix(WaveShared<N> &sh, double h_fixed, do
         st->two_over_h = (float)c2h;
         st->n = N;
     }
+    wave_sync();
 #pragma unroll
     for (int u = 0; u < VPL; ++u) // K per pair; 1 / h may be infinite
         if (lane + kWave * u < Pp) sh.pr[lane + kWave * u] = d2[u] > 0.0 ? exp(-d2[u] * inv_h) : 1.0;
+    wave_sync();
     // K, C, row sums: 8 or 16 lanes per row.  K_ij and K_ji are the same LDS entry, so K is exactly
     // symmetric; the diagonal is exactly 1.
     constexpr int L = N <= 8 ? 8 : 16;
@@ -719,6 +723,7 @@ __device__ inline float wave_kernel_matrix(WaveShared<N> &sh, double h_fixed, do
             if (j == 0) sh.C[i * WaveShared<N>::kRow + N] = (float)(c2h * r * inv_n);
         }
     }
+    wave_sync();
     return (float)c2h;
 }
 
@@ -793,7 +798,7 @@ __device__ inline void gather_wave_sums(GatherShared<N> &sh, const float *partia
             dst[0] = double2{s[0], s[1]};
             dst[1] = double2{s[2], s[3]};
         }
-        // (one wave's LDS operations execute in order)
+        wave_sync();
         for (int e = lane; e < 4 * P4; e += kWave) {
             double t = sh.scratch[wave][0][e];
 #pragma unroll

@@ -185,6 +185,14 @@ __device__ inline void tile_range(int64_t nfull, int64_t per, int64_t wg, int wa
 // (an integer offset is laundered, not the pointer, so the accesses stay global_load/store)
 __device__ inline void opaque(int64_t &v) { asm volatile("" : "+v"(v)); }
 
+// Between LDS writes and reads by which the lanes of one wave hand values to each other.  The wave's LDS operations
+// execute in program order, so this costs no instruction: it keeps the compiler to that order.
+__device__ inline void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // rows that all start on a 128-byte boundary
 __host__ inline bool rows_aligned(const void *base, int64_t ld)
 {
