@@ -80,14 +80,28 @@ void update_valu_kernel(float *__restrict__ X,
     // 15.1 at n = 7, D = 1,000,000; at n <= 5 no difference).
     constexpr bool PREFETCH = CARRY && N > 5;
     f32x4 x[N], z[N];
+    // All of X first, then all of G, in that order also in the machine code: in the mixed order that the compiler chose
+    // the loads of G, which come from memory, kept those of X, half of which a cache holds, waiting (carried sums,
+    // n = 8, padded rows, D = 1,000,003 18.5 -> 17.8 us per step, D = 11,173,962 164.2 -> 162.9; plain, n = 12,
+    // D = 1,000,003 41.4 -> 40.9).
     auto load_group = [&](int64_t g) __attribute__((always_inline)) {
         const RaggedGroup rg(g << 2, D);
 #pragma unroll
         for (int j = 0; j < N; ++j) {
             x[j] = rg.load<false>(X + (ROWS ? rt.x[ROWS ? j : 0] : (int64_t)j * ld));
+            asm volatile("" ::: "memory");
+        }
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
             z[j] = rg.load<true>(G + (ROWS ? rt.g[ROWS ? j : 0] : (int64_t)j * ld));
+            asm volatile("" ::: "memory");
         }
     };
+    // LATE_STORES: a group's results are stored together, behind the arithmetic on the last of them.  For an X beyond the
+    // memory-side cache that is the better way at 8 particles (D = 11,173,962, padded 162.9 -> 162.1 us per step, dense
+    // 171.6 -> 171.1; at D = 1,000,003 it loses half of what the order of the loads gained, 17.8 -> 18.2), not at 6 and 7
+    // (n = 7, padded, D = 1,000,003 14.8 -> 15.2, D = 11,173,962 140.2 -> 140.5).
+    constexpr bool LATE_STORES = CARRY && N == 8;
     // this thread's groups: grp0 + k * nthreads, k < cnt, visited upwards or (reverse) downwards
     const int64_t grp0 = (int)(blockIdx.x * 256 + threadIdx.x);
     const int cnt = split.count((int)grp0);
@@ -138,6 +152,9 @@ void update_valu_kernel(float *__restrict__ X,
         for (int j = 0; j < N; ++j) z[j] -= c2h * x[j];
         f32x4 y[N]; // the results; CARRY: then the centred new values
         float *__restrict__ OUT = EMIT ? PHI : X;
+        auto store = [&](int i, auto whole) __attribute__((always_inline)) {
+            store4(OUT + (ROWS ? rt.x[ROWS ? i : 0] : (int64_t)i * ld), col, D, decltype(whole)::value || full, y[i]);
+        };
         auto rows = [&](auto whole) __attribute__((always_inline)) {
 #pragma unroll
             for (int i = 0; i < N; ++i) {
@@ -148,7 +165,11 @@ void update_valu_kernel(float *__restrict__ X,
                 for (int j = 0; j < N; ++j) acc += C[j] * z[j];
                 if constexpr (EMIT) y[i] = acc;
                 else y[i] = x[i] + eps * acc;
-                store4(OUT + (ROWS ? rt.x[ROWS ? i : 0] : (int64_t)i * ld), col, D, decltype(whole)::value || full, y[i]);
+                if constexpr (!LATE_STORES) store(i, whole);
+            }
+            if constexpr (LATE_STORES) {
+#pragma unroll
+                for (int i = 0; i < N; ++i) store(i, whole);
             }
         };
         // one decision per wave: with a branch around every row's store no row's coefficients were read ahead
