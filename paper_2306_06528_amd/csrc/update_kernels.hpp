@@ -939,6 +939,12 @@ void update_mfma_kernel(float *__restrict__ X, const float *__restrict__ G, floa
 
     if constexpr (ALIGNED) { // no left edge to mask
         int64_t tile = t_first;
+        // Two waves per SIMD fetch their instructions faster or slower with the place of this loop (3.2 KB, 16 branches
+        // around loads and stores) against the 64-byte lines: us per step, n = 24, padded, carried sums, 52 bytes into a line,
+        // 0 and 40: D = 1,000,003 65.4, 66.1 and 67.1, D = 2,000,000 109.6, 110.3 and 112.5.  The compiler
+        // puts six instructions of its own between this and the loop, which makes it 52.  Other instances stay where they
+        // fall.
+        if constexpr (STREAM && CARRY && NB == 2 && !FULLROWS) asm volatile(".p2align 6\n\t.rept 7\n\ts_nop 0\n\t.endr");
         for (int64_t k = 0; k < ntiles; ++k, tile += t_step) process_tile(std::false_type{}, tile, k + 1 == ntiles);
     } else if (t0 < t1) {
         process_tile(std::true_type{}, t_first, ntiles == 1);
