@@ -528,7 +528,7 @@ __device__ inline void gather_sums(double *S, double *red, const float *partials
     // (quotients of small integers: half a unit off the next one, far more than the reciprocal's error)
     const float inv = __builtin_amdgcn_rcpf((float)P4);
     const int per_wg = (int)(((float)THREADS + 0.5f) * inv);
-    const int KL = per_wg < 32 ? per_wg : 32; // capped: the KL sums are added serially
+    const int KL = __builtin_amdgcn_readfirstlane(per_wg < 32 ? per_wg : 32); // capped: the KL sums are added serially
     const int kk = (int)(((float)tid + 0.5f) * inv), pp = tid - kk * P4;
     const f32x4 *base = reinterpret_cast<const f32x4 *>(partials) + pp;
     double s[4] = {0.0, 0.0, 0.0, 0.0};
@@ -542,11 +542,17 @@ __device__ inline void gather_sums(double *S, double *red, const float *partials
             v[u] = base[(int64_t)(k < nparts ? k : nparts - 1) * P4];
         }
         then();
+        // (four at a time, as long as there are any: summing sixteen where nine had been asked for took 0.2 to 1 us, at
+        // n = 2, D = 150,001 9.7 us per svgd_bandwidth, now 8.6)
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const bool in = decltype(whole)::value || k0 + kk + u * KL < nparts; // (a choice between floats: half the price of one between doubles)
+        for (int u0 = 0; u0 < U; u0 += 4) {
+            if (!decltype(whole)::value && u0 > 0 && k0 + u0 * KL >= nparts) break;
 #pragma unroll
-            for (int c = 0; c < 4; ++c) s[c] += (double)(in ? v[u][c] : 0.f);
+            for (int u = u0; u < u0 + 4; ++u) {
+                const bool in = decltype(whole)::value || k0 + kk + u * KL < nparts; // (a choice between floats: half the price of one between doubles)
+#pragma unroll
+                for (int c = 0; c < 4; ++c) s[c] += (double)(in ? v[u][c] : 0.f);
+            }
         }
     };
     auto both = [&]() __attribute__((always_inline)) {

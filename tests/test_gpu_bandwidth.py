@@ -76,6 +76,18 @@ def test_equal_particles_under_a_tiny_fixed_bandwidth(n, D):
             assert got_h == h and np.array_equal(K, want), h
 
 
+
+# The list of partial sums (one per 1,024 columns up to 12 particles, one per 256 above) is summed in shares of KL
+# partials, four at a time.  svgd_bandwidth: KL = 32 up to 12 particles, 30 at 16, 13 at 24; the update: 11 at
+# 13, 7 at 16, 4 at 20, 3 at 24.
+@pytest.mark.parametrize("n,nparts", [(n, k) for n, KL in ((2, 32), (8, 32), (13, 11), (16, 7), (16, 30), (20, 4), (24, 3), (24, 13))
+                                      for k in sorted({4 * KL, 4 * KL + 1, 8 * KL, 8 * KL + 1, 12 * KL + 1, 16 * KL, 16 * KL + 1})
+                                      if k <= (768 if n <= 12 else 256)])
+def test_lists_around_a_share_of_the_partials(n, nparts):
+    per = 1024 if n <= 12 else 256
+    _check(n, per * nparts - 3, "random")
+
+
 def _check(n, D, kind):
     from paper_2306_06528_amd import svgd
     Xh = _particles(kind, n, D)
