@@ -39,7 +39,7 @@ def test_median_with_infinite_distances(n, D):
     _check(n, D, "infinite")
 
 
-@pytest.mark.parametrize("n,D", [(13, 2001), (16, 200_001), (33, 200_001), (64, 100_001)])
+@pytest.mark.parametrize("n,D", [(13, 2001), (16, 200_001), (33, 200_001), (64, 100_001), (33, 1001), (48, 20_001), (64, 20_001)])
 def test_pair_sums_that_overflow(n, D):
     """One particle is far enough off in one column for its squares to overflow fp32 sums, at both ends of
     the range where products of its parts overflow to different signs.  The pair sums then have to be
