@@ -100,7 +100,7 @@ def check_carried_chain(svgd, X0, G, eps, padded, steps=2, chunk=1 << 20):
       X_new                                               == fl32(x + eps * phi_gpu) to 1 ulp, on
                                                           all n * D entries, on the device.
     padded: X, G and PHI are laid out with every row on a 128-byte boundary (the layout that selects
-    the update kernel's direct-store instance), else dense.  X0, G: dense (n, D) device tensors."""
+    the update kernel's streaming instance), else dense.  X0, G: dense (n, D) device tensors."""
     n, D = X0.shape
     if padded:
         X, Gv = padded_copy(svgd, X0), padded_copy(svgd, G)

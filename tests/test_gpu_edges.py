@@ -89,12 +89,15 @@ def test_where_pass_2_is_part_of_the_update(n, D, fused, flags):
             check_carried_chain(svgd, X, G, 0.05, padded=padded, steps=3)
 
 
-# (MiB of X up to which rows off the 128-byte boundaries are stored directly: 24, 40, 76 for phi; 184, 56, 144 for a
-# plain step; 92, 256 on carried sums)
-@pytest.mark.parametrize("n,mib", [(16, 184), (16, 92), (20, 24), (24, 56), (33, 40), (48, 56), (51, 76), (64, 76)])
+# MiB of X up to which rows off the 128-byte boundaries are stored directly, re-aligned above (n <= 16, 32, 48, 64): phi 24,
+# 24, 40, 76; a plain step 184, 56, 56, 144; carried sums 92, 92, 92, 256.  Every form of the kernel - padded
+# and full blocks of rows, one to four rows on top of them - stores both ways in all three here.
+@pytest.mark.parametrize("n,mib", [(13, 24), (14, 184), (15, 92), (16, 184), (16, 92), (18, 92), (20, 24), (24, 56), (26, 92), (32, 92),
+                                   (33, 40), (35, 92), (44, 92), (48, 56), (48, 92), (51, 76), (51, 256), (60, 144), (60, 256), (64, 76), (64, 256)])
 def test_direct_and_staged_stores(n, mib):
     """One column less and one more than the size at which the stores change, and odd row starts: what both leave
-    is the oracle's (through phi of the same sizes), nothing between the rows is touched."""
+    is the oracle's (through phi of the same sizes), nothing between the rows is touched.  Three carried steps: forwards,
+    backwards on the sums of that, forwards on the sums of the walk backwards."""
     from paper_2306_06528_amd import svgd
     D0 = (mib << 20) // (4 * n)
     for D in (D0 - 1, D0 + 1):
@@ -117,11 +120,12 @@ def test_direct_and_staged_stores(n, mib):
             X.copy_(old)
             eng.step(X, Gv, 0.05)
             assert ulp_diff_device(X, old, PHI, 0.05) <= 1.0
-            now = X.clone()
-            with svgd.Svgd(n, D) as plain:
-                plain.phi(X, Gv, PHI)
-            eng.step(X, Gv, 0.05)  # walks the other way
-            assert ulp_diff_device(X, now, PHI, 0.05) <= 1.0
+            for _ in range(2):
+                now = X.clone()
+                with svgd.Svgd(n, D) as plain:
+                    plain.phi(X, Gv, PHI)
+                eng.step(X, Gv, 0.05)
+                assert ulp_diff_device(X, now, PHI, 0.05) <= 1.0
         for b in (buf, pbuf):
             assert bool((b[:, 0] == 7.0).all()) and bool((b[:, D + 1:] == 7.0).all())
         del buf, G, X, Gv, PHI, pbuf, old, now, ref

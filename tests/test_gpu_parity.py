@@ -483,8 +483,8 @@ def test_more_than_2_to_31_elements(svgd, n, D, carry, padded):
                                  (8, 100_003), (4, 1024), (16, 8577), (12, 70_001), (1, 100), (2, 65),
                                  (8, 3_000_017), (16, 70_001), (48, 20_011), (49, 5003), (64, 300_007), (12, 600_001)])
 def test_carried_gram_matches_oracle_every_step(svgd, n, D, padded):
-    """Four steps in a row with carried pair sums, on dense rows and on rows padded to 128 bytes
-    (the layout that selects the direct-store instance of the matrix-core update kernel): h, K,
+    """Four steps in a row with carried pair sums, on dense rows (which the matrix-core update stores where
+    they lie at these sizes; re-aligned stores: test_gpu_edges.py) and on rows padded to 128 bytes: h, K,
     phi against the oracle and X_new == fl32(x + eps * phi_gpu) to one ulp, every step.  Successive
     carried updates walk X in alternating directions, so steps 1 and 3 are backward walks and
     step 2 takes its h and K from the sums a backward walk left; the larger D give every
@@ -501,7 +501,8 @@ def test_particle_counts_just_above_a_multiple_of_16(svgd, n, D, padded):
     as remainder rows of the kernel for that multiple: a plain step (h, K, phi on all columns,
     in-place update to one ulp) and four carried steps (both walking directions, the remainder
     rows' pair sums feeding the next step's h and K), at a D with a few tiles in all and one that
-    gives every wave several."""
+    gives every wave several.  (At these sizes rows off the 128-byte boundaries are stored where they lie;
+    re-aligned stores of such counts, in both directions: test_gpu_edges.py.)"""
     X, G = _random_problem(n, D, 7 * n + D, x_std=0.3)
     _plain_step_check(svgd, X, G, 0.05, padded=padded)
     check_carried_chain(svgd, X, G, 0.05, padded=padded, steps=4)
@@ -587,7 +588,7 @@ def test_carried_gram_is_dropped_on_another_stream(svgd):
 def test_full_size_carried_gram(svgd, cfg_index, padded):
     """Full-size configs in the launch configurations the benchmark times: pair sums carried from
     the previous update, rows padded to 128 bytes (the headline; at config 5 this is the instance
-    update_mfma_kernel<4, false, true, true, true>) and dense rows.  Three steps: the first after
+    update_mfma_kernel<4, false, true, true, kStoreLines>) and dense rows.  Three steps: the first after
     a Gram pass, the second on carried sums and walking X backwards, the third on the sums that
     backward walk left; each step: h and K against the oracle, phi of ALL columns against the
     oracle at 1e-4 of max|phi|, X_new == fl32(x + eps * phi_gpu) to one ulp on all n * D entries."""
@@ -630,7 +631,8 @@ def test_random_shapes(svgd, seed):
 @pytest.mark.parametrize("shift", [1, 3, 17])
 def test_buffers_with_odd_base_alignment(svgd, n, shift):
     """X, G and PHI that start `shift` floats into their allocations (each with a different
-    shift): the store windows of the update are aligned per row from the actual addresses."""
+    shift): no row starts on a 128-byte boundary, every one somewhere else.  (Stored where they lie at this
+    size; store windows aligned per row from such addresses: test_gpu_edges.py.)"""
     D = 5003
     g = torch.Generator(device="cuda")
     g.manual_seed(n + shift)

@@ -75,8 +75,8 @@ def test_equal_distances(n, D):
 @pytest.mark.parametrize("kind", ["line", "line_reversed", "two_places", "half_equal", "one_far", "random"])
 @pytest.mark.parametrize("n", [13, 14, 15, 16])
 def test_selection_by_a_wave(n, kind):
-    """13 to 16 particles, whose middle distances every wave finds by itself: orders in the data, ties on either
-    side of the wanted ranks, all sizes of what is left above them."""
+    """13 to 16 particles, whose distances the waves rank in shares, each picking the middle ones for itself: orders
+    in the data, ties on either side of the wanted ranks, all sizes of what is left above them."""
     from paper_2306_06528_amd import svgd
     D = 600
     base = _inputs(n, D, n)[0]
