@@ -323,10 +323,11 @@ int update_workers(const svgd_ctx *c, int n, int64_t D, int64_t ld, int cap)
 // Up to kFusedMaxN particles the update kernel does pass 2 itself, in every workgroup, if that costs
 // less than the launches it saves: 256 threads hold at most 496 pairs comfortably, and every
 // workgroup reads the whole list, in batches of sixteen 16-byte loads per thread, one after the
-// other (gather_sums).  Up to four batches it wins, from five on the list is better summed by a
-// launch of many workgroups: us per step on dense rows (before the loads of a list went out in known numbers; both
-// sides have gained since), in one launch and apart, n = 16, D = 300,007 (3 batches) 25.3 and 30.1; n = 24, D = 40,003 (4) 21.5 and 22.0, D = 50,001 (5) 23.4 and 22.7;
-// n = 32, D = 12,289 (4) 21.1 and 21.8, D = 20,001 (5) 24.0 and 22.1, D = 65,000 (16) 40.7 and 24.1.
+// other (gather_sums).  Up to four batches it wins clearly, at five still, from six on now the one and now the
+// other (the list is then summed by a launch of many workgroups): us per step on dense rows, in one launch and apart, n = 24,
+// D = 40,003 (4 batches) 17.1 and 19.2, D = 50,001 (5) 18.0 and 19.8; n = 28, D = 65,000 (8) 21.1 and 20.9; n = 32,
+// D = 12,289 (4) 16.6 and 18.4, D = 20,001 (5) 18.0 and 19.6, D = 30,001 (8) 20.1 and 19.8; carried sums, padded,
+// n = 24, D = 65,000 (6) 16.5 and 17.0, n = 31 19.3 and 17.9.
 // On the vector-ALU path every list is that short (run_gram sees to it), and one launch wins up to the
 // largest sizes (n = 8, D = 11,173,962: 281 -> 270 us; n = 10, D = 300,001: 31 -> 24).
 constexpr int kFusedMaxN = 32;
@@ -495,14 +496,16 @@ int fused_workers(const svgd_ctx *c, int n, int64_t D, int64_t ld, int workers, 
 // (kStoreDirect).  Staged, a tile is some three thousand cycles longer, and a wave's first tile and the end of
 // its range more than that; direct, a line that two tiles share is written twice, which costs little while the caches
 // hold what is in use, and most where phi is a third array.  The lines lie where the two cross (MiB of X; dense rows,
-// us per step staged and direct): plain n = 16 192 163.9 / 161.3, n = 24 58 62.7 / 61.4 and 96 94.5 / 96.2, n = 47
-// 56 71.4 / 71.0 and 94 98.8 / 106.8, n = 64 128 137.5 / 127.3 and 256 234.5 / 247.3; phi n = 20 24 34.2 / 32.2 and
-// 48 51.6 / 53.5, n = 48 38 55.2 / 54.1 and 58 73.3 / 76.8, n = 64 77 100.2 / 93.5; carried sums n = 16 64 40.9 / 39.9
-// and 128 68.7 / 70.7, n = 24 96 72.8 / 68.2 and 192 131.0 / 135.2, n = 64 256 201.3 / 186.5.  At small sizes:
-// n = 33, D = 20,001 25.6 / 22.2, n = 64, D = 8,577 33.1 / 28.4.
+// us per step staged and direct, other inputs from call to call): plain n = 13 70 68.6 / 67.5 and 172 152.6 / 154.0, n = 15
+// 70 65.9 / 64.7 and 116 103.5 / 104.7, n = 16 116 103.2 / 98.9 and 140 122.9 / 125.5, n = 24 52 60.0 / 59.0 and 72
+// 76.8 / 80.8, n = 47 52 69.5 / 69.1 and 72 85.8 / 91.3, n = 52 130 146.5 / 136.3, n = 60 150 161.4 / 153.7 and 180
+// 187.6 / 197.6; phi n = 14 26 28.2 / 27.7 and 32 32.9 / 35.7, n = 24 20 33.9 / 31.6 and 32 44.8 / 45.9, n = 40 38
+// 56.0 / 55.3 and 52 69.5 / 71.4, n = 64 77 100.2 / 93.5; carried sums n = 15 86 51.4 / 49.7 and 150 94.6 / 99.4, n = 28
+// 86 67.2 / 64.1 and 150 104.2 / 112.3, n = 36 86 74.3 / 72.7 and 150 108.2 / 118.0, n = 64 256 201.3 / 186.5.  At small
+// sizes: n = 33, D = 20,001 25.6 / 22.2, n = 64, D = 8,577 33.1 / 28.4.
 bool store_directly(int n, int64_t D, bool emit, bool carry)
 {
-    const int mib = emit ? (n <= 32 ? 24 : (n <= 48 ? 40 : 76)) : (carry ? (n <= 48 ? 92 : 256) : (n <= 16 ? 184 : (n <= 48 ? 56 : 144)));
+    const int mib = emit ? (n <= 32 ? 24 : (n <= 48 ? 40 : 76)) : (carry ? (n <= 48 ? 92 : 256) : (n < 16 ? 100 : (n == 16 ? 120 : (n <= 48 ? 56 : 144))));
     return (int64_t)n * D * (int64_t)sizeof(float) <= ((int64_t)mib << 20);
 }
 

@@ -90,9 +90,9 @@ def test_where_pass_2_is_part_of_the_update(n, D, fused, flags):
 
 
 # MiB of X up to which rows off the 128-byte boundaries are stored directly, re-aligned above (n <= 16, 32, 48, 64): phi 24,
-# 24, 40, 76; a plain step 184, 56, 56, 144; carried sums 92, 92, 92, 256.  Every form of the kernel - padded
+# 24, 40, 76; a plain step 100 (n = 16: 120), 56, 56, 144; carried sums 92, 92, 92, 256.  Every form of the kernel - padded
 # and full blocks of rows, one to four rows on top of them - stores both ways in all three here.
-@pytest.mark.parametrize("n,mib", [(13, 24), (14, 184), (15, 92), (16, 184), (16, 92), (18, 92), (20, 24), (24, 56), (26, 92), (32, 92),
+@pytest.mark.parametrize("n,mib", [(13, 24), (14, 100), (14, 184), (15, 92), (16, 120), (16, 184), (16, 92), (18, 92), (20, 24), (24, 56), (26, 92), (32, 92),
                                    (33, 40), (35, 92), (44, 92), (48, 56), (48, 92), (51, 76), (51, 256), (60, 144), (60, 256), (64, 76), (64, 256)])
 def test_direct_and_staged_stores(n, mib):
     """One column less and one more than the size at which the stores change, and odd row starts: what both leave
