@@ -370,7 +370,7 @@ int run_gram(svgd_ctx *c, const float *X, int n, int64_t D, int64_t ld, hipStrea
         const int64_t ngroups = (D + 3) / 4;
         // all resident at once; each ends with a reduction; the update sums the list (three per CU of
         // 256 are just what it takes at n = 12)
-        nparts = clampi((ngroups + 255) / 256, 1, mini(mini(c->num_cu * 3, cap_parts), mini(fused_max_parts(n), (int)(half_scratch(c) / pair_stride(n)))));
+        nparts = clampi((ngroups + 255) / 256, 1, mini(mini(c->num_cu * kGramPerCu, cap_parts), mini(fused_max_parts(n), (int)(half_scratch(c) / pair_stride(n)))));
         const int64_t x_bytes = (int64_t)n * D * (int64_t)sizeof(float);
         // An X that outgrows the memory-side cache is loaded with the streaming hint, above 8 particles up to
         // the three quarters of that cache which the update reads first (walked last, loaded plainly): n = 12,
@@ -554,8 +554,7 @@ int run_update(svgd_ctx *c, float *X, const float *G, float *PHI, int n, int64_t
     ua.adjacent = adjacent_tiles(n, ld);
     if (n <= kValuMaxN) {
         const int64_t ngroups = (D + 3) / 4;
-        const int per_cu = n <= (CARRY ? 8 : 10) ? 2 : 1; // kUpdatePerCu
-        const int grid = clampi((ngroups + 255) / 256, 1, mini(c->num_cu * per_cu, out_cap));
+        const int grid = clampi((ngroups + 255) / 256, 1, mini(c->num_cu * update_per_cu(n, CARRY), out_cap));
         if (CARRY) list = PairList{out_off, grid};
 #define CALL(N) launch_update_valu<N, EMIT, CARRY>(X, G, PHI, c->coef, c->state, D, ld, eps, gram_out, grid, s, rt, ua)
         SVGD_SWITCH_N(n, CALL)

@@ -49,11 +49,11 @@ struct UpdateArgs {
 // the end) is paid twice.  Two where that leaves each thread's rows enough registers for loads in flight: plain
 // step at D = 6,000,000, one against two per CU, n = 9 182 / 168 us, n = 12 235 / 240; at D = 1,000,000
 // 44 / 38 and 57 / 64.  The kernel claims the registers of that many waves, so that no CU takes more
-// workgroups than another.
-template <int N, bool CARRY> constexpr int kUpdatePerCu = N <= (CARRY ? 8 : 10) ? 2 : 1;
+// workgroups than another, and the host sizes the grid by it.
+__host__ __device__ constexpr int update_per_cu(int n, bool carry) { return n <= (carry ? 8 : 10) ? 2 : 1; }
 
 template <int N, bool EMIT, bool CARRY, bool ROWS = false>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kUpdatePerCu<N, CARRY>, kUpdatePerCu<N, CARRY>)))
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(update_per_cu(N, CARRY), update_per_cu(N, CARRY))))
 void update_valu_kernel(float *__restrict__ X,
                                                           const float *__restrict__ G,
                                                           float *__restrict__ PHI,
