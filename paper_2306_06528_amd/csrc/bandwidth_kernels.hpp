@@ -1,7 +1,8 @@
 // Pass 2: from the reduced pair sums to d2, the median-heuristic bandwidth h, the RBF kernel
-// matrix K, its row sums, and the coefficient tables of the update kernels.  One workgroup,
-// fp64 throughout (at most 2016 pairs: the cost is nil and none of the 1e-5 budget on h and K
-// is spent here).  Nothing returns to the host: the paper's routine (App. B.2) reads each kernel
+// matrix K, its row sums, and the coefficient tables of the update kernels.  By one workgroup as a kernel of its
+// own, by every workgroup or every wave for itself as the start of an update (two implementations: kernel_matrix,
+// and wave_kernel_matrix up to 12 particles); fp64 throughout (at most 2016 pairs: the cost is nil and none
+// of the 1e-5 budget on h and K is spent here).  Nothing returns to the host: the paper's routine (App. B.2) reads each kernel
 // value back to the host, one synchronisation per pair; here K stays on the device.
 #pragma once
 #include <type_traits>
@@ -835,7 +836,8 @@ static __global__ __launch_bounds__(kBwThreads) void bandwidth_kernel(SumSource 
 
 // What svgd_get_last reads, from the handle's state to its page-locked host memory, and behind it the number of the
 // request, which the host watches for.  A copy to pageable memory and a synchronisation took some ten us more:
-// bandwidth and get_last, n = 4, D = 1,003 27.4 -> 14.0 us, n = 48, D = 1,000,003 67.2 -> 58.8.
+// bandwidth and get_last, n = 4, D = 1,003 27.4 -> 14.0 us, n = 16, D = 8,577 34 -> 20, n = 48, D = 1,000,003 70 -> 62
+// (the same on a handle's first read-back).  Either way the host's core is busy until the result is there.
 struct Mirror {
     unsigned ticket;
     __attribute__((aligned(kStateBytes))) unsigned char data[kStateBytes + sizeof(float) * kMaxN * kMaxN];

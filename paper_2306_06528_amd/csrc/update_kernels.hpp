@@ -20,8 +20,9 @@
 namespace svgd {
 
 // Passes 2 and 3 in one launch: always on the vector ALU, FUSED on the matrix cores.  The kernel starts
-// with pass 2 (kernel_matrix: every workgroup derives h, C and rho for itself from a short list
-// of partials; workgroup 0 records h and K) and needs no tables in device memory.  A CARRY kernel
+// with pass 2 (every workgroup - kernel_matrix - or, on the vector ALU, every wave - wave_kernel_matrix - derives
+// h, C and rho for itself from a short list of partials; workgroup 0 records h and K) and needs no tables
+// in device memory.  A CARRY kernel
 // leaves the partials of the new X in the other half of the scratch, because workgroups still in their
 // prologue read the old list.
 struct UpdateArgs {
@@ -35,8 +36,8 @@ struct UpdateArgs {
     // on the part of X that the previous pass touched last, i.e. on what the memory-side cache
     // still holds.
     int reverse;
-    // ALIGNED matrix-core kernels: the four waves of a workgroup take adjacent tiles of one range
-    // instead of a range each (see tile_range).
+    // matrix-core kernels that store from the registers: the four waves of a workgroup take adjacent tiles of
+    // one range instead of a range each (see tile_range).
     int adjacent;
     int64_t per; // matrix-core kernels: tiles_per_range for the mode they take
 };
@@ -233,18 +234,19 @@ void update_valu_kernel(float *__restrict__ X,
 // Every store instruction then writes whole cache lines.  Only the two ends of a wave's range
 // see partial lines: the first tile masks what lies left of the range, and the carry is flushed
 // element-wise after the last tile.
-// ALIGNED: the caller guarantees that every row starts on a 128-byte boundary (ld a multiple of
-// 32 floats, base pointer aligned).  Then r_i = 0 for all rows, the windows are the tiles, and
-// the results are stored straight from the registers that computed them - no staging at all
-// unless the Gram operands need it.
-// Columns beyond the last full tile (D mod 64) are done by one extra workgroup (TailColumns).  Rows >= n (n not a multiple of 16) are neither loaded nor stored; their A entries are
+// The other two modes store the tile itself, straight from the registers that computed it
+// (FROM_REGS) - no staging at all unless the Gram operands need it: where every row starts on a
+// 128-byte boundary (kStoreLines: r_i = 0 for all rows, the windows are the tiles), and, wherever the rows
+// start, where the cut lines cost less than the staging (kStoreDirect; the host's choice, by size).
+// Columns beyond the last full tile (D mod 64) are done by one extra workgroup (TailColumns).  Rows >= n (n not
+// a multiple of 16) are neither loaded nor stored; their A entries are
 // zero (their contraction steps still run: skipping them behind wave-uniform branches cost more
 // than it saved, see below).  One to four rows beyond a multiple of 16 do not get a block of
 // their own at all (REM, below).
 // ---------------------------------------------------------------------------------------------
 enum StoreMode : int {
     kStoreStaged = 0, // re-aligned through LDS, as described above
-    kStoreLines = 1,  // every row starts on a 128-byte boundary: straight from the registers, G streamed (ALIGNED)
+    kStoreLines = 1,  // every row starts on a 128-byte boundary: straight from the registers, G streamed
     kStoreDirect = 2  // straight from the registers to wherever the row starts, all accesses plain: for an X
                       // that the caches hold, where lines written in two parts meet again before they leave
 };
@@ -443,11 +445,12 @@ void update_mfma_kernel(float *__restrict__ X, const float *__restrict__ G, floa
                         int64_t D, int64_t ld, float eps, float *__restrict__ gram_out,
                         typename RowArg<ROWS>::type rt, UpdateArgs ua)
 {
-    constexpr bool ALIGNED = STORE != kStoreStaged, STREAM = STORE == kStoreLines;
+    // FROM_REGS says nothing of where rows start; what needs them on 128-byte boundaries asks for STREAM
+    constexpr bool FROM_REGS = STORE != kStoreStaged, STREAM = STORE == kStoreLines;
     static_assert(!FUSED || NB <= 2, "pass 2 with 256 threads: n <= 32");
     static_assert(!(CARRY && EMIT), "the Gram is carried only when X is updated");
     static_assert(!(ROWS && (EMIT || CARRY)), "separate rows: plain in-place step");
-    static_assert(!REV || (CARRY && !ALIGNED), "the mirrored walk exists for re-aligned stores with carried sums");
+    static_assert(!REV || (CARRY && !FROM_REGS), "the mirrored walk exists for re-aligned stores with carried sums");
     static_assert(!REM || (FULLROWS && NB <= 3), "remainder rows come after full blocks");
     constexpr int NS = 4 * NB; // contraction steps = rows per lane
     constexpr int NBG = NB + (REM ? 1 : 0); // blocks as the pair sums see them
@@ -462,20 +465,20 @@ void update_mfma_kernel(float *__restrict__ X, const float *__restrict__ G, floa
     const int64_t nfull = D >> 6; // full 64-column tiles
     // The tiles of this wave: t0, t0 + TS, ... < t1.  Re-aligned stores hand a row's tail from one
     // tile to the next through the wave's carry, so there each wave walks a contiguous range of
-    // its own (TS = 1).  ALIGNED has nothing to hand over: on request (ua.adjacent, the host's
+    // its own (TS = 1).  FROM_REGS has nothing to hand over: on request (ua.adjacent, the host's
     // choice) the workgroup owns a contiguous range and its four waves take adjacent tiles
     // (TS = 4), which makes the workgroup's accesses 1 KiB contiguous per row.
-    const int64_t TS = (ALIGNED && ua.adjacent != 0) ? 4 : 1;
+    const int64_t TS = (FROM_REGS && ua.adjacent != 0) ? 4 : 1;
     int64_t t0, t1;
     const bool has_tail = (nfull << 6) < D; // the last workgroup does the columns after the last full tile
     const int nwork = (int)gridDim.x - (has_tail ? 1 : 0);
     tile_range(nfull, ua.per, blockIdx.x, wave, TS == 4, t0, t1);
     const int64_t c_begin = t0 << 6;
-    // visiting order: tiles t_first + k * t_step, k < ntiles.  ALIGNED kernels take the direction
+    // visiting order: tiles t_first + k * t_step, k < ntiles.  FROM_REGS kernels take the direction
     // at run time; re-aligned stores hand a row's leftover from tile to tile, so their mirror
     // image, which walks right to left, is an instance of its own (REV).
     const int64_t ntiles = (t1 - t0 + TS - 1) / TS;
-    const bool rev = REV || (ALIGNED && ua.reverse != 0);
+    const bool rev = REV || (FROM_REGS && ua.reverse != 0);
     const int64_t t_step = rev ? -TS : TS;
     const int64_t t_first = rev ? t0 + (ntiles - 1) * TS : t0;
 
@@ -533,7 +536,7 @@ void update_mfma_kernel(float *__restrict__ X, const float *__restrict__ G, floa
         rem_x = rem_g = (int64_t)(16 * NB - 3 * q) * ld;
     }
     // G is read exactly once per step.  When no cache line is shared between tiles or rows
-    // (ALIGNED) it is loaded with the streaming hint, which does not allocate on the way in:
+    // (STREAM) it is loaded with the streaming hint, which does not allocate on the way in:
     // measurably faster (a plain read-read-write stream over these buffers runs at 5.25 instead of
     // 5.08 TB/s), and it leaves the memory-side cache to X, which this kernel reads again in the
     // next step - at n = 32, D = 2,000,000 (X is 256 MB) that alone takes the update from 154 to
@@ -576,7 +579,7 @@ void update_mfma_kernel(float *__restrict__ X, const float *__restrict__ G, floa
     // the extra workgroup: ragged tail only
     // (staged stores with two blocks of rows have no register to spare for loads across pass 2: three to five were
     // spilled in the loop)
-    constexpr bool TAIL_EARLY = FUSED && (NB == 1 || ALIGNED);
+    constexpr bool TAIL_EARLY = FUSED && (NB == 1 || FROM_REGS);
     const bool in_tail = has_tail && (int)blockIdx.x == nwork;
     TailColumns<16 * NB + (REM ? 4 : 0), EMIT, CARRY, ROWS, FUSED> tail;
     auto first_loads = [&]() __attribute__((always_inline)) {
@@ -665,7 +668,7 @@ void update_mfma_kernel(float *__restrict__ X, const float *__restrict__ G, floa
     // do not suffice: with two waves per SIMD there are 256, and a spilled one read back in every tile
     // waits for all loads of the next tile, which are older (n = 24, D = 3,000,001, dense rows:
     // 203 us per step with three spilled, 188 now; n = 21 194 -> 172, n = 30, D = 1,000,003 88 -> 82).
-    constexpr bool RHO_LDS = CARRY && !ALIGNED && !FULLROWS && NB == 2;
+    constexpr bool RHO_LDS = CARRY && !FROM_REGS && !FULLROWS && NB == 2;
     __shared__ __attribute__((aligned(16))) float rho_lds[RHO_LDS ? 16 * NB : 4];
     float rho[RHO_LDS ? 1 : NS];
     if constexpr (RHO_LDS) {
@@ -862,13 +865,13 @@ void update_mfma_kernel(float *__restrict__ X, const float *__restrict__ G, floa
                     // the four store groups of the previous block are spread over the NB step groups
 #pragma unroll
                     for (int k = 0; k < 4; ++k)
-                        if (!ALIGNED && k * NB / 4 == sg) emit_group(bi - 1, k);
+                        if (!FROM_REGS && k * NB / 4 == sg) emit_group(bi - 1, k);
                     if constexpr (CARRY) {
                         if (sg < bi) gram_pair(sg, bi - 1); // pairs (0..bi-1, bi-1): one per step group
                     }
                 }
             }
-            if (!ALIGNED && bi > 0) carry_copy(bi - 1);
+            if (!FROM_REGS && bi > 0) carry_copy(bi - 1);
             // epilogue for rows 16bi + 4q + r, then stage the block in LDS
             f32x4 rho4;
             if constexpr (RHO_LDS) rho4 = *reinterpret_cast<const f32x4 *>(&rho_lds[16 * bi + 4 * q]);
@@ -881,10 +884,10 @@ void update_mfma_kernel(float *__restrict__ X, const float *__restrict__ G, floa
                     const float phi = fmaf(RHO_LDS ? rho4[r] : rho[RHO_LDS ? 0 : s], x[s][t], acc[t][r]);
                     o[t] = EMIT ? phi : fmaf(eps, phi, x[s][t]);
                 }
-                if constexpr (ALIGNED) {
+                if constexpr (FROM_REGS) {
                     if (FULLROWS || 16 * bi + 4 * q + r < n) store_direct(ROWS ? xro[ROWS ? s : 0] : (int64_t)(16 * bi + r) * ld, o);
                 }
-                if constexpr (!ALIGNED || CARRY) // staged for the re-aligned stores and/or as Gram operands
+                if constexpr (!FROM_REGS || CARRY) // staged for the re-aligned stores and/or as Gram operands
                     *reinterpret_cast<f32x4 *>(&cur[cur_index(4 * q + r, 4 * c16)]) = o;
             }
             if constexpr (!XBUF) { // x rows of this block are dead: fetch the next tile's
@@ -901,14 +904,14 @@ void update_mfma_kernel(float *__restrict__ X, const float *__restrict__ G, floa
         // E(NB-1) interleaved with G(NB-1)
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            if constexpr (!ALIGNED) emit_group(NB - 1, k);
+            if constexpr (!FROM_REGS) emit_group(NB - 1, k);
             if constexpr (CARRY) {
 #pragma unroll
                 for (int b0 = 0; b0 < NB; ++b0)
                     if (b0 * 4 / NB == k) gram_pair(b0, NB - 1);
             }
         }
-        if constexpr (!ALIGNED) carry_copy(NB - 1);
+        if constexpr (!FROM_REGS) carry_copy(NB - 1);
         if constexpr (REM) {
             // the remainder rows: epilogue, staging as rows 0..3 of a further block, one store group
             f32x4 o;
@@ -917,10 +920,10 @@ void update_mfma_kernel(float *__restrict__ X, const float *__restrict__ G, floa
                 const float phi = fmaf(rho_r, xr[t], phir[t]);
                 o[t] = EMIT ? phi : fmaf(eps, phi, xr[t]);
             }
-            if constexpr (ALIGNED) {
+            if constexpr (FROM_REGS) {
                 if (q < R) store_direct(rem_x, o);
             }
-            if constexpr (!ALIGNED || CARRY) *reinterpret_cast<f32x4 *>(&cur[cur_index(q, 4 * c16)]) = o;
+            if constexpr (!FROM_REGS || CARRY) *reinterpret_cast<f32x4 *>(&cur[cur_index(q, 4 * c16)]) = o;
             if constexpr (CARRY) {
 #pragma unroll
                 for (int st4 = 0; st4 < 4; ++st4) {
@@ -928,16 +931,16 @@ void update_mfma_kernel(float *__restrict__ X, const float *__restrict__ G, floa
                     ag[NB][st4] = (c16 < R) ? v : f32x4{0.f, 0.f, 0.f, 0.f};
                 }
             }
-            if constexpr (!ALIGNED) emit_group(NB, 0);
+            if constexpr (!FROM_REGS) emit_group(NB, 0);
             if constexpr (CARRY) {
 #pragma unroll
                 for (int b0 = 0; b0 <= NB; ++b0) gram_pair(b0, NB);
             }
-            if constexpr (!ALIGNED) carry_copy(NB);
+            if constexpr (!FROM_REGS) carry_copy(NB);
         }
     };
 
-    if constexpr (ALIGNED) { // no left edge to mask
+    if constexpr (FROM_REGS) { // no left edge to mask
         int64_t tile = t_first;
         // Two waves per SIMD fetch their instructions faster or slower with the place of this loop (3.2 KB, 16 branches
         // around loads and stores) against the 64-byte lines: us per step, n = 24, padded, carried sums, 52 bytes into a line,
@@ -953,7 +956,7 @@ void update_mfma_kernel(float *__restrict__ X, const float *__restrict__ G, floa
     }
 
     // flush: the last r_i columns of the range (REV: its first 32 - r_i) are still in the carry
-    if (!ALIGNED && t1 > t0) {
+    if (!FROM_REGS && t1 > t0) {
         const int64_t c_end = t1 << 6;
         for (int idx = lane; idx < 16 * NBG * 32; idx += 64) {
             const int row = idx >> 5, cc = idx & 31;
