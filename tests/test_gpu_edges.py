@@ -129,3 +129,20 @@ def test_direct_and_staged_stores(n, mib):
         for b in (buf, pbuf):
             assert bool((b[:, 0] == 7.0).all()) and bool((b[:, D + 1:] == 7.0).all())
         del buf, G, X, Gv, PHI, pbuf, old, now, ref
+
+
+@pytest.mark.parametrize("D", [65_600, 80_003, 98_300, 98_400, 131_100, 135_003, 147_500, 147_600])
+@pytest.mark.parametrize("n", [49, 52, 53, 64])
+def test_direct_stores_in_adjacent_tiles_or_ranges(n, D):
+    """More than 48 particles on dense rows at the sizes where the waves of a workgroup stop and start to share a range
+    of 64-column tiles (5, 6 and 9 tiles: not; a device of 256 CUs): phi, a plain step and carried steps in
+    both directions."""
+    from paper_2306_06528_amd import svgd
+    g = torch.Generator(device="cuda").manual_seed(n + D)
+    X, G = 0.3 * torch.randn(n, D, device="cuda", generator=g), torch.randn(n, D, device="cuda", generator=g)
+    check_carried_chain(svgd, X, G, 0.05, padded=False, steps=3)
+    old, PHI = X.clone(), torch.empty_like(X)
+    with svgd.Svgd(n, D) as eng:
+        eng.phi(X, G, PHI)
+        eng.step(X, G, 0.05)
+    assert ulp_diff_device(X, old, PHI, 0.05) <= 1.0
