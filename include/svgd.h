@@ -172,8 +172,8 @@ int svgd_step_rows(svgd_handle_t h, float *const *X_rows, const float *const *G_
  * routine reads back one by one) of the most recent svgd_bandwidth/svgd_step/svgd_phi call
  * to HOST memory: *h_out (nullable) receives h; K_host (nullable, row-major) receives K and must
  * have room for n*n floats with the n of that call - the library copies exactly that many and
- * cannot check the buffer.  Waits for the work enqueued on `stream` so far (DEVICE error while the stream
- * is being captured).  INVALID_ARG if no step has run yet.
+ * cannot check the buffer.  Waits for the work enqueued on `stream` so far, the calling thread polling
+ * for it (DEVICE error while the stream is being captured).  INVALID_ARG if no step has run yet.
  */
 int svgd_get_last(svgd_handle_t h, double *h_out, float *K_host, void *stream);
 

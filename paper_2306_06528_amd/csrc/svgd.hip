@@ -193,8 +193,8 @@ int refuse_capture(svgd_ctx *c, hipStream_t s)
 
 // The first `bytes` bytes of the handle's state (DevState, then K) as they are when the work enqueued on the stream
 // is done, in c->mirror->data.  A kernel writes them to page-locked memory and the host watches for its ticket;
-// if that does not come within a few milliseconds the stream is waited for as usual, which also
-// reports what went wrong.  Not for a stream that is being captured: the caller has looked (refuse_capture).
+// if that does not come within a few milliseconds the stream is waited for as usual - which keeps the host's core as
+// busy - and that also reports what went wrong.  Not for a stream that is being captured: the caller has looked (refuse_capture).
 int read_back(svgd_ctx *c, size_t bytes, hipStream_t s)
 {
     const unsigned ticket = ++c->ticket;
@@ -296,7 +296,8 @@ bool beyond_cache(int n, int64_t ld)
     return (int64_t)n * ld * (int64_t)sizeof(float) > kMemorySideCacheBytes + kMemorySideCacheBytes / 4;
 }
 
-// Whether the matrix-core update on aligned rows lets the waves of a workgroup share a range.
+// Whether the matrix-core update lets the waves of a workgroup share a range where its stores allow it (aligned rows; direct
+// stores, see run_update).
 bool adjacent_tiles(int n, int64_t ld) { return n > 48 || beyond_cache(n, ld); }
 
 // Worker workgroups of the matrix-core update (each walks ranges of 64-column tiles; one more
