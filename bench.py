@@ -25,21 +25,21 @@ HBM_PEAK_GBS = 8000.0          # MI355X HBM3E, published
 # the kernel source: if the hash below no longer matches, "traffic" is reported as null.
 TRAFFIC_COUNTERS = {
     # (config, carried Gram?, rows padded to 32 floats?) -> (FETCH_SIZE KiB, WRITE_SIZE KiB)
-    (5, True, True): (2801881.0, 2795580.2),
-    (5, False, True): (2801380.0, 2793492.1),
-    (5, True, False): (4072036.0, 2797112.9),   # mean of the two walking directions (separate instances)
-    (5, False, False): (4067105.5, 2795026.8),
-    (3, True, True): (253614.5, 250528.0),      # D = 2,000,000 is a multiple of 32: ld = D either way
-    (3, False, True): (253591.8, 250000.0),
-    (3, True, False): (253613.6, 250528.1),
-    (3, False, False): (253590.2, 250000.0),
-    (4, True, True): (349660.0, 349271.3),
-    (4, False, True): (349781.2, 349186.8),
-    (4, True, False): (369781.1, 356925.9),
-    (4, False, False): (370087.4, 357376.8),
+    (5, True, True): (2801879.0, 2795580.2),
+    (5, False, True): (2801382.8, 2793492.1),
+    (5, True, False): (4072367.3, 2797113.0),   # mean of the two walking directions (separate instances)
+    (5, False, False): (4067239.9, 2795026.6),
+    (3, True, True): (253618.3, 250528.0),      # D = 2,000,000 is a multiple of 32: ld = D either way
+    (3, False, True): (253596.7, 250000.0),
+    (3, True, False): (253632.5, 250528.0),
+    (3, False, False): (253595.0, 250000.0),
+    (4, True, True): (349650.7, 349271.5),
+    (4, False, True): (349781.6, 349186.8),
+    (4, True, False): (369205.6, 357964.0),
+    (4, False, False): (370164.7, 358337.6),
 }
 TRAFFIC_SCALE = (2.0, 1.0)     # FETCH_SIZE counts half of the bytes a plain copy reads, WRITE_SIZE all
-TRAFFIC_SOURCE_SHA256 = "1e390e20a917f137ea571067dfdef73ddbbe3b9ea61dc3f9cd5b42e3a1eeadff"
+TRAFFIC_SOURCE_SHA256 = "76e978373f2afb87398eb689dea5a74db93260142ff2804259fecb52374b0d2d"
 
 
 def kernel_source_hash():
