@@ -1,6 +1,7 @@
 """Sizes at which the split of the work leaves remainders: the columns after the last full tile of the
-matrix-core update (one workgroup, 4 x 4 tiles of rows and columns, pairs of row groups for the
-carried sums) and the last, partly filled round of the streaming moments kernel."""
+matrix-core update (one workgroup, four columns of every sixteenth row per thread, 4 x 4 tiles of pairs for
+the carried sums), the last, partly filled round of the streaming moments kernel, and the sizes at which a
+rule takes another way: pass 2 inside the update, direct and re-aligned stores, shared ranges."""
 import pytest
 import torch
 
