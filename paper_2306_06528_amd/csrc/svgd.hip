@@ -300,6 +300,10 @@ bool beyond_cache(int n, int64_t ld)
 // stores, see run_update).
 bool adjacent_tiles(int n, int64_t ld) { return n > 48 || beyond_cache(n, ld); }
 
+// The instances of the matrix-core update whose blocks of rows are full, and all above 32 particles, take the registers of a
+// whole CU with one workgroup; the others leave room for a second.
+bool takes_whole_cu(int n) { return n > 32 || (n & 15) == 0 || has_remainder_rows(n); }
+
 // Worker workgroups of the matrix-core update (each walks ranges of 64-column tiles; one more
 // workgroup does D mod 64): one per CU - the kernel overlaps its own loads with its multiplies, and
 // fewer concurrent row streams keep more HBM pages open.  Exception: 21 to 24 particles, whose
@@ -313,11 +317,19 @@ bool adjacent_tiles(int n, int64_t ld) { return n > 48 || beyond_cache(n, ld); }
 // costs 9 %).
 // The Gram pass splits the tiles the same way.  `cap` bounds the grid, the tail's workgroup included.
 // (D mod 64 = 0: no workgroup for the tail.)
+// Where a workgroup takes all registers of its CU, a tail's workgroup on top of a worker for every CU starts when the first
+// of those ends: up to kTailRoomTiles tiles per wave there is one worker less.  us per step with 256 and 255 workers:
+// n = 48, D = 120,011, padded, carried sums 35.0 and 28.6, n = 64 48.0 and 39.7, plain, dense 51.4 and 45.8; D = 300,007 (five
+// tiles per wave) 74.1 and 68.4, plain 91.3 and 90.2; D = 800,003 (12) 138.2 and 137.7.  Beyond, the workgroups end so
+// far apart that the tail is done in time, and a worker less costs its share (n = 64, D = 11,173,962, carried
+// sums 1698 and 1715).
+constexpr int kTailRoomTiles = 16;
 int update_workers(const svgd_ctx *c, int n, int64_t D, int64_t ld, int cap)
 {
     const int64_t nfull = D / 64;
     const int per_cu = (n >= 17 && n <= 24 && !has_remainder_rows(n) && beyond_cache(n, ld)) ? 2 : 1;
-    const int max_workers = mini(c->num_cu * per_cu, cap - 1);
+    const bool room = takes_whole_cu(n) && (D & 63) && nfull <= (int64_t)kTailRoomTiles * 4 * c->num_cu && c->num_cu > 1;
+    const int max_workers = mini(c->num_cu * per_cu - (room ? 1 : 0), cap - 1);
     return clampi((nfull + 3) / 4, 1, max_workers);
 }
 
@@ -479,7 +491,7 @@ int run_bandwidth(svgd_ctx *c, int n, const PairList &list, hipStream_t s)
 // Returns the number of workers, 0: not as one launch (21 particles or more only).
 int fused_workers(const svgd_ctx *c, int n, int64_t D, int64_t ld, int workers, bool carry)
 {
-    const bool full_rows = (n & 15) == 0 || has_remainder_rows(n);
+    const bool full_rows = takes_whole_cu(n);
     const int64_t nfull = D / 64, ranges = adjacent_tiles(n, ld) ? 1 : 4; // per workgroup
     auto tiles_per_wave = [&](int64_t w) {
         const int64_t per = (nfull + w * ranges - 1) / (w * ranges);
