@@ -498,16 +498,17 @@ struct SumSource {
     int nparts;
 };
 
-// Reads reduced sums into S [n (n + 1) / 2 <= 2080].
-template <int THREADS, class Meanwhile>
-__device__ inline void copy_sums(double *S, const double *sums, int n, Meanwhile meanwhile)
+// Reads reduced sums into S [n (n + 1) / 2], n <= MAXN.  meanwhile() and last() as in gather_sums.
+template <int THREADS, int MAXN, class Meanwhile, class Last>
+__device__ inline void copy_sums(double *S, const double *sums, int n, Meanwhile meanwhile, Last last)
 {
-    constexpr int U = (kMaxPairsFull + THREADS - 1) / THREADS;
+    constexpr int U = (MAXN * (MAXN + 1) / 2 + THREADS - 1) / THREADS;
     const int tid = threadIdx.x, P = n * (n + 1) / 2;
     double v[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) v[u] = sums[tid + u * THREADS < P ? tid + u * THREADS : 0];
     meanwhile();
+    last();
 #pragma unroll
     for (int u = 0; u < U; ++u)
         if (tid + u * THREADS < P) S[tid + u * THREADS] = v[u];
@@ -829,7 +830,7 @@ static __global__ __launch_bounds__(kBwThreads) void bandwidth_kernel(SumSource 
     kernel_matrix<kBwThreads, kMaxN, false>(
         sh, ba, st, coef, nullptr, true, c2h,
         [&](auto meanwhile) __attribute__((always_inline)) {
-            if (src.sums != nullptr) copy_sums<kBwThreads>(sh.S, src.sums, ba.n, meanwhile);
+            if (src.sums != nullptr) copy_sums<kBwThreads, kMaxN>(sh.S, src.sums, ba.n, meanwhile, NoCall{});
             else gather_sums<kBwThreads, false, kSumLoads>(sh.S, red, src.partials, src.nparts, ba.n, meanwhile, NoCall{});
         });
 }

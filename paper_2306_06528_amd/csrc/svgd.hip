@@ -446,20 +446,25 @@ int run_gram(svgd_ctx *c, const float *X, int n, int64_t D, int64_t ld, hipStrea
     return SVGD_OK;
 }
 
-// The list as the source of pass 2: as it is, or - longer than `max_floats` - reduced first.
-int sum_source(svgd_ctx *c, int n, const PairList &list, int max_floats, hipStream_t s, SumSource &src)
+// The list of partial sums added up, by a launch of many workgroups.
+int run_reduce(svgd_ctx *c, int n, const PairList &list, hipStream_t s)
 {
-    const int stride = pair_stride(n);
-    src.sums = nullptr;
-    src.partials = c->partials + list.off;
-    src.nparts = list.nparts;
-    if ((int64_t)list.nparts * stride <= max_floats) return SVGD_OK;
     KernelTimer t(c, SVGD_KERNEL_REDUCE, s);
-    reduce_partials_kernel<<<(stride + kReduceEntries - 1) / kReduceEntries, 256, 0, s>>>(src.partials, list.nparts, n, c->sums);
-    src.sums = c->sums;
+    reduce_partials_kernel<<<(pair_stride(n) + kReduceEntries - 1) / kReduceEntries, 256, 0, s>>>(c->partials + list.off, list.nparts, n, c->sums);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(c, e);
     return SVGD_OK;
+}
+
+// The list as the source of pass 2: as it is, or - longer than `max_floats` - reduced first.
+int sum_source(svgd_ctx *c, int n, const PairList &list, int max_floats, hipStream_t s, SumSource &src)
+{
+    src.sums = nullptr;
+    src.partials = c->partials + list.off;
+    src.nparts = list.nparts;
+    if ((int64_t)list.nparts * pair_stride(n) <= max_floats) return SVGD_OK;
+    src.sums = c->sums;
+    return run_reduce(c, n, list, s);
 }
 
 // The Gram kernels' format at this particle count (the update kernels with CARRY mirror it).
@@ -522,6 +527,17 @@ bool store_directly(int n, int64_t D, bool emit, bool carry)
     return (int64_t)n * D * (int64_t)sizeof(float) <= ((int64_t)mib << 20);
 }
 
+// 21 to kSumsMaxN particles and a list too long to be read by every workgroup: a launch of many workgroups sums it, and
+// the update's workgroups start with pass 2 on the sums - a launch less than with pass 2 in between, and the tile's first
+// loads and the tables of C are no longer waited for behind it.  us per step, apart and inside: n = 24, dense, D = 120,011
+// 23.6 and 21.5, n = 32, D = 50,021 20.5 and 18.7, carried, padded 16.8 and 14.8, n = 33 19.6 and 17.9, n = 40, plain 25.6 and
+// 23.9, n = 48 26.6 and 25.2; separate rows, n = 24, D = 1,500,001 120.9 and 118.4, padded, n = 32, D = 2,000,000 195.4 and 193.9.  From 49 particles on 256 threads take longer for pass 2 than
+// the 1024 of a launch of its own and that launch together (n = 50 30.3 and 30.1, n = 56 32.9 and 33.4, n = 64 32.4 and 34.0).
+// Not with re-aligned stores (two instances per kernel instead of three or four), and only where all workgroups are resident
+// without a tile more for any wave.  Lists that the launch of pass 2 sums by itself - up to 32 particles: somewhat longer ones - save no launch.
+constexpr int kSumsMaxN = 48;
+int sums_min_floats(int n) { return n <= kFusedMaxN ? 60 * 1024 : kDirectMaxFloats; }
+
 // Passes 2 and 3.  EMIT = false: X updated in place; EMIT = true: phi written to PHI.  CARRY (in
 // place): the update also leaves the pair-sum partials of the new X in the scratch, described by
 // `list` on return.
@@ -536,18 +552,31 @@ int run_update(svgd_ctx *c, float *X, const float *G, float *PHI, int n, int64_t
     int out_cap = CARRY ? (int)std::min<int64_t>(half / pair_stride(n), kMaxParts) : kMaxParts;
     if (CARRY && n <= kValuMaxN) out_cap = mini(out_cap, fused_max_parts(n));
     bool fused = n <= kFusedAlwaysN || (n <= kFusedMaxN && list.nparts <= fused_max_parts(n) && (!CARRY || (int64_t)list.nparts * pair_stride(n) <= half));
+    bool from_sums = false;
     int workers = 0;
+    // rows that all start on a 128-byte boundary (X's and G's, and PHI's) need no re-aligned stores and
+    // can be read with streaming loads
+    const bool aligned = rt ? rt->aligned != 0 : rows_aligned(X, ld) && rows_aligned(G, ld) && (!EMIT || rows_aligned(PHI, ld));
+    const bool direct = !rt && store_directly(n, D, EMIT, CARRY);
     if (n > kValuMaxN) {
         workers = update_workers(c, n, D, ld, out_cap);
-        const int w = n <= kFusedMaxN ? fused_workers(c, n, D, ld, workers, CARRY) : 0;
+        const int w = fused_workers(c, n, D, ld, workers, CARRY);
+        // (CARRY: by n, D and ld alone, see below)
+        const bool sums_inside = n > kFusedAlwaysN && n <= kSumsMaxN && (w == workers || (w > 0 && !takes_whole_cu(n))) && (direct || (!CARRY && aligned));
         // CARRY: the number of workgroups, which is that of the carried partial sums, depends on the
         // problem only, not on the list that is read: a captured step reads what any other one left
-        const bool adapt = w > 0 && (CARRY ? w + ((D & 63) ? 1 : 0) <= fused_max_parts(n) : fused);
+        const bool adapt = w > 0 && (sums_inside || (n <= kFusedMaxN && (CARRY ? w + ((D & 63) ? 1 : 0) <= fused_max_parts(n) : fused)));
         if (adapt) workers = w;
         fused = fused && workers == w;
+        from_sums = !fused && sums_inside && (int64_t)list.nparts * pair_stride(n) > sums_min_floats(n);
     }
     int64_t out_off = c->captured ? c->home : 0;
-    if (fused) {
+    if (from_sums) {
+        int rc = run_reduce(c, n, list, s);
+        if (rc) return rc;
+        ua.sums = c->sums;
+        c->last_n = n;
+    } else if (fused) {
         ua.partials = c->partials + list.off;
         ua.nparts = list.nparts;
         if (CARRY) out_off = other_half(c, list.off);
@@ -576,10 +605,6 @@ int run_update(svgd_ctx *c, float *X, const float *G, float *PHI, int n, int64_t
         // workers walk contiguous ranges of full 64-column tiles; one more workgroup does D mod 64
         const int grid = workers + ((D & 63) ? 1 : 0);
         if (CARRY) list = PairList{out_off, grid}; // one partial per workgroup, the tail's included
-        // rows that all start on a 128-byte boundary (X's and G's, and PHI's) need no re-aligned stores and
-        // can be read with streaming loads
-        const bool aligned = rt ? rt->aligned != 0 : rows_aligned(X, ld) && rows_aligned(G, ld) && (!EMIT || rows_aligned(PHI, ld));
-        const bool direct = !rt && store_directly(n, D, EMIT, CARRY);
         // Direct stores, adjacent tiles: not where the workgroups' ranges are of 5, 6 or 9 tiles (n > 48, D = 65,536 to
         // 98,368 and 131,072 to 147,520): one or two waves of each then have a tile more than the others, on nearly all
         // CUs, where ranges of their own give as many tiles to every wave of two thirds of them.  us per step re-aligned,
@@ -593,7 +618,8 @@ int run_update(svgd_ctx *c, float *X, const float *G, float *PHI, int n, int64_t
         }
         ua.per = tiles_per_range(D / 64, workers, ua.adjacent && (aligned || direct)); // (staged stores: a range per wave)
         const UpdateCall call{X, G, PHI, c->coef, c->state, n, D, ld, eps, gram_out, rt, ua, grid, s,
-                              aligned ? kStoreLines : (direct ? kStoreDirect : kStoreStaged), fused};
+                              aligned ? kStoreLines : (direct ? kStoreDirect : kStoreStaged),
+                              from_sums ? kPass2OnSums : (fused ? kPass2OnList : kPass2Apart)};
         if (n <= kFusedMaxN) launch_update_low<EMIT, CARRY>(call);
         else launch_update_high<EMIT, CARRY>(call);
     }

@@ -26,9 +26,10 @@ namespace svgd {
 // leaves the partials of the new X in the other half of the scratch, because workgroups still in their
 // prologue read the old list.
 struct UpdateArgs {
-    // passes 2 and 3 in one launch only
+    // passes 2 and 3 in one launch only: the list of partial sums, or (21 particles and more) what it adds up to
     const float *partials;
     int nparts;
+    const double *sums;
     double h_fixed, log_n1;
     // all update kernels:
     // walk the columns from the far end.  Which thread or wave owns which columns does not change, only the order in which it
@@ -244,6 +245,9 @@ void update_valu_kernel(float *__restrict__ X,
 // than it saved, see below).  One to four rows beyond a multiple of 16 do not get a block of
 // their own at all (REM, below).
 // ---------------------------------------------------------------------------------------------
+// Where pass 2 is done: before the update, in a launch of its own; or inside the update, by every workgroup, from the list
+// of partial sums (up to 32 particles) or from the sums that a launch in between has made of it (21 to 48 particles).
+enum Pass2 : int { kPass2Apart = 0, kPass2OnList = 1, kPass2OnSums = 2 };
 enum StoreMode : int {
     kStoreStaged = 0, // re-aligned through LDS, as described above
     kStoreLines = 1,  // every row starts on a 128-byte boundary: straight from the registers, G streamed
@@ -436,7 +440,7 @@ struct TailColumns {
 // is summed on the vector ALU (each lane over its own rows, then across the wave's four rows of
 // lanes); they are stored as one more store group, and their pair sums (CARRY) are accumulated
 // like those of a further block whose rows R..15 are zero.
-template <int NB, bool EMIT, bool FULLROWS, bool CARRY, int STORE = kStoreStaged, bool ROWS = false, bool FUSED = false,
+template <int NB, bool EMIT, bool FULLROWS, bool CARRY, int STORE = kStoreStaged, bool ROWS = false, int PASS2 = kPass2Apart,
           bool REV = false, bool REM = false>
 __global__ __launch_bounds__(256)
 __attribute__((amdgpu_waves_per_eu((NB <= 2 && !FULLROWS) ? 2 : 1, (NB <= 2 && !FULLROWS) ? 2 : 1)))
@@ -447,7 +451,10 @@ void update_mfma_kernel(float *__restrict__ X, const float *__restrict__ G, floa
 {
     // FROM_REGS says nothing of where rows start; what needs them on 128-byte boundaries asks for STREAM
     constexpr bool FROM_REGS = STORE != kStoreStaged, STREAM = STORE == kStoreLines;
-    static_assert(!FUSED || NB <= 2, "pass 2 with 256 threads: n <= 32");
+    constexpr bool FUSED = PASS2 != kPass2Apart;
+    constexpr int NMAX = 16 * NB + (REM ? 4 : 0); // particles
+    static_assert(PASS2 != kPass2OnList || NMAX <= 32, "256 threads read a list of up to 32 particles");
+    static_assert(PASS2 != kPass2OnSums || (NMAX <= 48 && FROM_REGS), "pass 2 on sums: problems that are never stored re-aligned");
     static_assert(!(CARRY && EMIT), "the Gram is carried only when X is updated");
     static_assert(!(ROWS && (EMIT || CARRY)), "separate rows: plain in-place step");
     static_assert(!REV || (CARRY && !FROM_REGS), "the mirrored walk exists for re-aligned stores with carried sums");
@@ -581,7 +588,7 @@ void update_mfma_kernel(float *__restrict__ X, const float *__restrict__ G, floa
     // spilled in the loop)
     constexpr bool TAIL_EARLY = FUSED && (NB == 1 || FROM_REGS);
     const bool in_tail = has_tail && (int)blockIdx.x == nwork;
-    TailColumns<16 * NB + (REM ? 4 : 0), EMIT, CARRY, ROWS, FUSED> tail;
+    TailColumns<NMAX, EMIT, CARRY, ROWS, FUSED> tail;
     auto first_loads = [&]() __attribute__((always_inline)) {
         if constexpr (TAIL_EARLY) {
             if (in_tail) tail.load(n, D, ld, X, G, srow, sgrow);
@@ -604,19 +611,24 @@ void update_mfma_kernel(float *__restrict__ X, const float *__restrict__ G, floa
 
     // C (n x n) and rho (n): the handle's tables, or - FUSED - this workgroup's own copies in LDS,
     // computed by the prologue in the (still unused) staging area
-    __shared__ __attribute__((aligned(16))) float cl[FUSED ? 32 * 32 + 32 : 1];
+    __shared__ __attribute__((aligned(16))) float cl[FUSED ? NMAX * NMAX + NMAX : 1];
     const float *Cm = coef + kOffC, *rhov = coef + kOffRho;
     const int cs = FUSED ? (n + 3) & ~3 : n; // rows of C (kernel_matrix pads its own with zeros)
     float c2h;
     if constexpr (FUSED) {
-        typedef BwShared<32, 256> Shared;
-        static_assert(sizeof(Shared) % 16 == 0 && sizeof(Shared) + 4 * 256 * sizeof(double) <= 4 * (kUpdCur + kUpdCarry) * sizeof(float),
+        constexpr int MAXN = NMAX <= 32 ? 32 : NMAX;
+        typedef BwShared<MAXN, 256> Shared;
+        static_assert(sizeof(Shared) % 16 == 0 && sizeof(Shared) + (PASS2 == kPass2OnList ? 4 * 256 * sizeof(double) : 0) <= 4 * (kUpdCur + kUpdCarry) * sizeof(float),
                       "pass 2 fits into the staging area");
         Shared &sh = *reinterpret_cast<Shared *>(lds + NB * NB * 64 * 4);
         double *red = reinterpret_cast<double *>(reinterpret_cast<char *>(&sh) + sizeof(Shared));
-        kernel_matrix<256, 32, true>(
+        kernel_matrix<256, MAXN, true>(
             sh, BwArgs{n, kModeGram, ua.h_fixed, ua.log_n1}, st, coef, cl, blockIdx.x == 0, c2h,
-            [&](auto meanwhile) __attribute__((always_inline)) { gather_sums<256, true, (NB == 1 || FULLROWS) && !ROWS ? 2 * kSumLoads : kSumLoads>(sh.S, red, ua.partials, ua.nparts, n, meanwhile, first_loads); });
+            [&](auto meanwhile) __attribute__((always_inline)) {
+                if constexpr (PASS2 == kPass2OnList)
+                    gather_sums<256, true, (NB == 1 || FULLROWS) && !ROWS ? 2 * kSumLoads : kSumLoads>(sh.S, red, ua.partials, ua.nparts, n, meanwhile, first_loads);
+                else copy_sums<256, MAXN>(sh.S, ua.sums, n, meanwhile, first_loads);
+            });
         // (the first tile is on its way while the list is summed and h and K are computed)
         Cm = cl;
         rhov = cl + n * cs;

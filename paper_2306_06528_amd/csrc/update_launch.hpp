@@ -21,40 +21,50 @@ struct UpdateCall {
     int grid;
     hipStream_t stream;
     int store;  // StoreMode
-    bool fused; // pass 2 inside
+    int pass2;  // Pass2
 };
 
 // One to four particles beyond a multiple of 16 ride along as remainder rows of the kernel for that multiple.
 inline bool has_remainder_rows(int n) { return n > 16 && (n & 15) >= 1 && (n & 15) <= 4; }
 
-template <int NB, bool EMIT, bool CARRY, bool FULL, bool REM, bool F>
+template <int NB, bool EMIT, bool CARRY, bool FULL, bool REM, int P2>
 void launch_update_instance(const UpdateCall &c)
 {
 #define UPD(STORE, ROWS, REV, rows)                                                                                   \
-    update_mfma_kernel<NB, EMIT, FULL, CARRY, STORE, ROWS, F, REV, REM><<<c.grid, 256, 0, c.stream>>>(                \
+    update_mfma_kernel<NB, EMIT, FULL, CARRY, STORE, ROWS, P2, REV, REM><<<c.grid, 256, 0, c.stream>>>(               \
         c.X, c.G, c.PHI, c.coef, c.st, c.n, c.D, c.ld, c.eps, c.gram_out, rows, c.ua)
+    constexpr bool STAGED = P2 != kPass2OnSums; // (the host sees to it)
     if constexpr (!EMIT && !CARRY) {
         if (c.rt) {
             if (c.store == kStoreLines) UPD(kStoreLines, true, false, *c.rt);
-            else UPD(kStoreStaged, true, false, *c.rt);
+            else if constexpr (STAGED) UPD(kStoreStaged, true, false, *c.rt);
             return;
         }
     }
     if (c.store == kStoreLines) UPD(kStoreLines, false, false, NoRows{});
     else if (c.store == kStoreDirect) UPD(kStoreDirect, false, false, NoRows{});
-    else if (CARRY && c.ua.reverse) UPD(kStoreStaged, false, CARRY, NoRows{});
-    else UPD(kStoreStaged, false, false, NoRows{});
+    else if constexpr (STAGED) {
+        if (CARRY && c.ua.reverse) UPD(kStoreStaged, false, CARRY, NoRows{});
+        else UPD(kStoreStaged, false, false, NoRows{});
+    }
 #undef UPD
 }
 
 template <int NB, bool EMIT, bool CARRY, bool FULL, bool REM>
 void launch_update_blocks(const UpdateCall &c)
 {
-    if constexpr (NB == 1) launch_update_instance<NB, EMIT, CARRY, FULL, REM, true>(c); // n <= kFusedAlwaysN
-    else if constexpr (NB == 2 && !REM) {                                               // n <= kFusedMaxN
-        if (c.fused) launch_update_instance<NB, EMIT, CARRY, FULL, REM, true>(c);
-        else launch_update_instance<NB, EMIT, CARRY, FULL, REM, false>(c);
-    } else launch_update_instance<NB, EMIT, CARRY, FULL, REM, false>(c);
+    constexpr int NMAX = 16 * NB + (REM ? 4 : 0);
+    if constexpr (NMAX <= 20) {
+        launch_update_instance<NB, EMIT, CARRY, FULL, REM, kPass2OnList>(c); // n <= kFusedAlwaysN
+    } else {
+        if constexpr (NMAX <= 32) {
+            if (c.pass2 == kPass2OnList) return launch_update_instance<NB, EMIT, CARRY, FULL, REM, kPass2OnList>(c);
+        }
+        if constexpr (NMAX <= 48) {
+            if (c.pass2 == kPass2OnSums) return launch_update_instance<NB, EMIT, CARRY, FULL, REM, kPass2OnSums>(c);
+        }
+        launch_update_instance<NB, EMIT, CARRY, FULL, REM, kPass2Apart>(c);
+    }
 }
 
 // 13 to 32 particles, and 33 to 64

@@ -1,0 +1,49 @@
+"""21 to 48 particles and a list of partial sums too long for every workgroup to read: a launch sums it, the update does
+pass 2 on the sums.  Sizes at the rule's edges: the shortest such lists and one below, columns after the last tile or none,
+full and padded blocks of rows, rows on top of them."""
+import pytest
+import torch
+
+from parity_checks import check_carried_chain, ulp_diff_device
+
+pytestmark = pytest.mark.gpu
+
+
+def _launches(svgd, eng, call):
+    eng.profile_begin()
+    call()
+    prof = eng.profile_end()
+    return [prof[k][1] for k in svgd.KERNEL_KINDS]
+
+
+@pytest.mark.parametrize("n,D,inside", [
+    (24, 52_301, True), (28, 38_600, True), (28, 38_400, False), (32, 29_800, True), (32, 29_600, False), (32, 32_768, True),
+    (33, 7_500, True), (33, 7_400, False), (36, 131_072, True), (37, 6_000, True), (44, 70_001, True), (48, 3_400, True),
+    (48, 3_300, False), (48, 65_600, True), (49, 3_400, False)])
+def test_pass_2_on_sums(n, D, inside):
+    from paper_2306_06528_amd import svgd
+    assert torch.cuda.get_device_properties(0).multi_processor_count == 256
+    g = torch.Generator().manual_seed(n + D)
+    X, G = (0.3 * torch.randn(n, D, generator=g)).cuda(), torch.randn(n, D, generator=g).cuda()
+    for padded in (False, True):
+        check_carried_chain(svgd, X, G, 0.05, padded=padded, steps=3)
+    old, PHI = X.clone(), torch.empty_like(X)
+    rows, grows = [X[i].clone() for i in range(n)], [G[i].clone() for i in range(n)]
+    with svgd.Svgd(n, D) as eng:
+        for call in (lambda: eng.phi(X, G, PHI), lambda: eng.step(X, G, 0.05), lambda: eng.step_rows(rows, grows, 0.05)):
+            got = _launches(svgd, eng, call)
+            assert got == [1, 1, 0, 1] if inside else got[0] == 1 and got[2:] == [1, 1]
+            h, K = eng.get_last(n)  # workgroup 0 of the update leaves them
+            assert abs(h - svgd_h(old)) <= 1e-5 * h and float(K[0, 0]) == 1.0
+    assert ulp_diff_device(X, old, PHI, 0.05) <= 1.0
+    assert ulp_diff_device(torch.stack(rows), old, PHI, 0.05) <= 1.0
+
+
+def svgd_h(X):
+    """The median bandwidth in 64 bits."""
+    Y = X.double() - X.double().mean(0, keepdim=True)
+    S = Y @ Y.t().contiguous()
+    s = S.diagonal()
+    v = (s[:, None] + s[None, :] - 2.0 * S).clamp_(min=0.0).fill_diagonal_(0.0).flatten().sort().values
+    m = v.numel()
+    return float(0.5 * (v[(m - 1) // 2] + v[m // 2])) / float(torch.log(torch.tensor(X.shape[0] + 1.0, dtype=torch.float64)))
