@@ -277,12 +277,29 @@ __global__ __launch_bounds__(64 * W) void gram_mfma_kernel(const float *__restri
 #pragma unroll
         for (int i = 0; i < RPL; ++i) xro[i] = srow[4 * i + q];
     }
+    // WIDE (small X, a slab per wave): rows beyond n are loaded as row n - 1 and set to 0 when the slab is used, and the
+    // partial slab is loaded like the others, at min(column, D - 4), and moved into place then (RaggedGroup): no branch around
+    // any load.  With guarded ones - four per slab, and 64 single columns per row and wave in the partial slab, whose
+    // wave was the last of its launch to end - svgd_bandwidth took 18.1 us at n = 64, D = 25,003, now 16.5, and 21.6 at D = 65,003,
+    // now 18.4; n = 40 15.1 and 14.3, 17.1 and 15.4.  In the loop over many slabs what is moved and set to 0 costs more than
+    // the branches (n = 64, D = 1,500,003 87.8 and 101).
+    constexpr bool WIDE = W == kGramWavesSmall;
+    int64_t last_row[WIDE && !ROWS ? 4 : 1];
+    if constexpr (WIDE && !ROWS) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int row = 4 * (RPL - 4 + k) + q;
+            last_row[k] = (int64_t)(row < n ? row : n - 1) * ld;
+        }
+    }
     // The slab at `at` (then on to the next index): where it lies and how it is to be loaded -
-    // 0: plain 16-byte loads, 1: streaming ones, 2: the partial slab, 3: an empty slab.  One
-    // wave-uniform decision per slab, then sixteen loads in a row: decided per row, every load
+    // 0: plain 16-byte loads, 1: streaming ones, 2: the partial slab (WIDE: only one of fewer than four columns), 3: an
+    // empty slab.  One wave-uniform decision per slab, then sixteen loads in a row: decided per row, every load
     // sat behind its own little tree of branches, a hundred branches per slab during which the
     // matrix pipe had nothing from this wave.
     int64_t col = 0;
+    bool partial = false; // WIDE: the slab in x is the partial one; then how far its columns are to be moved:
+    int shift = 0;
     auto next_slab = [&]() __attribute__((always_inline)) -> int {
         const bool is_cold = ORDERED && phase == 0;
         int64_t tile = ORDERED ? nfull : (int64_t)at; // ordered, phase 2: the partial slab
@@ -295,6 +312,16 @@ __global__ __launch_bounds__(64 * W) void gram_mfma_kernel(const float *__restri
         const int64_t wcol = tile << 6;
         col = wcol + 4 * c16;
         if (ORDERED && tile < 0) return 3;
+        if constexpr (WIDE) {
+            partial = wcol + 64 > D && D >= 4;
+            int how = wcol + 64 > D && D < 4 ? 2 : 0;
+            if (partial) {
+                const RaggedGroup rg(col, D);
+                col = rg.at;
+                shift = rg.s;
+            }
+            return __builtin_amdgcn_readfirstlane(how);
+        }
         if (wcol + 64 > D) return 2;
         return (STREAM && is_cold) ? 1 : 0;
     };
@@ -307,12 +334,13 @@ __global__ __launch_bounds__(64 * W) void gram_mfma_kernel(const float *__restri
 #pragma unroll
         for (int i = 0; i < RPL; ++i) {
             const int row = 4 * i + q;
-            const float *xr = RREG ? X + xro[RREG ? i : 0] + col : (ROWS ? X + srow[ROWS ? 4 * i + qv : 0] + col : X + at0 + (int64_t)(4 * i) * ld);
+            const float *xr = RREG ? X + xro[RREG ? i : 0] + col : (ROWS ? X + srow[ROWS ? 4 * i + qv : 0] + col : X + (!WIDE || i < RPL - 4 ? at0 + (int64_t)(4 * i) * ld : col + last_row[!WIDE || i < RPL - 4 ? 0 : i - (RPL - 4)]));
             f32x4 v = {0.f, 0.f, 0.f, 0.f}; // rows beyond n, and empty slabs, add nothing to any sum
             // (only the last block of 16 rows can reach beyond n)
-            if (HOW != 3 && (i < RPL - 4 || row < n)) {
+            if (HOW != 3 && (WIDE || i < RPL - 4 || row < n)) {
                 if constexpr (HOW == 0) v = *reinterpret_cast<const f32x4u *>(xr);
                 else if constexpr (HOW == 1) v = __builtin_nontemporal_load(reinterpret_cast<const f32x4u *>(xr));
+                else if constexpr (WIDE) v = c16 == 0 ? load_narrow(xr - col, D) : v;
                 else v = load4(xr - col, col, D, false);
             }
             x[i] = v;
@@ -328,6 +356,17 @@ __global__ __launch_bounds__(64 * W) void gram_mfma_kernel(const float *__restri
     auto load_slab = [&]() __attribute__((always_inline)) { with_mode(next_slab(), rows); };
     // steps 2 and 3: the slab in x, centred, into `buf`
     auto centre_and_stage = [&](float *buf) __attribute__((always_inline)) {
+        if constexpr (WIDE) {
+            if (partial) {
+                RaggedGroup rg(0, 4);
+                rg.s = shift;
+#pragma unroll
+                for (int i = 0; i < RPL; ++i) x[i] = rg.fix(x[i]);
+            }
+#pragma unroll
+            for (int i = RPL - 4; i < RPL; ++i)
+                if (4 * i + q >= n) x[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
         f32x4 s = x[0];
 #pragma unroll
         for (int i = 1; i < RPL; ++i) s += x[i];
