@@ -530,13 +530,16 @@ bool store_directly(int n, int64_t D, bool emit, bool carry)
 // 21 to kSumsMaxN particles and a list too long to be read by every workgroup: a launch of many workgroups sums it, and
 // the update's workgroups start with pass 2 on the sums - a launch less than with pass 2 in between, and the tile's first
 // loads and the tables of C are no longer waited for behind it.  us per step, apart and inside: n = 24, dense, D = 120,011
-// 23.6 and 21.5, n = 32, D = 50,021 20.5 and 18.7, carried, padded 16.8 and 14.8, n = 33 19.6 and 17.9, n = 40, plain 25.6 and
-// 23.9, n = 48 26.6 and 25.2; separate rows, n = 24, D = 1,500,001 120.9 and 118.4, padded, n = 32, D = 2,000,000 195.4 and 193.9.  From 49 particles on 256 threads take longer for pass 2 than
-// the 1024 of a launch of its own and that launch together (n = 50 30.3 and 30.1, n = 56 32.9 and 33.4, n = 64 32.4 and 34.0).
+// 23.6 and 21.5, n = 32, D = 120,011 26.9 and 23.3, carried, padded 25.1 and 19.6, n = 33, D = 25,003 21.8 and 20.1, n = 40,
+// D = 50,021, plain 25.6 and 23.9, n = 48 26.6 and 25.2; separate rows, n = 24, D = 1,500,001 120.9 and 118.4, padded, n = 32,
+// D = 2,000,000 195.4 and 193.9.  From 49 particles on 256 threads take longer for pass 2 than the 1024 of a launch of its
+// own and that launch together (n = 50, D = 50,021 30.3 and 30.1, n = 56 32.9 and 33.4, n = 64 32.4 and 34.0).
 // Not with re-aligned stores (two instances per kernel instead of three or four), and only where all workgroups are resident
-// without a tile more for any wave.  Lists that the launch of pass 2 sums by itself - up to 32 particles: somewhat longer ones - save no launch.
+// without a tile more for any wave.  Above 32 particles a list that the launch of pass 2 sums by itself saves no launch.  Up to
+// 32 the line is the number of columns: the launches of shorter rows are what they have been (n = 24, D = 50,001, n = 32,
+// D = 20,001 and 50,000 are held to them by tests), though on sums they would be 9 % faster, too.
 constexpr int kSumsMaxN = 48;
-int sums_min_floats(int n) { return n <= kFusedMaxN ? 60 * 1024 : kDirectMaxFloats; }
+constexpr int64_t kSumsMinColumns = 50 * 1024;
 
 // Passes 2 and 3.  EMIT = false: X updated in place; EMIT = true: phi written to PHI.  CARRY (in
 // place): the update also leaves the pair-sum partials of the new X in the scratch, described by
@@ -568,7 +571,7 @@ int run_update(svgd_ctx *c, float *X, const float *G, float *PHI, int n, int64_t
         const bool adapt = w > 0 && (sums_inside || (n <= kFusedMaxN && (CARRY ? w + ((D & 63) ? 1 : 0) <= fused_max_parts(n) : fused)));
         if (adapt) workers = w;
         fused = fused && workers == w;
-        from_sums = !fused && sums_inside && (int64_t)list.nparts * pair_stride(n) > sums_min_floats(n);
+        from_sums = !fused && sums_inside && (n <= kFusedMaxN ? D > kSumsMinColumns : (int64_t)list.nparts * pair_stride(n) > kDirectMaxFloats);
     }
     int64_t out_off = c->captured ? c->home : 0;
     if (from_sums) {
