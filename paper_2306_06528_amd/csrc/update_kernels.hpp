@@ -556,13 +556,19 @@ void update_mfma_kernel(float *__restrict__ X, const float *__restrict__ G, floa
         if constexpr (STREAM) return __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(p));
         else return *reinterpret_cast<const f32x4u *>(p);
     };
+    // The rows of step s are all there and need no predicate.  Blocks before the last one never reach beyond n, but
+    // only two blocks that are stored from the registers gain from knowing it (us per step, n = 24, padded, carried sums,
+    // D = 300,007 31.7 -> 29.3, D = 1,000,003 66.0 -> 60.3, D = 2,000,003 112.4 -> 107.3; dense, D = 500,009, plain 51.6 -> 50.3,
+    // phi, n = 28, D = 120,011 23.8 -> 22.3): with re-aligned stores and carried sums the registers do not suffice, and with three or
+    // four blocks the compiler then moves the loads to where they cost 4 to 7 %.
+    auto whole = [](int s) { return FULLROWS || (NB == 2 && FROM_REGS && s < NS - 4); };
     auto load_x = [&](const float *xt, int s) __attribute__((always_inline)) {
         const int urow = 16 * (s >> 2) + (s & 3); // uniform part of the row index
-        if (FULLROWS || urow + 4 * q < n) x[s] = load16x(xt + (ROWS ? xro[ROWS ? s : 0] : (int64_t)urow * ld));
+        if (whole(s) || urow + 4 * q < n) x[s] = load16x(xt + (ROWS ? xro[ROWS ? s : 0] : (int64_t)urow * ld));
     };
     auto load_g = [&](const float *gt, int s) __attribute__((always_inline)) {
         const int urow = 16 * (s >> 2) + (s & 3);
-        if (FULLROWS || urow + 4 * q < n) z[s] = load16g(gt + (ROWS ? gro[ROWS ? s : 0] : (int64_t)urow * ld));
+        if (whole(s) || urow + 4 * q < n) z[s] = load16g(gt + (ROWS ? gro[ROWS ? s : 0] : (int64_t)urow * ld));
     };
     auto load_next_rem = [&](const float *xt, const float *gt) __attribute__((always_inline)) {
         if constexpr (REM) {
@@ -576,7 +582,7 @@ void update_mfma_kernel(float *__restrict__ X, const float *__restrict__ G, floa
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
             const int urow = 16 * (s >> 2) + (s & 3);
-            if (FULLROWS || urow + 4 * q < n) {
+            if (whole(s) || urow + 4 * q < n) {
                 if constexpr (XBUF) xn[s] = load16x(xt + (ROWS ? xro[ROWS ? s : 0] : (int64_t)urow * ld));
                 if constexpr (GBUF) gn[s] = load16g(gt + (ROWS ? gro[ROWS ? s : 0] : (int64_t)urow * ld));
             }
@@ -897,7 +903,7 @@ void update_mfma_kernel(float *__restrict__ X, const float *__restrict__ G, floa
                     o[t] = EMIT ? phi : fmaf(eps, phi, x[s][t]);
                 }
                 if constexpr (FROM_REGS) {
-                    if (FULLROWS || 16 * bi + 4 * q + r < n) store_direct(ROWS ? xro[ROWS ? s : 0] : (int64_t)(16 * bi + r) * ld, o);
+                    if (whole(s) || 16 * bi + 4 * q + r < n) store_direct(ROWS ? xro[ROWS ? s : 0] : (int64_t)(16 * bi + r) * ld, o);
                 }
                 if constexpr (!FROM_REGS || CARRY) // staged for the re-aligned stores and/or as Gram operands
                     *reinterpret_cast<f32x4 *>(&cur[cur_index(4 * q + r, 4 * c16)]) = o;
@@ -954,12 +960,11 @@ void update_mfma_kernel(float *__restrict__ X, const float *__restrict__ G, floa
 
     if constexpr (FROM_REGS) { // no left edge to mask
         int64_t tile = t_first;
-        // Two waves per SIMD fetch their instructions faster or slower with the place of this loop (3.2 KB, 16 branches
-        // around loads and stores) against the 64-byte lines: us per step, n = 24, padded, carried sums, 52 bytes into a line,
-        // 0 and 40: D = 1,000,003 65.4, 66.1 and 67.1, D = 2,000,000 109.6, 110.3 and 112.5.  The compiler
-        // puts six instructions of its own between this and the loop, which makes it 52.  Other instances stay where they
-        // fall.
-        if constexpr (STREAM && CARRY && NB == 2 && !FULLROWS) asm volatile(".p2align 6\n\t.rept 7\n\ts_nop 0\n\t.endr");
+        // Two waves per SIMD fetch their instructions faster or slower with the place of this loop against the 64-byte lines:
+        // us per step, n = 24, padded, carried sums, with 12 instructions between a line's start and the compiler's own
+        // before the loop, with 7 and where it falls: D = 300,007 29.3, 29.6 and 29.4, D = 1,000,003 60.3, 61.8 and 61.0, n = 21
+        // 59.1, 59.9 and 60.1.  Other instances stay where they fall.
+        if constexpr (STREAM && CARRY && NB == 2 && !FULLROWS) asm volatile(".p2align 6\n\t.rept 12\n\ts_nop 0\n\t.endr");
         for (int64_t k = 0; k < ntiles; ++k, tile += t_step) process_tile(std::false_type{}, tile, k + 1 == ntiles);
     } else if (t0 < t1) {
         process_tile(std::true_type{}, t_first, ntiles == 1);
