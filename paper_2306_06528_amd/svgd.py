@@ -24,6 +24,7 @@ if not os.path.exists(LIB_PATH):
         f"{LIB_PATH} is missing: build it first (python -m paper_2306_06528_amd.build, or "
         "__graft_entry__.build()); there is no fallback implementation")
 _lib = ctypes.CDLL(LIB_PATH)
+from . import _binding  # noqa: E402  (built beside the library: the calls whose tensors are checked in native code)
 
 _H = ctypes.c_void_p
 _lib.svgd_create.argtypes = [ctypes.POINTER(_H), ctypes.c_int, ctypes.c_int64, ctypes.c_int, ctypes.c_uint32]
@@ -78,7 +79,7 @@ for _f in ("svgd_create", "svgd_set_bandwidth", "svgd_bandwidth", "svgd_step", "
            "svgd_profile_end"):
     getattr(_lib, _f).restype = ctypes.c_int
 
-_step_ld, _step_static, _Tensor, _float32 = _lib.svgd_step_ld, _lib.svgd_step_static, torch.Tensor, torch.float32
+_step, _phi, _step_rows, _step_static = _binding.step, _binding.phi, _binding.step_rows, _binding.step_static
 
 SVGD_OK = 0
 FLAG_CARRY_GRAM = 1
@@ -176,15 +177,10 @@ def diag_read_rows(X: torch.Tensor, sink: torch.Tensor, pattern: int, stream=Non
 def step_static(X: torch.Tensor, G: torch.Tensor, eps: float, stream=None):
     """svgd_step_static: one plain step on the current device with the library's static scratch -
     no handle, nothing allocated.  X and G as in Svgd.step."""
-    shape = _rows_of(X, "X")
-    if _rows_of(G, "G") != shape:
-        raise ValueError("G must have the shape and row stride of X")
-    n, D, ld = shape
-    if X.get_device() == _cuda_getDevice():
-        rc = _step_static(X.data_ptr(), G.data_ptr(), n, D, ld, float(eps), _stream_ptr(stream))
-    else:
+    rc = _step_static(_cuda_getDevice(), X, G, eps, _stream_ptr(stream))
+    if rc == 1:  # X is on another device: nothing has been done
         with torch.cuda.device(X.device):
-            rc = _step_static(X.data_ptr(), G.data_ptr(), n, D, ld, float(eps), _stream_ptr(stream))
+            rc = _step_static(_cuda_getDevice(), X, G, eps, _stream_ptr(stream))
     if rc != SVGD_OK:
         raise SvgdError(rc)
 
@@ -215,24 +211,11 @@ class Svgd:
 
     def _rows(self, t, name):
         """Checks a matrix argument (2-D float32, rows contiguous, on the handle's device - a
-        pointer of another GPU would fault) and returns (n, D, ld).  Kept short: at small sizes
-        a step costs less than these checks."""
-        if not isinstance(t, _Tensor) or t.dtype is not _float32 or not t.is_cuda:
-            raise TypeError(f"{name} must be a 2-D float32 CUDA tensor")
-        st = t.stride()
-        if len(st) != 2:
-            raise TypeError(f"{name} must be a 2-D float32 CUDA tensor")
-        n, D = t.shape
-        ld, s1 = st
-        if (D != 1 and s1 != 1) or (n != 1 and ld < D):
-            raise TypeError(f"{name} must have contiguous rows, at least D elements apart")
+        pointer of another GPU would fault) and returns (n, D, ld)."""
+        shape = _rows_of(t, name)
         if t.get_device() != self._device:
             raise ValueError(f"{name} is on cuda:{t.get_device()}, the handle on cuda:{self._device}")
-        return n, D, (ld if n != 1 else D)
-
-    def _same(self, a, b, name):
-        if a != b:
-            raise ValueError(f"{name} has (n, D, row stride) = {b}, X has {a}")
+        return shape
 
     def _check(self, rc):
         if rc != SVGD_OK:
@@ -255,43 +238,23 @@ class Svgd:
     def step(self, X, G, eps: float, stream=None):
         """X <- X + eps * phi(X, G) in place.  X and G: (n, D) with contiguous rows and the same
         row stride (dense, or views like buf[:, :D] of an (n, ld) buffer, see padded_rows)."""
-        shape = self._rows(X, "X")
-        other = self._rows(G, "G")
-        if other != shape:
-            self._same(shape, other, "G")
-        n, D, ld = shape
-        rc = _step_ld(self._h, X.data_ptr(), G.data_ptr(), n, D, ld, float(eps), _stream_ptr(stream))
-        if rc:
-            self._check(rc)
+        n = _step(self._h.value or 0, self._device, X, G, eps, _stream_ptr(stream))
+        if n < 0:
+            self._check(n)
         self._last_n = n
 
     def step_rows(self, X_rows, G_rows, eps: float, stream=None):
         """svgd_step_rows: the particles are n separately allocated 1-D float32 CUDA tensors of equal
         length (X_rows[i], updated in place) with their scores (G_rows[i]); nothing is copied."""
-        n = len(X_rows)
-        if n < 1 or len(G_rows) != n:
-            raise ValueError("X_rows and G_rows must be non-empty sequences of the same length")
-        D = X_rows[0].numel()
-        size, device = (D,), self._device
-        for name, rows in (("X_rows", X_rows), ("G_rows", G_rows)):
-            for t in rows:
-                if not (isinstance(t, _Tensor) and t.dtype is _float32 and t.is_cuda and t.shape == size
-                        and (D == 1 or t.stride(0) == 1)):
-                    raise TypeError(f"{name} must hold contiguous 1-D float32 CUDA tensors of one length")
-                if t.get_device() != device:
-                    raise ValueError(f"a row of {name} is on cuda:{t.get_device()}, the handle on cuda:{self._device}")
-        xp = (ctypes.c_void_p * n)(*[t.data_ptr() for t in X_rows])
-        gp = (ctypes.c_void_p * n)(*[t.data_ptr() for t in G_rows])
-        self._check(_lib.svgd_step_rows(self._h, xp, gp, n, D, float(eps), _stream_ptr(stream)))
+        n = _step_rows(self._h.value or 0, self._device, X_rows, G_rows, eps, _stream_ptr(stream))
+        if n < 0:
+            self._check(n)
         self._last_n = n
 
     def phi(self, X, G, PHI, stream=None):
-        shape = self._rows(X, "X")
-        self._same(shape, self._rows(G, "G"), "G")
-        self._same(shape, self._rows(PHI, "PHI"), "PHI")
-        n, D, ld = shape
-        self._check(_lib.svgd_phi_ld(self._h, X.data_ptr(), G.data_ptr(), n, D, ld, PHI.data_ptr(),
-                                     _stream_ptr(stream)))
+        n = _phi(self._h.value or 0, self._device, X, G, PHI, _stream_ptr(stream))
+        if n < 0:
+            self._check(n)
         self._last_n = n
 
     def get_last(self, n: int, stream=None):
