@@ -25,21 +25,21 @@ HBM_PEAK_GBS = 8000.0          # MI355X HBM3E, published
 # the kernel source: if the hash below no longer matches, "traffic" is reported as null.
 TRAFFIC_COUNTERS = {
     # (config, carried Gram?, rows padded to 32 floats?) -> (FETCH_SIZE KiB, WRITE_SIZE KiB)
-    (5, True, True): (2801879.0, 2795580.2),
-    (5, False, True): (2801382.8, 2793492.1),
-    (5, True, False): (4072367.3, 2797113.0),   # mean of the two walking directions (separate instances)
-    (5, False, False): (4067239.9, 2795026.6),
-    (3, True, True): (253618.3, 250528.0),      # D = 2,000,000 is a multiple of 32: ld = D either way
-    (3, False, True): (253596.7, 250000.0),
-    (3, True, False): (253632.5, 250528.0),
-    (3, False, False): (253595.0, 250000.0),
-    (4, True, True): (349650.7, 349271.5),
-    (4, False, True): (349781.6, 349186.8),
-    (4, True, False): (369205.6, 357964.0),
-    (4, False, False): (370164.7, 358337.6),
+    (5, True, True): (2801885.0, 2795580.2),
+    (5, False, True): (2801379.0, 2793492.1),
+    (5, True, False): (4072723.3, 2797112.8),   # mean of the two walking directions (separate instances)
+    (5, False, False): (4067160.4, 2795026.7),
+    (3, True, True): (253625.0, 250528.0),      # D = 2,000,000 is a multiple of 32: ld = D either way
+    (3, False, True): (253635.0, 250004.0),
+    (3, True, False): (253615.0, 250528.1),
+    (3, False, False): (253639.6, 250004.0),
+    (4, True, True): (349653.6, 349270.7),
+    (4, False, True): (349785.4, 349186.8),
+    (4, True, False): (369245.4, 357996.3),
+    (4, False, False): (370079.9, 358312.8),
 }
 TRAFFIC_SCALE = (2.0, 1.0)     # FETCH_SIZE counts half of the bytes a plain copy reads, WRITE_SIZE all
-TRAFFIC_SOURCE_SHA256 = "76e978373f2afb87398eb689dea5a74db93260142ff2804259fecb52374b0d2d"
+TRAFFIC_SOURCE_SHA256 = "85a20efdae6cc951dfbb1754067dc2691d86a0c9058bf165ea4c2056d1e6c87a"
 
 
 def kernel_source_hash():

@@ -281,9 +281,10 @@ __global__ __launch_bounds__(64 * W) void gram_mfma_kernel(const float *__restri
     // partial slab is loaded like the others, at min(column, D - 4), and moved into place then (RaggedGroup): no branch around
     // any load.  With guarded ones - four per slab, and 64 single columns per row and wave in the partial slab, whose
     // wave was the last of its launch to end - svgd_bandwidth took 18.1 us at n = 64, D = 25,003, now 16.5, and 21.6 at D = 65,003,
-    // now 18.4; n = 40 15.1 and 14.3, 17.1 and 15.4.  In the loop over many slabs what is moved and set to 0 costs more than
-    // the branches (n = 64, D = 1,500,003 87.8 and 101).
-    constexpr bool WIDE = W == kGramWavesSmall;
+    // now 18.4; n = 40 15.1 and 14.3, 17.1 and 15.4.  With one block, four rows per lane, it gains nothing (the pass alone, n = 16,
+    // D = 8,577 3.3 and 3.5; n = 20, D = 20,001 4.8 and 3.9), and in the loop over many slabs what is moved and set to 0 costs more
+    // than the branches (n = 64, D = 1,500,003 87.8 and 101).
+    constexpr bool WIDE = W == kGramWavesSmall && NB >= 2;
     int64_t last_row[WIDE && !ROWS ? 4 : 1];
     if constexpr (WIDE && !ROWS) {
 #pragma unroll

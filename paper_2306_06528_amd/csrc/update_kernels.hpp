@@ -21,8 +21,8 @@ namespace svgd {
 
 // Passes 2 and 3 in one launch: always on the vector ALU, FUSED on the matrix cores.  The kernel starts
 // with pass 2 (every workgroup - kernel_matrix - or, on the vector ALU, every wave - wave_kernel_matrix - derives
-// h, C and rho for itself from a short list of partials; workgroup 0 records h and K) and needs no tables
-// in device memory.  A CARRY kernel
+// h, C and rho for itself from a short list of partials, or (21 to 48 particles) from the sums that a launch in
+// between has made of a longer one; workgroup 0 records h and K) and needs no tables in device memory.  A CARRY kernel
 // leaves the partials of the new X in the other half of the scratch, because workgroups still in their
 // prologue read the old list.
 struct UpdateArgs {
