@@ -183,7 +183,13 @@ struct GramOrder {
 // ORDER 2: the same, and the cold tiles are loaded with the streaming hint (no allocation on the
 //   way in) - for rows on 128-byte boundaries (nothing is shared between the slabs of neighbouring
 //   waves).  The pass itself then runs 5 % (n = 64, D = 11.2 M) to 28 % (n = 16, same D) faster.
-// The host takes ORDER 1 or 2 when X is larger than twice the memory-side cache.
+// ORDER 3: as 1, and the eight waves of a workgroup send off their loads together, so that the line which two slabs
+//   of unaligned rows share is asked for by both at once (reads alone, n = 64, D = 11.2 M: 516 -> 466 us).  What the waves
+//   then wait for each other costs as much where little bounds the pass but itself (svgd_bandwidth 563 and 573 us) or the
+//   last block of rows is mostly empty; behind the writes of an update, us per dense step, ORDER 1 and 3: n = 64, D = 11,173,962
+//   2340 and 2300, D = 5,324,817 1134 and 1125, D = 2,293,777 496 and 497, n = 60, D = 9,175,057 1812 and 1793, n = 48,
+//   D = 7,099,750 1096 and 1079, n = 44, D = 7,745,180 1094 and 1087; n = 40 1115 and 1116, n = 33 1092 and 1120, n = 50 1787 and 1805.
+// The host takes ORDER 1, 2 or 3 when X is larger than twice the memory-side cache.
 // What bounds the pass is memory, since the multiplies are in bf16: at n = 64 the matrix pipe is busy for
 // 27 % of the cycles (120 instructions of 16 per slab) and the vector ALU for 32.  In fp32
 // (v_mfma_f32_16x16x4_f32, 160 per slab) they took 32 cycles each during which the vector ALU stood
@@ -218,7 +224,7 @@ __global__ __launch_bounds__(64 * W) void gram_mfma_kernel(const float *__restri
     };
     const SplitConst sc = split_const();
 
-    constexpr bool ORDERED = ORDER != 0, STREAM = ORDER == 2;
+    constexpr bool ORDERED = ORDER != 0, STREAM = ORDER == 2, IN_STEP = ORDER == 3;
     constexpr bool F32 = W == kGramWavesSmall && NB <= kGramF32Blocks;
     const int64_t nfull = D >> 6;
     const uint32_t uper = go.per, uhot = go.hot, ucold = uper - uhot, unfull = (uint32_t)nfull;
@@ -469,6 +475,16 @@ __global__ __launch_bounds__(64 * W) void gram_mfma_kernel(const float *__restri
         clear();
         start();
         if (first < nidx) load_slab();
+        if constexpr (IN_STEP && !decltype(f32)::value) {
+            uint32_t idx = first; // as many rounds, and barriers, for every wave as for the workgroup's first one
+            for (uint32_t idx0 = (uint32_t)W * blockIdx.x; idx0 < nidx; idx0 += stride, idx += stride) {
+                if (idx < nidx) centre_and_stage(my);
+                block_sync<true>();
+                if (idx + stride < nidx) load_slab();
+                if (idx < nidx) multiply(my);
+            }
+            return;
+        }
         for (uint32_t idx = first; idx < nidx; idx += stride) {
             centre_and_stage(my);
             // the next slab's loads are in flight while this one is multiplied

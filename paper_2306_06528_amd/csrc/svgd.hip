@@ -416,6 +416,9 @@ int run_gram(svgd_ctx *c, const float *X, int n, int64_t D, int64_t ld, hipStrea
             hot = 0;
         }
         const bool stream_x = big_x && x_aligned; // slabs of unaligned rows share lines
+        // the waves in step (ORDER 3): a step on dense rows, X beyond 1 GiB, the last of three or four blocks at least three quarters full
+        const bool in_step = !x_aligned && G_next && NB >= 3 && ((n & 15) == 0 || (n & 15) >= 12) &&
+                             (int64_t)n * D * (int64_t)sizeof(float) > (int64_t)1 << 30;
         const uint32_t stride = (uint32_t)kGramWaves * (uint32_t)nparts, cold = (uint32_t)(per - hot);
         GramOrder go{(uint32_t)nranges, (uint32_t)per, (uint32_t)hot, 0, 0, 0, 0};
         if (cold) { go.q_cold = stride / cold; go.r_cold = stride % cold; }
@@ -430,6 +433,7 @@ int run_gram(svgd_ctx *c, const float *X, int n, int64_t D, int64_t ld, hipStrea
         else if (rt) GRAM_W(NB, kGramWaves, true, 0, *rt);                                                   \
         else if (small) GRAM_W(NB, kGramWavesSmall, false, 0, NoRows{});                                     \
         else if (stream_x) GRAM_W(NB, kGramWaves, false, 2, NoRows{});                                       \
+        else if (in_step) GRAM_W(NB, kGramWaves, false, (NB >= 3 ? 3 : 1), NoRows{});                        \
         else if (big_x) GRAM_W(NB, kGramWaves, false, 1, NoRows{});                                          \
         else GRAM_W(NB, kGramWaves, false, 0, NoRows{});                                                     \
     } while (0)
