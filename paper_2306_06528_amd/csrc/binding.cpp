@@ -68,7 +68,7 @@ bool number(PyObject *obj, double &out) // what float() takes
     return !(out == -1.0 && PyErr_Occurred());
 }
 
-// The first `count` arguments as pointers or integers: handle, device, ..., the last one: the stream
+// A handle or a stream, as an integer
 bool word(PyObject *obj, void *&out)
 {
     out = PyLong_AsVoidPtr(obj);
