@@ -197,8 +197,10 @@ PyObject *step_rows(PyObject *, PyObject *const *a, Py_ssize_t na)
         void *h, *stream;
         const long device = PyLong_AsLong(a[1]);
         if (!word(a[0], h) || (device == -1 && PyErr_Occurred())) return nullptr;
-        const Sequence xs(a[2]), gs(a[3]);
-        if (!xs.p || !gs.p) return nullptr;
+        const Sequence xs(a[2]);
+        if (!xs.p) return nullptr;
+        const Sequence gs(a[3]);
+        if (!gs.p) return nullptr;
         const Py_ssize_t n = PySequence_Fast_GET_SIZE(xs.p);
         if (n < 1 || PySequence_Fast_GET_SIZE(gs.p) != n) {
             PyErr_SetString(PyExc_ValueError, "X_rows and G_rows must be non-empty sequences of the same length");

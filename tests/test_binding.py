@@ -31,6 +31,18 @@ def test_what_is_no_sequence_of_rows(eng, rows, error):
         eng.step_rows(*rows, 0.1, stream=_Stream)
 
 
+class _Yields:
+    """Yields a row, by code of its own."""
+    def __iter__(self):
+        return iter([torch.zeros(3)])
+
+
+@pytest.mark.parametrize("second", [torch.zeros(2, 3), _Yields(), [torch.zeros(3)], None])
+def test_first_argument_is_refused_before_the_second_is_looked_at(eng, second):
+    with pytest.raises(TypeError):
+        eng.step_rows(3, second, 0.1, stream=_Stream)
+
+
 @pytest.mark.gpu
 def test_what_is_refused_on_the_gpu():
     from paper_2306_06528_amd import svgd
