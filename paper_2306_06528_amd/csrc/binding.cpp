@@ -163,15 +163,15 @@ PyObject *step_static(PyObject *, PyObject *const *a, Py_ssize_t na)
     });
 }
 
-// The n rows of a sequence: 1-D float32 CUDA tensors of D contiguous elements on `device`.
-bool row_pointers(PyObject *seq, const char *name, int64_t D, long device, std::vector<void *> &out)
+// The rows of a tuple: 1-D float32 CUDA tensors of D contiguous elements on `device`.
+bool row_pointers(PyObject *rows, const char *name, int64_t D, long device, std::vector<void *> &out)
 {
-    const Py_ssize_t n = PySequence_Fast_GET_SIZE(seq);
-    PyObject **items = PySequence_Fast_ITEMS(seq);
+    const Py_ssize_t n = PyTuple_GET_SIZE(rows);
     out.resize((size_t)n);
     for (Py_ssize_t i = 0; i < n; ++i) {
-        if (!THPVariable_Check(items[i])) return type_error("%s must hold contiguous 1-D float32 CUDA tensors of one length", name);
-        const at::Tensor &t = THPVariable_Unpack(items[i]);
+        PyObject *row = PyTuple_GET_ITEM(rows, i);
+        if (!THPVariable_Check(row)) return type_error("%s must hold contiguous 1-D float32 CUDA tensors of one length", name);
+        const at::Tensor &t = THPVariable_Unpack(row);
         if (t.scalar_type() != at::kFloat || !t.is_cuda() || t.dim() != 1 || t.size(0) != D || (D != 1 && t.stride(0) != 1))
             return type_error("%s must hold contiguous 1-D float32 CUDA tensors of one length", name);
         if (t.get_device() != device) {
@@ -183,11 +183,17 @@ bool row_pointers(PyObject *seq, const char *name, int64_t D, long device, std::
     return true;
 }
 
-struct Sequence { // a list or tuple, or a list of what the object yields
+struct Owned { // a reference, given back at the end
     PyObject *p;
-    explicit Sequence(PyObject *o) : p(PySequence_Fast(o, "X_rows and G_rows must be sequences")) {}
-    ~Sequence() { Py_XDECREF(p); }
+    ~Owned() { Py_XDECREF(p); }
 };
+
+// seq[0], or null with an error set
+PyObject *first_item(PyObject *seq)
+{
+    const Owned zero{PyLong_FromLong(0)};
+    return zero.p ? PyObject_GetItem(seq, zero.p) : nullptr;
+}
 
 // step_rows(handle, device, X_rows, G_rows, eps, stream)
 PyObject *step_rows(PyObject *, PyObject *const *a, Py_ssize_t na)
@@ -197,21 +203,29 @@ PyObject *step_rows(PyObject *, PyObject *const *a, Py_ssize_t na)
         void *h, *stream;
         const long device = PyLong_AsLong(a[1]);
         if (!word(a[0], h) || (device == -1 && PyErr_Occurred())) return nullptr;
-        const Sequence xs(a[2]);
-        if (!xs.p) return nullptr;
-        const Sequence gs(a[3]);
-        if (!gs.p) return nullptr;
-        const Py_ssize_t n = PySequence_Fast_GET_SIZE(xs.p);
-        if (n < 1 || PySequence_Fast_GET_SIZE(gs.p) != n) {
+        const Py_ssize_t n = PyObject_Size(a[2]), ng = n > 0 ? PyObject_Size(a[3]) : 0;
+        if (n < 0 || ng < 0) return nullptr;
+        if (n < 1 || ng != n) {
             PyErr_SetString(PyExc_ValueError, "X_rows and G_rows must be non-empty sequences of the same length");
             return nullptr;
         }
-        PyObject *first = PySequence_Fast_GET_ITEM(xs.p, 0);
-        if (!THPVariable_Check(first)) {
+        // X_rows[0] says how long all are.  What has no length or no order (a generator, a set) is refused: particles
+        // and scores would meet by chance.
+        const Owned first{first_item(a[2])};
+        if (!first.p) return nullptr;
+        if (!THPVariable_Check(first.p)) {
             type_error("%s must hold contiguous 1-D float32 CUDA tensors of one length", "X_rows");
             return nullptr;
         }
-        const int64_t D = THPVariable_Unpack(first).numel();
+        const int64_t D = THPVariable_Unpack(first.p).numel();
+        const Owned xs{PySequence_Tuple(a[2])}; // the rows are held until the call is done
+        if (!xs.p) return nullptr;
+        const Owned gs{PySequence_Tuple(a[3])};
+        if (!gs.p) return nullptr;
+        if (PyTuple_GET_SIZE(xs.p) != n || PyTuple_GET_SIZE(gs.p) != n) { // (not as many as they say)
+            PyErr_SetString(PyExc_ValueError, "X_rows and G_rows must be non-empty sequences of the same length");
+            return nullptr;
+        }
         std::vector<void *> x, g;
         double eps;
         if (!row_pointers(xs.p, "X_rows", D, device, x) || !row_pointers(gs.p, "G_rows", D, device, g) || !number(a[4], eps) ||

@@ -7,6 +7,44 @@ class _Stream:
     cuda_stream = 0
 
 
+class Wrapped(torch.Tensor):
+    """Says of itself that it is on a GPU, without one."""
+    @staticmethod
+    def __new__(cls, *size, strides=None, device="cuda:0", dtype=torch.float32):
+        return torch.Tensor._make_wrapper_subclass(cls, size, strides=strides, device=device, dtype=dtype)
+
+    @classmethod
+    def __torch_dispatch__(cls, func, types, args=(), kwargs=None):
+        raise NotImplementedError(func)
+
+
+def rows(n):
+    return [Wrapped(3) for _ in range(n)]
+
+
+class NoIndex:
+    def __len__(self):
+        return 2
+
+    def __iter__(self):
+        return iter(rows(2))
+
+
+class NoLength:
+    def __getitem__(self, i):
+        return rows(2)[i]
+
+
+class Indexed(NoLength):
+    def __len__(self):
+        return 2
+
+
+class Short(Indexed):
+    def __len__(self):
+        return 3
+
+
 @pytest.fixture
 def eng():
     """A handle without a device behind it: the checks come first."""
@@ -41,6 +79,35 @@ class _Yields:
 def test_first_argument_is_refused_before_the_second_is_looked_at(eng, second):
     with pytest.raises(TypeError):
         eng.step_rows(3, second, 0.1, stream=_Stream)
+
+
+@pytest.mark.parametrize("make", [lambda: set(rows(2)), lambda: (r for r in rows(2)), lambda: dict(enumerate(rows(2))).values(),
+                                  lambda: dict(enumerate(rows(2))), lambda: iter(rows(2)), NoIndex, NoLength, lambda: torch.tensor(1.0)])
+def test_particles_without_length_or_order_are_refused(eng, make):
+    """Also where there are as many scores, of whatever kind."""
+    for scores in (rows(2), make()):
+        with pytest.raises(TypeError):
+            eng.step_rows(make(), scores, 0.1, stream=_Stream)
+
+
+@pytest.mark.parametrize("make", [lambda: (r for r in rows(2)), lambda: iter(rows(2)), NoLength, lambda: torch.tensor(1.0), lambda: 5])
+def test_scores_without_a_length_are_refused(eng, make):
+    with pytest.raises(TypeError):
+        eng.step_rows(rows(2), make(), 0.1, stream=_Stream)
+
+
+@pytest.mark.parametrize("make", [list, tuple, lambda r: Indexed()])
+def test_sequences_reach_the_library(eng, make):
+    """All checks passed: the library is called, and refuses the handle that is none."""
+    from paper_2306_06528_amd import svgd
+    with pytest.raises(svgd.SvgdError, match="HANDLE"):
+        eng.step_rows(make(rows(2)), make(rows(2)), 0.1, stream=_Stream)
+
+
+def test_sequences_that_yield_fewer_than_they_say(eng):
+    for X, G in ((Short(), rows(3)), (rows(3), Short())):
+        with pytest.raises((ValueError, IndexError)):
+            eng.step_rows(X, G, 0.1, stream=_Stream)
 
 
 @pytest.mark.gpu
