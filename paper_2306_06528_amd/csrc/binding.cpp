@@ -14,7 +14,6 @@
 namespace {
 
 struct Matrix {
-    void *data;
     int64_t n, D, ld;
     bool operator!=(const Matrix &o) const { return n != o.n || D != o.D || ld != o.ld; }
     int rows() const { return n > INT_MAX ? INT_MAX : (int)n; } // (refused by the library)
@@ -43,9 +42,10 @@ bool matrix(PyObject *obj, const char *name, long device, Matrix &m)
         PyErr_Format(PyExc_ValueError, "%s is on cuda:%d, the handle on cuda:%ld", name, (int)t.get_device(), device);
         return false;
     }
-    m.data = t.data_ptr();
     return true;
 }
+
+void *data(PyObject *tensor) { return THPVariable_Unpack(tensor).data_ptr(); }
 
 bool same(const Matrix &x, const Matrix &m, const char *name)
 {
@@ -75,6 +75,19 @@ bool word(PyObject *obj, void *&out)
     return !(out == nullptr && PyErr_Occurred());
 }
 
+struct Owned { // a reference, given back at the end
+    PyObject *p;
+    ~Owned() { Py_XDECREF(p); }
+};
+
+// What stream_ptr makes of a stream object or of None.  Asked for behind the checks, like eps: both run code of the
+// caller's or need a GPU, and what is no tensor on one is to be named first.
+bool stream_of(PyObject *stream_ptr, PyObject *stream, void *&out)
+{
+    const Owned r{PyObject_CallFunctionObjArgs(stream_ptr, stream, nullptr)};
+    return r.p && word(r.p, out);
+}
+
 // C++ exceptions (a tensor without memory, a sparse one) as Python's
 template <class F>
 PyObject *guarded(F f)
@@ -99,75 +112,78 @@ bool arguments(Py_ssize_t got, Py_ssize_t want)
 // n of a call that succeeded, or its (negative) status
 PyObject *result(int rc, int64_t n) { return PyLong_FromLongLong(rc == SVGD_OK ? n : rc); }
 
-// step(handle, device, X, G, eps, stream)
+// step(handle, device, X, G, eps, stream, stream_ptr).  Pointers are taken last, behind everything that can run other code.
 PyObject *step(PyObject *, PyObject *const *a, Py_ssize_t na)
 {
     return guarded([&]() -> PyObject * {
-        if (!arguments(na, 6)) return nullptr;
+        if (!arguments(na, 7)) return nullptr;
         void *h, *stream;
         const long device = PyLong_AsLong(a[1]);
         Matrix x, g;
         double eps;
         if (!word(a[0], h) || (device == -1 && PyErr_Occurred()) || !matrix(a[2], "X", device, x) || !matrix(a[3], "G", device, g) ||
-            !same(x, g, "G") || !number(a[4], eps) || !word(a[5], stream))
+            !same(x, g, "G") || !number(a[4], eps) || !stream_of(a[6], a[5], stream))
             return nullptr;
+        void *const xp = data(a[2]), *const gp = data(a[3]);
         int rc;
         Py_BEGIN_ALLOW_THREADS
-        rc = svgd_step_ld((svgd_handle_t)h, (float *)x.data, (const float *)g.data, x.rows(), x.D, x.ld, (float)eps, stream);
+        rc = svgd_step_ld((svgd_handle_t)h, (float *)xp, (const float *)gp, x.rows(), x.D, x.ld, (float)eps, stream);
         Py_END_ALLOW_THREADS
         return result(rc, x.n);
     });
 }
 
-// phi(handle, device, X, G, PHI, stream)
+// phi(handle, device, X, G, PHI, stream, stream_ptr)
 PyObject *phi(PyObject *, PyObject *const *a, Py_ssize_t na)
 {
     return guarded([&]() -> PyObject * {
-        if (!arguments(na, 6)) return nullptr;
+        if (!arguments(na, 7)) return nullptr;
         void *h, *stream;
         const long device = PyLong_AsLong(a[1]);
         Matrix x, g, p;
         if (!word(a[0], h) || (device == -1 && PyErr_Occurred()) || !matrix(a[2], "X", device, x) || !matrix(a[3], "G", device, g) ||
-            !same(x, g, "G") || !matrix(a[4], "PHI", device, p) || !same(x, p, "PHI") || !word(a[5], stream))
+            !same(x, g, "G") || !matrix(a[4], "PHI", device, p) || !same(x, p, "PHI") || !stream_of(a[6], a[5], stream))
             return nullptr;
+        void *const xp = data(a[2]), *const gp = data(a[3]), *const pp = data(a[4]);
         int rc;
         Py_BEGIN_ALLOW_THREADS
-        rc = svgd_phi_ld((svgd_handle_t)h, (const float *)x.data, (const float *)g.data, x.rows(), x.D, x.ld, (float *)p.data, stream);
+        rc = svgd_phi_ld((svgd_handle_t)h, (const float *)xp, (const float *)gp, x.rows(), x.D, x.ld, (float *)pp, stream);
         Py_END_ALLOW_THREADS
         return result(rc, x.n);
     });
 }
 
-// step_static(current device, X, G, eps, stream): the status, or 1 for an X on another device (nothing done)
+// step_static(current_device, X, G, eps, stream, stream_ptr): the status, or 1 for an X on another device (nothing done)
 PyObject *step_static(PyObject *, PyObject *const *a, Py_ssize_t na)
 {
     return guarded([&]() -> PyObject * {
-        if (!arguments(na, 5)) return nullptr;
+        if (!arguments(na, 6)) return nullptr;
         void *stream;
-        const long device = PyLong_AsLong(a[0]);
         Matrix x, g;
         double eps;
-        if ((device == -1 && PyErr_Occurred()) || !matrix(a[1], "X", -1, x) || !matrix(a[2], "G", -1, g)) return nullptr;
+        if (!matrix(a[1], "X", -1, x) || !matrix(a[2], "G", -1, g)) return nullptr;
         if (g != x) {
             PyErr_SetString(PyExc_ValueError, "G must have the shape and row stride of X");
             return nullptr;
         }
-        if (!number(a[3], eps)) return nullptr;
+        const Owned current{PyObject_CallNoArgs(a[0])};
+        const long device = current.p ? PyLong_AsLong(current.p) : -1;
+        if (device == -1 && PyErr_Occurred()) return nullptr;
         if (THPVariable_Unpack(a[1]).get_device() != device) return PyLong_FromLong(1);
-        if (!word(a[4], stream)) return nullptr;
+        if (!number(a[3], eps) || !stream_of(a[5], a[4], stream)) return nullptr;
+        void *const xp = data(a[1]), *const gp = data(a[2]);
         int rc;
         Py_BEGIN_ALLOW_THREADS
-        rc = svgd_step_static((float *)x.data, (const float *)g.data, x.rows(), x.D, x.ld, (float)eps, stream);
+        rc = svgd_step_static((float *)xp, (const float *)gp, x.rows(), x.D, x.ld, (float)eps, stream);
         Py_END_ALLOW_THREADS
         return PyLong_FromLong(rc);
     });
 }
 
 // The rows of a tuple: 1-D float32 CUDA tensors of D contiguous elements on `device`.
-bool row_pointers(PyObject *rows, const char *name, int64_t D, long device, std::vector<void *> &out)
+bool check_rows(PyObject *rows, const char *name, int64_t D, long device)
 {
     const Py_ssize_t n = PyTuple_GET_SIZE(rows);
-    out.resize((size_t)n);
     for (Py_ssize_t i = 0; i < n; ++i) {
         PyObject *row = PyTuple_GET_ITEM(rows, i);
         if (!THPVariable_Check(row)) return type_error("%s must hold contiguous 1-D float32 CUDA tensors of one length", name);
@@ -178,15 +194,16 @@ bool row_pointers(PyObject *rows, const char *name, int64_t D, long device, std:
             PyErr_Format(PyExc_ValueError, "a row of %s is on cuda:%d, the handle on cuda:%ld", name, (int)t.get_device(), device);
             return false;
         }
-        out[(size_t)i] = t.data_ptr();
     }
     return true;
 }
 
-struct Owned { // a reference, given back at the end
-    PyObject *p;
-    ~Owned() { Py_XDECREF(p); }
-};
+std::vector<void *> row_pointers(PyObject *rows)
+{
+    std::vector<void *> out((size_t)PyTuple_GET_SIZE(rows));
+    for (size_t i = 0; i < out.size(); ++i) out[i] = data(PyTuple_GET_ITEM(rows, (Py_ssize_t)i));
+    return out;
+}
 
 // seq[0], or null with an error set
 PyObject *first_item(PyObject *seq)
@@ -195,11 +212,11 @@ PyObject *first_item(PyObject *seq)
     return zero.p ? PyObject_GetItem(seq, zero.p) : nullptr;
 }
 
-// step_rows(handle, device, X_rows, G_rows, eps, stream)
+// step_rows(handle, device, X_rows, G_rows, eps, stream, stream_ptr)
 PyObject *step_rows(PyObject *, PyObject *const *a, Py_ssize_t na)
 {
     return guarded([&]() -> PyObject * {
-        if (!arguments(na, 6)) return nullptr;
+        if (!arguments(na, 7)) return nullptr;
         void *h, *stream;
         const long device = PyLong_AsLong(a[1]);
         if (!word(a[0], h) || (device == -1 && PyErr_Occurred())) return nullptr;
@@ -226,11 +243,11 @@ PyObject *step_rows(PyObject *, PyObject *const *a, Py_ssize_t na)
             PyErr_SetString(PyExc_ValueError, "X_rows and G_rows must be non-empty sequences of the same length");
             return nullptr;
         }
-        std::vector<void *> x, g;
         double eps;
-        if (!row_pointers(xs.p, "X_rows", D, device, x) || !row_pointers(gs.p, "G_rows", D, device, g) || !number(a[4], eps) ||
-            !word(a[5], stream))
+        if (!check_rows(xs.p, "X_rows", D, device) || !check_rows(gs.p, "G_rows", D, device) || !number(a[4], eps) ||
+            !stream_of(a[6], a[5], stream))
             return nullptr;
+        const std::vector<void *> x = row_pointers(xs.p), g = row_pointers(gs.p);
         int rc;
         Py_BEGIN_ALLOW_THREADS
         rc = svgd_step_rows((svgd_handle_t)h, (float *const *)x.data(), (const float *const *)g.data(), n > INT_MAX ? INT_MAX : (int)n, D,

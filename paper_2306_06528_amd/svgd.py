@@ -177,10 +177,10 @@ def diag_read_rows(X: torch.Tensor, sink: torch.Tensor, pattern: int, stream=Non
 def step_static(X: torch.Tensor, G: torch.Tensor, eps: float, stream=None):
     """svgd_step_static: one plain step on the current device with the library's static scratch -
     no handle, nothing allocated.  X and G as in Svgd.step."""
-    rc = _step_static(_cuda_getDevice(), X, G, eps, _stream_ptr(stream))
+    rc = _step_static(_cuda_getDevice, X, G, eps, stream, _stream_ptr)
     if rc == 1:  # X is on another device: nothing has been done
         with torch.cuda.device(X.device):
-            rc = _step_static(_cuda_getDevice(), X, G, eps, _stream_ptr(stream))
+            rc = _step_static(_cuda_getDevice, X, G, eps, stream, _stream_ptr)
     if rc != SVGD_OK:
         raise SvgdError(rc)
 
@@ -238,7 +238,7 @@ class Svgd:
     def step(self, X, G, eps: float, stream=None):
         """X <- X + eps * phi(X, G) in place.  X and G: (n, D) with contiguous rows and the same
         row stride (dense, or views like buf[:, :D] of an (n, ld) buffer, see padded_rows)."""
-        n = _step(self._h.value or 0, self._device, X, G, eps, _stream_ptr(stream))
+        n = _step(self._h.value or 0, self._device, X, G, eps, stream, _stream_ptr)
         if n < 0:
             self._check(n)
         self._last_n = n
@@ -246,13 +246,13 @@ class Svgd:
     def step_rows(self, X_rows, G_rows, eps: float, stream=None):
         """svgd_step_rows: the particles are n separately allocated 1-D float32 CUDA tensors of equal
         length (X_rows[i], updated in place) with their scores (G_rows[i]); nothing is copied."""
-        n = _step_rows(self._h.value or 0, self._device, X_rows, G_rows, eps, _stream_ptr(stream))
+        n = _step_rows(self._h.value or 0, self._device, X_rows, G_rows, eps, stream, _stream_ptr)
         if n < 0:
             self._check(n)
         self._last_n = n
 
     def phi(self, X, G, PHI, stream=None):
-        n = _phi(self._h.value or 0, self._device, X, G, PHI, _stream_ptr(stream))
+        n = _phi(self._h.value or 0, self._device, X, G, PHI, stream, _stream_ptr)
         if n < 0:
             self._check(n)
         self._last_n = n

@@ -81,6 +81,57 @@ def test_first_argument_is_refused_before_the_second_is_looked_at(eng, second):
         eng.step_rows(3, second, 0.1, stream=_Stream)
 
 
+@pytest.mark.skipif(torch.cuda.is_available(), reason="of a machine without a GPU")
+def test_what_is_no_matrix_is_named_also_without_a_gpu(eng):
+    """The stream and the current device are asked for behind the checks."""
+    from paper_2306_06528_amd import svgd
+    X, row = torch.zeros(2, 3), [torch.zeros(3)]
+    for call in (lambda: eng.step(X, X, 0.1), lambda: eng.phi(X, X, X), lambda: eng.step_rows(row, row, 0.1), lambda: svgd.step_static(X, X, 0.1)):
+        with pytest.raises(TypeError, match="float32 CUDA tensor"):
+            call()
+
+
+class Number:
+    """An eps, or a stream, that runs `code` when it is asked for."""
+    def __init__(self, code):
+        self.code = code
+
+    def __float__(self):
+        self.code()
+        return 0.1
+
+    @property
+    def cuda_stream(self):
+        self.code()
+        return 0
+
+
+def test_eps_and_stream_are_asked_for_behind_the_checks(eng):
+    """And a list of rows that they empty is none of the call's any more."""
+    from paper_2306_06528_amd import svgd
+    asked = []
+    ask = Number(lambda: asked.append(1))
+    bad, X = Wrapped(2, 3, dtype=torch.float64), Wrapped(2, 3)
+    for call in (lambda: eng.step(X, bad, ask, stream=ask), lambda: eng.phi(X, X, bad, stream=ask), lambda: eng.step_rows([bad], [bad], ask, stream=ask),
+                 lambda: svgd.step_static(X, bad, ask, stream=ask)):
+        with pytest.raises(TypeError):
+            call()
+    assert not asked
+    X_rows, G_rows = rows(2), rows(2)
+    def empty():
+        asked.append(1)
+        X_rows.clear()
+        G_rows.clear()
+    with pytest.raises(svgd.SvgdError, match="HANDLE"):
+        eng.step_rows(X_rows, G_rows, Number(empty), stream=Number(empty))
+    assert len(asked) == 2
+    for eps, error in ((None, TypeError), ("x", ValueError), ([1.0], TypeError)):
+        with pytest.raises(error):
+            eng.step(X, X, eps, stream=_Stream)
+        with pytest.raises(error):
+            eng.step_rows(rows(2), rows(2), eps, stream=_Stream)
+
+
 @pytest.mark.parametrize("make", [lambda: set(rows(2)), lambda: (r for r in rows(2)), lambda: dict(enumerate(rows(2))).values(),
                                   lambda: dict(enumerate(rows(2))), lambda: iter(rows(2)), NoIndex, NoLength, lambda: torch.tensor(1.0)])
 def test_particles_without_length_or_order_are_refused(eng, make):
