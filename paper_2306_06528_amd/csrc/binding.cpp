@@ -4,6 +4,7 @@
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <climits>
@@ -88,18 +89,14 @@ bool stream_of(PyObject *stream_ptr, PyObject *stream, void *&out)
     return r.p && word(r.p, out);
 }
 
-// C++ exceptions (a tensor without memory, a sparse one) as Python's
+// Errors and warnings of torch as its own Python functions raise them: the error that a tensor subclass raised in Python,
+// the type of torch's, a warning through Python's filters.
 template <class F>
 PyObject *guarded(F f)
 {
-    try {
-        return f();
-    } catch (const c10::Error &e) {
-        PyErr_SetString(PyExc_RuntimeError, e.what_without_backtrace());
-    } catch (const std::exception &e) {
-        PyErr_SetString(PyExc_RuntimeError, e.what());
-    }
-    return nullptr;
+    HANDLE_TH_ERRORS
+    return f();
+    END_HANDLE_TH_ERRORS
 }
 
 bool arguments(Py_ssize_t got, Py_ssize_t want)

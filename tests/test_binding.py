@@ -132,6 +132,25 @@ def test_eps_and_stream_are_asked_for_behind_the_checks(eng):
             eng.step_rows(rows(2), rows(2), eps, stream=_Stream)
 
 
+class Sizeless(Wrapped):
+    """Asked for its size, it raises an error of its own."""
+    @staticmethod
+    def __new__(cls, *size):
+        return torch.Tensor._make_wrapper_subclass(cls, size, device="cuda:0", dtype=torch.float32, dispatch_sizes_strides_policy="sizes")
+
+    @classmethod
+    def __torch_dispatch__(cls, func, types, args=(), kwargs=None):
+        raise KeyError("no size")
+
+
+def test_errors_of_a_tensor_are_raised_as_they_are(eng):
+    from paper_2306_06528_amd import svgd
+    for call in (lambda: eng.step(Sizeless(2, 3), Wrapped(2, 3), 0.1, stream=_Stream), lambda: eng.phi(Wrapped(2, 3), Sizeless(2, 3), None, stream=_Stream),
+                 lambda: eng.step_rows([Sizeless(3)], rows(1), 0.1, stream=_Stream), lambda: svgd.step_static(Sizeless(2, 3), None, 0.1, stream=_Stream)):
+        with pytest.raises(KeyError, match="no size"):
+            call()
+
+
 @pytest.mark.parametrize("make", [lambda: set(rows(2)), lambda: (r for r in rows(2)), lambda: dict(enumerate(rows(2))).values(),
                                   lambda: dict(enumerate(rows(2))), lambda: iter(rows(2)), NoIndex, NoLength, lambda: torch.tensor(1.0)])
 def test_particles_without_length_or_order_are_refused(eng, make):
