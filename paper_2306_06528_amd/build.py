@@ -1,5 +1,5 @@
 """Build the C-ABI library (csrc/*.hip -> libsvgd.so) for gfx950 with hipcc, and what Python calls it through
-(csrc/binding.cpp -> _binding.so, host code against torch's C++ interface)."""
+(csrc/binding.cpp -> _binding.<ABI of this Python>.so, host code against torch's C++ interface)."""
 import glob
 import os
 import subprocess
@@ -10,7 +10,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 SOURCES = sorted(glob.glob(os.path.join(HERE, "csrc", "*.hip")))
 LIB = os.path.join(HERE, "libsvgd.so")
-BINDING = os.path.join(HERE, "_binding.so")
+BINDING = os.path.join(HERE, "_binding" + sysconfig.get_config_var("EXT_SUFFIX"))  # (another Python does not take it for its own)
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
@@ -31,7 +31,8 @@ def _binding_flags():
     from torch.utils.cpp_extension import include_paths, library_paths
     includes = [f"-I{p}" for p in include_paths() + [sysconfig.get_paths()["include"]]]
     libs = [f for p in library_paths() for f in (f"-L{p}", f"-Wl,-rpath,{p}")]
-    return (["-O2", "-std=c++17", "-fPIC", "-w", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", *includes],
+    return (["-O2", "-std=c++17", "-fPIC", "-w", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+             f'-DSVGD_TORCH_VERSION="{torch.__version__}"', *includes],
             [f"-L{HERE}", "-Wl,-rpath,$ORIGIN", "-lsvgd", *libs, "-ltorch_python", "-ltorch_cpu", "-lc10"])
 
 

@@ -260,4 +260,12 @@ PyModuleDef definition = {PyModuleDef_HEAD_INIT, "_binding", nullptr, -1, method
 
 } // namespace
 
-PyMODINIT_FUNC PyInit__binding() { return PyModule_Create(&definition); }
+PyMODINIT_FUNC PyInit__binding()
+{
+    PyObject *m = PyModule_Create(&definition);
+    if (m && PyModule_AddStringConstant(m, "torch_version", SVGD_TORCH_VERSION) < 0) { // (whose C++ interface this is built against)
+        Py_DECREF(m);
+        return nullptr;
+    }
+    return m;
+}

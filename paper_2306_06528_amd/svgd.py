@@ -24,7 +24,17 @@ if not os.path.exists(LIB_PATH):
         f"{LIB_PATH} is missing: build it first (python -m paper_2306_06528_amd.build, or "
         "__graft_entry__.build()); there is no fallback implementation")
 _lib = ctypes.CDLL(LIB_PATH)
-from . import _binding  # noqa: E402  (built beside the library: the calls whose tensors are checked in native code)
+try:  # built beside the library: the calls whose tensors are checked in native code
+    from . import _binding
+    _built_for = _binding.torch_version
+except (ImportError, AttributeError) as e:
+    raise ImportError(
+        f"the binding beside {LIB_PATH} is missing or of another Python or torch ({e}): build it first (python -m "
+        "paper_2306_06528_amd.build, or __graft_entry__.build()); there is no fallback implementation") from e
+if _built_for != torch.__version__:
+    raise ImportError(
+        f"the binding beside {LIB_PATH} was built for torch {_built_for}, this is {torch.__version__}: build it again "
+        "(python -m paper_2306_06528_amd.build, or __graft_entry__.build())")
 
 _H = ctypes.c_void_p
 _lib.svgd_create.argtypes = [ctypes.POINTER(_H), ctypes.c_int, ctypes.c_int64, ctypes.c_int, ctypes.c_uint32]

@@ -1,4 +1,9 @@
 """The checks that stand before the library, in native code: what is refused and how, and what is taken."""
+import os
+import shutil
+import subprocess
+import sys
+
 import pytest
 import torch
 
@@ -130,6 +135,23 @@ def test_eps_and_stream_are_asked_for_behind_the_checks(eng):
             eng.step(X, X, eps, stream=_Stream)
         with pytest.raises(error):
             eng.step_rows(rows(2), rows(2), eps, stream=_Stream)
+
+
+@pytest.mark.parametrize("binding", ["missing", "untagged", "of_another_torch"])
+def test_a_binding_that_does_not_fit_names_the_build(tmp_path, binding):
+    from paper_2306_06528_amd import _binding, svgd
+    package = tmp_path / "paper_2306_06528_amd"
+    package.mkdir()
+    here = os.path.dirname(svgd.__file__)
+    for name in ("__init__.py", "svgd.py", "libsvgd.so"):
+        shutil.copy(os.path.join(here, name), package)
+    assert ".cpython-" in os.path.basename(_binding.__file__)  # no other interpreter takes it for its own
+    if binding == "untagged":
+        (package / "_binding.so").write_bytes(b"")
+    if binding == "of_another_torch":
+        (package / "_binding.py").write_text("torch_version = '0.0'\n")
+    got = subprocess.run([sys.executable, "-c", "import paper_2306_06528_amd.svgd"], cwd=tmp_path, capture_output=True, text=True, timeout=300)
+    assert got.returncode and "ImportError" in got.stderr and "paper_2306_06528_amd.build" in got.stderr.splitlines()[-1]
 
 
 class Sizeless(Wrapped):
