@@ -22,16 +22,16 @@ def _run(cmd):
     res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     out = "\n".join(l for l in res.stdout.splitlines() if "packed-fp32-ops" not in l)
     if res.returncode != 0:
-        raise RuntimeError("hipcc failed:\n" + out)
+        raise RuntimeError(f"{cmd[0]} failed:\n" + out)
     return out
 
 
 def _binding_flags():
     import torch
     from torch.utils.cpp_extension import include_paths, library_paths
-    includes = [f"-I{p}" for p in include_paths() + [sysconfig.get_paths()["include"]]]
+    includes = [f for p in include_paths() + [sysconfig.get_paths()["include"]] for f in ("-isystem", p)]  # (their warnings are not ours)
     libs = [f for p in library_paths() for f in (f"-L{p}", f"-Wl,-rpath,{p}")]
-    return (["-O2", "-std=c++17", "-fPIC", "-w", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+    return (["-O2", "-std=c++17", "-fPIC", "-Wall", "-Wextra", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
              f'-DSVGD_TORCH_VERSION="{torch.__version__}"', *includes],
             [f"-L{HERE}", "-Wl,-rpath,$ORIGIN", "-lsvgd", *libs, "-ltorch_python", "-ltorch_cpu", "-lc10"])
 

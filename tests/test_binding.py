@@ -258,3 +258,9 @@ def test_what_is_taken():
         col, gc = torch.randn(n, 3, device="cuda")[:, :1], torch.randn(n, 3, device="cuda")[:, :1]
         eng.step(col, gc, 0.25)  # a single column
         assert bool(torch.isfinite(col).all())
+
+
+def test_a_failed_build_names_the_compiler():
+    from paper_2306_06528_amd import build
+    with pytest.raises(RuntimeError, match=r"^g\+\+ failed"):
+        build._run(["g++", "-c", os.path.join(os.path.dirname(__file__), "no_such_file.cpp")])
