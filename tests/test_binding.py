@@ -137,6 +137,48 @@ def test_eps_and_stream_are_asked_for_behind_the_checks(eng):
             eng.step_rows(rows(2), rows(2), eps, stream=_Stream)
 
 
+def _outcome(call):
+    from paper_2306_06528_amd import svgd
+    try:
+        call()
+    except svgd.SvgdError:
+        return "taken"  # by the library, which refuses the handle that is none
+    except (TypeError, ValueError) as e:
+        return type(e), str(e)
+    return "taken"
+
+
+@pytest.mark.parametrize("X", [
+    Wrapped(2, 3), Wrapped(1, 3), Wrapped(2, 1), Wrapped(1, 1), Wrapped(0, 3), Wrapped(2, 0), Wrapped(0, 0), Wrapped(6), Wrapped(2, 3, 1), Wrapped(),
+    Wrapped(2, 3, strides=(5, 1)), Wrapped(2, 3, strides=(2, 1)), Wrapped(2, 3, strides=(0, 1)), Wrapped(2, 3, strides=(1, 2)), Wrapped(2, 3, strides=(6, 2)),
+    Wrapped(1, 3, strides=(7, 1)), Wrapped(1, 3, strides=(1, 1)), Wrapped(1, 3, strides=(3, 2)), Wrapped(2, 1, strides=(3, 2)), Wrapped(2, 1, strides=(1, 9)),
+    Wrapped(2, 1, strides=(0, 1)), Wrapped(1, 1, strides=(0, 0)), Wrapped(0, 3, strides=(1, 1)),
+    Wrapped(2, 3, dtype=torch.float64), Wrapped(2, 3, dtype=torch.bfloat16), Wrapped(2, 3, device="cuda:1"), Wrapped(2, 3, device="cpu"),
+    Wrapped(1, 3, device="cuda:1"), torch.zeros(2, 3), None, [[1.0]]], ids=lambda X: f"{tuple(X.shape)}{X.stride()}{X.dtype}{X.device}" if torch.is_tensor(X) else str(X))
+def test_native_checks_are_those_of_the_calls_that_check_in_python(eng, X):
+    """svgd_bandwidth's matrix is checked in Python (svgd._rows_of), those of step, phi and step_static in native code."""
+    from paper_2306_06528_amd import svgd
+    want = _outcome(lambda: eng._rows(X, "X"))
+    assert _outcome(lambda: eng.step(X, X, 0.1, stream=_Stream)) == want
+    assert _outcome(lambda: eng.phi(X, X, X, stream=_Stream)) == want
+    G = Wrapped(2, 3)
+    for x in (X, G):
+        def check():
+            shape = svgd._rows_of(x, "X")
+            if svgd._rows_of(X, "G") != shape:
+                raise ValueError("G must have the shape and row stride of X")
+            raise TypeError("eps")
+        class Eps:
+            def __float__(self):
+                raise TypeError("eps")
+        if not torch.cuda.is_available():  # (without one, nothing is known of the current device)
+            svgd_device, svgd._cuda_getDevice = svgd._cuda_getDevice, lambda: x.get_device()
+            try:
+                assert _outcome(lambda: svgd.step_static(x, X, Eps(), stream=_Stream)) == _outcome(check)
+            finally:
+                svgd._cuda_getDevice = svgd_device
+
+
 @pytest.mark.parametrize("binding", ["missing", "untagged", "of_another_torch"])
 def test_a_binding_that_does_not_fit_names_the_build(tmp_path, binding):
     from paper_2306_06528_amd import _binding, svgd
