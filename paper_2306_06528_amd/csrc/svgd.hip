@@ -336,11 +336,11 @@ int update_workers(const svgd_ctx *c, int n, int64_t D, int64_t ld, int cap)
 // Up to kFusedMaxN particles the update kernel does pass 2 itself, in every workgroup, if that costs
 // less than the launches it saves: 256 threads hold at most 496 pairs comfortably, and every
 // workgroup reads the whole list, in batches of sixteen 16-byte loads per thread, one after the
-// other (gather_sums).  Up to four batches it wins clearly, at five still, from six on now the one and now the
-// other (the list is then summed by a launch of many workgroups): us per step on dense rows, in one launch and apart, n = 24,
-// D = 40,003 (4 batches) 17.1 and 19.2, D = 50,001 (5) 18.0 and 19.8; n = 28, D = 65,000 (8) 21.1 and 20.9; n = 32,
-// D = 12,289 (4) 16.6 and 18.4, D = 20,001 (5) 18.0 and 19.6, D = 30,001 (8) 20.1 and 19.8; carried sums, padded,
-// n = 24, D = 65,000 (6) 16.5 and 17.0, n = 31 19.3 and 17.9.
+// other (gather_sums).  Up to four batches it wins; a longer list is summed by a launch of many workgroups, and the update
+// does pass 2 on the sums (see kSumsMaxN).  us per step on dense rows, on the list, with pass 2 in a launch of its own and on sums:
+// n = 24, D = 40,003 (4 batches) 17.1, 19.2 and -, D = 50,001 (5) 18.0, 18.2 to 19.8 and 15.9; n = 32, D = 12,289 (4) 16.6, 18.4
+// and -, D = 20,001 (5) 18.0, 17.7 to 19.6 and 15.6, D = 30,001 (8) 20.1, 18.1 to 19.8 and 15.8; carried sums, padded,
+// n = 24, D = 65,000 (6) 16.5, 17.0 and -, n = 31 19.3, 17.9 and -.
 // On the vector-ALU path every list is that short (run_gram sees to it), and one launch wins up to the
 // largest sizes (n = 8, D = 11,173,962: 281 -> 270 us; n = 10, D = 300,001: 31 -> 24).
 constexpr int kFusedMaxN = 32;
@@ -533,17 +533,15 @@ bool store_directly(int n, int64_t D, bool emit, bool carry)
 
 // 21 to kSumsMaxN particles and a list too long to be read by every workgroup: a launch of many workgroups sums it, and
 // the update's workgroups start with pass 2 on the sums - a launch less than with pass 2 in between, and the tile's first
-// loads and the tables of C are no longer waited for behind it.  us per step, apart and inside: n = 24, dense, D = 120,011
-// 23.6 and 21.5, n = 32, D = 120,011 26.9 and 23.3, carried, padded 25.1 and 19.6, n = 33, D = 25,003 21.8 and 20.1, n = 40,
+// loads and the tables of C are no longer waited for behind it.  us per step, apart and inside: n = 24, dense, D = 50,001
+// 18.2 and 15.9, D = 120,011 23.6 and 21.5, n = 28, carried, padded, D = 40,003 15.6 and 13.7, n = 32, D = 16,403 17.7 and 15.2,
+// phi 17.1 and 14.9, D = 120,011 26.9 and 23.3, carried, padded 25.1 and 19.6, n = 33, D = 25,003 21.8 and 20.1, n = 40,
 // D = 50,021, plain 25.6 and 23.9, n = 48 26.6 and 25.2; separate rows, n = 24, D = 1,500,001 120.9 and 118.4, padded, n = 32,
 // D = 2,000,000 195.4 and 193.9.  From 49 particles on 256 threads take longer for pass 2 than the 1024 of a launch of its
 // own and that launch together (n = 50, D = 50,021 30.3 and 30.1, n = 56 32.9 and 33.4, n = 64 32.4 and 34.0).
 // Not with re-aligned stores (two instances per kernel instead of three or four), and only where all workgroups are resident
-// without a tile more for any wave.  Above 32 particles a list that the launch of pass 2 sums by itself saves no launch.  Up to
-// 32 the line is the number of columns: the launches of shorter rows are what they have been (n = 24, D = 50,001, n = 32,
-// D = 20,001 and 50,000 are held to them by tests), though on sums they would be 9 % faster, too.
+// without a tile more for any wave.  Above 32 particles a list that the launch of pass 2 sums by itself saves no launch.
 constexpr int kSumsMaxN = 48;
-constexpr int64_t kSumsMinColumns = 50 * 1024;
 
 // Passes 2 and 3.  EMIT = false: X updated in place; EMIT = true: phi written to PHI.  CARRY (in
 // place): the update also leaves the pair-sum partials of the new X in the scratch, described by
@@ -575,7 +573,7 @@ int run_update(svgd_ctx *c, float *X, const float *G, float *PHI, int n, int64_t
         const bool adapt = w > 0 && (sums_inside || (n <= kFusedMaxN && (CARRY ? w + ((D & 63) ? 1 : 0) <= fused_max_parts(n) : fused)));
         if (adapt) workers = w;
         fused = fused && workers == w;
-        from_sums = !fused && sums_inside && (n <= kFusedMaxN ? D > kSumsMinColumns : (int64_t)list.nparts * pair_stride(n) > kDirectMaxFloats);
+        from_sums = !fused && sums_inside && (n <= kFusedMaxN || (int64_t)list.nparts * pair_stride(n) > kDirectMaxFloats);
     }
     int64_t out_off = c->captured ? c->home : 0;
     if (from_sums) {

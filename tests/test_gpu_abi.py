@@ -70,9 +70,9 @@ def test_binding_raises(mod):
 
 
 def test_profiling_selects_kernel_kinds(mod):
-    X = torch.randn(32, 50_000, device="cuda")
+    X = torch.randn(64, 50_000, device="cuda")  # all four kinds
     G = torch.randn_like(X)
-    with mod.Svgd(32, 50_000) as eng:
+    with mod.Svgd(64, 50_000) as eng:
         eng.profile_begin()
         eng.step(X, G, 0.01)
         prof = eng.profile_end()

@@ -1,5 +1,5 @@
 """21 to 48 particles and a list of partial sums too long for every workgroup to read: a launch sums it, the update does
-pass 2 on the sums.  Sizes at the rule's edges: the shortest such rows and lists and one below, columns after the last tile or none,
+pass 2 on the sums.  Sizes at the rule's edges: the shortest such lists and one partial less, columns after the last tile or none,
 full and padded blocks of rows, rows on top of them."""
 import pytest
 import torch
@@ -16,11 +16,16 @@ def _launches(svgd, eng, call):
     return [prof[k][1] for k in svgd.KERNEL_KINDS]
 
 
-@pytest.mark.parametrize("n,D,inside", [
-    (24, 51_203, True), (28, 51_201, True), (28, 51_199, False), (32, 52_003, True), (32, 65_536, True),
-    (33, 7_500, True), (33, 7_400, False), (36, 131_072, True), (37, 6_000, True), (44, 70_001, True), (48, 3_400, True),
-    (48, 3_300, False), (48, 65_600, True), (49, 3_400, False)])
-def test_pass_2_on_sums(n, D, inside):
+# launches of a step: the list read by the update, summed for it, or pass 2 apart (with the list read there or summed before)
+ON_LIST, ON_SUMS, APART, APART_ON_SUMS = [1, 0, 0, 1], [1, 1, 0, 1], [1, 0, 1, 1], [1, 1, 1, 1]
+
+
+@pytest.mark.parametrize("n,D,launches", [
+    (22, 70_001, ON_LIST), (23, 49_152, ON_LIST), (23, 49_153, ON_SUMS), (24, 49_150, ON_LIST), (24, 51_203, ON_SUMS), (28, 32_768, ON_LIST), (28, 32_769, ON_SUMS),
+    (32, 16_384, ON_LIST), (32, 16_385, ON_SUMS), (32, 52_003, ON_SUMS), (32, 65_536, ON_SUMS),
+    (33, 7_500, ON_SUMS), (33, 7_400, APART), (36, 131_072, ON_SUMS), (37, 6_000, ON_SUMS), (44, 70_001, ON_SUMS), (48, 3_400, ON_SUMS),
+    (48, 3_300, APART), (48, 65_600, ON_SUMS), (49, 3_400, APART_ON_SUMS)])
+def test_pass_2_on_sums(n, D, launches):
     from paper_2306_06528_amd import svgd
     assert torch.cuda.get_device_properties(0).multi_processor_count == 256
     g = torch.Generator().manual_seed(n + D)
@@ -31,9 +36,8 @@ def test_pass_2_on_sums(n, D, inside):
     rows, grows = [X[i].clone() for i in range(n)], [G[i].clone() for i in range(n)]
     with svgd.Svgd(n, D) as eng:
         for call in (lambda: eng.phi(X, G, PHI), lambda: eng.step(X, G, 0.05), lambda: eng.step_rows(rows, grows, 0.05)):
-            got = _launches(svgd, eng, call)
-            assert got == [1, 1, 0, 1] if inside else got[0] == 1 and got[2:] == [1, 1]
-            h, K = eng.get_last(n)  # workgroup 0 of the update leaves them
+            assert _launches(svgd, eng, call) == launches
+            h, K = eng.get_last(n)  # workgroup 0 of the update leaves them, where pass 2 is done there
             assert abs(h - svgd_h(old)) <= 1e-5 * h and float(K[0, 0]) == 1.0
     assert ulp_diff_device(X, old, PHI, 0.05) <= 1.0
     assert ulp_diff_device(torch.stack(rows), old, PHI, 0.05) <= 1.0
