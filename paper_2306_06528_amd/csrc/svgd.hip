@@ -300,10 +300,6 @@ bool beyond_cache(int n, int64_t ld)
 // stores, see run_update).
 bool adjacent_tiles(int n, int64_t ld) { return n > 48 || beyond_cache(n, ld); }
 
-// The instances of the matrix-core update whose blocks of rows are full, and all above 32 particles, take the registers of a
-// whole CU with one workgroup; the others leave room for a second.
-bool takes_whole_cu(int n) { return n > 32 || (n & 15) == 0 || has_remainder_rows(n); }
-
 // Worker workgroups of the matrix-core update (each walks ranges of 64-column tiles; one more
 // workgroup does D mod 64): one per CU - the kernel overlaps its own loads with its multiplies, and
 // fewer concurrent row streams keep more HBM pages open.  Exception: 21 to 24 particles, whose
@@ -317,19 +313,12 @@ bool takes_whole_cu(int n) { return n > 32 || (n & 15) == 0 || has_remainder_row
 // costs 9 %).
 // The Gram pass splits the tiles the same way.  `cap` bounds the grid, the tail's workgroup included.
 // (D mod 64 = 0: no workgroup for the tail.)
-// Where a workgroup takes all registers of its CU, a tail's workgroup on top of a worker for every CU starts when the first
-// of those ends: up to kTailRoomTiles tiles per wave there is one worker less.  us per step with 256 and 255 workers:
-// n = 48, D = 120,011, padded, carried sums 35.0 and 28.6, n = 64 48.0 and 39.7, plain, dense 51.4 and 45.8; D = 300,007 (five
-// tiles per wave) 74.1 and 68.4, plain 91.3 and 90.2; D = 800,003 (12) 138.2 and 137.7.  Beyond, the workgroups end so
-// far apart that the tail is done in time, and a worker less costs its share (n = 64, D = 11,173,962, carried
-// sums 1698 and 1715).
-constexpr int kTailRoomTiles = 16;
-int update_workers(const svgd_ctx *c, int n, int64_t D, int64_t ld, int cap)
+// One worker less where that makes room for the tail's workgroup (leaves_room_for_tail).
+int update_workers(const svgd_ctx *c, int n, int64_t D, int64_t ld, int cap, bool aligned, bool emit, bool carry)
 {
     const int64_t nfull = D / 64;
     const int per_cu = (n >= 17 && n <= 24 && !has_remainder_rows(n) && beyond_cache(n, ld)) ? 2 : 1;
-    const bool room = takes_whole_cu(n) && (D & 63) && nfull <= (int64_t)kTailRoomTiles * 4 * c->num_cu && c->num_cu > 1;
-    const int max_workers = mini(c->num_cu * per_cu - (room ? 1 : 0), cap - 1);
+    const int max_workers = mini(c->num_cu * per_cu - (leaves_room_for_tail(n, D, c->num_cu, aligned, emit, carry) ? 1 : 0), cap - 1);
     return clampi((nfull + 3) / 4, 1, max_workers);
 }
 
@@ -405,7 +394,7 @@ int run_gram(svgd_ctx *c, const float *X, int n, int64_t D, int64_t ld, hipStrea
         // tiles three quarters of the memory-side cache can hold
         const bool aligned_next = G_next && x_aligned && (rt || rows_aligned(G_next, ld));
         const bool shared_ranges = aligned_next && adjacent_tiles(n, ld);
-        int64_t nranges = (int64_t)update_workers(c, n, D, ld, carry_next ? cap_parts : kMaxParts) * (shared_ranges ? 1 : 4);
+        int64_t nranges = (int64_t)update_workers(c, n, D, ld, carry_next ? cap_parts : kMaxParts, aligned_next, false, carry_next) * (shared_ranges ? 1 : 4);
         int64_t per = (nfull + nranges - 1) / nranges > 0 ? (nfull + nranges - 1) / nranges : 1;
         int64_t hot = (3 * kMemorySideCacheBytes / 4) / ((int64_t)n * 256) / nranges;
         if (shared_ranges) hot &= ~(int64_t)3; // four waves share the start of a range
@@ -498,18 +487,14 @@ int run_bandwidth(svgd_ctx *c, int n, const PairList &list, hipStream_t s)
 // particles (n = 15, same D, padded: 17.8 and 14.2); otherwise two workgroups share a CU (n = 15,
 // plain step: 17.5, 21.1 with a tile more; n = 21, carried: 23.8 and 27.3).
 // Returns the number of workers, 0: not as one launch (21 particles or more only).
-int fused_workers(const svgd_ctx *c, int n, int64_t D, int64_t ld, int workers, bool carry)
+int fused_workers(const svgd_ctx *c, int n, int64_t D, int workers, bool carry)
 {
     const bool full_rows = takes_whole_cu(n);
-    const int64_t nfull = D / 64, ranges = adjacent_tiles(n, ld) ? 1 : 4; // per workgroup
-    auto tiles_per_wave = [&](int64_t w) {
-        const int64_t per = (nfull + w * ranges - 1) / (w * ranges);
-        return ranges == 1 ? (per + 3) / 4 : per;
-    };
+    const int64_t nfull = D / 64;
     for (int per_cu = 1; per_cu <= (full_rows ? 1 : 2); ++per_cu) {
         const int room = std::max(c->num_cu * per_cu - ((D & 63) ? 1 : 0), 1);
         if (workers <= room) return workers;
-        if (full_rows || (carry && n < 16) || tiles_per_wave(room) == tiles_per_wave(workers)) return room;
+        if (full_rows || (carry && n < 16) || tiles_per_wave(nfull, room) == tiles_per_wave(nfull, workers)) return room;
     }
     return 0;
 }
@@ -564,8 +549,8 @@ int run_update(svgd_ctx *c, float *X, const float *G, float *PHI, int n, int64_t
     const bool aligned = rt ? rt->aligned != 0 : rows_aligned(X, ld) && rows_aligned(G, ld) && (!EMIT || rows_aligned(PHI, ld));
     const bool direct = !rt && store_directly(n, D, EMIT, CARRY);
     if (n > kValuMaxN) {
-        workers = update_workers(c, n, D, ld, out_cap);
-        const int w = fused_workers(c, n, D, ld, workers, CARRY);
+        workers = update_workers(c, n, D, ld, out_cap, aligned, EMIT, CARRY);
+        const int w = fused_workers(c, n, D, workers, CARRY);
         // (CARRY: by n, D and ld alone, see below)
         const bool sums_inside = n > kFusedAlwaysN && n <= kSumsMaxN && (w == workers || (w > 0 && !takes_whole_cu(n))) && (direct || (!CARRY && aligned));
         // CARRY: the number of workgroups, which is that of the carried partial sums, depends on the

@@ -2,6 +2,7 @@
 // files of their own (update_*.hip), one per kind of call and half of the particle counts, so that
 // they build side by side.
 #pragma once
+#include "launch_rules.hpp"
 #include "update_kernels.hpp"
 
 namespace svgd {
@@ -23,9 +24,6 @@ struct UpdateCall {
     int store;  // StoreMode
     int pass2;  // Pass2
 };
-
-// One to four particles beyond a multiple of 16 ride along as remainder rows of the kernel for that multiple.
-inline bool has_remainder_rows(int n) { return n > 16 && (n & 15) >= 1 && (n & 15) <= 4; }
 
 template <int NB, bool EMIT, bool CARRY, bool FULL, bool REM, int P2>
 void launch_update_instance(const UpdateCall &c)

@@ -43,6 +43,30 @@ def test_pass_2_on_sums(n, D, launches):
     assert ulp_diff_device(torch.stack(rows), old, PHI, 0.05) <= 1.0
 
 
+@pytest.mark.parametrize("n,D,launches", [(33, 65_407, APART_ON_SUMS), (44, 65_407, APART_ON_SUMS), (44, 65_563, ON_SUMS), (33, 131_070, APART_ON_SUMS), (33, 196_100, ON_SUMS),
+                                          (48, 196_100, ON_SUMS), (52, 65_407, APART_ON_SUMS), (64, 131_070, APART_ON_SUMS)])
+def test_where_a_worker_less_costs_a_tile(n, D, launches):
+    """Just below a multiple of 1,024 tiles of 64 columns (a device of 256 CUs): 256 workers and the tail's workgroup for most plain
+    steps with two or three tiles per wave; 255, and pass 2 on the sums, for phi and on carried sums up to 48 particles (dense rows)."""
+    from paper_2306_06528_amd import svgd
+    g = torch.Generator(device="cuda").manual_seed(n + D)
+    X, G = 0.3 * torch.randn(n, D, device="cuda", generator=g), torch.randn(n, D, device="cuda", generator=g)
+    old, PHI = X.clone(), torch.empty_like(X)
+    inside = ON_SUMS if n <= 48 else APART_ON_SUMS
+    with svgd.Svgd(n, D) as eng:
+        assert _launches(svgd, eng, lambda: eng.phi(X, G, PHI)) == inside
+        assert _launches(svgd, eng, lambda: eng.step(X, G, 0.05)) == launches
+        h, K = eng.get_last(n)
+        assert abs(h - svgd_h(old)) <= 1e-5 * h
+    assert ulp_diff_device(X, old, PHI, 0.05) <= 1.0
+    with svgd.Svgd(n, D, flags=svgd.FLAG_CARRY_GRAM) as eng:
+        Y = old.clone()
+        assert _launches(svgd, eng, lambda: eng.step(Y, G, 0.05)) == inside
+        assert _launches(svgd, eng, lambda: eng.step(Y, G, 0.05)) == [0] + inside[1:]
+        h, K = eng.get_last(n)
+        assert abs(h - svgd_h(X)) <= 1e-5 * h
+
+
 def svgd_h(X):
     """The median bandwidth in 64 bits."""
     Y = X.double() - X.double().mean(0, keepdim=True)

@@ -1,0 +1,79 @@
+"""How the matrix-core update's work is split, as far as numbers decide it: compiled for the host and asked."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+CUS = 256
+
+PROGRAM = r"""
+#include <cstdio>
+#include "launch_rules.hpp"
+int main()
+{
+    long long n, D;
+    int aligned, emit, carry;
+    while (std::scanf("%lld %lld %d %d %d", &n, &D, &aligned, &emit, &carry) == 5) {
+        const bool room = svgd::leaves_room_for_tail((int)n, D, 256, aligned, emit, carry);
+        std::printf("%d %lld\n", room, (long long)svgd::tiles_per_wave(D / 64, 256 - room));
+    }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    if shutil.which("g++") is None:
+        pytest.skip("g++ not installed")
+    d = tmp_path_factory.mktemp("rules")
+    (d / "rules.cpp").write_text(PROGRAM)
+    csrc = os.path.join(HERE, "..", "paper_2306_06528_amd", "csrc")
+    subprocess.run(["g++", "-std=c++17", "-I", csrc, "-o", str(d / "rules"), str(d / "rules.cpp")], check=True, timeout=120)
+
+    def ask(cases):
+        text = "".join("%d %d %d %d %d\n" % c for c in cases)
+        out = subprocess.run([str(d / "rules")], input=text, capture_output=True, text=True, check=True, timeout=120).stdout
+        return [tuple(map(int, line.split())) for line in out.splitlines()]
+    return ask
+
+
+# (rows on 128-byte boundaries, phi written out, carried sums)
+STEP, PHI, CARRY, STEP_PADDED, PHI_PADDED, CARRY_PADDED = KINDS = [(a, e, c) for a in (0, 1) for e, c in ((0, 0), (1, 0), (0, 1))]
+
+
+def test_a_worker_less_gives_no_wave_a_tile_more_unless_measured_to_be_faster(rules):
+    cases = [(n, 64 * t + 1, *k) for n in range(13, 65) for t in [*range(1, 4200, 5), *range(1000, 16500, 61), *(1024 * k + d for k in range(1, 16) for d in range(-17, 2))]
+             for k in KINDS]
+    whole = lambda n: n > 32 or n % 16 == 0 or (n > 16 and 1 <= n % 16 <= 4)
+    seen = 0
+    for (n, D, _, e, c), (room, tiles) in zip(cases, rules(cases)):
+        t = D // 64
+        before, after = -(-t // (4 * CUS)), -(-t // (4 * (CUS - 1)))
+        assert tiles == (after if room else before)
+        if not whole(n) or t > 16 * 4 * CUS:
+            assert not room
+        elif before == after:
+            assert room
+        elif room:
+            seen += 1
+            assert c or n <= 48  # carried sums, or a launch less
+            assert after <= (16 if n <= 36 else 5)
+    assert seen
+
+
+@pytest.mark.parametrize("n,tiles,kind,room", [
+    # measured to be slower with a tile more, by 3 to 13 %
+    (33, 1021, STEP_PADDED, False), (48, 1022, STEP_PADDED, False), (48, 1022, PHI_PADDED, False), (44, 1023, STEP, False), (44, 2048, STEP_PADDED, False),
+    (48, 1024, STEP_PADDED, False), (44, 2046, PHI, False), (40, 6130, PHI_PADDED, False), (33, 12_270, CARRY_PADDED, False), (40, 8180, CARRY_PADDED, False), (50, 2046, STEP, False), (52, 1021, STEP, False),
+    (52, 2048, PHI_PADDED, False), (52, 4092, CARRY, False), (64, 1022, STEP_PADDED, False), (64, 3064, PHI, False),
+    # and faster all the same
+    (32, 1021, CARRY, True), (33, 1022, PHI, True), (44, 1022, PHI_PADDED, True), (33, 3068, STEP, True), (48, 3068, STEP, True), (48, 2046, STEP, True),
+    (48, 4090, STEP, True), (48, 2046, CARRY, True), (64, 1024, CARRY, True), (64, 2046, CARRY_PADDED, True), (33, 8180, STEP_PADDED, True), (44, 1024, STEP, True)])
+def test_where_a_worker_less_costs_a_tile(rules, n, tiles, kind, room):
+    assert rules([(n, 64 * tiles + 27, *kind)])[0][0] == room
+
+
+def test_nothing_is_left_out_without_a_tail(rules):
+    assert all(not room for room, _ in rules([(n, 64 * t, *k) for n in (16, 33, 64) for t in (1019, 1024, 3000) for k in KINDS]))
