@@ -1,4 +1,4 @@
-// How many workers the matrix-core update gets, as far as numbers decide it (host code, nothing of HIP).
+// How the matrix-core update's work is split, as far as numbers decide it (host code, nothing of HIP).
 #pragma once
 #include <cstdint>
 
@@ -50,5 +50,16 @@ inline bool leaves_room_for_tail(int n, int64_t D, int num_cu, bool aligned, boo
     if (tiles == 3) return full_dense || (emit && n <= 36);
     return tiles <= (n <= 36 ? kTailRoomTiles : (full_dense ? 5 : 4));
 }
+
+// Direct stores above 48 particles: whether the waves of a workgroup take ranges of their own rather than adjacent tiles of one of
+// `per` tiles.  With five or six, one or two waves of each workgroup have a tile more than the others, on nearly all CUs, where
+// ranges of their own give as many tiles to every wave of two thirds of them.  us, adjacent and in ranges of their own, with 255 workers
+// and the tail's workgroup: a plain step with five tiles n = 52, D = 73,627 37.6 and 36.7, n = 56 41.6 and 38.9, n = 64 41.2 and
+// 38.7, with six n = 52, D = 83,227 38.7 and 37.5, D = 97,627 41.3 and 40.5, n = 64 42.0 and 41.6, 45.0 and 45.9; phi with five
+// n = 52 37.0 and 37.4, n = 56 41.8 and 39.6, n = 64 41.3 and 40.0, with six n = 52 38.1 and 38.7, n = 64 41.6 and 43.0.  On
+// carried sums the adjacent tiles are ahead (n = 64, five 35.5 and 36.7, six 35.4 and 37.7), and with seven tiles and more
+// for all (n = 64, D = 108,827, seven, 45.4 and 48.3; D = 131,163, nine, 51.6 and 53.1, phi 51.4 and 53.9; D = 146,971 54.7 and 58.2).
+// With 256 workers and no tail the same: a step with five 36.5 and 34.3 (n = 52, D = 76,800), with nine 3 % the other way.
+inline bool own_ranges(int64_t per, bool emit, bool carry) { return !carry && (per == 5 || (per == 6 && !emit)); }
 
 } // namespace svgd

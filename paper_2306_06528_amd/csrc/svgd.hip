@@ -595,17 +595,7 @@ int run_update(svgd_ctx *c, float *X, const float *G, float *PHI, int n, int64_t
         // workers walk contiguous ranges of full 64-column tiles; one more workgroup does D mod 64
         const int grid = workers + ((D & 63) ? 1 : 0);
         if (CARRY) list = PairList{out_off, grid}; // one partial per workgroup, the tail's included
-        // Direct stores, adjacent tiles: not where the workgroups' ranges are of 5, 6 or 9 tiles (n > 48, D = 65,536 to
-        // 98,368 and 131,072 to 147,520): one or two waves of each then have a tile more than the others, on nearly all
-        // CUs, where ranges of their own give as many tiles to every wave of two thirds of them.  us per step re-aligned,
-        // adjacent and in ranges of their own: n = 64, D = 80,003 44.6, 46.6 and 39.6, phi 45.0, 46.3 and 41.7, carried
-        // sums 47.0, 46.3 and 36.9; n = 50, D = 90,003 41.0, 42.4 and 37.6; n = 56, D = 140,003 61.2, 60.0 and 56.6.  (At
-        // the near ends of these stretches the adjacent ones are up to 4 % ahead, 8 % on carried sums.)  From ranges of
-        // 10 on neither is the better one throughout (n = 64, D = 162,003 60.4 and 61.7, n = 53 59.2 and 57.0).
-        if (direct && !aligned && ua.adjacent) {
-            const int64_t per = tiles_per_range(D / 64, workers, true);
-            if (per == 5 || per == 6 || per == 9) ua.adjacent = 0;
-        }
+        if (direct && !aligned && ua.adjacent && own_ranges(tiles_per_range(D / 64, workers, true), EMIT, CARRY)) ua.adjacent = 0;
         ua.per = tiles_per_range(D / 64, workers, ua.adjacent && (aligned || direct)); // (staged stores: a range per wave)
         const UpdateCall call{X, G, PHI, c->coef, c->state, n, D, ld, eps, gram_out, rt, ua, grid, s,
                               aligned ? kStoreLines : (direct ? kStoreDirect : kStoreStaged),

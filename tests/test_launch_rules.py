@@ -17,7 +17,8 @@ int main()
     int aligned, emit, carry;
     while (std::scanf("%lld %lld %d %d %d", &n, &D, &aligned, &emit, &carry) == 5) {
         const bool room = svgd::leaves_room_for_tail((int)n, D, 256, aligned, emit, carry);
-        std::printf("%d %lld\n", room, (long long)svgd::tiles_per_wave(D / 64, 256 - room));
+        const long long workers = 256 - room, per = (D / 64 + workers - 1) / workers;
+        std::printf("%d %lld %d\n", room, (long long)svgd::tiles_per_wave(D / 64, workers), svgd::own_ranges(per, emit, carry));
     }
 }
 """
@@ -48,7 +49,7 @@ def test_a_worker_less_gives_no_wave_a_tile_more_unless_measured_to_be_faster(ru
              for k in KINDS]
     whole = lambda n: n > 32 or n % 16 == 0 or (n > 16 and 1 <= n % 16 <= 4)
     seen = 0
-    for (n, D, _, e, c), (room, tiles) in zip(cases, rules(cases)):
+    for (n, D, _, e, c), (room, tiles, _) in zip(cases, rules(cases)):
         t = D // 64
         before, after = -(-t // (4 * CUS)), -(-t // (4 * (CUS - 1)))
         assert tiles == (after if room else before)
@@ -76,4 +77,15 @@ def test_where_a_worker_less_costs_a_tile(rules, n, tiles, kind, room):
 
 
 def test_nothing_is_left_out_without_a_tail(rules):
-    assert all(not room for room, _ in rules([(n, 64 * t, *k) for n in (16, 33, 64) for t in (1019, 1024, 3000) for k in KINDS]))
+    assert all(not room for room, *_ in rules([(n, 64 * t, *k) for n in (16, 33, 64) for t in (1019, 1024, 3000) for k in KINDS]))
+
+
+@pytest.mark.parametrize("tiles,tail,step,phi", [
+    (1024, 27, False, False),  # four per workgroup, 256 workers
+    (1025, 27, True, True), (1275, 27, True, True), (1276, 27, True, False), (1530, 27, True, False), (1531, 27, False, False), (1535, 27, False, False),
+    (2048, 27, False, False), (2049, 27, False, False), (2295, 27, False, False),
+    (1280, 0, True, True), (1281, 0, True, False), (1536, 0, True, False), (1537, 0, False, False), (2049, 0, False, False)])
+def test_ranges_of_their_own_by_the_workers_that_are_launched(rules, tiles, tail, step, phi):
+    """Above 48 particles: five tiles per workgroup, in a plain step six; never on carried sums."""
+    D = 64 * tiles + tail
+    assert [bool(own) for *_, own in rules([(n, D, *k) for n in (49, 56, 64) for k in (STEP, PHI, CARRY)])] == 3 * [step, phi, False]
