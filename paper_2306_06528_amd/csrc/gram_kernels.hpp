@@ -338,10 +338,16 @@ __global__ __launch_bounds__(64 * W) void gram_mfma_kernel(const float *__restri
         opaque(at0);
         int qv = q;
         if constexpr (ROWS && !RREG) asm volatile("" : "+v"(qv)); // (or the reads would be hoisted out of the loop)
+        auto row_at = [&](int i) __attribute__((always_inline)) { // row 4i + q
+            if constexpr (RREG) return X + xro[i] + col;
+            else if constexpr (ROWS) return X + srow[4 * i + qv] + col;
+            else if constexpr (WIDE) return X + (i < RPL - 4 ? at0 + (int64_t)(4 * i) * ld : col + last_row[i & 3]);
+            else return X + (at0 + (int64_t)(4 * i) * ld);
+        };
 #pragma unroll
         for (int i = 0; i < RPL; ++i) {
             const int row = 4 * i + q;
-            const float *xr = RREG ? X + xro[RREG ? i : 0] + col : (ROWS ? X + srow[ROWS ? 4 * i + qv : 0] + col : X + (!WIDE || i < RPL - 4 ? at0 + (int64_t)(4 * i) * ld : col + last_row[!WIDE || i < RPL - 4 ? 0 : i - (RPL - 4)]));
+            const float *xr = row_at(i);
             f32x4 v = {0.f, 0.f, 0.f, 0.f}; // rows beyond n, and empty slabs, add nothing to any sum
             // (only the last block of 16 rows can reach beyond n)
             if (HOW != 3 && (WIDE || i < RPL - 4 || row < n)) {
