@@ -1,7 +1,8 @@
 """Pass 2 (bandwidth and kernel matrix) where its rule can go wrong: the median of sets that are all
 equal, that crowd into one bucket of the selection, or that hold infinities, at the particle counts
 where the way it is computed changes - by the kernel of its own (svgd_bandwidth) and as the prologue
-of the update (svgd_step, which up to 32 particles derives h and K in every workgroup)."""
+of the update (svgd_step, which up to 48 particles derives h and K in every workgroup, from the list of partial sums or,
+from 21 on where that is long, from what a launch in between has made of it)."""
 import numpy as np
 import pytest
 import torch
@@ -32,6 +33,14 @@ def _particles(kind, n, D):
 @pytest.mark.parametrize("n", [2, 8, 9, 11, 12, 13, 16, 17, 32, 33, 64])
 def test_median_of_awkward_sets(n, kind):
     _check(n, 3001, kind)
+
+
+@pytest.mark.parametrize("kind", ["equal", "crowded", "random"])
+@pytest.mark.parametrize("n,D", [(24, 52_003), (32, 16_387), (33, 8_001), (36, 8_001), (44, 6_001), (48, 6_001)])
+def test_median_of_awkward_sets_on_sums(n, D, kind):
+    """256 threads and up to five pairs each: the refining levels of the selection, and a fixed bandwidth."""
+    _check(n, D, kind, launches=[1, 1, 0, 1])
+    _check(n, D, kind, launches=[1, 1, 0, 1], fixed=2.0 * D if kind == "random" else 2.5)
 
 
 @pytest.mark.parametrize("n,D", [(4, 100), (8, 3001)])   # direct differences: infinite d2, not inf - inf
@@ -88,15 +97,26 @@ def test_lists_around_a_share_of_the_partials(n, nparts):
     _check(n, per * nparts - 3, "random")
 
 
-def _check(n, D, kind):
+def _check(n, D, kind, launches=None, fixed=0.0):
     from paper_2306_06528_amd import svgd
     Xh = _particles(kind, n, D)
-    ref = orc.step(Xh.numpy(), np.zeros((n, D), np.float32), 0.0, want_phi=False, want_xnew=False)
+    if fixed:
+        d2 = orc.pairwise_d2(Xh.numpy())
+        K_ref, _ = orc.kernel(d2, fixed)
+        ref = {"h": fixed, "K": K_ref}
+    else:
+        ref = orc.step(Xh.numpy(), np.zeros((n, D), np.float32), 0.0, want_phi=False, want_xnew=False)
     X, G = Xh.cuda(), torch.zeros(n, D, device="cuda")
     with svgd.Svgd(n, D) as eng:
+        eng.set_bandwidth(fixed)
         eng.bandwidth(X)
         got = [eng.get_last(n)]
+        if launches:
+            eng.profile_begin()
         eng.step(X, G, 0.0)
+        if launches:
+            prof = eng.profile_end()
+            assert [prof[k][1] for k in svgd.KERNEL_KINDS] == launches
         got.append(eng.get_last(n))
     for h, K in got:
         assert abs(h - ref["h"]) <= TOL_H * ref["h"]
