@@ -338,11 +338,13 @@ __global__ __launch_bounds__(64 * W) void gram_mfma_kernel(const float *__restri
         opaque(at0);
         int qv = q;
         if constexpr (ROWS && !RREG) asm volatile("" : "+v"(qv)); // (or the reads would be hoisted out of the loop)
-        auto row_at = [&](int i) __attribute__((always_inline)) { // row 4i + q
+        // Row 4i + q.  (Base plus place in row q first: what is added for the others is uniform.  With the three added up before the base
+        // every load had an instruction or two of its own: n = 33, D = 100,003 14.6 us, 14.4 without.)
+        auto row_at = [&](int i) __attribute__((always_inline)) {
             if constexpr (RREG) return X + xro[i] + col;
             else if constexpr (ROWS) return X + srow[4 * i + qv] + col;
-            else if constexpr (WIDE) return X + (i < RPL - 4 ? at0 + (int64_t)(4 * i) * ld : col + last_row[i & 3]);
-            else return X + (at0 + (int64_t)(4 * i) * ld);
+            else if constexpr (WIDE) return i < RPL - 4 ? X + at0 + (int64_t)(4 * i) * ld : X + col + last_row[i & 3];
+            else return X + at0 + (int64_t)(4 * i) * ld;
         };
 #pragma unroll
         for (int i = 0; i < RPL; ++i) {
