@@ -1,5 +1,6 @@
 // How the matrix-core update's work is split, as far as numbers decide it (host code, nothing of HIP).
 #pragma once
+#include <algorithm>
 #include <cstdint>
 
 namespace svgd {
@@ -49,6 +50,78 @@ inline bool leaves_room_for_tail(int n, int64_t D, int num_cu, bool aligned, boo
     if (tiles == 2) return full_dense || ((emit || nfull == 4 * (int64_t)num_cu) && (n < 48 || !aligned));
     if (tiles == 3) return full_dense || (emit && n <= 36);
     return tiles <= (n <= 36 ? kTailRoomTiles : (full_dense ? 5 : 4));
+}
+
+// Worker workgroups of the matrix-core update (each walks ranges of 64-column tiles; one more
+// workgroup does D mod 64): one per CU - the kernel overlaps its own loads with its multiplies, and
+// fewer concurrent row streams keep more HBM pages open.  Exception: 21 to 24 particles, whose
+// tiles cost the instructions of 32 rows but move little more than half the bytes, so that the
+// fixed costs of a tile show (17 to 20 are 16 rows plus remainder rows, see has_remainder_rows).
+// The kernel instances for n not a multiple of 16, n < 32, are built for two waves per SIMD, and
+// for those particle counts and an X beyond the memory-side cache two workgroups per CU overlap
+// one's arithmetic with the other's loads (with carried sums at D = 5,000,000: n = 24
+// 258 -> 241 us; from n = 25 on the gain is below the cost of the longer list of partial sums,
+// with 16 or 32 particles the second workgroup costs 2-5 %, and for an X that cache serves it
+// costs 9 %).
+// `cap` bounds the grid, the tail's workgroup included; beyond_cache: of an X that the memory-side cache does not hold.
+// (D mod 64 = 0: no workgroup for the tail.)
+// One worker less where that makes room for the tail's workgroup (leaves_room_for_tail).
+inline int update_workers(int n, int64_t D, int num_cu, int cap, bool beyond_cache, bool aligned, bool emit, bool carry)
+{
+    const int64_t nfull = D / 64;
+    const int per_cu = (n >= 17 && n <= 24 && !has_remainder_rows(n) && beyond_cache) ? 2 : 1;
+    const int max_workers = std::min(num_cu * per_cu - (leaves_room_for_tail(n, D, num_cu, aligned, emit, carry) ? 1 : 0), cap - 1);
+    return (int)std::max<int64_t>(std::min<int64_t>((nfull + 3) / 4, max_workers), 1);
+}
+
+// Pass 2 is part of the update only if all its workgroups are resident at once, or it is paid for twice: the instances
+// whose blocks are full take a CU's registers for one workgroup, the others for half of one.  Where
+// the tail's workgroup comes on top of a worker for every CU, one worker less makes room for it
+// (257 and 256 workgroups: n = 16, D = 300,007 35 and 25 us per step; n = 13, D = 100,003, padded rows,
+// carried sums 16.1 and 13.8).  That may give the waves a tile more, which is still the faster way
+// with full blocks (n = 16, D = 131,100, two tiles per wave or three: 32 us in 257 workgroups, 22.9
+// in launches of their own, 21.9) and, carrying sums, where the tail's workgroup takes longer, up to 15
+// particles (n = 15, same D, padded: 17.8 and 14.2); otherwise two workgroups share a CU (n = 15,
+// plain step: 17.5, 21.1 with a tile more; n = 21, carried: 23.8 and 27.3).
+// Returns the number of workers, 0: not as one launch (21 particles or more only).
+inline int fused_workers(int n, int64_t D, int num_cu, int workers, bool carry)
+{
+    const bool full_rows = takes_whole_cu(n);
+    const int64_t nfull = D / 64;
+    for (int per_cu = 1; per_cu <= (full_rows ? 1 : 2); ++per_cu) {
+        const int room = std::max(num_cu * per_cu - ((D & 63) ? 1 : 0), 1);
+        if (workers <= room) return workers;
+        if (full_rows || (carry && n < 16) || tiles_per_wave(nfull, room) == tiles_per_wave(nfull, workers)) return room;
+    }
+    return 0;
+}
+
+// 21 to kSumsMaxN particles and a list too long to be read by every workgroup: a launch of many workgroups sums it, and
+// the update's workgroups start with pass 2 on the sums - a launch less than with pass 2 in between, and the tile's first
+// loads and the tables of C are no longer waited for behind it.  us per step, apart and inside: n = 24, dense, D = 50,001
+// 18.2 and 15.9, D = 120,011 23.6 and 21.5, n = 28, carried, padded, D = 40,003 15.6 and 13.7, n = 32, D = 16,403 17.7 and 15.2,
+// phi 17.1 and 14.9, D = 120,011 26.9 and 23.3, carried, padded 25.1 and 19.6, n = 33, D = 25,003 21.8 and 20.1, n = 40,
+// D = 50,021, plain 25.6 and 23.9, n = 48 26.6 and 25.2; separate rows, n = 24, D = 1,500,001 120.9 and 118.4, padded, n = 32,
+// D = 2,000,000 195.4 and 193.9.  From 49 particles on 256 threads take longer for pass 2 than the 1024 of a launch of its
+// own and that launch together (n = 50, D = 50,021 30.3 and 30.1, n = 56 32.9 and 33.4, n = 64 32.4 and 34.0).
+// Not with re-aligned stores (two instances per kernel instead of three or four), and only where all workgroups are resident
+// without a tile more for any wave, or where leaves_room_for_tail has it so.  Above 32 particles a list that the launch of pass 2 sums by itself saves no launch.
+constexpr int kFusedAlwaysN = 20; // (their lists are never that long)
+constexpr int kSumsMaxN = 48;
+
+// Whether it does: `workers` and `w` as update_workers and fused_workers have them.
+inline bool sums_inside(int n, int workers, int w, bool aligned, bool direct, bool carry)
+{
+    return n > kFusedAlwaysN && n <= kSumsMaxN && (w == workers || (w > 0 && !takes_whole_cu(n))) && (direct || (!carry && aligned));
+}
+
+// The workers of an update that reads a long list: all resident where pass 2 is inside.  The pairwise pass orders its slabs by
+// their ranges (with 256 there and 255 here, few of the tiles that it leaves in the cache are the first of a range: n = 31,
+// D = 5,000,003, padded 448 us per step, 432 with the same; n = 16, D = 9,000,003 414 and 402).
+inline int long_list_workers(int n, int64_t D, int num_cu, int cap, bool beyond_cache, bool aligned, bool direct, bool emit, bool carry)
+{
+    const int workers = update_workers(n, D, num_cu, cap, beyond_cache, aligned, emit, carry), w = fused_workers(n, D, num_cu, workers, carry);
+    return w > 0 && (n <= kFusedAlwaysN || sums_inside(n, workers, w, aligned, direct, carry)) ? w : workers;
 }
 
 // Direct stores above 48 particles: whether the waves of a workgroup take ranges of their own rather than adjacent tiles of one of

@@ -300,28 +300,6 @@ bool beyond_cache(int n, int64_t ld)
 // stores, see run_update).
 bool adjacent_tiles(int n, int64_t ld) { return n > 48 || beyond_cache(n, ld); }
 
-// Worker workgroups of the matrix-core update (each walks ranges of 64-column tiles; one more
-// workgroup does D mod 64): one per CU - the kernel overlaps its own loads with its multiplies, and
-// fewer concurrent row streams keep more HBM pages open.  Exception: 21 to 24 particles, whose
-// tiles cost the instructions of 32 rows but move little more than half the bytes, so that the
-// fixed costs of a tile show (17 to 20 are 16 rows plus remainder rows, see has_remainder_rows).
-// The kernel instances for n not a multiple of 16, n < 32, are built for two waves per SIMD, and
-// for those particle counts and an X beyond the memory-side cache two workgroups per CU overlap
-// one's arithmetic with the other's loads (with carried sums at D = 5,000,000: n = 24
-// 258 -> 241 us; from n = 25 on the gain is below the cost of the longer list of partial sums,
-// with 16 or 32 particles the second workgroup costs 2-5 %, and for an X that cache serves it
-// costs 9 %).
-// The Gram pass splits the tiles the same way.  `cap` bounds the grid, the tail's workgroup included.
-// (D mod 64 = 0: no workgroup for the tail.)
-// One worker less where that makes room for the tail's workgroup (leaves_room_for_tail).
-int update_workers(const svgd_ctx *c, int n, int64_t D, int64_t ld, int cap, bool aligned, bool emit, bool carry)
-{
-    const int64_t nfull = D / 64;
-    const int per_cu = (n >= 17 && n <= 24 && !has_remainder_rows(n) && beyond_cache(n, ld)) ? 2 : 1;
-    const int max_workers = mini(c->num_cu * per_cu - (leaves_room_for_tail(n, D, c->num_cu, aligned, emit, carry) ? 1 : 0), cap - 1);
-    return clampi((nfull + 3) / 4, 1, max_workers);
-}
-
 // Up to kFusedMaxN particles the update kernel does pass 2 itself, in every workgroup, if that costs
 // less than the launches it saves: 256 threads hold at most 496 pairs comfortably, and every
 // workgroup reads the whole list, in batches of sixteen 16-byte loads per thread, one after the
@@ -340,9 +318,8 @@ constexpr int fused_max_parts(int n) // n <= kFusedMaxN
     const int groups = 256 / (pair_stride(n) / 4);
     return kFusedMaxBatches * kSumLoads * (groups < 32 ? groups : 32);
 }
-// Up to 20 particles (one block of rows, remainder rows included) no list is longer: the grids whose workgroups
+// Up to kFusedAlwaysN particles (one block of rows, remainder rows included) no list is longer: the grids whose workgroups
 // leave a partial each have one per CU on the matrix-core path, the tail's workgroup included.
-constexpr int kFusedAlwaysN = 20;
 static_assert(fused_max_parts(kFusedAlwaysN) >= kMaxCu, "one partial per CU is a short list");
 
 // A list of pair-sum partials in the handle's scratch.
@@ -394,7 +371,8 @@ int run_gram(svgd_ctx *c, const float *X, int n, int64_t D, int64_t ld, hipStrea
         // tiles three quarters of the memory-side cache can hold
         const bool aligned_next = G_next && x_aligned && (rt || rows_aligned(G_next, ld));
         const bool shared_ranges = aligned_next && adjacent_tiles(n, ld);
-        int64_t nranges = (int64_t)update_workers(c, n, D, ld, carry_next ? cap_parts : kMaxParts, aligned_next, false, carry_next) * (shared_ranges ? 1 : 4);
+        int64_t nranges = (int64_t)long_list_workers(n, D, c->num_cu, carry_next ? cap_parts : kMaxParts, beyond_cache(n, ld), aligned_next, false, false, carry_next) *
+                          (shared_ranges ? 1 : 4);
         int64_t per = (nfull + nranges - 1) / nranges > 0 ? (nfull + nranges - 1) / nranges : 1;
         int64_t hot = (3 * kMemorySideCacheBytes / 4) / ((int64_t)n * 256) / nranges;
         if (shared_ranges) hot &= ~(int64_t)3; // four waves share the start of a range
@@ -477,28 +455,6 @@ int run_bandwidth(svgd_ctx *c, int n, const PairList &list, hipStream_t s)
     return SVGD_OK;
 }
 
-// And only if all its workgroups are resident at once, or pass 2 is paid for twice: the instances
-// whose blocks are full take a CU's registers for one workgroup, the others for half of one.  Where
-// the tail's workgroup comes on top of a worker for every CU, one worker less makes room for it
-// (257 and 256 workgroups: n = 16, D = 300,007 35 and 25 us per step; n = 13, D = 100,003, padded rows,
-// carried sums 16.1 and 13.8).  That may give the waves a tile more, which is still the faster way
-// with full blocks (n = 16, D = 131,100, two tiles per wave or three: 32 us in 257 workgroups, 22.9
-// in launches of their own, 21.9) and, carrying sums, where the tail's workgroup takes longer, up to 15
-// particles (n = 15, same D, padded: 17.8 and 14.2); otherwise two workgroups share a CU (n = 15,
-// plain step: 17.5, 21.1 with a tile more; n = 21, carried: 23.8 and 27.3).
-// Returns the number of workers, 0: not as one launch (21 particles or more only).
-int fused_workers(const svgd_ctx *c, int n, int64_t D, int workers, bool carry)
-{
-    const bool full_rows = takes_whole_cu(n);
-    const int64_t nfull = D / 64;
-    for (int per_cu = 1; per_cu <= (full_rows ? 1 : 2); ++per_cu) {
-        const int room = std::max(c->num_cu * per_cu - ((D & 63) ? 1 : 0), 1);
-        if (workers <= room) return workers;
-        if (full_rows || (carry && n < 16) || tiles_per_wave(nfull, room) == tiles_per_wave(nfull, workers)) return room;
-    }
-    return 0;
-}
-
 // Rows that do not start on 128-byte boundaries: whether the update stores its tiles where they lie all the same
 // (kStoreDirect).  Staged, a tile is some three thousand cycles longer, and a wave's first tile and the end of
 // its range more than that; direct, a line that two tiles share is written twice, which costs little while the caches
@@ -515,18 +471,6 @@ bool store_directly(int n, int64_t D, bool emit, bool carry)
     const int mib = emit ? (n <= 32 ? 24 : (n <= 48 ? 40 : 76)) : (carry ? (n <= 48 ? 92 : 256) : (n < 16 ? 100 : (n == 16 ? 120 : (n <= 48 ? 56 : 144))));
     return (int64_t)n * D * (int64_t)sizeof(float) <= ((int64_t)mib << 20);
 }
-
-// 21 to kSumsMaxN particles and a list too long to be read by every workgroup: a launch of many workgroups sums it, and
-// the update's workgroups start with pass 2 on the sums - a launch less than with pass 2 in between, and the tile's first
-// loads and the tables of C are no longer waited for behind it.  us per step, apart and inside: n = 24, dense, D = 50,001
-// 18.2 and 15.9, D = 120,011 23.6 and 21.5, n = 28, carried, padded, D = 40,003 15.6 and 13.7, n = 32, D = 16,403 17.7 and 15.2,
-// phi 17.1 and 14.9, D = 120,011 26.9 and 23.3, carried, padded 25.1 and 19.6, n = 33, D = 25,003 21.8 and 20.1, n = 40,
-// D = 50,021, plain 25.6 and 23.9, n = 48 26.6 and 25.2; separate rows, n = 24, D = 1,500,001 120.9 and 118.4, padded, n = 32,
-// D = 2,000,000 195.4 and 193.9.  From 49 particles on 256 threads take longer for pass 2 than the 1024 of a launch of its
-// own and that launch together (n = 50, D = 50,021 30.3 and 30.1, n = 56 32.9 and 33.4, n = 64 32.4 and 34.0).
-// Not with re-aligned stores (two instances per kernel instead of three or four), and only where all workgroups are resident
-// without a tile more for any wave.  Above 32 particles a list that the launch of pass 2 sums by itself saves no launch.
-constexpr int kSumsMaxN = 48;
 
 // Passes 2 and 3.  EMIT = false: X updated in place; EMIT = true: phi written to PHI.  CARRY (in
 // place): the update also leaves the pair-sum partials of the new X in the scratch, described by
@@ -549,16 +493,14 @@ int run_update(svgd_ctx *c, float *X, const float *G, float *PHI, int n, int64_t
     const bool aligned = rt ? rt->aligned != 0 : rows_aligned(X, ld) && rows_aligned(G, ld) && (!EMIT || rows_aligned(PHI, ld));
     const bool direct = !rt && store_directly(n, D, EMIT, CARRY);
     if (n > kValuMaxN) {
-        workers = update_workers(c, n, D, ld, out_cap, aligned, EMIT, CARRY);
-        const int w = fused_workers(c, n, D, workers, CARRY);
-        // (CARRY: by n, D and ld alone, see below)
-        const bool sums_inside = n > kFusedAlwaysN && n <= kSumsMaxN && (w == workers || (w > 0 && !takes_whole_cu(n))) && (direct || (!CARRY && aligned));
+        const int most = update_workers(n, D, c->num_cu, out_cap, beyond_cache(n, ld), aligned, EMIT, CARRY);
+        const int w = fused_workers(n, D, c->num_cu, most, CARRY);
+        workers = long_list_workers(n, D, c->num_cu, out_cap, beyond_cache(n, ld), aligned, direct, EMIT, CARRY);
         // CARRY: the number of workgroups, which is that of the carried partial sums, depends on the
         // problem only, not on the list that is read: a captured step reads what any other one left
-        const bool adapt = w > 0 && (sums_inside || (n <= kFusedMaxN && (CARRY ? w + ((D & 63) ? 1 : 0) <= fused_max_parts(n) : fused)));
-        if (adapt) workers = w;
+        if (w > 0 && n <= kFusedMaxN && (CARRY ? w + ((D & 63) ? 1 : 0) <= fused_max_parts(n) : fused)) workers = w;
         fused = fused && workers == w;
-        from_sums = !fused && sums_inside && (n <= kFusedMaxN || (int64_t)list.nparts * pair_stride(n) > kDirectMaxFloats);
+        from_sums = !fused && sums_inside(n, most, w, aligned, direct, CARRY) && (n <= kFusedMaxN || (int64_t)list.nparts * pair_stride(n) > kDirectMaxFloats);
     }
     int64_t out_off = c->captured ? c->home : 0;
     if (from_sums) {

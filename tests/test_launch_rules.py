@@ -18,7 +18,13 @@ int main()
     while (std::scanf("%lld %lld %d %d %d", &n, &D, &aligned, &emit, &carry) == 5) {
         const bool room = svgd::leaves_room_for_tail((int)n, D, 256, aligned, emit, carry);
         const long long workers = 256 - room, per = (D / 64 + workers - 1) / workers;
-        std::printf("%d %lld %d\n", room, (long long)svgd::tiles_per_wave(D / 64, workers), svgd::own_ranges(per, emit, carry));
+        // workers of an update that reads a long list, with direct stores and without; and those that the pairwise pass
+        // before it reckons with (which knows nothing of the two)
+        const bool beyond = 4 * n * D > (320ll << 20);
+        std::printf("%d %lld %d %d %d %d\n", room, (long long)svgd::tiles_per_wave(D / 64, workers), svgd::own_ranges(per, emit, carry),
+                    svgd::long_list_workers((int)n, D, 256, 2048, beyond, aligned, true, emit, carry),
+                    svgd::long_list_workers((int)n, D, 256, 2048, beyond, aligned, false, emit, carry),
+                    svgd::long_list_workers((int)n, D, 256, 2048, beyond, aligned, false, false, carry));
     }
 }
 """
@@ -49,7 +55,7 @@ def test_a_worker_less_gives_no_wave_a_tile_more_unless_measured_to_be_faster(ru
              for k in KINDS]
     whole = lambda n: n > 32 or n % 16 == 0 or (n > 16 and 1 <= n % 16 <= 4)
     seen = 0
-    for (n, D, _, e, c), (room, tiles, _) in zip(cases, rules(cases)):
+    for (n, D, _, e, c), (room, tiles, *_) in zip(cases, rules(cases)):
         t = D // 64
         before, after = -(-t // (4 * CUS)), -(-t // (4 * (CUS - 1)))
         assert tiles == (after if room else before)
@@ -88,4 +94,21 @@ def test_nothing_is_left_out_without_a_tail(rules):
 def test_ranges_of_their_own_by_the_workers_that_are_launched(rules, tiles, tail, step, phi):
     """Above 48 particles: five tiles per workgroup, in a plain step six; never on carried sums."""
     D = 64 * tiles + tail
-    assert [bool(own) for *_, own in rules([(n, D, *k) for n in (49, 56, 64) for k in (STEP, PHI, CARRY)])] == 3 * [step, phi, False]
+    assert [bool(own) for _, _, own, *_ in rules([(n, D, *k) for n in (49, 56, 64) for k in (STEP, PHI, CARRY)])] == 3 * [step, phi, False]
+
+
+def test_the_pairwise_pass_reckons_with_the_workers_of_the_update(rules):
+    """An X larger than twice the memory-side cache: the pass visits the first tiles of the update's ranges last.  (Stores off the
+    line boundaries are re-aligned at these sizes.)"""
+    cases = [(n, D, *k) for n in range(13, 65) for D in ((1 << 27) // n + 1, 5_000_003, 9_000_003, 11_173_962, 11_173_888) for k in KINDS if n * D > 1 << 27]
+    for (n, D, *_), (*_, launched, reckoned) in zip(cases, rules(cases)):
+        assert launched == reckoned, (n, D)
+
+
+def test_pass_2_inside_the_update_only_with_all_workgroups_resident(rules):
+    cases = [(n, D, *k) for n in range(13, 49) for D in (70_001, 131_071, 300_007, 5_000_003) for k in KINDS if n <= 20 or k in (STEP_PADDED, PHI_PADDED)]
+    for (n, D, *_), (*_, launched, _) in zip(cases, rules(cases)):
+        inside = n <= 20 or launched != 256
+        whole = n > 32 or n % 16 == 0 or (n > 16 and 1 <= n % 16 <= 4)
+        if inside:
+            assert launched + 1 <= CUS * (1 if whole else 2), (n, D)
