@@ -189,6 +189,7 @@ struct GramOrder {
 //   last block of rows is mostly empty; behind the writes of an update, us per dense step, ORDER 1 and 3: n = 64, D = 11,173,962
 //   2340 and 2300, D = 5,324,817 1134 and 1125, D = 2,293,777 496 and 497, n = 60, D = 9,175,057 1812 and 1793, n = 48,
 //   D = 7,099,750 1096 and 1079, n = 44, D = 7,745,180 1094 and 1087; n = 40 1115 and 1116, n = 33 1092 and 1120, n = 50 1787 and 1805.
+// ORDER 4: plain order, and no branch around any load (WIDE, below) - for small X with columns after the last slab.
 // The host takes ORDER 1, 2 or 3 when X is larger than twice the memory-side cache.
 // What bounds the pass is memory, since the multiplies are in bf16: at n = 64 the matrix pipe is busy for
 // 27 % of the cycles (120 instructions of 16 per slab) and the vector ALU for 32.  In fp32
@@ -224,7 +225,8 @@ __global__ __launch_bounds__(64 * W) void gram_mfma_kernel(const float *__restri
     };
     const SplitConst sc = split_const();
 
-    constexpr bool ORDERED = ORDER != 0, STREAM = ORDER == 2, IN_STEP = ORDER == 3;
+    constexpr bool WIDE = ORDER == 4, ORDERED = ORDER != 0 && !WIDE, STREAM = ORDER == 2, IN_STEP = ORDER == 3;
+    static_assert(!WIDE || W == kGramWavesSmall, "a slab or two per wave");
     constexpr bool F32 = W == kGramWavesSmall && NB <= kGramF32Blocks;
     const int64_t nfull = D >> 6;
     const uint32_t uper = go.per, uhot = go.hot, ucold = uper - uhot, unfull = (uint32_t)nfull;
@@ -286,11 +288,11 @@ __global__ __launch_bounds__(64 * W) void gram_mfma_kernel(const float *__restri
     // WIDE (small X, a slab per wave): rows beyond n are loaded as row n - 1 and set to 0 when the slab is used, and the
     // partial slab is loaded like the others, at min(column, D - 4), and moved into place then (RaggedGroup): no branch around
     // any load.  With guarded ones - four per slab, and 64 single columns per row and wave in the partial slab, whose
-    // wave was the last of its launch to end - svgd_bandwidth took 18.1 us at n = 64, D = 25,003, now 16.5, and 21.6 at D = 65,003,
-    // now 18.4; n = 40 15.1 and 14.3, 17.1 and 15.4.  With one block, four rows per lane, it gains nothing (the pass alone, n = 16,
-    // D = 8,577 3.3 and 3.5; n = 20, D = 20,001 4.8 and 3.9), and in the loop over many slabs what is moved and set to 0 costs more
+    // wave was the last of its launch to end - svgd_bandwidth takes 17.5 us at n = 64, D = 20,001, 16.2 without, n = 40 14.4 and 13.8;
+    // D = 65,003 18.6 and 17.2, 15.2 and 14.5.  Without a partial slab it is the guards that are faster (n = 64, D = 20,032 16.0
+    // and 16.3, n = 36 13.3 and 13.7, n = 18 10.5 and 10.9: the code is shorter), with one block, four rows per lane, always (the pass
+    // alone, n = 16, D = 8,577 3.3 and 3.5), and in the loop over many slabs what is moved and set to 0 costs more
     // than the branches (n = 64, D = 1,500,003 87.8 and 101).
-    constexpr bool WIDE = W == kGramWavesSmall && NB >= 2;
     int64_t last_row[WIDE && !ROWS ? 4 : 1];
     if constexpr (WIDE && !ROWS) {
 #pragma unroll

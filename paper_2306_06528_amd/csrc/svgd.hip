@@ -365,6 +365,7 @@ int run_gram(svgd_ctx *c, const float *X, int n, int64_t D, int64_t ld, hipStrea
         const int NB = (n + 15) / 16;
         const int64_t nfull = D / 64;
         const bool small = nfull < (int64_t)kGramWavesSmall * mini(c->num_cu, cap_parts); // a slab per wave, the partial one included
+        const bool wide = small && NB >= 2 && (D & 63); // a partial slab: no branch around any load
         const int waves = small ? kGramWavesSmall : kGramWaves;
         nparts = clampi((D + 64 * waves - 1) / (64 * waves), 1, mini(c->num_cu, cap_parts));
         // the ranges of the update that follows (tile_range) and how many of each range's first
@@ -394,10 +395,12 @@ int run_gram(svgd_ctx *c, const float *X, int n, int64_t D, int64_t ld, hipStrea
 #define GRAM_W(NB, W, ROWS, ORDER, rows) gram_mfma_kernel<NB, W, ROWS, ORDER><<<nparts, 64 * W, 0, s>>>(X, n, D, ld, partials, rows, go)
 #define GRAM(NB)                                                                                             \
     do {                                                                                                     \
-        if (rt && small) GRAM_W(NB, kGramWavesSmall, true, 0, *rt);                                          \
+        if (rt && wide) GRAM_W(NB, kGramWavesSmall, true, (NB >= 2 ? 4 : 0), *rt);                           \
+        else if (rt && small) GRAM_W(NB, kGramWavesSmall, true, 0, *rt);                                     \
         else if (rt && stream_x) GRAM_W(NB, kGramWaves, true, 2, *rt);                                       \
         else if (rt && big_x) GRAM_W(NB, kGramWaves, true, 1, *rt);                                          \
         else if (rt) GRAM_W(NB, kGramWaves, true, 0, *rt);                                                   \
+        else if (wide) GRAM_W(NB, kGramWavesSmall, false, (NB >= 2 ? 4 : 0), NoRows{});                      \
         else if (small) GRAM_W(NB, kGramWavesSmall, false, 0, NoRows{});                                     \
         else if (stream_x) GRAM_W(NB, kGramWaves, false, 2, NoRows{});                                       \
         else if (in_step) GRAM_W(NB, kGramWaves, false, (NB >= 3 ? 3 : 1), NoRows{});                        \
