@@ -187,8 +187,10 @@ int svgd_get_last(svgd_handle_t h, double *h_out, float *K_host, void *stream);
  * Not every kind runs in every step: a short list of partial sums is reduced inside the kernel
  * that needs it (no REDUCE launch), carried pair sums replace the GRAM pass, at n <= 32 a short
  * list is consumed by the UPDATE kernel itself (no BANDWIDTH launch; with carried sums the whole step
- * is then that one launch), at 21 <= n <= 48 the sums of a longer one are (REDUCE, no BANDWIDTH), and problems with n <= 8 and n * D <= 16384 run as one kernel, which is counted as
- * UPDATE (as BANDWIDTH when svgd_bandwidth launches it).
+ * is then that one launch), at 21 <= n <= 48 the sums of a longer one may be (REDUCE, no BANDWIDTH: not where rows off the
+ * 128-byte boundaries are too large for the caches to hold, not on carried sums above 92 MiB of X, not where it would take a worker
+ * that the columns need, and above 32 particles only if the list is too long for BANDWIDTH to sum), and problems with
+ * n <= 8 and n * D <= 16384 run as one kernel, which is counted as UPDATE (as BANDWIDTH when svgd_bandwidth launches it).
  */
 enum svgd_kernel_kind {
     SVGD_KERNEL_GRAM = 0,      /* pairwise-d2 partial sums (pass over X) */

@@ -184,7 +184,8 @@ struct GramOrder {
 //   way in) - for rows on 128-byte boundaries (nothing is shared between the slabs of neighbouring
 //   waves).  The pass itself then runs 5 % (n = 64, D = 11.2 M) to 28 % (n = 16, same D) faster.
 // ORDER 3: as 1, and the eight waves of a workgroup send off their loads together, so that the line which two slabs
-//   of unaligned rows share is asked for by both at once (reads alone, n = 64, D = 11.2 M: 516 -> 466 us).  What the waves
+//   of unaligned rows share is asked for by both at once (fetched, n = 64, D = 11.2 M: 1.25 times the bytes, 1.06 in step; reads alone
+//   516 -> 466 us).  What the waves
 //   then wait for each other costs as much where little bounds the pass but itself (svgd_bandwidth 563 and 573 us) or the
 //   last block of rows is mostly empty; behind the writes of an update, us per dense step, ORDER 1 and 3: n = 64, D = 11,173,962
 //   2340 and 2300, D = 5,324,817 1134 and 1125, D = 2,293,777 496 and 497, n = 60, D = 9,175,057 1812 and 1793, n = 48,

@@ -963,7 +963,8 @@ void update_mfma_kernel(float *__restrict__ X, const float *__restrict__ G, floa
         // Two waves per SIMD fetch their instructions faster or slower with the place of this loop against the 64-byte lines:
         // us per step, n = 24, padded, carried sums, with 12 instructions between a line's start and the compiler's own
         // before the loop, with 7 and where it falls: D = 300,007 29.3, 29.6 and 29.4, D = 1,000,003 60.3, 61.8 and 61.0, n = 21
-        // 59.1, 59.9 and 60.1.  Other instances stay where they fall.
+        // 59.1, 59.9 and 60.1.  Other instances stay where they fall.  (What the compiler puts in between is that of ROCm 7.2; with another
+        // one the number is to be found again, and one that does not fit costs those 1 to 2 %, nothing else.)
         if constexpr (STREAM && CARRY && NB == 2 && !FULLROWS) asm volatile(".p2align 6\n\t.rept 12\n\ts_nop 0\n\t.endr");
         for (int64_t k = 0; k < ntiles; ++k, tile += t_step) process_tile(std::false_type{}, tile, k + 1 == ntiles);
     } else if (t0 < t1) {
