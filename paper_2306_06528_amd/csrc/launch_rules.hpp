@@ -21,6 +21,11 @@ inline int64_t tiles_per_wave(int64_t nfull, int64_t workers) { return (nfull + 
 // 39.7, plain, dense 51.4 and 45.8; D = 300,007 (five tiles per wave) 74.1 and 68.4, plain 91.3 and 90.2; D = 800,003 (12) 138.2
 // and 137.7.  Beyond, the workgroups end so far apart that the tail is done in time, and a worker less costs its share
 // (n = 64, D = 11,173,962, carried sums 1698 and 1715).
+// Above 48 particles a workgroup's waves share a range, and just above a multiple of 1,024 tiles so few workgroups have one that the
+// tail finds a CU all the same, up to seven eighths of them (28 of the 32 of an XCD, seven in each of its four shader engines): us with
+// 256 and 255 workers, padded, seven tiles per workgroup, n = 64, 224 workgroups 45.4 and 45.4, 225 49.7 and 45.9, phi 42.7 and
+// 42.7, 48.3 and 42.9; five, 218, n = 50 35.6 and 37.3, n = 56 40.1 and 41.6.  (Dense rows without carried sums, in ranges of their own at five and
+// six tiles: a worker less is 1 to 2 % faster at 56 and 60 particles and up to 4 % slower at 49 to 51.)
 // Just below a multiple of 1,024 tiles a worker less gives the waves a tile more.  Still the faster way, us with 256 and 255
 // (tiles per wave with 255):
 // - on carried sums, whose tail takes longer, up to 8 tiles at 36 particles, 5 at 48, 3 above: padded, D = 65,500 (2), n = 33
@@ -42,6 +47,8 @@ inline bool leaves_room_for_tail(int n, int64_t D, int num_cu, bool aligned, boo
 {
     const int64_t nfull = D / 64;
     if (!takes_whole_cu(n) || (D & 63) == 0 || num_cu < 2 || nfull > (int64_t)kTailRoomTiles * 4 * num_cu) return false;
+    const int64_t per = std::max<int64_t>((nfull + num_cu - 1) / num_cu, 1);
+    if (n > 48 && (aligned || carry) && 8 * ((nfull + per - 1) / per) <= 7 * (int64_t)num_cu) return false;
     const int64_t tiles = tiles_per_wave(nfull, num_cu - 1);
     if (tiles == tiles_per_wave(nfull, num_cu)) return true;
     if (carry) return tiles <= (n <= 36 ? 8 : (n <= 48 ? 5 : 3));

@@ -134,7 +134,7 @@ def test_direct_and_staged_stores(n, mib):
         del buf, G, X, Gv, PHI, pbuf, old, now, ref
 
 
-@pytest.mark.parametrize("D", [65_590, 65_600, 80_003, 81_660, 81_700, 97_980, 98_000, 98_300, 98_400, 131_100, 135_003, 147_500, 147_600, 196_150])
+@pytest.mark.parametrize("D", [65_590, 65_600, 71_700, 71_750, 80_003, 81_660, 81_700, 97_980, 98_000, 98_300, 98_400, 131_100, 135_003, 147_500, 147_600, 196_150])
 @pytest.mark.parametrize("n", [49, 52, 53, 64])
 def test_direct_stores_in_adjacent_tiles_or_ranges(n, D):
     """More than 48 particles on dense rows at the sizes where the waves of a workgroup stop and start to share a range

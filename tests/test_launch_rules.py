@@ -55,11 +55,12 @@ def test_a_worker_less_gives_no_wave_a_tile_more_unless_measured_to_be_faster(ru
              for k in KINDS]
     whole = lambda n: n > 32 or n % 16 == 0 or (n > 16 and 1 <= n % 16 <= 4)
     seen = 0
-    for (n, D, _, e, c), (room, tiles, *_) in zip(cases, rules(cases)):
+    for (n, D, a, e, c), (room, tiles, *_) in zip(cases, rules(cases)):
         t = D // 64
         before, after = -(-t // (4 * CUS)), -(-t // (4 * (CUS - 1)))
         assert tiles == (after if room else before)
-        if not whole(n) or t > 16 * 4 * CUS:
+        per = -(-t // CUS)
+        if not whole(n) or t > 16 * 4 * CUS or (n > 48 and (a or c) and 8 * -(-t // per) <= 7 * CUS):
             assert not room
         elif before == after:
             assert room
@@ -71,13 +72,13 @@ def test_a_worker_less_gives_no_wave_a_tile_more_unless_measured_to_be_faster(ru
 
 
 @pytest.mark.parametrize("n,tiles,kind,room", [
-    # measured to be slower with a tile more, by 3 to 13 %
+    # measured to be slower with a tile more, or with nothing to make room for, by 2 to 13 %
     (33, 1021, STEP_PADDED, False), (48, 1022, STEP_PADDED, False), (48, 1022, PHI_PADDED, False), (44, 1023, STEP, False), (44, 2048, STEP_PADDED, False),
     (48, 1024, STEP_PADDED, False), (44, 2046, PHI, False), (40, 6130, PHI_PADDED, False), (33, 12_270, CARRY_PADDED, False), (40, 8180, CARRY_PADDED, False), (50, 2046, STEP, False), (52, 1021, STEP, False),
-    (52, 2048, PHI_PADDED, False), (52, 4092, CARRY, False), (64, 1022, STEP_PADDED, False), (64, 3064, PHI, False),
+    (50, 1093, STEP_PADDED, False), (64, 1120, STEP_PADDED, False), (52, 2048, PHI_PADDED, False), (52, 4092, CARRY, False), (64, 1022, STEP_PADDED, False), (64, 3064, PHI, False),
     # and faster all the same
     (32, 1021, CARRY, True), (33, 1022, PHI, True), (44, 1022, PHI_PADDED, True), (33, 3068, STEP, True), (48, 3068, STEP, True), (48, 2046, STEP, True),
-    (48, 4090, STEP, True), (48, 2046, CARRY, True), (64, 1024, CARRY, True), (64, 2046, CARRY_PADDED, True), (33, 8180, STEP_PADDED, True), (44, 1024, STEP, True)])
+    (50, 1150, STEP_PADDED, True), (64, 1121, CARRY_PADDED, True), (48, 4090, STEP, True), (48, 2046, CARRY, True), (64, 1024, CARRY, True), (64, 2046, CARRY_PADDED, True), (33, 8180, STEP_PADDED, True), (44, 1024, STEP, True)])
 def test_where_a_worker_less_costs_a_tile(rules, n, tiles, kind, room):
     assert rules([(n, 64 * tiles + 27, *kind)])[0][0] == room
 
@@ -88,7 +89,7 @@ def test_nothing_is_left_out_without_a_tail(rules):
 
 @pytest.mark.parametrize("tiles,tail,step,phi", [
     (1024, 27, False, False),  # four per workgroup, 256 workers
-    (1025, 27, True, True), (1275, 27, True, True), (1276, 27, True, False), (1530, 27, True, False), (1531, 27, False, False), (1535, 27, False, False),
+    (1025, 27, True, True), (1275, 27, True, True), (1276, 27, True, False), (1281, 27, True, False), (1530, 27, True, False), (1531, 27, False, False), (1535, 27, False, False),
     (2048, 27, False, False), (2049, 27, False, False), (2295, 27, False, False),
     (1280, 0, True, True), (1281, 0, True, False), (1536, 0, True, False), (1537, 0, False, False), (2049, 0, False, False)])
 def test_ranges_of_their_own_by_the_workers_that_are_launched(rules, tiles, tail, step, phi):
