@@ -342,11 +342,14 @@ __global__ __launch_bounds__(64 * W) void gram_mfma_kernel(const float *__restri
         int qv = q;
         if constexpr (ROWS && !RREG) asm volatile("" : "+v"(qv)); // (or the reads would be hoisted out of the loop)
         // Row 4i + q.  (Base plus place in row q first: what is added for the others is uniform.  With the three added up before the base
-        // every load had an instruction or two of its own: n = 33, D = 100,003 14.6 us, 14.4 without.)
+        // every load has an instruction or two of its own: n = 33, D = 100,003 14.6 us, 14.4 without.  With four blocks in plain
+        // order that is the faster way all the same: svgd_bandwidth at 49 to 64 particles, D = 300,007 to 1,800,007 0.3 to 1 %, a padded
+        // step n = 64, D = 300,007 80.2 and 79.7; D = 70,003 to 100,003 0.7 % slower.)
         auto row_at = [&](int i) __attribute__((always_inline)) {
             if constexpr (RREG) return X + xro[i] + col;
             else if constexpr (ROWS) return X + srow[4 * i + qv] + col;
             else if constexpr (WIDE) return i < RPL - 4 ? X + at0 + (int64_t)(4 * i) * ld : X + col + last_row[i & 3];
+            else if constexpr (NB == 4 && ORDER == 0 && W == kGramWaves) return X + (at0 + (int64_t)(4 * i) * ld);
             else return X + at0 + (int64_t)(4 * i) * ld;
         };
 #pragma unroll
